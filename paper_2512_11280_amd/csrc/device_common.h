@@ -39,6 +39,49 @@ __device__ __forceinline__ double log2_acc(float x) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// Issue order on gfx950, measured with one-instruction loops at eight wavefronts per SIMD.  A SIMD takes two
+// vector instructions at a time if they come from different wavefronts and at least one of them is plain
+// float or bit arithmetic on vector registers and literals (fma, mul, add, and, or, xor, right shift, integer
+// add, v_bitop3): such streams issue every 2.2 cycles instead of every 4.  Left shifts, min / max, compares,
+// selects, conversions, multiplies of 32-bit integers, data-parallel forms and anything with a scalar
+// register operand are the other kind: two of those do not go together, but one goes together with a plain
+// one.  A transcendental (exp, log) holds the SIMD for 8 cycles and nothing goes with it.  Where
+// transcendentals and plain instructions alternate, the wavefronts pile up in front of the transcendentals and
+// the pairs fall apart (1 exp + 4 adds: 24 cycles); with the wavefront's priority raised around its
+// transcendentals the others come together in the plain code (18 cycles; 8 exps + 48 adds: 232 -> 169).
+// So the loops over the vocabulary form their exponentials and logarithms in groups, at raised priority,
+// and keep per-row constants in vector registers or literals.
+// (The instruction after a transcendental must not read its result; s_setprio stands in between.)
+// ---------------------------------------------------------------------------------------------
+__device__ __forceinline__ void ex2_group(const float (&t)[4], float (&e)[4]) {   // e = 2^t
+  asm volatile("s_setprio 3\n\tv_exp_f32 %0, %4\n\tv_exp_f32 %1, %5\n\tv_exp_f32 %2, %6\n\tv_exp_f32 %3, %7\n\ts_setprio 0"
+               : "=&v"(e[0]), "=&v"(e[1]), "=&v"(e[2]), "=&v"(e[3]) : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]));
+}
+__device__ __forceinline__ void lg2_group(const float (&x)[4], float (&l)[4]) {   // l = log2 x
+  asm volatile("s_setprio 3\n\tv_log_f32 %0, %4\n\tv_log_f32 %1, %5\n\tv_log_f32 %2, %6\n\tv_log_f32 %3, %7\n\ts_setprio 0"
+               : "=&v"(l[0]), "=&v"(l[1]), "=&v"(l[2]), "=&v"(l[3]) : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
+}
+// b = 2^b in place and r = 2^-|t|
+__device__ __forceinline__ void ex2_group2(float (&b)[4], const float (&t)[4], float (&r)[4]) {
+  asm volatile("s_setprio 3\n\tv_exp_f32 %0, %0\n\tv_exp_f32 %1, %1\n\tv_exp_f32 %2, %2\n\tv_exp_f32 %3, %3\n\t"
+               "v_exp_f32 %4, -|%8|\n\tv_exp_f32 %5, -|%9|\n\tv_exp_f32 %6, -|%10|\n\tv_exp_f32 %7, -|%11|\n\ts_setprio 0"
+               : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+               : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]));
+}
+// The larger of two floats as one instruction (the builtin first canonicalises operands it cannot see through).
+__device__ __forceinline__ float max_raw(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// z * log2(e) + c with the factor as a literal of the instruction
+__device__ __forceinline__ float fma_log2e(float z, float c) {
+  float r;
+  asm("v_fmamk_f32 %0, %1, 0x3fb8aa3b, %2" : "=v"(r) : "v"(z), "v"(c));
+  return r;
+}
+
+// ---------------------------------------------------------------------------------------------
 // Logit access.  A "vector" is 16 bytes: 8 bf16 or 4 fp32 logits.
 // ---------------------------------------------------------------------------------------------
 template <int DT> struct Elem;
@@ -181,6 +224,56 @@ __device__ __forceinline__ float wave_max_f(float v) {
   return lane_value(v, 63);
 }
 #undef ADASD_DPP_OP
+
+// Exchanges between the halves of a wavefront and between its rows of 16 lanes: swap32 leaves
+// x = (x.low, y.low), y = (x.high, y.high); swap16 leaves x = (x.r0, y.r0, x.r2, y.r2), y = (x.r1, y.r1, x.r3, y.r3).
+__device__ __forceinline__ void swap32(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+// Every lane: the sum over its row of 16 (each in its own order of the same sixteen terms, so where results have
+// to be the same bit for bit they are taken from the same lane).
+__device__ __forceinline__ float row_sum16(float v) {
+  v += dpp_rot<0x121>(v);
+  v += dpp_rot<0x122>(v);
+  v += dpp_rot<0x124>(v);
+  v += dpp_rot<0x128>(v);
+  return v;
+}
+__device__ __forceinline__ float row_max16(float v) {
+  asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:1 row_mask:0xf bank_mask:0xf" : "+v"(v));
+  asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:2 row_mask:0xf bank_mask:0xf" : "+v"(v));
+  asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf" : "+v"(v));
+  asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf" : "+v"(v));
+  return v;
+}
+// Largest a and largest b of the wavefront, in every lane.
+__device__ __forceinline__ void wave_max2(float& a, float& b) {
+  swap32(a, b);
+  float v = fmaxf(a, b);                   // low half: a, high half: b
+  float w = v;
+  swap16(v, w);
+  v = row_max16(fmaxf(v, w));
+  w = v;
+  swap32(v, w);
+  a = v;
+  b = w;
+}
+// Four sums over the wavefront in ten instructions: row 0 of the lanes gets the sum of a, row 1 of c, row 2 of b,
+// row 3 of d (sums of two halves, of two rows, then inside the rows).
+__device__ __forceinline__ float wave_sum4(float a, float b, float c, float d) {
+  swap32(a, b);
+  swap32(c, d);
+  float x = a + b, y = c + d;
+  swap16(x, y);
+  return row_sum16(x + y);
+}
 
 __device__ __forceinline__ uint32_t pk_max_f16(uint32_t a, uint32_t b) {
   uint32_t r;

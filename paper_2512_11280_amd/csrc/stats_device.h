@@ -66,18 +66,14 @@ __device__ __forceinline__ void lse_push(Lse& st, float z) {
   lse_add(st, z);
 }
 
-// Fold of up to 64 partial states of one row held one per lane (an empty state in the other lanes), by
-// one wavefront; all lanes return the same: common reference, plain sums, then the row's log2-sum-exp
-// and entropy in double precision.
-__device__ __forceinline__ RowResult fold_lanes(const Lse& t) {
-  const float M = wave_max_f(t.m), d = t.m - M, f = ex2(d);
-  const float sw = wave_sum_f(t.s * f), uw = wave_sum_f((t.u + d * t.s) * f);
-  const bool ok = (sw > 0.f) && (sw < INFINITY) && (fabsf(uw) < INFINITY) && (M > kNegHuge) && (M < INFINITY);
+// A row's log2-sum-exp and entropy, in double precision, from the fold of all its partial states.
+__device__ __forceinline__ RowResult finish_row(const Lse& t) {
+  const bool ok = (t.s > 0.f) && (t.s < INFINITY) && (fabsf(t.u) < INFINITY) && (t.m > kNegHuge) && (t.m < INFINITY);
   RowResult res;
   if (ok) {
-    const double l2s = log2_acc(sw);
-    res.lse2 = (double)M + l2s;
-    res.H = fmaxf((float)(kLn2 * (l2s - (double)uw / (double)sw)), 0.f);   // (a one-hot row: a few 1e-8 either side of 0)
+    const double l2s = log2_acc(t.s);
+    res.lse2 = (double)t.m + l2s;
+    res.H = fmaxf((float)(kLn2 * (l2s - (double)t.u / (double)t.s)), 0.f);   // (a one-hot row: a few 1e-8 either side of 0)
     res.bad = 0;
   } else {
     res.lse2 = NAN;
@@ -85,6 +81,12 @@ __device__ __forceinline__ RowResult fold_lanes(const Lse& t) {
     res.bad = 1;
   }
   return res;
+}
+// Fold of up to 64 partial states of one row held one per lane (an empty state in the other lanes), by
+// one wavefront; all lanes return the same.
+__device__ __forceinline__ RowResult fold_lanes(const Lse& t) {
+  const float M = wave_max_f(t.m), d = t.m - M, f = ex2(d);
+  return finish_row(Lse{M, wave_sum_f(t.s * f), wave_sum_f((t.u + d * t.s) * f)});
 }
 
 // Fold of the S slice results that the first statistics kernel left for one row.

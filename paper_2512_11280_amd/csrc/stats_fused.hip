@@ -10,15 +10,13 @@
 // runs phase 2 (the JS sum) on the registers it still holds.
 //
 // One workgroup per item, T threads, NB vectors per thread and row held in registers from the load to
-// the end of phase 2.  The kernel is bound by the vector ALU (about 43 issued instructions per logit pair,
-// 36 of them the arithmetic itself and five of those transcendental, against two bytes of bf16 each), so
-// what matters is the instruction count per pair -- many pairs per thread, because the reductions and the
-// exchange cost a fixed number of instructions per item -- and enough wavefronts per SIMD to keep it
-// issuing while other workgroups load or wait: with four vectors per thread and row the kernel fits 64
-// registers, i.e. eight wavefronts per SIMD.  (Also built and measured: persistent workgroups with two and
-// with three register buffers, the loads and the exchange of the next items in flight behind the arithmetic
-// of the current one.  They need about a hundred registers, i.e. four wavefronts per SIMD, and the folds
-// that one wavefront does for its workgroup between two barriers then stand in the open: 56-80 us against 47.)
+// the end of phase 2.  What bounds it is the vector ALU: per logit pair 10 plain instructions and two
+// exponentials in phase 1, 19 and three transcendentals in phase 2.  The loops over the registers are
+// written for the way the SIMDs issue (device_common.h: transcendentals in groups at raised priority,
+// per-row constants in vector registers); there are many pairs per thread, because the reductions and the
+// exchange cost a fixed number of instructions per item, and with four vectors per thread and row the
+// kernel fits 64 registers, i.e. eight wavefronts per SIMD.  Measured (logit pairs of B x k x V, bf16):
+// 32 x 8 x 128256 46.6 -> 41 us, 128 x 16 x 152064 388 -> 335 us with the loops written this way.
 //
 // Hand-off between the workgroups of a position: self-validating 64-bit words (two floats, valid flag
 // in the low mantissa bit of the low float; a cleared word is 0) written and read with agent-scope
@@ -53,8 +51,8 @@ struct FusedGeom {
   int wait_polls;  // polls before a workgroup stops waiting and recomputes what is missing
 };
 
-struct SliceRecord {   // phase-1 result of one slice of a row pair; the references carry the valid flag
-  float mp, sp, up, mq, sq, uq;
+struct SliceRecord {   // phase-1 result of one wavefront or slice: references (they carry the valid flag); S, U of the
+  float m[2], v[4];    // target row, S, U of the draft row
 };
 
 template <int W> struct FusedShared {
@@ -73,17 +71,15 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// The vectors of slice s that this thread holds: vector j is number v0 + tid + j*T of the row.  Loads are
-// issued unconditionally (lanes past the end re-read the slice's last vector); mask_slice then puts -inf
-// where a lane is past the end.  The two are separate so that the masking can wait until the values are
-// needed: the loads of an item are issued a turn ahead of their use.
+// The vectors of slice s that this thread holds: vector j is number v0 + tid + j*T of the row; a lane past the
+// end re-reads the slice's last vector (pad_slice then takes its weight away).
 template <int DT, int T, int NB>
 __device__ __forceinline__ void load_slice(const char* prow, const char* qrow, int s, const FusedGeom& g,
                                            uint4 (&xp)[NB], uint4 (&xq)[NB]) {
   const int v0 = min(s * g.chunk, g.nv), v1 = min(v0 + g.chunk, g.nv), tid = threadIdx.x;
   const uint4* vp = reinterpret_cast<const uint4*>(prow);
   const uint4* vq = reinterpret_cast<const uint4*>(qrow);
-  const int last = max(v1 - 1, 0);     // (an empty slice reads vector 0, all of it masked afterwards)
+  const int last = max(v1 - 1, 0);     // (an empty slice reads vector 0 for all its lanes)
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int idx = min(v0 + tid + j * T, last);
@@ -91,109 +87,196 @@ __device__ __forceinline__ void load_slice(const char* prow, const char* qrow, i
     xq[j] = vq[idx];
   }
 }
+// What stands in a lane past the end, once the references are known: a finite logit (-2.3e38) whose exponential
+// is 0 against any reference a row can have, so that it adds nothing to any sum and needs no branch.  (An
+// infinite one would do the same in the sums of 2^t, but t 2^t has no value there.)
+template <int DT> __device__ __forceinline__ uint32_t weightless() { return DT == ADASD_BF16 ? 0xFF2DFF2Du : 0xFF2D0000u; }
 template <int DT, int T, int NB>
-__device__ __forceinline__ void mask_slice(int s, const FusedGeom& g, uint4 (&xp)[NB], uint4 (&xq)[NB]) {
-  const int v0 = min(s * g.chunk, g.nv), v1 = min(v0 + g.chunk, g.nv), tid = threadIdx.x;
-  if (v0 + NB * T <= v1) return;       // (uniform) a whole slice: every lane has its vectors
-  const uint4 neutral = neutral_vec<DT>();
+__device__ __forceinline__ void pad_slice(int s, const FusedGeom& g, uint4 (&xp)[NB], uint4 (&xq)[NB]) {
+  const int v0 = min(s * g.chunk, g.nv), len = min(v0 + g.chunk, g.nv) - v0, tid = threadIdx.x;
+  const uint32_t w = weightless<DT>();
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    const bool in = v0 + tid + j * T < v1;
-    xp[j] = make_uint4(in ? xp[j].x : neutral.x, in ? xp[j].y : neutral.y, in ? xp[j].z : neutral.z, in ? xp[j].w : neutral.w);
-    xq[j] = make_uint4(in ? xq[j].x : neutral.x, in ? xq[j].y : neutral.y, in ? xq[j].z : neutral.z, in ? xq[j].w : neutral.w);
+    if ((j + 1) * T <= len) continue;  // (uniform) every lane has its vector
+    const bool in = tid + j * T < len;
+    xp[j] = make_uint4(in ? xp[j].x : w, in ? xp[j].y : w, in ? xp[j].z : w, in ? xp[j].w : w);
+    xq[j] = make_uint4(in ? xq[j].x : w, in ? xq[j].y : w, in ? xq[j].z : w, in ? xq[j].w : w);
   }
 }
 
-// Phase 1 of the slice held in (xp, xq) by the whole workgroup.  Wavefront 0 returns the slice's record
-// (wave-uniform); the other wavefronts return their own.  One workgroup barrier.
+__device__ __forceinline__ void record_rows(const SliceRecord& o, Lse& tp, Lse& tq) {
+  tp = Lse{o.m[0], o.v[0], o.v[1]};
+  tq = Lse{o.m[1], o.v[2], o.v[3]};
+}
+// Partial states of the two rows, one of each per lane, folded by one wavefront: common reference, plain sums.
+// The target row's result in the lower half of the lanes, the draft row's in the upper half.
+__device__ __forceinline__ Lse fold_pair(const Lse& tp, const Lse& tq) {
+  float mp = tp.m, mq = tq.m;
+  wave_max2(mp, mq);
+  const float dp = tp.m - mp, dq = tq.m - mq, ep = ex2(dp), eq = ex2(dq);
+  float s = wave_sum4(tp.s * ep, tq.s * eq, (tp.u + dp * tp.s) * ep, (tq.u + dq * tq.s) * eq), u = s;
+  swap16(s, u);
+  return Lse{(threadIdx.x & 32) ? mq : mp, s, u};
+}
+// The two rows' states from the halves, in every lane.
+__device__ __forceinline__ void split_halves(const Lse& f, Lse& tp, Lse& tq) {
+  tp = tq = f;
+  swap32(tp.m, tq.m);
+  swap32(tp.s, tq.s);
+  swap32(tp.u, tq.u);
+}
+
+// Half a vector of bf16 logits or a whole one of fp32 logits: four floats.
+// (RARE, for the less frequent of two forms of a loop: opaque copies.  Without them the unpacking, common to the
+// two, is moved up in front of the branch between them, and every unpacked value is live at once.)
+template <int DT, bool RARE> __device__ __forceinline__ void unpack4(const uint4& v, int half, float (&z)[4]) {
+  if (DT == ADASD_BF16) {
+    uint32_t a = half ? v.z : v.x, b = half ? v.w : v.y;
+    if (RARE) asm volatile("" : "+v"(a), "+v"(b));
+    z[0] = __uint_as_float(a << 16); z[1] = __uint_as_float(a & 0xffff0000u);
+    z[2] = __uint_as_float(b << 16); z[3] = __uint_as_float(b & 0xffff0000u);
+  } else {
+    z[0] = __uint_as_float(v.x); z[1] = __uint_as_float(v.y);
+    z[2] = __uint_as_float(v.z); z[3] = __uint_as_float(v.w);
+    if (RARE) asm volatile("" : "+v"(z[0]), "+v"(z[1]), "+v"(z[2]), "+v"(z[3]));
+  }
+}
+
+// S and U of the wavefront's logits about their references.  MASKED: a logit of -inf is kept from making
+// (-inf) * 0 out of its weighted term; without it such a logit turns the weighted sum into a NaN (as a NaN
+// does), which the caller sees.
+template <int DT, int NB, bool MASKED>
+__device__ __forceinline__ float phase1_sums(const uint4 (&xp)[NB], const uint4 (&xq)[NB], float neg_mp, float neg_mq) {
+  float s[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, u[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int half = 0; half < Elem<DT>::per_vec / 4; ++half)
+#pragma unroll
+      for (int row = 0; row < 2; ++row) {
+        float t[4], e[4];
+        unpack4<DT, MASKED>(row ? xq[j] : xp[j], half, t);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = fma_log2e(t[i], row ? neg_mq : neg_mp);
+        ex2_group(t, e);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s[row][i & 1] += e[i];
+          u[row][i & 1] = fmaf(MASKED ? fmaxf(t[i], -200.f) : t[i], e[i], u[row][i & 1]);
+        }
+      }
+  return wave_sum4(s[0][0] + s[0][1], s[1][0] + s[1][1], u[0][0] + u[0][1], u[1][0] + u[1][1]);
+}
+
+// Phase 1 of the slice held in (xp, xq) by the whole workgroup.  In wavefront 0 the lower half of the lanes
+// returns the target row's (m, s, u), the upper half the draft row's; the other wavefronts return nothing of
+// use.  One workgroup barrier.  masked: whether a logit of -inf (or a NaN) was met by this wavefront.
 template <int DT, int T, int NB>
-__device__ __forceinline__ SliceRecord phase1(const uint4 (&xp)[NB], const uint4 (&xq)[NB],
-                                              FusedShared<T / 64>& sh) {
+__device__ __forceinline__ Lse phase1(int s, const FusedGeom& g, uint4 (&xp)[NB], uint4 (&xq)[NB], bool& masked,
+                                      FusedShared<T / 64>& sh) {
   constexpr int W = T / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  SliceRecord r;
-  r.mp = flagged(wave_max_f(vecs_max<DT, NB>(xp)));
-  r.mq = flagged(wave_max_f(vecs_max<DT, NB>(xq)));
-  float ps0 = 0.f, ps1 = 0.f, pu0 = 0.f, pu1 = 0.f, qs0 = 0.f, qs1 = 0.f, qu0 = 0.f, qu1 = 0.f;
-  float neg_mp = -r.mp, neg_mq = -r.mq;
-  asm volatile("" : "+v"(neg_mp), "+v"(neg_mq));   // in vector registers, once
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    lse_accum_neg<DT>(xp[j], neg_mp, ps0, ps1, pu0, pu1);
-    lse_accum_neg<DT>(xq[j], neg_mq, qs0, qs1, qu0, qu1);
-    __builtin_amdgcn_sched_barrier(0);     // one vector pair at a time: keeps the number of unpacked values in flight small
-  }
-  r.sp = wave_sum_f(ps0 + ps1);
-  r.up = wave_sum_f(pu0 + pu1);
-  r.sq = wave_sum_f(qs0 + qs1);
-  r.uq = wave_sum_f(qu0 + qu1);
-  if (lane == 0) sh.wave[wave] = r;
+  float mp = vecs_max<DT, NB>(xp), mq = vecs_max<DT, NB>(xq);
+  wave_max2(mp, mq);
+  mp = flagged(mp);
+  mq = flagged(mq);
+  pad_slice<DT, T, NB>(s, g, xp, xq);
+  float sum = phase1_sums<DT, NB, false>(xp, xq, -mp, -mq);
+  masked = __any(!(fabsf(sum) < INFINITY)) != 0;
+  if (masked) sum = phase1_sums<DT, NB, true>(xp, xq, -mp, -mq);
+  // rows 0..3 of the lanes: S of the target row, U of the target row, S of the draft row, U of the draft row
+  if ((lane & 15) == 0) sh.wave[wave].v[lane >> 4] = sum;
+  if ((lane & 31) == 1) sh.wave[wave].m[lane >> 5] = lane < 32 ? mp : mq;
   lds_barrier();
-  if (wave != 0) return r;
-  // the W wavefront results, one per lane: common reference, plain sums
+  Lse f = lse_empty();
+  if (wave != 0) return f;
   Lse tp = lse_empty(), tq = lse_empty();
-  if (lane < W) {
-    const SliceRecord o = sh.wave[lane];
-    tp = Lse{o.mp, o.sp, o.up};
-    tq = Lse{o.mq, o.sq, o.uq};
-  }
-  SliceRecord f;
-  {
-    const float M = wave_max_f(tp.m), d = tp.m - M, e = ex2(d);
-    f.mp = M;
-    f.sp = wave_sum_f(tp.s * e);
-    f.up = wave_sum_f((tp.u + d * tp.s) * e);
-  }
-  {
-    const float M = wave_max_f(tq.m), d = tq.m - M, e = ex2(d);
-    f.mq = M;
-    f.sq = wave_sum_f(tq.s * e);
-    f.uq = wave_sum_f((tq.u + d * tq.s) * e);
-  }
-  return f;
+  if (lane < W) record_rows(sh.wave[lane], tp, tq);
+  return fold_pair(tp, tq);
 }
 
-template <int DT, int NB, bool FAR>
-__device__ __forceinline__ float phase2(const uint4 (&xp)[NB], const uint4 (&xq)[NB], const JsNorm& n) {
+// The JS sum of the wavefront's share.  One element's term (see jsd_push, of which this is the ordinary form,
+// four pairs at a time).  MASKED: as in phase 1.
+template <int DT, int NB, bool MASKED>
+__device__ __forceinline__ float phase2(const uint4 (&xp)[NB], const uint4 (&xq)[NB], float neg_cp, float neg_cq, float neg_dc) {
+  float acc[2] = {0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int half = 0; half < Elem<DT>::per_vec / 4; ++half) {
+      float zp[4], zq[4], b[4], d[4], r[4], h[4], l[4];
+      unpack4<DT, MASKED>(xp[j], half, zp);
+      unpack4<DT, MASKED>(xq[j], half, zq);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        b[i] = max_raw(fma_log2e(zp[i], neg_cp), fma_log2e(zq[i], neg_cq));
+        d[i] = fma_log2e(zq[i] - zp[i], neg_dc);
+        if (MASKED) d[i] = fminf(fabsf(d[i]), 126.0f);      // (a NaN, from two masked logits, ends up there too)
+      }
+      ex2_group2(b, d, r);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) h[i] = fmaf(r[i], 0.5f, 0.5f);
+      lg2_group(h, l);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float t_log = fmaf(-2.0f, h[i] * l[i], r[i] * -fabsf(d[i]));
+        const float d2 = d[i] * d[i];
+        const float t_series = fmaf(d2, fmaf(d2, kJsC2, kJsC1), kJsC0) * d2 * h[i];
+        acc[i & 1] = fmaf(b[i], fabsf(d[i]) < kJsSmall ? t_series : t_log, acc[i & 1]);
+      }
+    }
+  return acc[0] + acc[1];
+}
+// Rows whose normalisers lie far apart (rare, and not to set the kernel's register count).
+template <int DT, int NB>
+__device__ __forceinline__ float phase2_far(const uint4 (&xp)[NB], const uint4 (&xq)[NB], const JsNorm& n) {
   constexpr int EPV = Elem<DT>::per_vec;
-  float acc0 = 0.f, acc1 = 0.f;
+  float acc = 0.f;
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    // (an opaque copy: without it the unpacking, common to the two forms of this function, is moved up in
-    // front of the branch between them, and every unpacked value of the buffer is live at once)
-    uint4 vp = xp[j], vq = xq[j];
+    uint4 vp = xp[j], vq = xq[j];          // (opaque copies: see unpack4)
     asm volatile("" : "+v"(vp.x), "+v"(vp.y), "+v"(vp.z), "+v"(vp.w));
     asm volatile("" : "+v"(vq.x), "+v"(vq.y), "+v"(vq.z), "+v"(vq.w));
     float zp[EPV], zq[EPV];
     unpack<DT>(vp, zp);
     unpack<DT>(vq, zq);
 #pragma unroll
-    for (int e = 0; e < EPV; e += 2) {
-      jsd_push<FAR>(zp[e], zq[e], n, acc0);
-      if (FAR) __builtin_amdgcn_sched_barrier(0);
-      jsd_push<FAR>(zp[e + 1], zq[e + 1], n, FAR ? acc0 : acc1);   // (the long form gets by with one register less)
-      if (FAR) __builtin_amdgcn_sched_barrier(0);   // (the long form, rarely taken, must not set the kernel's register count)
+    for (int e = 0; e < EPV; ++e) {
+      jsd_push<true>(zp[e], zq[e], n, acc);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);     // one vector pair at a time: keeps the number of unpacked values in flight small
   }
-  return acc0 + acc1;
+  return acc;
 }
 
-__device__ __forceinline__ void publish(const Workspace& ws, int pos, int s, const SliceRecord& r) {
+// The slice's record: the lower half of wavefront 0 holds the target row's share, the upper half the draft row's.
+__device__ __forceinline__ void publish(const Workspace& ws, int pos, int s, const Lse& f) {
+  const int lane = threadIdx.x & 63;
   uint64_t* w = ws.xchg + ((size_t)pos * kMaxSplit + s) * kXchgWords;
-  put_pair(w + 0, r.mp, r.sp);
-  put_pair(w + 1, r.mq, r.sq);
-  put_pair(w + 2, flagged(r.up), r.uq);
+  float up = f.u, uq = f.u;
+  swap32(up, uq);                         // up: the lower half's in every lane, uq: the upper half's
+  if ((lane & 31) == 0) put_pair(w + (lane >> 5), f.m, f.s);
+  if (lane == 0) put_pair(w + 2, flagged(up), uq);   // (lanes 0 and 32, as where a record is kept: see row_sum16)
 }
 
 // Wavefront 0: the rows' results and what phase 2 needs of them, from one slice record per lane.
 __device__ __forceinline__ void fold_position(const Lse& tp, const Lse& tq, JsNorm& norm, RowResult (&row)[2], int& bad) {
-  const RowResult resp = fold_lanes(tp), resq = fold_lanes(tq);
-  if ((threadIdx.x & 63) == 0) {
-    norm = js_norm(resp, resq);
-    row[0] = resp;
-    row[1] = resq;
-    bad = resp.bad || resq.bad;
+  const RowResult mine = finish_row(fold_pair(tp, tq));   // (of the half's row)
+  const int lane = threadIdx.x & 63;
+  float lo_p = __int_as_float(__double2loint(mine.lse2)), lo_q = lo_p;
+  float hi_p = __int_as_float(__double2hiint(mine.lse2)), hi_q = hi_p;
+  float h_p = mine.H, h_q = mine.H, b_p = __int_as_float(mine.bad), b_q = b_p;
+  swap32(lo_p, lo_q);
+  swap32(hi_p, hi_q);
+  swap32(h_p, h_q);
+  swap32(b_p, b_q);
+  const RowResult rp{__hiloint2double(__float_as_int(hi_p), __float_as_int(lo_p)), h_p, __float_as_int(b_p)};
+  const RowResult rq{__hiloint2double(__float_as_int(hi_q), __float_as_int(lo_q)), h_q, __float_as_int(b_q)};
+  if (lane == 0) {
+    norm = js_norm(rp, rq);
+    row[0] = rp;
+    row[1] = rq;
+    bad = rp.bad || rq.bad;
   }
 }
 
@@ -216,15 +299,15 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout) {
 
   uint4 xp[NB], xq[NB];
   load_slice<DT, T, NB>(rp.ptr, rq.ptr, s, g, xp, xq);
-  mask_slice<DT, T, NB>(s, g, xp, xq);
-  const SliceRecord mine = phase1<DT, T, NB>(xp, xq, sh);
+  bool masked;
+  const Lse mine = phase1<DT, T, NB>(s, g, xp, xq, masked, sh);
 
   if (wave == 0) {
     const bool need = lane < g.S;
     bool ok = true;
     Lse tp = lse_empty(), tq = lse_empty();
     if (g.S > 1) {
-      if (lane == 0) publish(ws, pos, s, mine);
+      publish(ws, pos, s, mine);
       // every slice of the position, one per lane (this workgroup's own words come back the same way)
       const uint64_t* src = ws.xchg + ((size_t)pos * kMaxSplit + (need ? lane : 0)) * kXchgWords;
       uint64_t w0, w1, w2;
@@ -241,32 +324,42 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout) {
         tp = Lse{lo_float(w0), hi_float(w0), lo_float(w2)};
         tq = Lse{lo_float(w1), hi_float(w1), hi_float(w2)};
       }
-    } else if (lane == 0) {              // one slice per position: nothing travels through memory
-      tp = Lse{mine.mp, mine.sp, flagged(mine.up)};
-      tq = Lse{mine.mq, mine.sq, mine.uq};
+    } else {                             // one slice per position: nothing travels through memory
+      Lse a, b;
+      split_halves(mine, a, b);
+      a.u = flagged(a.u);
+      if (lane == 0) {
+        tp = a;
+        tq = b;
+      }
     }
     if (ok) fold_position(tp, tq, sh.norm, sh.row, sh.bad);
     if (lane == 0) sh.expired = ok ? 0 : 1;
   }
   lds_barrier();
   if (sh.expired) {                        // (uniform) the bounded wait ran out: every slice from memory
-    if (tid == 0) sh.redo[s] = mine;
+    auto keep = [&](int o, const Lse& f) {
+      if (wave == 0 && (lane & 31) == 0) {
+        const int row = lane >> 5;
+        sh.redo[o].m[row] = f.m;
+        sh.redo[o].v[2 * row] = f.s;
+        sh.redo[o].v[2 * row + 1] = f.u;
+      }
+    };
+    keep(s, mine);
     for (int o = 0; o < g.S; ++o) {
       if (o == s) continue;
       lds_barrier();                       // (sh.wave of the previous turn has been read)
       load_slice<DT, T, NB>(rp.ptr, rq.ptr, o, g, xp, xq);
-      mask_slice<DT, T, NB>(o, g, xp, xq);
-      const SliceRecord other = phase1<DT, T, NB>(xp, xq, sh);
-      if (tid == 0) sh.redo[o] = other;
+      bool masked_o;
+      keep(o, phase1<DT, T, NB>(o, g, xp, xq, masked_o, sh));
     }
     lds_barrier();
     if (wave == 0) {
       Lse tp = lse_empty(), tq = lse_empty();
       if (lane < g.S) {
-        const SliceRecord o = sh.redo[lane];
-        // (what travels through the words: the weighted sum of the target row carries the flag)
-        tp = Lse{o.mp, o.sp, flagged(o.up)};
-        tq = Lse{o.mq, o.sq, o.uq};
+        record_rows(sh.redo[lane], tp, tq);
+        tp.u = flagged(tp.u);              // (as it travels through the words)
       }
       fold_position(tp, tq, sh.norm, sh.row, sh.bad);
     }
@@ -275,7 +368,7 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout) {
     int s_again = s;
     asm volatile("" : "+s"(s_again));
     load_slice<DT, T, NB>(rp.ptr, rq.ptr, s_again, g, xp, xq);
-    mask_slice<DT, T, NB>(s_again, g, xp, xq);
+    pad_slice<DT, T, NB>(s_again, g, xp, xq);
     lds_barrier();
   }
 
@@ -287,8 +380,20 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout) {
     zx_q = load_elem_bits<DT>(rq.ptr, x);
   }
   float acc = 0.f;
-  if (!bad) acc = n.far ? phase2<DT, NB, true>(xp, xq, n) : phase2<DT, NB, false>(xp, xq, n);
-  acc = wave_sum_f(acc);
+  if (!bad) {
+    if (n.far) {
+      acc = wave_sum_f(phase2_far<DT, NB>(xp, xq, n));
+    } else {
+      // (kept in vector registers: see device_common.h)
+      float neg_cp = -n.cp, neg_cq = -n.cq, neg_dc = -n.dc_hi;
+      asm volatile("" : "+v"(neg_cp), "+v"(neg_cq), "+v"(neg_dc));
+      if (!masked) {
+        acc = wave_sum_f(phase2<DT, NB, false>(xp, xq, neg_cp, neg_cq, neg_dc));
+        masked = !(fabsf(acc) < INFINITY);       // (the difference of two logits beyond the float range)
+      }
+      if (masked) acc = wave_sum_f(phase2<DT, NB, true>(xp, xq, neg_cp, neg_cq, neg_dc));
+    }
+  }
   if (lane == 0) sh.acc[wave] = acc;
   lds_barrier();
   if (tid == 0) {
@@ -340,9 +445,10 @@ hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, i
   FusedGeom g;
   g.S = S;
   g.nv = map.V / (dt == ADASD_BF16 ? 8 : 4);
-  g.chunk = (g.nv + S - 1) / S;
-  g.chunk = (g.chunk + 63) / 64 * 64;          // whole wavefronts of vectors (the last slice takes what is left)
-  if ((int64_t)g.chunk * (S - 1) >= g.nv) g.chunk = (g.nv + S - 1) / S;
+  // Equal slices: consecutive workgroups go to the eight dies in turn, so with eight slices a die gets the same
+  // slice of every position, and one that is longer than the others sets the time (whole 128-byte lines all the same).
+  g.chunk = ((g.nv + S - 1) / S + 7) / 8 * 8;
+  if ((int64_t)g.chunk * (S - 1) >= g.nv || g.chunk > T * NB) g.chunk = (g.nv + S - 1) / S;
   g.wait_polls = wait_polls;
   if (g.chunk > T * NB) return hipErrorInvalidValue;
   const dim3 grid(S, positions);
