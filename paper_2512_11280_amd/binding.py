@@ -1,4 +1,4 @@
-"""Thin ctypes binding of ``libadasd.so``: argument marshalling only.
+"""Thin binding of ``libadasd.so``: argument marshalling only (native for the calls of a decode loop, ctypes otherwise).
 
 Function names mirror the C ABI in ``include/adasd.h`` (``adasd_draft_entropy`` ->
 ``draft_entropy`` and so on).  Tensors are torch CUDA tensors (PyTorch is used for device memory
@@ -20,6 +20,7 @@ SHARD_CAND_BYTES = 128
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libadasd.so")
 _lib = None
+_native = None         # csrc/py_native.cpp, once connected to the library
 
 
 class AdasdError(RuntimeError):
@@ -106,6 +107,22 @@ def load_library():
     L.adasd_profile_read.argtypes = [C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int)]
     _lib = L
     return L
+
+
+def _connect():
+    """The native half of the binding, connected to the loaded library (like the library, never optional)."""
+    global _native
+    L = load_library()
+    try:
+        from . import _native as native
+    except ImportError as e:
+        raise RuntimeError("the native half of the binding is missing or does not load: build it with "
+                           "`python -m paper_2512_11280_amd.build`") from e
+    native.connect(AdasdError, alloc_verify_result,
+                   *(C.cast(getattr(L, "adasd_" + f), C.c_void_p).value
+                     for f in ("draft_entropy", "draft_step", "verify", "verify_noalloc")))
+    _native = native
+    return native
 
 
 def _check(rc: int, where: str):
@@ -208,28 +225,14 @@ class State:
                 for k in ("T_G", "ent_sum", "ent_cnt", "LA", "LR", "nA", "nR")}
 
 
+# The calls of a decode loop are marshalled by the native half of the binding (csrc/py_native.cpp), which checks
+# the arguments as _need above does: at one sequence their kernels run no longer than the same work took in Python.
+
 def draft_entropy(draft_logits: torch.Tensor, workspace: Workspace, T_G: Optional[torch.Tensor] = None,
                   active: Optional[torch.Tensor] = None, step: int = 0, k_max: int = 1 << 30,
                   H_out: Optional[torch.Tensor] = None, stop_out: Optional[torch.Tensor] = None):
     """adasd_draft_entropy: H(q) of every row of draft_logits [B, V] and the stop flag."""
-    if draft_logits.dim() != 2 or not draft_logits.is_cuda or draft_logits.stride(1) != 1:
-        raise ValueError("draft_logits must be a CUDA tensor [B, V] with contiguous vocabulary")
-    B, V = draft_logits.shape
-    dev = draft_logits.device
-    if H_out is None:
-        H_out = torch.empty(B, dtype=torch.float32, device=dev)
-    if stop_out is None:
-        stop_out = torch.empty(B, dtype=torch.uint8, device=dev)
-    _need(T_G, torch.float32, "T_G", optional=True)
-    _need(active, torch.uint8, "active", optional=True)
-    _need(H_out, torch.float32, "H_out")
-    _need(stop_out, torch.uint8, "stop_out")
-    rc = load_library().adasd_draft_entropy(
-        draft_logits.data_ptr(), _dtype_code(draft_logits), B, V, draft_logits.stride(0) if B > 1 else V,
-        _p(T_G), _p(active), step, k_max, H_out.data_ptr(), stop_out.data_ptr(), workspace.ptr,
-        workspace.bytes, _stream())
-    _check(rc, "adasd_draft_entropy")
-    return H_out, stop_out
+    return (_native or _connect()).draft_entropy(draft_logits, workspace, T_G, active, step, k_max, H_out, stop_out)
 
 
 def draft_step(draft_logits: torch.Tensor, workspace: Workspace, T_G: Optional[torch.Tensor] = None,
@@ -239,33 +242,8 @@ def draft_step(draft_logits: torch.Tensor, workspace: Workspace, T_G: Optional[t
                token_out: Optional[torch.Tensor] = None, status_out: Optional[torch.Tensor] = None):
     """adasd_draft_step: H(q), the stop flag and a token drawn from softmax(row) for every row of
     draft_logits [B, V].  Returns (H, stop, token, status)."""
-    if draft_logits.dim() != 2 or not draft_logits.is_cuda or draft_logits.stride(1) != 1:
-        raise ValueError("draft_logits must be a CUDA tensor [B, V] with contiguous vocabulary")
-    B, V = draft_logits.shape
-    dev = draft_logits.device
-    if H_out is None:
-        H_out = torch.empty(B, dtype=torch.float32, device=dev)
-    if stop_out is None:
-        stop_out = torch.empty(B, dtype=torch.uint8, device=dev)
-    if token_out is None:
-        token_out = torch.empty(B, dtype=torch.int32, device=dev)
-    if status_out is None:
-        status_out = torch.empty(B, dtype=torch.int32, device=dev)
-    _need(T_G, torch.float32, "T_G", optional=True)
-    _need(active, torch.uint8, "active", optional=True)
-    _need(seq_id, torch.int32, "seq_id", optional=True)
-    _need(rounds, torch.int32, "rounds", optional=True)
-    _need(H_out, torch.float32, "H_out")
-    _need(stop_out, torch.uint8, "stop_out")
-    _need(token_out, torch.int32, "token_out")
-    _need(status_out, torch.int32, "status_out")
-    rc = load_library().adasd_draft_step(
-        draft_logits.data_ptr(), _dtype_code(draft_logits), B, V, draft_logits.stride(0) if B > 1 else V,
-        _p(T_G), _p(active), step, k_max, seed & 0xFFFFFFFFFFFFFFFF, _p(seq_id), _p(rounds),
-        round0 & 0xFFFFFFFF, H_out.data_ptr(), stop_out.data_ptr(), token_out.data_ptr(),
-        status_out.data_ptr(), workspace.ptr, workspace.bytes, _stream())
-    _check(rc, "adasd_draft_step")
-    return H_out, stop_out, token_out, status_out
+    return (_native or _connect()).draft_step(draft_logits, workspace, T_G, active, step, k_max, seed, seq_id, rounds,
+                                              round0, H_out, stop_out, token_out, status_out)
 
 
 @dataclass
@@ -297,41 +275,8 @@ def verify(target_logits: torch.Tensor, draft_logits: torch.Tensor, draft_tokens
     """adasd_verify on target_logits [B, k+1, V], draft_logits [B, k, V], draft_tokens [B, k].
     workspace=None: adasd_verify_noalloc (the library's built-in scratch array; `out` should then be
     given too, so that the call allocates nothing at all)."""
-    if target_logits.dim() != 3 or draft_logits.dim() != 3:
-        raise ValueError("logits must be [B, k(+1), V]")
-    B, K1, V = target_logits.shape
-    K = K1 - 1
-    if tuple(draft_logits.shape) != (B, K, V):
-        raise ValueError(f"draft_logits must be [{B}, {K}, {V}]")
-    if target_logits.stride(2) != 1 or (K > 0 and draft_logits.stride(2) != 1):
-        raise ValueError("vocabulary dimension must be contiguous")
-    if draft_logits.dtype != target_logits.dtype:
-        raise TypeError("target and draft logits must share a dtype")
-    _need(draft_tokens, torch.int32, "draft_tokens")
-    _need(draft_len, torch.int32, "draft_len", optional=True)
-    _need(seq_id, torch.int32, "seq_id", optional=True)
-    _need(rounds, torch.int32, "rounds", optional=True)
-    if out is None:
-        out = alloc_verify_result(B, K, target_logits.device)
-    st = state._c() if state is not None else None
-    a = _VerifyArgs(
-        target_logits.data_ptr(), draft_logits.data_ptr(), _dtype_code(target_logits), B, K, V,
-        target_logits.stride(0), target_logits.stride(1),
-        draft_logits.stride(0) if K > 0 else V, draft_logits.stride(1) if K > 0 else V,
-        draft_tokens.data_ptr(), _p(draft_len), C.pointer(st) if st is not None else None,
-        seed & 0xFFFFFFFFFFFFFFFF, _p(seq_id), _p(rounds), round0 & 0xFFFFFFFF,
-        out.n_accept.data_ptr(), out.next_token.data_ptr(), out.H_p.data_ptr(), out.H_q.data_ptr(),
-        out.d_js.data_ptr(), out.p_accept.data_ptr(), out.accept_mask.data_ptr(),
-        out.status.data_ptr(), workspace.ptr if workspace is not None else None,
-        workspace.bytes if workspace is not None else 0)
-    opt = options._c() if options is not None else None
-    if workspace is None:
-        rc = load_library().adasd_verify_noalloc(C.byref(a), C.byref(opt) if opt is not None else None, _stream())
-        _check(rc, "adasd_verify_noalloc")
-        return out
-    rc = load_library().adasd_verify(C.byref(a), C.byref(opt) if opt is not None else None, _stream())
-    _check(rc, "adasd_verify")
-    return out
+    return (_native or _connect()).verify(target_logits, draft_logits, draft_tokens, workspace, state, draft_len, seed,
+                                          seq_id, rounds, round0, options, out)
 
 
 @dataclass

@@ -1,8 +1,10 @@
-"""Builds libadasd.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libadasd.so (HIP, gfx950 only) and the native half of the binding in-tree with hipcc and g++."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -23,6 +25,24 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
+NATIVE = os.path.join(HERE, "_native.so")
+NATIVE_SRC = os.path.join(CSRC, "py_native.cpp")
+
+
+def _compile_native() -> str:
+    """The Python extension, against the headers and libraries of the installed torch."""
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    inc = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           *[a for i in inc for a in ("-isystem", i)], NATIVE_SRC, "-o", NATIVE,
+           "-L" + os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on {NATIVE_SRC}:\n{res.stderr}")
+    return NATIVE
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, src.replace(".hip", ".o"))
     cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
@@ -40,11 +60,13 @@ def build(force: bool = True, jobs: int = 4) -> str:
     """Compile every HIP source and link the shared library.  With force=False the build is
     skipped when the library is newer than every source and header."""
     os.makedirs(BUILD, exist_ok=True)
-    deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= max(map(os.path.getmtime, deps)):
+    deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS + [NATIVE_SRC]
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= max(map(os.path.getmtime, deps)) for f in (LIB, NATIVE)):
         return LIB
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        native = ex.submit(_compile_native)
         objs = list(ex.map(_compile, SOURCES))
+        native.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:

@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "adasd.h")
@@ -108,3 +109,20 @@ def test_binding_refuses_to_run_without_the_library(monkeypatch, tmp_path):
     monkeypatch.setattr(b, "_LIB_PATH", str(tmp_path / "missing.so"))
     with pytest.raises(RuntimeError, match="missing"):
         b.load_library()
+
+
+@pytest.mark.parametrize("call, error, text", [
+    (lambda am, z: am.draft_step(z[0], None), ValueError, "draft_logits must be a CUDA tensor"),
+    (lambda am, z: am.draft_entropy(z, None), ValueError, "draft_logits must be a CUDA tensor"),
+    (lambda am, z: am.verify(z[0], z[0], None, None), ValueError, "logits must be"),
+    (lambda am, z: am.verify(z, z, None, None), ValueError, "draft_logits must be"),
+    (lambda am, z: am.verify(z, z[:, :2], None, None), TypeError, "draft_tokens must be a torch tensor"),
+    (lambda am, z: am.verify(z, z[:, :2].double(), None, None), TypeError, "share a dtype"),
+    (lambda am, z: am.verify(z, z[:, :2], torch.zeros(2, 2, dtype=torch.int32), None), ValueError, "contiguous CUDA tensor of torch.int32"),
+    (lambda am, z: am.verify("x", z, None, None), TypeError, "target_logits must be a torch tensor"),
+])
+def test_native_binding_checks_its_arguments(call, error, text):
+    """What is wrong with an argument is said before anything reaches the library (no GPU needed)."""
+    import paper_2512_11280_amd as am
+    with pytest.raises(error, match=text):
+        call(am, torch.zeros(2, 3, 8))
