@@ -209,9 +209,8 @@ int adasd_draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V, 
   map.V = V;
   DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0};
   hipStream_t st = (hipStream_t)stream;
-  const int S = pick_draft_split(B, V, (int)dt);
   Scope sc(5, st);
-  return launch_draft_step(map, (int)dt, S, ws, dout, nullptr, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
+  return launch_draft_step(map, (int)dt, ws, dout, nullptr, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
 }
 
 int adasd_draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
@@ -245,9 +244,8 @@ int adasd_draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, int
   DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0};
   DraftDraw draw{(uint32_t)seed, (uint32_t)(seed >> 32), seq_id, round, round0, (uint32_t)step, token_out, status_out};
   hipStream_t st = (hipStream_t)stream;
-  const int S = pick_draft_split(B, V, (int)dt);
   Scope sc(5, st);
-  return launch_draft_step(map, (int)dt, S, ws, dout, &draw, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
+  return launch_draft_step(map, (int)dt, ws, dout, &draw, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
 }
 
 namespace {
@@ -384,13 +382,16 @@ SampleArgs sample_args(const adasd_verify_args* a, const VerifySetup& v) {
   return s;
 }
 
-// about two 16-byte vectors per thread: enough workgroups to cover the chip for a handful of rows
-int sample_split(int V, int dt) {
-  const int nvec = V / (dt == ADASD_BF16 ? 8 : 4);
-  int S3 = (nvec + 2 * kBlock - 1) / (2 * kBlock);
-  if (S3 < 1) S3 = 1;
-  if (S3 > kMaxSampleSplit) S3 = kMaxSampleSplit;
-  return S3;
+// Slices per sequence of the sampling scan: as few vectors per thread as keep every workgroup resident (seven on each
+// of 256 compute units) and the slices within the limit of the hand-off words.
+int sample_split(int V, int dt, int B) {
+  const int epv = dt == ADASD_BF16 ? 8 : 4, nv = (V + epv - 1) / epv;
+  int turns = 1, S = 1;
+  while (true) {
+    S = (nv + turns * kBlock - 1) / (turns * kBlock);
+    if (S == 1 || (S <= kMaxSplit && (int64_t)S * B <= 1792)) return S;
+    ++turns;
+  }
 }
 
 }  // namespace
@@ -449,7 +450,7 @@ int adasd_verify(const adasd_verify_args* a, const adasd_options* opt_in, void* 
   }
 
   const SampleArgs s = sample_args(a, v);
-  const int S3 = sample_split(V, (int)a->dt);
+  const int S3 = sample_split(V, (int)a->dt, B);
   {
     Scope sc(3, st);
     if (launch_sample(s, S3, ws, st) != hipSuccess) return ADASD_ERR_HIP;
@@ -609,7 +610,7 @@ int adasd_verify_shard_sample(const adasd_verify_args* local, const adasd_shard*
   hipStream_t st = (hipStream_t)stream;
   Scope sc(3, st);
   const SampleArgs s = sample_args(local, v);
-  return launch_shard_sample(s, sample_split(local->V, (int)local->dt), sh->col_begin, v.ws,
+  return launch_shard_sample(s, sample_split(local->V, (int)local->dt, local->B), sh->col_begin, v.ws,
                              reinterpret_cast<float4*>(top_out), st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
 }
 
@@ -640,7 +641,7 @@ int adasd_verify_shard_refine(const adasd_verify_args* local, const adasd_shard*
   hipStream_t st = (hipStream_t)stream;
   Scope sc(3, st);
   const SampleArgs s = sample_args(local, v);
-  return launch_shard_refine(s, sample_split(local->V, (int)local->dt), sh->col_begin, tau, exact_sums, v.ws, cand_out, st) == hipSuccess
+  return launch_shard_refine(s, sample_split(local->V, (int)local->dt, local->B), sh->col_begin, tau, exact_sums, v.ws, cand_out, st) == hipSuccess
              ? ADASD_OK : ADASD_ERR_HIP;
 }
 

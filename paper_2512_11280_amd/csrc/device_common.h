@@ -61,6 +61,10 @@ __device__ __forceinline__ void lg2_group(const float (&x)[4], float (&l)[4]) { 
   asm volatile("s_setprio 3\n\tv_log_f32 %0, %4\n\tv_log_f32 %1, %5\n\tv_log_f32 %2, %6\n\tv_log_f32 %3, %7\n\ts_setprio 0"
                : "=&v"(l[0]), "=&v"(l[1]), "=&v"(l[2]), "=&v"(l[3]) : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
 }
+__device__ __forceinline__ void lg2_abs_group(float (&x)[4]) {                     // x = log2 |x|
+  asm volatile("s_setprio 3\n\tv_log_f32 %0, |%0|\n\tv_log_f32 %1, |%1|\n\tv_log_f32 %2, |%2|\n\tv_log_f32 %3, |%3|\n\ts_setprio 0"
+               : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+}
 // b = 2^b in place and r = 2^-|t|
 __device__ __forceinline__ void ex2_group2(float (&b)[4], const float (&t)[4], float (&r)[4]) {
   asm volatile("s_setprio 3\n\tv_exp_f32 %0, %0\n\tv_exp_f32 %1, %1\n\tv_exp_f32 %2, %2\n\tv_exp_f32 %3, %3\n\t"
@@ -117,6 +121,47 @@ template <int DT> __device__ __forceinline__ void unpack(const uint4& q, float* 
     z[0] = __uint_as_float(q.x); z[1] = __uint_as_float(q.y);
     z[2] = __uint_as_float(q.z); z[3] = __uint_as_float(q.w);
   }
+}
+
+// Half a vector of bf16 logits or a whole one of fp32 logits: four floats.
+// (RARE, for the less frequent of two forms of a loop: opaque copies.  Without them the unpacking, common to the
+// two, is moved up in front of the branch between them, and every unpacked value is live at once.)
+template <int DT, bool RARE = false> __device__ __forceinline__ void unpack4(const uint4& v, int half, float (&z)[4]) {
+  if (DT == ADASD_BF16) {
+    uint32_t a = half ? v.z : v.x, b = half ? v.w : v.y;
+    if (RARE) asm volatile("" : "+v"(a), "+v"(b));
+    z[0] = __uint_as_float(a << 16); z[1] = __uint_as_float(a & 0xffff0000u);
+    z[2] = __uint_as_float(b << 16); z[3] = __uint_as_float(b & 0xffff0000u);
+  } else {
+    z[0] = __uint_as_float(v.x); z[1] = __uint_as_float(v.y);
+    z[2] = __uint_as_float(v.z); z[3] = __uint_as_float(v.w);
+    if (RARE) asm volatile("" : "+v"(z[0]), "+v"(z[1]), "+v"(z[2]), "+v"(z[3]));
+  }
+}
+
+// A row as vectors, whatever its alignment and length: vector number idx holds the logits EPV idx ... of the row
+// (global memory takes 16-byte loads at any element's address), and the last one is filled up with -inf where
+// the row's length is not a whole number of vectors.
+typedef uint32_t vec16_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ uint4 load_vec_any(const char* row, int idx) {
+  const vec16_any v = *reinterpret_cast<const vec16_any*>(row + (size_t)idx * 16);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+template <int DT> __device__ __forceinline__ int vectors_of(int V) { return (V + Elem<DT>::per_vec - 1) / Elem<DT>::per_vec; }
+template <int DT> __device__ __forceinline__ uint4 load_last_vec(const char* row, int V) {   // the one that is not whole
+  constexpr int EPV = Elem<DT>::per_vec;
+  const int first = V / EPV * EPV;
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = DT == ADASD_BF16 ? 0xFF80FF80u : 0xFF800000u;
+#pragma unroll
+  for (int e = 0; e < EPV - 1; ++e) {
+    if (first + e >= V) break;
+    const uint32_t b = load_elem_bits<DT>(row, first + e);
+    if (DT == ADASD_BF16) w[e / 2] = (e & 1) ? (w[e / 2] & 0xffffu) | (b << 16) : (w[e / 2] & 0xffff0000u) | b;
+    else w[e] = b;
+  }
+  return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -416,6 +461,57 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
     k1 += 0xBB67AE85u;
   }
   return U4{{c0, c1, c2, c3}};
+}
+
+// The same for many blocks c0 of one (c1, c2, c3, key): what the first rounds do to the words that do not depend on
+// c0 is done once, and everything a block then needs is in vector registers (a scalar operand would keep the
+// exclusive ors from being issued in pairs): 18 multiplications and 19 exclusive ors a block.
+struct PhiloxRow {
+  uint32_t r0, r1a, r1b, r2a, r2b, k[14];
+};
+__device__ __forceinline__ PhiloxRow philox_row(uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1) {
+  constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
+  PhiloxRow p;
+  const uint64_t b0 = (uint64_t)0xCD9E8D57u * c2;                       // round 0: its second product
+  const uint32_t n0 = (uint32_t)(b0 >> 32) ^ c1 ^ k0;
+  p.r0 = c3 ^ k1;
+  const uint64_t a1 = (uint64_t)0xD2511F53u * n0;                       // round 1: its first product
+  p.r1a = (uint32_t)b0 ^ (k0 + W0);
+  p.r1b = (uint32_t)(a1 >> 32) ^ (k1 + W1);
+  p.r2a = k0 + 2 * W0;
+  p.r2b = (uint32_t)a1 ^ (k1 + 2 * W1);
+#pragma unroll
+  for (int r = 0; r < 7; ++r) {
+    p.k[2 * r] = k0 + (uint32_t)(r + 3) * W0;
+    p.k[2 * r + 1] = k1 + (uint32_t)(r + 3) * W1;
+  }
+  asm volatile("" : "+v"(p.r0), "+v"(p.r1a), "+v"(p.r1b), "+v"(p.r2a), "+v"(p.r2b));
+#pragma unroll
+  for (int r = 0; r < 14; ++r) asm volatile("" : "+v"(p.k[r]));
+  return p;
+}
+__device__ __forceinline__ U4 philox_block(const PhiloxRow& p, uint32_t c0) {
+  const uint64_t a0 = (uint64_t)0xD2511F53u * c0;
+  uint32_t x2 = (uint32_t)(a0 >> 32) ^ p.r0, x3 = (uint32_t)a0;
+  const uint64_t b1 = (uint64_t)0xCD9E8D57u * x2;
+  uint32_t x0 = (uint32_t)(b1 >> 32) ^ p.r1a, x1 = (uint32_t)b1;
+  x2 = x3 ^ p.r1b;
+  {
+    const uint64_t a = (uint64_t)0xD2511F53u * x0, b = (uint64_t)0xCD9E8D57u * x2;
+    x0 = __builtin_amdgcn_bitop3_b32((uint32_t)(b >> 32), x1, p.r2a, 0x96);
+    x2 = (uint32_t)(a >> 32) ^ p.r2b;
+    x1 = (uint32_t)b;
+    x3 = (uint32_t)a;
+  }
+#pragma unroll
+  for (int r = 0; r < 7; ++r) {
+    const uint64_t a = (uint64_t)0xD2511F53u * x0, b = (uint64_t)0xCD9E8D57u * x2;
+    x0 = __builtin_amdgcn_bitop3_b32((uint32_t)(b >> 32), x1, p.k[2 * r], 0x96);
+    x2 = __builtin_amdgcn_bitop3_b32((uint32_t)(a >> 32), x3, p.k[2 * r + 1], 0x96);
+    x1 = (uint32_t)b;
+    x3 = (uint32_t)a;
+  }
+  return U4{{x0, x1, x2, x3}};
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -80,8 +80,7 @@ struct DraftDraw {    // token draw of a drafting step (x_i ~ q_i)
   uint32_t* status;   // may be null
 };
 // One drafting call: entropy and stop flag of each row, and with `draw` the drawn token (one kernel)
-int pick_draft_split(int rows, int V, int dt);
-hipError_t launch_draft_step(const RowMap& map, int dt, int S, const Workspace& ws, const DraftOut& dout,
+hipError_t launch_draft_step(const RowMap& map, int dt, const Workspace& ws, const DraftOut& dout,
                              const DraftDraw* draw /* or null */, hipStream_t st);
 
 struct VerifyOut {

@@ -16,81 +16,21 @@ namespace {
 
 using namespace sampling;
 
-template <int DT, int MODE>
-__device__ __forceinline__ void scan_slice(const char* prow, const char* qrow, int V, int s, int S,
-                                           float cp, float cq, int excluded, int col0, uint32_t c1, uint32_t c2,
-                                           uint32_t c3, uint32_t k0, uint32_t k1, Top2& best, bool& poison) {
-  // col0: vocabulary index of the row's first element (0 unless the row is a column slice); indices,
-  // the excluded token and the noise counters are in vocabulary indices.
-  // kExclude gives a key to every finite logit but the excluded one, also to those whose probability is 0
-  // in float64 (which the float64 path skips).  Such an element cannot win: this mode only runs after the
-  // match test rejected the excluded token x, i.e. ln u1 >= ln p(x) with u1 < 1 - 2^-25, so the rest of the
-  // row holds a mass of at least 3e-8 and some element at least 3e-8 / V of it; its key is above -50 nats
-  // whatever its noise, the key of an element with p < 5e-324 below -720.
-  constexpr bool RESIDUAL = MODE == kResidual;
-  constexpr int EPV = Elem<DT>::per_vec;
-  const int tid = threadIdx.x;
-  const bool fast = (reinterpret_cast<uintptr_t>(prow) & 15u) == 0 &&
-                    (!RESIDUAL || (reinterpret_cast<uintptr_t>(qrow) & 15u) == 0);
-  const int nv = fast ? V / EPV : 0;
-  if (fast) {
-    const int chunk = (nv + S - 1) / S, v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
-    const uint4* vp = reinterpret_cast<const uint4*>(prow);
-    const uint4* vq = reinterpret_cast<const uint4*>(qrow);
-    constexpr int NB = 2;                       // vectors per thread and batch, all loads in flight at once
-    for (int base_v = v0; base_v < v1; base_v += NB * kBlock) {
-      uint4 xp[NB], xq[NB];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int idx = min(base_v + tid + j * kBlock, v1 - 1);
-        xp[j] = vp[idx];
-        if (RESIDUAL) xq[j] = vq[idx];
-      }
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int idx = base_v + tid + j * kBlock;
-        const bool in = idx < v1;
-        float zp[EPV], zq[EPV];
-        unpack<DT>(xp[j], zp);
-        if (RESIDUAL) unpack<DT>(xq[j], zq);
-        const int base = col0 + idx * EPV;
-#pragma unroll
-        for (int g = 0; g < EPV / 4; ++g) {
-          const U4 r = philox4x32_10((uint32_t)(base >> 2) + g, c1, c2, c3, k0, k1);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float a = zp[4 * g + e];
-            if (MODE == kPlain) poison |= in && !(a < INFINITY);   // NaN or +inf in the bonus row
-            float k = key_ub<RESIDUAL>(a, RESIDUAL ? zq[4 * g + e] : 0.f, cp, cq, r.w[e]);
-            const bool use = MODE == kExclude ? (in && base + 4 * g + e != excluded) : in;
-            top2_push(best, use ? k : -INFINITY, base + 4 * g + e);
-          }
-        }
-      }
-    }
-  }
-  // elements not covered by whole aligned vectors: tail of the last slice, or the whole slice
-  int e0, e1;
-  if (fast) {
-    e0 = nv * EPV;
-    e1 = (s == S - 1) ? V : e0;
-  } else {
-    e0 = (int)(((int64_t)s * V) / S);
-    e1 = (int)(((int64_t)(s + 1) * V) / S);
-  }
-  for (int v = e0 + tid; v < e1; v += kBlock) {
-    const int gv = col0 + v;
-    const U4 r = philox4x32_10((uint32_t)gv >> 2, c1, c2, c3, k0, k1);
-    const float a = load_elem<DT>(prow, v);
-    if (MODE == kPlain) poison |= !(a < INFINITY);
-    float k = key_ub<RESIDUAL>(a, RESIDUAL ? load_elem<DT>(qrow, v) : 0.f, cp, cq, pick_word(r, gv));
-    top2_push(best, (MODE == kExclude && gv == excluded) ? -INFINITY : k, gv);
-  }
+// The scan of a sequence's row(s) under its plan.
+template <int DT>
+__device__ __forceinline__ void scan_plan(const SamplePlan& plan, const char* prow, const char* qrow, int V, int v0, int v1,
+                                          int col0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
+                                          Top2& best, bool& poison) {
+  const float cp = (float)plan.lse2_p, cq = (float)plan.lse2_q;
+  const PhiloxRow noise = philox_row(c1, c2, c3, k0, k1);
+  if (plan.residual == kResidual) scan_slice<DT, kResidual>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, poison);
+  else if (plan.residual == kExclude) scan_slice<DT, kExclude>(prow, qrow, V, v0, v1, cp, cq, plan.excluded, col0, noise, best, poison);
+  else scan_slice<DT, kPlain>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, poison);
 }
 
 template <int DT>
-__global__ void __launch_bounds__(kBlock, 5) k_sample(SampleArgs a, int S, Workspace ws) {
-  warm_kernargs<sizeof(SampleArgs) + sizeof(int) + sizeof(Workspace)>();
+__global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int chunk, Workspace ws) {
+  warm_kernargs<sizeof(SampleArgs) + 2 * sizeof(int) + sizeof(Workspace)>();
   const int b = blockIdx.y, s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const SamplePlan plan = ws.plan[b];
   if (!plan.valid) {
@@ -105,93 +45,97 @@ __global__ void __launch_bounds__(kBlock, 5) k_sample(SampleArgs a, int S, Works
   const uint32_t c1 = (uint32_t)plan.row | (1u << 16);
   const uint32_t c2 = a.round ? a.round[b] : a.round0;
   const uint32_t c3 = a.seq_id ? a.seq_id[b] : (uint32_t)b;
-  const float cp = (float)plan.lse2_p, cq = (float)plan.lse2_q;
 
+  const int nv = vectors_of<DT>(V), v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
   Top2 best{-INFINITY, -1, -INFINITY, -1};
   bool poison = false;
-  if (plan.residual == kResidual)
-    scan_slice<DT, kResidual>(prow, qrow, V, s, S, cp, cq, -1, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
-  else if (plan.residual == kExclude)
-    scan_slice<DT, kExclude>(prow, qrow, V, s, S, cp, cq, plan.excluded, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
-  else
-    scan_slice<DT, kPlain>(prow, qrow, V, s, S, cp, cq, -1, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
+  scan_plan<DT>(plan, prow, qrow, V, v0, v1, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
 
   __shared__ Top2 sh_top[kWaves];
-  __shared__ int sh_flag[kWaves];
-  __shared__ int sh_mode;   // 0: not last, 1: last & certain, 2: last & needs the exact path
+  // modes: 0 not the last workgroup; 1 final; 2 settle among the close candidates; 3 broken bonus row; 4 whole row in float64
+  __shared__ int sh_mode;
+  __shared__ float sh_tau;
   __shared__ double sh_red[kWaves];
   best = top2_wave_reduce(best);
-  const int any_poison = __any(poison);
-  if (lane == 0) {
-    sh_top[wave] = best;
-    sh_flag[wave] = any_poison;
-  }
+  best.i2 = __any(poison) ? -2 : -1;          // (the poison marker travels in the runner-up's index)
+  if (lane == 0) sh_top[wave] = best;
   __syncthreads();
-  if (tid == 0) {
-    Top2 t = sh_top[0];
-    int flag = sh_flag[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) {
-      t = top2_merge(t, sh_top[w]);
-      flag |= sh_flag[w];
-    }
-    t.i2 = flag ? -2 : -1;   // poison marker travels in the runner-up index
-    Top2* dst = &ws.part3[(size_t)b * kMaxSampleSplit + s];
-    st_agent(&dst->k1, t.k1); st_agent(&dst->i1, t.i1);
-    st_agent(&dst->k2, t.k2); st_agent(&dst->i2, t.i2);
-    publish_barrier();
-    int ticket = atomicAdd(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], 1);
-    sh_mode = (ticket == S - 1) ? 1 : 0;
-  }
-  __syncthreads();
-  if (!sh_mode) return;
-
-  // ---- last workgroup of this sequence: fold the S partial top-2 sets
-  // modes: 1 final; 2 settle among the close candidates; 3 broken bonus row; 4 whole row in float64
-  __shared__ float sh_tau;
   if (wave == 0) {
-    Top2 t{-INFINITY, -1, -INFINITY, -1};
-    int flag = 0;
-    for (int j = lane; j < S; j += 64) {
-      const Top2* src = &ws.part3[(size_t)b * kMaxSampleSplit + j];
-      Top2 o;
-      o.k1 = ld_agent(&src->k1); o.i1 = ld_agent(&src->i1);
-      o.k2 = ld_agent(&src->k2); o.i2 = ld_agent(&src->i2);
-      if (o.i2 == -2) { flag = 1; o.i2 = -1; }
-      t = top2_merge(t, o);
+    best = Top2{-INFINITY, -1, -INFINITY, -1};
+    if (lane < kWaves) best = sh_top[lane];
+    poison = __any(best.i2 == -2);
+    best = top2_wave_reduce(best);
+    // the slice's record: best key and its index, runner-up key, the logits of the best (they arrive while the others
+    // are under way: the error of the best key depends on them)
+    bool last = true;
+    float zp = 0.f, zq = 0.f;
+    if (best.i1 >= 0) {
+      zp = load_elem<DT>(prow, best.i1);
+      if (plan.residual == kResidual) zq = load_elem<DT>(qrow, best.i1);
     }
-    t = top2_wave_reduce(t);
-    flag = __any(flag);
-    if (lane == 0) {
-      int mode = 1;
-      if (flag) {
+    if (S > 1) {
+      uint64_t* words = ws.xchg + ((size_t)b * kMaxSplit + s) * kXchgWords;
+      if (lane < 2)
+        __hip_atomic_store(words + lane, lane == 0 ? record_word(word_index(best.i1), best.k1) : record_word(poison ? 3u : 1u, best.k2),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (lane == 2)
+        __hip_atomic_store(words + 2, record_word(__float_as_uint(zp) | 1u, zq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S);
+    }
+    int mode = 0;
+    if (last) {
+      // ---- last workgroup of this sequence: fold the S records
+      Top2 t{-INFINITY, -1, -INFINITY, -1};
+      if (S > 1) {
+        uint64_t w[kXchgWords];
+        take_words(ws.xchg + ((size_t)b * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w);
+        if (lane < S) {
+          t = Top2{word_hi(w[0]), index_of_word(w[0]), word_hi(w[1]), -1};
+          poison = ((uint32_t)w[1] & 2u) != 0;
+          zp = word_lo(w[2]);
+          zq = word_hi(w[2]);
+        } else {
+          poison = false;
+        }
+        poison = __any(poison);
+      } else if (lane == 0) {
+        t = best;
+      }
+      const Top2 top = top2_wave_reduce(t);
+      float margin = kGuard;
+      mode = 1;
+      if (poison) {
         mode = 3;   // NaN / +inf in the bonus row
-      } else if (t.i1 < 0) {
+      } else if (top.i1 < 0) {
         mode = 4;   // nothing had (certain) mass
       } else {
-        float margin = kGuard;
         if (plan.residual == kResidual) {
-          float p = ex2(fmaf(load_elem<DT>(prow, t.i1), kLog2e, -cp));
-          float q = ex2(fmaf(load_elem<DT>(qrow, t.i1), kLog2e, -cq));
-          float err = kErrRel * (p + q), w = p - q;
+          const int owner = S > 1 ? __ffsll((long long)__ballot(t.i1 == top.i1)) - 1 : 0;
+          const float p = ex2(fmaf(lane_value(zp, owner), kLog2e, -(float)plan.lse2_p));
+          const float q = ex2(fmaf(lane_value(zq, owner), kLog2e, -(float)plan.lse2_q));
+          const float err = kErrRel * (p + q), w = p - q;
           // true key >= key_ub - log2((w+err)/(w-err)); for err/w < 1/2 that is < 3 log2(e) err/w
           if (!(w > 2.f * err)) mode = 4;
           else margin += 3.f * kLog2e * err / w;
         }
         // an element whose upper bound stays below the winner's lower bound cannot be the true winner
-        if (mode == 1 && !(t.k1 - t.k2 > margin)) {
-          mode = 2;
-          sh_tau = t.k1 - margin;
-        }
+        if (mode == 1 && !(top.k1 - top.k2 > margin)) mode = 2;
       }
-      if (mode == 1) a.next_token[b] = t.i1;
-      sh_mode = mode;
-      __hip_atomic_store(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (mode == 2 && lane < S) {            // the slices' records, for the search for close candidates
+        Top2* dst = &ws.part3[(size_t)b * kMaxSampleSplit + lane];
+        st_agent(&dst->k1, t.k1);
+        st_agent(&dst->i1, t.i1);
+        st_agent(&dst->k2, t.k2);
+        publish_barrier();
+      }
+      if (mode == 1 && lane == 0) a.next_token[b] = top.i1;
+      if (lane == 0) sh_tau = top.k1 - margin;
     }
+    if (lane == 0) sh_mode = mode;
   }
   __syncthreads();
-  int mode = sh_mode;
-  if (mode == 1) return;
+  const int mode = sh_mode;
+  if (mode <= 1) return;
   if (mode == 3) {
     if (tid == 0) {
       a.next_token[b] = -1;
@@ -204,7 +148,7 @@ __global__ void __launch_bounds__(kBlock, 5) k_sample(SampleArgs a, int S, Works
   int tok = -1;
   if (mode == 2) {
     __shared__ RefineShared sh_refine;
-    tok = sample_refine<DT>(prow, qrow, plan.residual, excluded, V, b, S, sh_tau, cp, cq, plan.lse2_p,
+    tok = sample_refine<DT>(prow, qrow, plan.residual, excluded, V, b, S, sh_tau, (float)plan.lse2_p, (float)plan.lse2_q, plan.lse2_p,
                             plan.lse2_q, c1, c2, c3, a.seed_lo, a.seed_hi, ws, sh_red, sh_refine);
   }
   if (tok < 0)
@@ -245,15 +189,10 @@ __global__ void __launch_bounds__(kBlock, 5) k_shard_scan(SampleArgs a, int S, i
   const uint32_t c1 = (uint32_t)plan.row | (1u << 16);
   const uint32_t c2 = a.round ? a.round[b] : a.round0;
   const uint32_t c3 = a.seq_id ? a.seq_id[b] : (uint32_t)b;
-  const float cp = (float)plan.lse2_p, cq = (float)plan.lse2_q;
+  const int nv = vectors_of<DT>(V), chunk = slice_chunk(nv, S), v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
   Top2 best{-INFINITY, -1, -INFINITY, -1};
   bool poison = false;
-  if (plan.residual == kResidual)
-    scan_slice<DT, kResidual>(prow, qrow, V, s, S, cp, cq, -1, col0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
-  else if (plan.residual == kExclude)
-    scan_slice<DT, kExclude>(prow, qrow, V, s, S, cp, cq, plan.excluded, col0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
-  else
-    scan_slice<DT, kPlain>(prow, qrow, V, s, S, cp, cq, -1, col0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
+  scan_plan<DT>(plan, prow, qrow, V, v0, v1, col0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
   __shared__ Top2 sh_top[kWaves];
   __shared__ int sh_flag[kWaves];
   best = top2_wave_reduce(best);
@@ -514,9 +453,10 @@ __global__ void __launch_bounds__(kBlock) k_shard_settle(SampleArgs a, int G, fl
 
 hipError_t launch_sample(const SampleArgs& a, int S, const Workspace& ws, hipStream_t st) {
   if (a.map.B <= 0) return hipSuccess;
-  dim3 grid(S, a.map.B), block(kBlock);
-  if (a.dt == ADASD_BF16) launch_kernel(k_sample<ADASD_BF16>, grid, block, st, a, S, ws);
-  else launch_kernel(k_sample<ADASD_F32>, grid, block, st, a, S, ws);
+  const dim3 grid(S, a.map.B), block(kBlock);
+  const int epv = a.dt == ADASD_BF16 ? 8 : 4, chunk = slice_chunk((a.map.V + epv - 1) / epv, S);
+  if (a.dt == ADASD_BF16) launch_kernel(k_sample<ADASD_BF16>, grid, block, st, a, S, chunk, ws);
+  else launch_kernel(k_sample<ADASD_F32>, grid, block, st, a, S, chunk, ws);
   return hipGetLastError();
 }
 

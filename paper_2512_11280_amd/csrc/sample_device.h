@@ -28,9 +28,9 @@ __device__ __forceinline__ bool better(float ka, int ia, float kb, int ib) {
 // across lanes `better` decides.  No branches.
 __device__ __forceinline__ void top2_push(Top2& t, float k, int i) {
   const bool gt = k > t.k1;
-  t.k2 = fmaxf(t.k2, gt ? t.k1 : k);
+  t.k2 = __builtin_amdgcn_fmed3f(k, t.k1, t.k2);     // (k1 >= k2: the middle one of the three is the new runner-up)
   t.i1 = gt ? i : t.i1;
-  t.k1 = gt ? k : t.k1;
+  t.k1 = max_raw(t.k1, k);
 }
 
 __device__ __forceinline__ Top2 top2_merge(const Top2& a, const Top2& b) {
@@ -43,43 +43,51 @@ __device__ __forceinline__ Top2 top2_merge(const Top2& a, const Top2& b) {
   return r;
 }
 
-template <int CTRL> __device__ __forceinline__ int dpp_rot_i(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
-}
-template <int CTRL> __device__ __forceinline__ Top2 top2_rot(const Top2& v) {
-  Top2 o;
-  o.k1 = dpp_rot<CTRL>(v.k1);
-  o.i1 = dpp_rot_i<CTRL>(v.i1);
-  o.k2 = dpp_rot<CTRL>(v.k2);
-  o.i2 = -1;
-  return o;
-}
-__device__ __forceinline__ Top2 top2_lane(const Top2& v, int lane) {
-  Top2 o;
-  o.k1 = lane_value(v.k1, lane);
-  o.i1 = __builtin_amdgcn_readlane(v.i1, lane);
-  o.k2 = lane_value(v.k2, lane);
-  o.i2 = -1;
-  return o;
-}
-// Wave-uniform result: rotations inside the rows of 16 lanes, then the four rows through scalars.
-__device__ __forceinline__ Top2 top2_wave_reduce(Top2 v) {
-  v = top2_merge(v, top2_rot<0x121>(v));
-  v = top2_merge(v, top2_rot<0x122>(v));
-  v = top2_merge(v, top2_rot<0x124>(v));
-  v = top2_merge(v, top2_rot<0x128>(v));
-  return top2_merge(top2_merge(top2_lane(v, 0), top2_lane(v, 16)), top2_merge(top2_lane(v, 32), top2_lane(v, 48)));
+// Wave-uniform result.  The best key of the wavefront, its lane by a ballot (the lowest index of all of them where
+// several lanes hold that very key), then the best of what is left.
+__device__ __forceinline__ Top2 top2_wave_reduce(const Top2& v) {
+  Top2 r;
+  r.i2 = -1;
+  r.k1 = wave_max_f(v.k1);
+  unsigned long long at = __ballot(v.k1 == r.k1);
+  const int first = __ffsll((long long)at) - 1;
+  r.i1 = __builtin_amdgcn_readlane(v.i1, first);
+  if ((at & (at - 1)) == 0) {                                    // (uniform) one lane, the usual case
+    r.k2 = wave_max_f((int)(threadIdx.x & 63) == first ? v.k2 : v.k1);
+    return r;
+  }
+  r.k2 = r.k1;
+  while (at &= at - 1) {
+    const int i = __builtin_amdgcn_readlane(v.i1, __ffsll((long long)at) - 1);
+    r.i1 = (unsigned)i < (unsigned)r.i1 ? i : r.i1;
+  }
+  return r;
 }
 
-// log2 of E = -ln(u), u = (word + 0.5) / 2^32, accurate to a few 1e-6 relative in E everywhere:
-// near u = 1 the series of -ln(1 - t) in t = 1 - u is used (t is exact there).
+// log2 of -log2(u), u = (word + 0.5) / 2^32, i.e. log2 of E = -ln u up to a constant that every key shares: accurate
+// to a few 1e-6.  With t = 1 - u (formed from the complement of the word, so exact where it is small) it is the
+// logarithm of 1 - t, and below 1/64 its series -(t + t^2/2 + t^3/3)/ln2 (next term 1e-6 relative).
+constexpr float kSer0 = -1.44269504f, kSer1 = -0.72134752f, kSer2 = -0.48089835f, kSerBelow = 0.015625f;
 __device__ __forceinline__ float log2_exponential(uint32_t word) {
-  float u = fmaf((float)word, 0x1p-32f, 0x1p-33f);
-  float e_direct = -0.69314718056f * lg2(u);
-  float t = fmaf((float)(~word), 0x1p-32f, 0x1p-33f);
-  float e_series = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 0.2f, 0.25f), 0.33333333333f), 0.5f), 1.0f);
-  float e = word >= 0xF0000000u ? e_series : e_direct;
-  return lg2(e);
+  const float t = fmaf((float)(~word), 0x1p-32f, 0x1p-33f);
+  const float series = t * fmaf(t, fmaf(t, kSer2, kSer1), kSer0), direct = lg2(1.0f - t);
+  return lg2(fabsf(t < kSerBelow ? series : direct));
+}
+// The same for the four words of a block, transcendentals in groups (device_common.h).
+__device__ __forceinline__ void log2_exponential4(const U4& r, float (&lE)[4]) {
+  float t[4], v[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    t[i] = fmaf((float)(~r.w[i]), 0x1p-32f, 0x1p-33f);
+    v[i] = 1.0f - t[i];
+  }
+  lg2_group(v, l);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float series = t[i] * fmaf(t[i], fmaf(t[i], kSer2, kSer1), kSer0);
+    lE[i] = t[i] < kSerBelow ? series : l[i];
+  }
+  lg2_abs_group(lE);
 }
 
 // Sampling modes of a sequence (SamplePlan::residual)
@@ -95,6 +103,106 @@ __device__ __forceinline__ float key_ub(float zp, float zq, float cp, float cq, 
   float p = ex2(fmaf(zp, kLog2e, -cp)), q = ex2(fmaf(zq, kLog2e, -cq));
   float w = fmaxf(fmaf(kErrRel, p + q, p - q), 0.f);   // (p - q) + error bound; <= 0: certainly no mass
   return lg2(w) - lE;
+}
+
+// Hand-off of slice records inside one launch: NW 64-bit words per slice, each of which says itself that it is there
+// (bit 0 is set in every record; cleared words are 0).  A workgroup sends its words, then takes a ticket, and does not
+// wait for the words to arrive in between: the one that takes the last ticket knows that all words of the row have
+// been sent, so it reads until they are there (which ends: nothing has to happen but stores already under way),
+// and clears them for the next launch.
+__device__ __forceinline__ uint64_t record_word(uint32_t lo, float hi) { return ((uint64_t)__float_as_uint(hi) << 32) | lo; }
+__device__ __forceinline__ float word_hi(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
+__device__ __forceinline__ float word_lo(uint64_t w) { return __uint_as_float((uint32_t)w); }
+__device__ __forceinline__ uint32_t word_index(int i) { return (uint32_t)(i + 2) * 2u + 1u; }
+__device__ __forceinline__ int index_of_word(uint64_t w) { return (int)((uint32_t)w >> 1) - 2; }
+template <int NW> __device__ __forceinline__ void take_words(uint64_t* words, bool mine, uint64_t (&w)[NW]) {
+  bool ok;
+  do {
+    ok = true;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      w[i] = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ok = ok && (w[i] & 1ull);
+    }
+  } while (!__all(ok || !mine));
+  if (mine) {
+#pragma unroll
+    for (int i = 0; i < NW; ++i) __hip_atomic_store(words + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+// (lane 0 takes it; true in every lane for the last of `count`)
+__device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {
+  int t = 0;
+  if ((threadIdx.x & 63) == 0) t = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool last = __builtin_amdgcn_readfirstlane(t) == count - 1;
+  if (last && (threadIdx.x & 63) == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return last;
+}
+
+// ---- the scan of one slice ----------------------------------------------------------------------
+// Vectors v0 .. v1 of the row(s), one per thread and turn, the next one always on its way.  col0: vocabulary index of
+// the row's first element (0 unless the row is a column slice; a multiple of eight); indices, the excluded token
+// and the noise counters are in vocabulary indices.
+// kExclude gives a key to every finite logit but the excluded one, also to those whose probability is 0
+// in float64 (which the float64 path skips).  Such an element cannot win: this mode only runs after the
+// match test rejected the excluded token x, i.e. ln u1 >= ln p(x) with u1 < 1 - 2^-25, so the rest of the
+// row holds a mass of at least 3e-8 and some element at least 3e-8 / V of it; its key is above -50 nats
+// whatever its noise, the key of an element with p < 5e-324 below -720.
+template <int DT, int MODE>
+__device__ __forceinline__ void scan_slice(const char* prow, const char* qrow, int V, int v0, int v1, float cp, float cq,
+                                           int excluded, int col0, const PhiloxRow& noise, Top2& best, bool& poison) {
+  constexpr bool RESIDUAL = MODE == kResidual;
+  constexpr int EPV = Elem<DT>::per_vec;
+  const int tid = threadIdx.x, whole = V / EPV;
+  auto load = [&](const char* row, int idx) {
+    uint4 x = neutral_vec<DT>();
+    if (idx < v1) {
+      if (idx < whole) x = load_vec_any(row, idx);
+      else x = load_last_vec<DT>(row, V);
+    }
+    return x;
+  };
+  float neg_cp = -cp, neg_cq = -cq;
+  asm volatile("" : "+v"(neg_cp), "+v"(neg_cq));
+  uint4 next_p = load(prow, v0 + tid), next_q = next_p;
+  if (RESIDUAL) next_q = load(qrow, v0 + tid);
+  for (int base = v0; base < v1; base += kBlock) {
+    const uint4 xp = next_p, xq = next_q;
+    const int idx = base + tid;
+    if (base + kBlock < v1) {
+      next_p = load(prow, idx + kBlock);
+      if (RESIDUAL) next_q = load(qrow, idx + kBlock);
+    }
+    if (base + (tid & ~63) >= v1) continue;     // (a whole wavefront past the end)
+#pragma unroll
+    for (int g = 0; g < EPV / 4; ++g) {
+      const int first = col0 + idx * EPV + 4 * g;
+      float zp[4], key[4], lE[4];
+      unpack4<DT>(xp, g, zp);
+      if (RESIDUAL) {
+        float zq[4], p[4], q[4];
+        unpack4<DT>(xq, g, zq);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          zp[i] = fma_log2e(zp[i], neg_cp);
+          zq[i] = fma_log2e(zq[i], neg_cq);
+        }
+        ex2_group(zp, p);
+        ex2_group(zq, q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = max_raw(fmaf(kErrRel, p[i] + q[i], p[i] - q[i]), 0.f);
+        lg2_group(p, key);
+      }
+      log2_exponential4(philox_block(noise, (uint32_t)first >> 2), lE);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (MODE == kPlain) poison |= !(zp[i] < INFINITY);       // NaN or +inf in the bonus row
+        float k = RESIDUAL ? key[i] - lE[i] : fma_log2e(zp[i], -lE[i]);
+        if (MODE == kExclude) k = first + i == excluded ? -INFINITY : k;
+        top2_push(best, k, first + i);
+      }
+    }
+  }
 }
 
 // ---- float64 re-evaluation of one sequence by one workgroup ------------------------------------
@@ -194,21 +302,11 @@ __device__ int sample_exact(const char* prow, const char* qrow, bool residual, i
   return t == 0x7fffffff ? -1 : t;
 }
 
-// Element ranges of slice s as scan_slice covers them: [a0, a1) and the row's unaligned tail [b0, b1).
-template <int DT>
-__device__ __forceinline__ void slice_ranges(bool fast, int V, int s, int S, int& a0, int& a1, int& b0, int& b1) {
-  constexpr int EPV = Elem<DT>::per_vec;
-  if (fast) {
-    const int nv = V / EPV, chunk = (nv + S - 1) / S, v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
-    a0 = v0 * EPV;
-    a1 = v1 * EPV;
-    b0 = nv * EPV;
-    b1 = (s == S - 1) ? V : b0;
-  } else {
-    a0 = (int)(((int64_t)s * V) / S);
-    a1 = (int)(((int64_t)(s + 1) * V) / S);
-    b0 = b1 = 0;
-  }
+// Vectors per slice of a row of nv vectors cut into S slices: equal shares, in whole 128-byte lines where the last
+// slice then still has work.
+__host__ __device__ inline int slice_chunk(int nv, int S) {
+  const int even = (nv + S - 1) / S, lines = (even + 7) / 8 * 8;
+  return (int64_t)lines * (S - 1) < nv ? lines : even;
 }
 
 constexpr int kMaxCand = 64;      // elements that may still win
@@ -291,23 +389,20 @@ __device__ bool refine_gather(const char* prow, const char* qrow, bool residual,
   __syncthreads();
   const int n_rescan = R.n_rescan;
   if (n_rescan > kMaxRescan) return false;
-  const bool fast = (reinterpret_cast<uintptr_t>(prow) & 15u) == 0 &&
-                    (!residual || (reinterpret_cast<uintptr_t>(qrow) & 15u) == 0);
+  const int width = slice_chunk(vectors_of<DT>(V), S) * Elem<DT>::per_vec;    // logits per slice
   for (int n = 0; n < n_rescan; ++n) {
-    int lo[2], hi[2];
-    slice_ranges<DT>(fast, V, R.rescan[n], S, lo[0], hi[0], lo[1], hi[1]);
-    for (int part = 0; part < 2; ++part)
-      for (int v = lo[part] + tid; v < hi[part]; v += kBlock) {
-        const int gv = col0 + v;
-        const U4 r = philox4x32_10((uint32_t)gv >> 2, c1, c2, c3, k0, k1);
-        const float zp = load_elem<DT>(prow, v);
-        const float k = residual ? key_ub<true>(zp, load_elem<DT>(qrow, v), cp, cq, pick_word(r, gv))
-                                 : key_ub<false>(zp, 0.f, cp, cq, pick_word(r, gv));
-        if (k >= tau && gv != excluded) {
-          const int at = atomicAdd(&R.n_cand, 1);
-          if (at < kMaxCand) R.cand[at] = gv;
-        }
+    const int lo = min(R.rescan[n] * width, V), hi = min(lo + width, V);
+    for (int v = lo + tid; v < hi; v += kBlock) {
+      const int gv = col0 + v;
+      const U4 r = philox4x32_10((uint32_t)gv >> 2, c1, c2, c3, k0, k1);
+      const float zp = load_elem<DT>(prow, v);
+      const float k = residual ? key_ub<true>(zp, load_elem<DT>(qrow, v), cp, cq, pick_word(r, gv))
+                               : key_ub<false>(zp, 0.f, cp, cq, pick_word(r, gv));
+      if (k >= tau && gv != excluded) {
+        const int at = atomicAdd(&R.n_cand, 1);
+        if (at < kMaxCand) R.cand[at] = gv;
       }
+    }
   }
   __syncthreads();
   return R.n_cand <= kMaxCand;

@@ -126,22 +126,6 @@ __device__ __forceinline__ void split_halves(const Lse& f, Lse& tp, Lse& tq) {
   swap32(tp.u, tq.u);
 }
 
-// Half a vector of bf16 logits or a whole one of fp32 logits: four floats.
-// (RARE, for the less frequent of two forms of a loop: opaque copies.  Without them the unpacking, common to the
-// two, is moved up in front of the branch between them, and every unpacked value is live at once.)
-template <int DT, bool RARE> __device__ __forceinline__ void unpack4(const uint4& v, int half, float (&z)[4]) {
-  if (DT == ADASD_BF16) {
-    uint32_t a = half ? v.z : v.x, b = half ? v.w : v.y;
-    if (RARE) asm volatile("" : "+v"(a), "+v"(b));
-    z[0] = __uint_as_float(a << 16); z[1] = __uint_as_float(a & 0xffff0000u);
-    z[2] = __uint_as_float(b << 16); z[3] = __uint_as_float(b & 0xffff0000u);
-  } else {
-    z[0] = __uint_as_float(v.x); z[1] = __uint_as_float(v.y);
-    z[2] = __uint_as_float(v.z); z[3] = __uint_as_float(v.w);
-    if (RARE) asm volatile("" : "+v"(z[0]), "+v"(z[1]), "+v"(z[2]), "+v"(z[3]));
-  }
-}
-
 // S and U of the wavefront's logits about their references.  MASKED: a logit of -inf is kept from making
 // (-inf) * 0 out of its weighted term; without it such a logit turns the weighted sum into a NaN (as a NaN
 // does), which the caller sees.
