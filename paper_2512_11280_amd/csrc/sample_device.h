@@ -8,7 +8,6 @@
 namespace adasd {
 namespace sampling {
 
-
 constexpr float kErrRel = 1.52587890625e-05f;   // 2^-16: bound on the relative error of a float p or q
 constexpr float kGuard = 1.220703125e-04f;      // 2^-13: bound on the log2-domain rounding of two keys
 
@@ -143,6 +142,8 @@ __device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {
 // Vectors v0 .. v1 of the row(s), one per thread and turn, the next one always on its way.  col0: vocabulary index of
 // the row's first element (0 unless the row is a column slice; a multiple of eight); indices, the excluded token
 // and the noise counters are in vocabulary indices.
+// Bound by the vector ALU as the drafting kernel is (draft.hip); the whole round against the scan in batches of two
+// vectors: 128 x 16 x 152064 385 -> 376 us, ragged 64 x 16 x 128256 127 -> 116 us, 32 x 8 x 128256 64.8 -> 62.2 us.
 // kExclude gives a key to every finite logit but the excluded one, also to those whose probability is 0
 // in float64 (which the float64 path skips).  Such an element cannot win: this mode only runs after the
 // match test rejected the excluded token x, i.e. ln u1 >= ln p(x) with u1 < 1 - 2^-25, so the rest of the

@@ -1039,6 +1039,33 @@ def test_draft_step_many_rows(am, wl, oracle, B, V):
     assert G.close(H, Href).all()
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [1, 3, 9, 2041, 2048, 2055, 4104, 131071, 2 * 131072 + 1])
+@pytest.mark.parametrize("off", [0, 1])
+def test_slices_at_their_edges_and_rows_off_the_vector_boundary(am, wl, oracle, dtype, V, off):
+    """Vocabularies around whole vectors, whole workgroups and more than one turn of 64 slices; rows that start `off`
+    elements past a 16-byte boundary.  Tokens bit for bit, entropies within the oracle's tolerance."""
+    g = torch.Generator().manual_seed(V)
+    B = 3
+    z = (torch.randn(B, V, generator=g) * 3).to(dtype)
+    z[1, V - 1] = 30.0                                   # all mass on the last logit, which no whole vector may hold
+    buf = torch.full((B, (V + off + 15) // 8 * 8), float("nan"), dtype=dtype, device="cuda")   # (never read past a row)
+    rows = buf[:, off:off + V]
+    rows.copy_(z)
+    ws = am.Workspace(B, 1, V, dtype)
+    for _ in range(2):                                   # (and the workspace is clean afterwards)
+        H, stop, tok, st = am.draft_step(rows, ws, step=2, k_max=9, seed=77, round0=3)
+        He = am.draft_entropy(rows, ws, step=2, k_max=9)
+        He = He[0] if isinstance(He, tuple) else He
+        torch.cuda.synchronize()
+        Href, _ = oracle.draft_entropy(z, step=2, k_max=9)
+        assert G.close(H.cpu().numpy(), Href).all() and G.close(He.cpu().numpy(), Href).all()
+        ref = oracle.draft_sample(z, step=2, seed=77, round0=3)
+        ref_tok = ref[0] if isinstance(ref, tuple) else ref
+        assert np.array_equal(tok.cpu().numpy(), ref_tok), (tok, ref_tok)
+        assert tok[1] == V - 1 and (st.cpu().numpy() & ~16 == 0).all()
+
+
 def test_draft_step_unaligned_rows_and_broken_rows(am, wl, oracle):
     g = torch.Generator().manual_seed(3)
     B, V = 6, 4099                                       # odd row length: most rows are not 16-byte aligned
