@@ -64,23 +64,24 @@ __device__ __forceinline__ Top2 top2_wave_reduce(const Top2& v) {
 }
 
 // log2 of -log2(u), u = (word + 0.5) / 2^32, i.e. log2 of E = -ln u up to a constant that every key shares: accurate
-// to a few 1e-6.  With t = 1 - u (formed from the complement of the word, so exact where it is small) it is the
-// logarithm of 1 - t, and below 1/64 its series -(t + t^2/2 + t^3/3)/ln2 (next term 1e-6 relative).
+// to a few 1e-6.  u is formed from the word and t = 1 - u from its complement, so that each is exact to a rounding
+// where it is small (u as 1 - t would be 0 for the lowest 128 words).  The logarithm is u's, and where t is below
+// 1/64 its series -(t + t^2/2 + t^3/3)/ln2 (next term 1e-6 relative).
 constexpr float kSer0 = -1.44269504f, kSer1 = -0.72134752f, kSer2 = -0.48089835f, kSerBelow = 0.015625f;
 __device__ __forceinline__ float log2_exponential(uint32_t word) {
-  const float t = fmaf((float)(~word), 0x1p-32f, 0x1p-33f);
-  const float series = t * fmaf(t, fmaf(t, kSer2, kSer1), kSer0), direct = lg2(1.0f - t);
+  const float u = fmaf((float)word, 0x1p-32f, 0x1p-33f), t = fmaf((float)(~word), 0x1p-32f, 0x1p-33f);
+  const float series = t * fmaf(t, fmaf(t, kSer2, kSer1), kSer0), direct = lg2(u);
   return lg2(fabsf(t < kSerBelow ? series : direct));
 }
 // The same for the four words of a block, transcendentals in groups (device_common.h).
 __device__ __forceinline__ void log2_exponential4(const U4& r, float (&lE)[4]) {
-  float t[4], v[4], l[4];
+  float t[4], u[4], l[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    u[i] = fmaf((float)r.w[i], 0x1p-32f, 0x1p-33f);
     t[i] = fmaf((float)(~r.w[i]), 0x1p-32f, 0x1p-33f);
-    v[i] = 1.0f - t[i];
   }
-  lg2_group(v, l);
+  lg2_group(u, l);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const float series = t[i] * fmaf(t[i], fmaf(t[i], kSer2, kSer1), kSer0);

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import gpu_util as G
+from philox_ref import noise_words_of_row
 
 pytestmark = pytest.mark.gpu
 
@@ -1098,6 +1099,25 @@ def test_draft_step_near_ties_are_settled_in_float64(am, wl, oracle, dtype, V):
     assert np.array_equal(tok, ref_b), (tok, ref_b, gap_b)
     print(f"[draft near ties] V={V}: {B} draws, {(st & 16 != 0).sum()} settled in float64, gaps {np.sort(gap_b)[:4]}", flush=True)
     assert V > 10000 or (st & 16 != 0).sum() >= 1        # the closest draws of the short search at the large V may still be decidable in float
+
+
+@pytest.mark.parametrize("round0,v,word", [(725, 6734, 14), (168, 26999, 335), (0, 3922, 4506), (2, 2916, 222529),
+                                           (31, 7956, 542209)])
+@pytest.mark.parametrize("lead", [1e-3, -1e-3])
+def test_draft_step_weighs_the_smallest_noise_words(am, oracle, round0, v, word, lead):
+    """An element whose noise word is next to 0 against one that it beats, or misses, by 1e-3 nats (the float keys are
+    good to 1e-5, or the float64 settlement is asked): u has to be formed from the word itself, not as 1 - (1 - u)."""
+    seed, V = 2718, 32000
+    words = noise_words_of_row(seed, 0, round0, 0, 2, V)
+    assert words[v] == word
+    other = int(np.argmin(np.abs(words.astype(np.int64) - 2**31)))
+    gum = lambda w: -np.log(-np.log((float(w) + 0.5) * 2.0**-32))
+    z = torch.full((1, V), -60.0)
+    z[0, other] = 0.0
+    z[0, v] = gum(words[other]) - gum(word) + lead
+    H, stop, tok, st, ref_tok, gap = _draft_step_case(am, oracle, z, step=0, seed=seed, round0=round0)
+    assert ref_tok[0] == (v if lead > 0 else other)
+    assert np.array_equal(tok, ref_tok)
 
 
 def test_draft_step_argument_errors(am):
