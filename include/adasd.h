@@ -28,8 +28,8 @@
  *     that depend on device data (token id outside the vocabulary, NaN/+inf logits,
  *     full history list, ...) are reported per sequence in a `status` bit mask;
  *   - logits are row-major with the vocabulary contiguous; strides are in ELEMENTS;
- *     rows whose byte address is 16-byte aligned take the 128-bit load path, other
- *     rows are still handled correctly by an element-wise path;
+ *     rows may start at any element's address and have any length (128-bit loads either
+ *     way; only the two-kernel statistics path reads rows off a 16-byte boundary by element);
  *   - units: entropies in nats; the Jensen-Shannon distance is reported as
  *     d = sqrt(D_JS / ln 2), i.e. the base-2 normalisation under which the paper
  *     states the [0,1] bound and the "exactly 0 or 1" exclusion (Sections 2.2, 4.4);
@@ -127,8 +127,8 @@ typedef struct {
                           recorded (Section 4.4); 0 selects the default 1e-6 */
   int32_t stats_path;  /* kernels of the statistics stage: 0 the library's choice; 1 the two-kernel path
                           (normalisers, then JS distance: the logits are read twice); 2 the single-read
-                          kernel when every row is 16-byte aligned and V is a whole number of 16-byte
-                          vectors of at most 2^18, else the two-kernel path.  Same results to the
+                          kernel when a row is at least 16 bytes and at most 2^18 vectors of 16 bytes
+                          long, at any alignment, else the two-kernel path.  Same results to the
                           documented tolerance either way. */
   int32_t apply_update; /* 1: adasd_verify also applies the round to args->state, exactly as
                           adasd_update_thresholds would with the same d_eps (the decision kernel

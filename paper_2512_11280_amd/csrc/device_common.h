@@ -143,6 +143,10 @@ template <int DT, bool RARE = false> __device__ __forceinline__ void unpack4(con
 // (global memory takes 16-byte loads at any element's address), and the last one is filled up with -inf where
 // the row's length is not a whole number of vectors.
 typedef uint32_t vec16_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ uint4 load_vec_at(const char* row, int byte) {
+  const vec16_any v = *reinterpret_cast<const vec16_any*>(row + (uint32_t)byte);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
 __device__ __forceinline__ uint4 load_vec_any(const char* row, int idx) {
   const vec16_any v = *reinterpret_cast<const vec16_any*>(row + (size_t)idx * 16);
   return make_uint4(v[0], v[1], v[2], v[3]);

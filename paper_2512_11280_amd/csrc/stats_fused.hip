@@ -46,7 +46,9 @@ __device__ __forceinline__ float hi_float(uint64_t w) { return __uint_as_float((
 
 struct FusedGeom {
   int S;           // slices (work items) per position
-  int nv;          // 16-byte vectors per row
+  int nv;          // 16-byte vectors per row, the last one maybe not whole
+  int missing;     // logits that the last vector lacks of a whole one
+  int last_byte;   // offset of the last 16 bytes of a row
   int chunk;       // vectors per slice
   int wait_polls;  // polls before a workgroup stops waiting and recomputes what is missing
 };
@@ -72,19 +74,20 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // The vectors of slice s that this thread holds: vector j is number v0 + tid + j*T of the row; a lane past the
-// end re-reads the slice's last vector (pad_slice then takes its weight away).
+// end re-reads the slice's last vector (pad_slice then takes its weight away).  A row may start at any logit and
+// have any length: where its last vector is not whole, the row's last 16 bytes are read in its place, and pad_slice
+// takes the weight off the logits that the vector before has too.  (Which logit sits where in a vector is of no
+// consequence here.)
 template <int DT, int T, int NB>
 __device__ __forceinline__ void load_slice(const char* prow, const char* qrow, int s, const FusedGeom& g,
                                            uint4 (&xp)[NB], uint4 (&xq)[NB]) {
   const int v0 = min(s * g.chunk, g.nv), v1 = min(v0 + g.chunk, g.nv), tid = threadIdx.x;
-  const uint4* vp = reinterpret_cast<const uint4*>(prow);
-  const uint4* vq = reinterpret_cast<const uint4*>(qrow);
-  const int last = max(v1 - 1, 0);     // (an empty slice reads vector 0 for all its lanes)
+  const int last = min(v1 * 16 - 16, g.last_byte);     // (an empty slice reads the row's end for all its lanes)
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    const int idx = min(v0 + tid + j * T, last);
-    xp[j] = vp[idx];
-    xq[j] = vq[idx];
+    const int at = min((v0 + tid + j * T) * 16, last);
+    xp[j] = load_vec_at(prow, at);
+    xq[j] = load_vec_at(qrow, at);
   }
 }
 // What stands in a lane past the end, once the references are known: a finite logit (-2.3e38) whose exponential
@@ -101,6 +104,21 @@ __device__ __forceinline__ void pad_slice(int s, const FusedGeom& g, uint4 (&xp)
     const bool in = tid + j * T < len;
     xp[j] = make_uint4(in ? xp[j].x : w, in ? xp[j].y : w, in ? xp[j].z : w, in ? xp[j].w : w);
     xq[j] = make_uint4(in ? xq[j].x : w, in ? xq[j].y : w, in ? xq[j].z : w, in ? xq[j].w : w);
+  }
+  if (g.missing == 0 || v0 + len != g.nv || len == 0) return;     // (uniform)
+  // the row's last vector: its first logits are the vector's before
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    if ((len - 1) / T != j) continue;  // (uniform)
+    const bool here = tid + j * T == len - 1;
+    auto take = [&](int i) -> uint32_t {              // mask of what word i keeps
+      if (DT == ADASD_F32) return i < g.missing ? 0u : ~0u;
+      return (2 * i < g.missing ? 0u : 0xffffu) | (2 * i + 1 < g.missing ? 0u : 0xffff0000u);
+    };
+    auto keep = [&](uint32_t x, uint32_t m) { return here ? (x & m) | (w & ~m) : x; };
+    const uint32_t m0 = take(0), m1 = take(1), m2 = take(2), m3 = take(3);
+    xp[j] = make_uint4(keep(xp[j].x, m0), keep(xp[j].y, m1), keep(xp[j].z, m2), keep(xp[j].w, m3));
+    xq[j] = make_uint4(keep(xq[j].x, m0), keep(xq[j].y, m1), keep(xq[j].z, m2), keep(xq[j].w, m3));
   }
 }
 
@@ -399,17 +417,16 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout) {
 
 }  // namespace
 
-// Can the single-read kernel take this call, and with which tiling?  Requirements: every row starts on
-// a 16-byte boundary, the vocabulary is a whole number of vectors, and at most kMaxSplit slices of at
-// most eight vectors per thread and row.
+// Can the single-read kernel take this call, and with which tiling?  Rows of any alignment and of any length from one
+// vector up, in at most kMaxSplit slices of at most eight vectors per thread and row.  Rows off a 16-byte boundary
+// cost a cache line more per wavefront and load; the two-kernel path reads every logit twice, and such rows by
+// element.  A round with this kernel against one with those two, bf16: 1 x 4 x 2001 15.5 / 19.8 us, 8 x 8 x 32003
+// 23.6 / 28.2, 64 x 3 x 16001 23 / 33, 48 x 16 x 64001 78 / 209; float 1 x 4 x 32003 20.1 / 21.6, 48 x 16 x 64001
+// 97 / 250: faster at all of the 48 odd shapes timed, from 2001 logits on, so there is no other lower bound.
 bool fused_plan(const RowMap& map, int dt, int* T_out, int* NB_out, int* S_out) {
-  const int es = dt == ADASD_BF16 ? 2 : 4, epv = 16 / es;
-  if (map.K <= 0 || map.V % epv != 0) return false;
-  for (int w = 0; w < 2; ++w) {
-    if (reinterpret_cast<uintptr_t>(map.base[w]) % 16 != 0) return false;
-    if ((map.seq_stride[w] * es) % 16 != 0 || (map.pos_stride[w] * es) % 16 != 0) return false;
-  }
-  const int nv = map.V / epv;
+  const int epv = dt == ADASD_BF16 ? 8 : 4;
+  if (map.K <= 0 || map.V < epv) return false;
+  const int nv = (map.V + epv - 1) / epv;
   int T = 512, NB = 4;
   while (T > 256 && nv <= (T / 2) * NB) T /= 2;                 // small vocabularies: smaller workgroups
   while (NB > 1 && nv <= T * (NB / 2)) NB /= 2;
@@ -428,7 +445,10 @@ hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, i
   if (positions <= 0) return hipSuccess;
   FusedGeom g;
   g.S = S;
-  g.nv = map.V / (dt == ADASD_BF16 ? 8 : 4);
+  const int epv = dt == ADASD_BF16 ? 8 : 4;
+  g.nv = (map.V + epv - 1) / epv;
+  g.missing = g.nv * epv - map.V;
+  g.last_byte = map.V * (16 / epv) - 16;
   // Equal slices: consecutive workgroups go to the eight dies in turn, so with eight slices a die gets the same
   // slice of every position, and one that is longer than the others sets the time (whole 128-byte lines all the same).
   g.chunk = ((g.nv + S - 1) / S + 7) / 8 * 8;

@@ -1466,6 +1466,42 @@ def test_bounded_wait_expiry_gives_identical_results(am, wl):
         assert torch.equal(getattr(c, k), v), k
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("vectors,extra", [(1, 0), (1, 1), (2, -1), (256, 1), (257, 3), (512, 1), (1024, 3), (2048, -1),
+                                           (2048, 1), (4096, 1), (8017, 3)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_single_read_kernel_takes_rows_of_any_length_and_start(am, wl, oracle, dtype, vectors, extra, offset):
+    """A last vector that is not whole, alone in its turn or in a slice of its own, with the favoured token or a masked one
+    in it and in the logits that the vector before shares with it; rows that start off a 16-byte boundary."""
+    V, B, K = vectors * (8 if dtype == torch.bfloat16 else 4) + extra, 4, 3
+    batch = wl.config_batched(B=B, k=K, V=V, dtype=dtype, seed=V + offset)
+    top = batch.target.float().amax().item() + 2.0
+    batch.target[1, :, V - 1] = top                       # the last logit carries the row
+    batch.draft[1, :, max(V - 2, 0)] = top
+    batch.target[2, :, max(V - 9, 1):V - 1] = -math.inf   # masked logits on both sides of the cut
+    batch.draft[2, :, max(V - 9, 1):V - 2] = -math.inf
+    batch.draft[3, :, V - 1] = -math.inf
+    batch.draft_tokens[1:] = 0                            # (never a masked one)
+
+    def placed(x):
+        room = torch.full((x.shape[0], x.shape[1], V + 2 * offset), math.nan, dtype=dtype, device="cuda")
+        room[:, :, offset:offset + V] = x.cuda()
+        return room[:, :, offset:offset + V]
+    t, d, tok = placed(batch.target), placed(batch.draft), batch.draft_tokens.cuda()
+    ws = am.Workspace(B, K, V, dtype)
+
+    def call(**options):
+        st = G.state_to_device(am, batch.state, B, batch.state["LA"].shape[1])
+        out = am.verify(t, d, tok, ws, state=st, seed=batch.seed, options=am.Options(**options))
+        torch.cuda.synchronize()
+        return out
+    out = call(stats_path=2)
+    G.compare_verify(out, G.run_oracle(oracle, batch))
+    again = call(stats_path=2, wait_polls=-1)             # and where the slices are loaded a second time
+    for name in ("n_accept", "next_token", "H_p", "H_q", "d_js"):
+        assert torch.equal(getattr(out, name), getattr(again, name)), name
+
+
 def test_results_are_bitwise_reproducible(am, wl, path):
     batch = wl.config_batched(B=4, k=4, V=50000, seed=123)
     a, _, ws = G.run_gpu(am, batch, stats_path=path)
