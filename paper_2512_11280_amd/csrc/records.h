@@ -1,0 +1,56 @@
+// Slice records as they travel between the workgroups of one launch: 64-bit words of two 32-bit halves, each of which
+// says itself that it is there (bit 0 of its low half is set in every record; cleared words are 0).  A record
+// arrives as it was sent, to the last bit: where a float gives its lowest bit to the flag, that bit travels elsewhere
+// in the record.  Nothing but bit arithmetic, so that the CPU tests compile this file as it is.
+#pragma once
+#include <stdint.h>
+
+#if defined(__HIPCC__)
+#define ADASD_ANYWHERE __host__ __device__ __forceinline__
+#else
+#define ADASD_ANYWHERE inline
+#endif
+
+namespace adasd {
+
+ADASD_ANYWHERE uint32_t bits_of(float v) {
+  uint32_t b;
+  __builtin_memcpy(&b, &v, 4);
+  return b;
+}
+ADASD_ANYWHERE float float_of(uint32_t b) {
+  float v;
+  __builtin_memcpy(&v, &b, 4);
+  return v;
+}
+
+ADASD_ANYWHERE uint64_t record_word(uint32_t lo, float hi) { return ((uint64_t)bits_of(hi) << 32) | lo; }
+ADASD_ANYWHERE float word_hi(uint64_t w) { return float_of((uint32_t)(w >> 32)); }
+ADASD_ANYWHERE float word_lo(uint64_t w) { return float_of((uint32_t)w); }
+ADASD_ANYWHERE uint32_t word_index(int i) { return (uint32_t)(i + 2) * 2u + 1u; }
+ADASD_ANYWHERE int index_of_word(uint64_t w) { return (int)((uint32_t)w >> 1) - 2; }
+
+// A slice of the token kernel: best key and its index, runner-up key, whether a broken logit was met, the logits of the
+// best (the error of its key is formed from them, and has to be the same however the row is cut).
+struct DrawRecord {
+  float k1, k2, zp, zq;
+  int i1;
+  bool poison;
+};
+ADASD_ANYWHERE void pack_draw(const DrawRecord& r, uint64_t (&w)[3]) {
+  w[0] = record_word(word_index(r.i1), r.k1);
+  w[1] = record_word(1u | (r.poison ? 2u : 0u) | ((bits_of(r.zp) & 1u) << 2), r.k2);
+  w[2] = record_word(bits_of(r.zp) | 1u, r.zq);
+}
+ADASD_ANYWHERE DrawRecord unpack_draw(const uint64_t (&w)[3]) {
+  DrawRecord r;
+  r.k1 = word_hi(w[0]);
+  r.i1 = index_of_word(w[0]);
+  r.k2 = word_hi(w[1]);
+  r.poison = ((uint32_t)w[1] & 2u) != 0;
+  r.zp = float_of(((uint32_t)w[2] & ~1u) | (((uint32_t)w[1] >> 2) & 1u));
+  r.zq = word_hi(w[2]);
+  return r;
+}
+
+}  // namespace adasd

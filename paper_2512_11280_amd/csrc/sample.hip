@@ -75,11 +75,10 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
     }
     if (S > 1) {
       uint64_t* words = ws.xchg + ((size_t)b * kMaxSplit + s) * kXchgWords;
-      if (lane < 2)
-        __hip_atomic_store(words + lane, lane == 0 ? record_word(word_index(best.i1), best.k1) : record_word(poison ? 3u : 1u, best.k2),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (lane == 2)
-        __hip_atomic_store(words + 2, record_word(__float_as_uint(zp) | 1u, zq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint64_t w[kXchgWords];
+      pack_draw(DrawRecord{best.k1, best.k2, zp, zq, best.i1, poison}, w);
+      if (lane < kXchgWords)
+        __hip_atomic_store(words + lane, lane == 0 ? w[0] : (lane == 1 ? w[1] : w[2]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last = take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S);
     }
     int mode = 0;
@@ -90,10 +89,11 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
         uint64_t w[kXchgWords];
         take_words(ws.xchg + ((size_t)b * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w);
         if (lane < S) {
-          t = Top2{word_hi(w[0]), index_of_word(w[0]), word_hi(w[1]), -1};
-          poison = ((uint32_t)w[1] & 2u) != 0;
-          zp = word_lo(w[2]);
-          zq = word_hi(w[2]);
+          const DrawRecord r = unpack_draw(w);
+          t = Top2{r.k1, r.i1, r.k2, -1};
+          poison = r.poison;
+          zp = r.zp;
+          zq = r.zq;
         } else {
           poison = false;
         }

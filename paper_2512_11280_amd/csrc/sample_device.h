@@ -4,6 +4,7 @@
 // runner-up, and the float64 settlement of close calls.
 #pragma once
 #include "internal.h"
+#include "records.h"
 
 namespace adasd {
 namespace sampling {
@@ -105,16 +106,10 @@ __device__ __forceinline__ float key_ub(float zp, float zq, float cp, float cq, 
   return lg2(w) - lE;
 }
 
-// Hand-off of slice records inside one launch: NW 64-bit words per slice, each of which says itself that it is there
-// (bit 0 is set in every record; cleared words are 0).  A workgroup sends its words, then takes a ticket, and does not
-// wait for the words to arrive in between: the one that takes the last ticket knows that all words of the row have
-// been sent, so it reads until they are there (which ends: nothing has to happen but stores already under way),
-// and clears them for the next launch.
-__device__ __forceinline__ uint64_t record_word(uint32_t lo, float hi) { return ((uint64_t)__float_as_uint(hi) << 32) | lo; }
-__device__ __forceinline__ float word_hi(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
-__device__ __forceinline__ float word_lo(uint64_t w) { return __uint_as_float((uint32_t)w); }
-__device__ __forceinline__ uint32_t word_index(int i) { return (uint32_t)(i + 2) * 2u + 1u; }
-__device__ __forceinline__ int index_of_word(uint64_t w) { return (int)((uint32_t)w >> 1) - 2; }
+// Hand-off of slice records inside one launch: NW words per slice (records.h).  A workgroup sends its words, then takes a
+// ticket, and does not wait for the words to arrive in between: the one that takes the last ticket knows that all words
+// of the row have been sent, so it reads until they are there (which ends: nothing has to happen but stores already
+// under way), and clears them for the next launch.
 template <int NW> __device__ __forceinline__ void take_words(uint64_t* words, bool mine, uint64_t (&w)[NW]) {
   bool ok;
   do {
