@@ -140,9 +140,10 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
     bool last = true;
     if (S > 1) {
       uint64_t* words = ws.xchg + ((size_t)rho * kMaxSplit + s) * kXchgWords;
-      const uint64_t w = lane == 0 ? record_word(__float_as_uint(st.m), st.s)
-                                   : (lane == 1 ? record_word(__float_as_uint(st.u) | 1u, best.k1) : record_word(word_index(best.i1), best.k2));
-      if (lane < kXchgWords) __hip_atomic_store(words + lane, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint64_t w[kXchgWords];
+      pack_draft(DraftRecord{st.m, st.s, st.u, best.k1, best.k2, best.i1}, w);
+      if (lane < kXchgWords)
+        __hip_atomic_store(words + lane, lane == 0 ? w[0] : (lane == 1 ? w[1] : w[2]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last = take_ticket(&ws.ticket1[rho * ticket_stride(map.B, kTicket1Len)], S);
     }
     if (last) {
@@ -153,8 +154,9 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
         st = lse_empty();
         best = Top2{-INFINITY, -1, -INFINITY, -1};
         if (lane < S) {
-          st = Lse{word_lo(w[0]), word_hi(w[0]), word_lo(w[1])};
-          best = Top2{word_hi(w[1]), index_of_word(w[2]), word_hi(w[2]), -1};
+          const DraftRecord rec = unpack_draft(w);
+          st = Lse{rec.m, rec.s, rec.u};
+          best = Top2{rec.k1, rec.i1, rec.k2, -1};
         }
       } else if (lane != 0) {
         st = lse_empty();

@@ -53,4 +53,32 @@ ADASD_ANYWHERE DrawRecord unpack_draw(const uint64_t (&w)[3]) {
   return r;
 }
 
+// A weighted sum u whose word also holds the flag: its lowest bit travels as the sign of the sum s, which has none.
+ADASD_ANYWHERE float sum_with_bit(float s, float u) { return float_of((bits_of(s) & 0x7fffffffu) | (bits_of(u) << 31)); }
+ADASD_ANYWHERE float sum_alone(float s) { return float_of(bits_of(s) & 0x7fffffffu); }
+ADASD_ANYWHERE float flagged(float u) { return float_of(bits_of(u) | 1u); }
+ADASD_ANYWHERE float with_bit_of(float u, float s) { return float_of((bits_of(u) & ~1u) | (bits_of(s) >> 31)); }
+
+// A slice of the drafting kernel: reference (whose lowest bit is set, the sums being formed about such a one), sum of
+// exponentials (>= 0, or NaN), weighted sum; best key and its index, runner-up key.
+struct DraftRecord {
+  float m, s, u, k1, k2;
+  int i1;
+};
+ADASD_ANYWHERE void pack_draft(const DraftRecord& r, uint64_t (&w)[3]) {
+  w[0] = record_word(bits_of(r.m), sum_with_bit(r.s, r.u));
+  w[1] = record_word(bits_of(flagged(r.u)), r.k1);
+  w[2] = record_word(word_index(r.i1), r.k2);
+}
+ADASD_ANYWHERE DraftRecord unpack_draft(const uint64_t (&w)[3]) {
+  DraftRecord r;
+  r.m = word_lo(w[0]);
+  r.s = sum_alone(word_hi(w[0]));
+  r.u = with_bit_of(word_lo(w[1]), word_hi(w[0]));
+  r.k1 = word_hi(w[1]);
+  r.i1 = index_of_word(w[2]);
+  r.k2 = word_hi(w[2]);
+  return r;
+}
+
 }  // namespace adasd

@@ -24,6 +24,16 @@ extern "C" void draw(int n, const float* f, const int* i1, const unsigned char* 
     poison_out[k] = r.poison;
   }
 }
+extern "C" void draft(int n, const float* f, const int* i1, uint64_t* words, float* f_out, int* i1_out) {
+  for (int k = 0; k < n; ++k) {
+    uint64_t w[3];
+    pack_draft(DraftRecord{f[5 * k], f[5 * k + 1], f[5 * k + 2], f[5 * k + 3], f[5 * k + 4], i1[k]}, w);
+    for (int j = 0; j < 3; ++j) words[3 * k + j] = w[j];
+    const DraftRecord r = unpack_draft(w);
+    f_out[5 * k] = r.m; f_out[5 * k + 1] = r.s; f_out[5 * k + 2] = r.u; f_out[5 * k + 3] = r.k1; f_out[5 * k + 4] = r.k2;
+    i1_out[k] = r.i1;
+  }
+}
 """
 
 
@@ -60,3 +70,15 @@ def test_draw_records_arrive_as_they_were_sent(lib):
     assert (words & np.uint64(1)).all()                       # every word says that it is there
     assert np.array_equal(f.view(np.uint32), f2.view(np.uint32))
     assert np.array_equal(i1, i2) and np.array_equal(poison, p2)
+
+
+def test_draft_records_arrive_as_they_were_sent(lib):
+    n = 20000
+    f = np.stack([_floats(n, 20 + s) for s in range(5)], 1).copy()
+    f[:, 0] = (f[:, 0].view(np.uint32) | 1).view(np.float32)          # a reference carries the flag
+    f[:, 1] = np.abs(f[:, 1])                                         # a sum of exponentials has no sign
+    i1 = np.random.default_rng(29).integers(-1, 1 << 24, n).astype(np.int32)
+    words, f2, i2 = np.zeros((n, 3), np.uint64), np.zeros_like(f), np.zeros_like(i1)
+    lib.draft(n, _p(f), _p(i1), _p(words), _p(f2), _p(i2))
+    assert (words & np.uint64(1)).all()
+    assert np.array_equal(f.view(np.uint32), f2.view(np.uint32)) and np.array_equal(i1, i2)
