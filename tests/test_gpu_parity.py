@@ -1466,6 +1466,29 @@ def test_bounded_wait_expiry_gives_identical_results(am, wl):
         assert torch.equal(getattr(c, k), v), k
 
 
+@pytest.mark.parametrize("dtype,B,V", [(torch.bfloat16, 128, 152064), (torch.float32, 128, 32000), (torch.float32, 900, 32000),
+                                       (torch.bfloat16, 900, 32000)])
+def test_entropies_are_as_accurate_as_their_sums_allow(am, dtype, B, V):
+    """Against 64 bits, over all rows of a call.  The result's own rounding is 2.4e-8 rms (a last place of 2^-23 to 2^-24
+    of the value, uniform), the two sums and the logarithm add about as much again: 3.5e-8 to 4.5e-8 rms and a mean
+    of 1e-8 in all.  A record that loses a bit on its way, or a chain of additions over all of a lane's logits where a row
+    is one slice (900 rows), shows as 5.5e-8 and more; 5e-8 and 2e-8 lie between."""
+    g = torch.Generator(device="cuda").manual_seed(V + B)
+    z = torch.empty(B, V, dtype=dtype, device="cuda")
+    for b in range(0, B, 100):
+        z[b:b + 100] = 3.0 * torch.randn(min(100, B - b), V, generator=g, device="cuda")
+    exact = torch.empty(B, dtype=torch.float64, device="cuda")
+    for b in range(0, B, 25):
+        lp = torch.log_softmax(z[b:b + 25].double(), -1)
+        exact[b:b + 25] = -(lp.exp() * lp).sum(-1)
+    ws = am.Workspace(B, 1, V, dtype)
+    for H in (am.draft_entropy(z, ws)[0], am.draft_step(z, ws, seed=5)[0]):
+        e = (H.double() - exact) / exact
+        rms, mean = e.pow(2).mean().sqrt().item(), e.mean().item()
+        print(f"[entropy error {dtype} {B}x{V}] rms {rms:.2e} mean {mean:+.2e}", flush=True)
+        assert rms < 5e-8 and abs(mean) < 2e-8
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("vectors,extra", [(1, 0), (1, 1), (2, -1), (256, 1), (257, 3), (512, 1), (1024, 3), (2048, -1),
                                            (2048, 1), (4096, 1), (8017, 3)])
