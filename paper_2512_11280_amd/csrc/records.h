@@ -81,4 +81,18 @@ ADASD_ANYWHERE DraftRecord unpack_draft(const uint64_t (&w)[3]) {
   return r;
 }
 
+// A slice of a row pair in the statistics kernel: target row (p) and draft row (q), references with their lowest bit set.
+struct PairRecord {
+  float mp, sp, up, mq, sq, uq;
+};
+ADASD_ANYWHERE void pack_pair(const PairRecord& r, uint64_t (&w)[3]) {
+  w[0] = record_word(bits_of(r.mp), sum_with_bit(r.sp, r.up));
+  w[1] = record_word(bits_of(r.mq), r.sq);
+  w[2] = record_word(bits_of(flagged(r.up)), r.uq);
+}
+ADASD_ANYWHERE PairRecord unpack_pair(const uint64_t (&w)[3]) {
+  return PairRecord{word_lo(w[0]), sum_alone(word_hi(w[0])), with_bit_of(word_lo(w[2]), word_hi(w[0])),
+                    word_lo(w[1]), word_hi(w[1]), word_hi(w[2])};
+}
+
 }  // namespace adasd

@@ -18,31 +18,24 @@
 // kernel fits 64 registers, i.e. eight wavefronts per SIMD.  Measured (logit pairs of B x k x V, bf16):
 // 32 x 8 x 128256 46.6 -> 41 us, 128 x 16 x 152064 388 -> 335 us with the loops written this way.
 //
-// Hand-off between the workgroups of a position: self-validating 64-bit words (two floats, valid flag
-// in the low mantissa bit of the low float; a cleared word is 0) written and read with agent-scope
-// atomic accesses: no fence, no separate flag, no read-modify-write, and since every word carries its
-// own validity no ordering between different words is relied on.  The decision kernel, which runs
-// next, clears the words of the positions it handles.  The slices of a position are consecutive
-// workgroups of the grid and workgroups are dispatched in order, so whenever one waits, the ones it waits
-// for are resident or next in line; all the same every wait is bounded: after `wait_polls` polls the
-// workgroup recomputes the other slices' results itself from memory with the very same code
-// (bit-identical), so every wave exits whatever the dispatch order is.
+// Hand-off between the workgroups of a position: self-validating 64-bit words (records.h; a cleared word
+// is 0) written and read with agent-scope atomic accesses: no fence, no separate flag, no
+// read-modify-write, and since every word carries its own validity no ordering between different words is
+// relied on.  The decision kernel, which runs next, clears the words of the positions it handles.  The
+// slices of a position are consecutive workgroups of the grid and workgroups are dispatched in order, so
+// whenever one waits, the ones it waits for are resident or next in line; all the same every wait is
+// bounded: after `wait_polls` polls the workgroup recomputes the other slices' results itself from memory
+// with the very same code (bit-identical), so every wave exits whatever the dispatch order is.
 #include "stats_device.h"
+#include "records.h"
 
 namespace adasd {
 
 namespace {
 
-__device__ __forceinline__ float flagged(float v) { return __uint_as_float(__float_as_uint(v) | 1u); }
-__device__ __forceinline__ void put_pair(uint64_t* p, float lo_flagged, float hi) {
-  const uint64_t w = ((uint64_t)__float_as_uint(hi) << 32) | (uint64_t)__float_as_uint(lo_flagged);
-  __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ uint64_t get_word(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float lo_float(uint64_t w) { return __uint_as_float((uint32_t)w); }
-__device__ __forceinline__ float hi_float(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
 
 struct FusedGeom {
   int S;           // slices (work items) per position
@@ -257,8 +250,10 @@ __device__ __forceinline__ void publish(const Workspace& ws, int pos, int s, con
   uint64_t* w = ws.xchg + ((size_t)pos * kMaxSplit + s) * kXchgWords;
   float up = f.u, uq = f.u;
   swap32(up, uq);                         // up: the lower half's in every lane, uq: the upper half's
-  if ((lane & 31) == 0) put_pair(w + (lane >> 5), f.m, f.s);
-  if (lane == 0) put_pair(w + 2, flagged(up), uq);   // (lanes 0 and 32, as where a record is kept: see row_sum16)
+  // (lane 0 has the target row's share, lane 32 the draft row's, as where a record is kept: see row_sum16)
+  auto put = [](uint64_t* p, uint64_t word) { __hip_atomic_store(p, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  if ((lane & 31) == 0) put(w + (lane >> 5), record_word(bits_of(f.m), lane == 0 ? sum_with_bit(f.s, f.u) : f.s));
+  if (lane == 0) put(w + 2, record_word(bits_of(flagged(up)), uq));
 }
 
 // Wavefront 0: the rows' results and what phase 2 needs of them, from one slice record per lane.
@@ -323,13 +318,14 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout) {
         __builtin_amdgcn_s_sleep(4);
       }
       if (need) {
-        tp = Lse{lo_float(w0), hi_float(w0), lo_float(w2)};
-        tq = Lse{lo_float(w1), hi_float(w1), hi_float(w2)};
+        const uint64_t w[kXchgWords] = {w0, w1, w2};
+        const PairRecord r = unpack_pair(w);
+        tp = Lse{r.mp, r.sp, r.up};
+        tq = Lse{r.mq, r.sq, r.uq};
       }
     } else {                             // one slice per position: nothing travels through memory
       Lse a, b;
       split_halves(mine, a, b);
-      a.u = flagged(a.u);
       if (lane == 0) {
         tp = a;
         tq = b;
@@ -359,10 +355,7 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout) {
     lds_barrier();
     if (wave == 0) {
       Lse tp = lse_empty(), tq = lse_empty();
-      if (lane < g.S) {
-        record_rows(sh.redo[lane], tp, tq);
-        tp.u = flagged(tp.u);              // (as it travels through the words)
-      }
+      if (lane < g.S) record_rows(sh.redo[lane], tp, tq);
       fold_position(tp, tq, sh.norm, sh.row, sh.bad);
     }
     // (the slice number goes through an opaque copy: otherwise the addresses of the loads at the top of the

@@ -34,6 +34,17 @@ extern "C" void draft(int n, const float* f, const int* i1, uint64_t* words, flo
     i1_out[k] = r.i1;
   }
 }
+extern "C" void pair(int n, const float* f, uint64_t* words, float* f_out) {
+  for (int k = 0; k < n; ++k) {
+    uint64_t w[3];
+    const float* x = f + 6 * k;
+    pack_pair(PairRecord{x[0], x[1], x[2], x[3], x[4], x[5]}, w);
+    for (int j = 0; j < 3; ++j) words[3 * k + j] = w[j];
+    const PairRecord r = unpack_pair(w);
+    const float y[6] = {r.mp, r.sp, r.up, r.mq, r.sq, r.uq};
+    for (int j = 0; j < 6; ++j) f_out[6 * k + j] = y[j];
+  }
+}
 """
 
 
@@ -82,3 +93,16 @@ def test_draft_records_arrive_as_they_were_sent(lib):
     lib.draft(n, _p(f), _p(i1), _p(words), _p(f2), _p(i2))
     assert (words & np.uint64(1)).all()
     assert np.array_equal(f.view(np.uint32), f2.view(np.uint32)) and np.array_equal(i1, i2)
+
+
+def test_row_pair_records_arrive_as_they_were_sent(lib):
+    n = 20000
+    f = np.stack([_floats(n, 40 + s) for s in range(6)], 1).copy()
+    for c in (0, 3):
+        f[:, c] = (f[:, c].view(np.uint32) | 1).view(np.float32)
+    for c in (1, 4):
+        f[:, c] = np.abs(f[:, c])
+    words, f2 = np.zeros((n, 3), np.uint64), np.zeros_like(f)
+    lib.pair(n, _p(f), _p(words), _p(f2))
+    assert (words & np.uint64(1)).all()
+    assert np.array_equal(f.view(np.uint32), f2.view(np.uint32))
