@@ -187,7 +187,9 @@ __device__ __forceinline__ Lse phase1(int s, const FusedGeom& g, uint4 (&xp)[NB]
   if (wave != 0) return f;
   Lse tp = lse_empty(), tq = lse_empty();
   if (lane < W) record_rows(sh.wave[lane], tp, tq);
-  return fold_pair(tp, tq);
+  f = fold_pair(tp, tq);
+  f.m = flagged(f.m);       // (where every logit of the slice is masked, the lanes without a record have the largest reference)
+  return f;
 }
 
 // The JS sum of the wavefront's share.  One element's term (see jsd_push, of which this is the ordinary form,

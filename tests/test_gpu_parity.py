@@ -1,5 +1,6 @@
 """GPU parity tests: the HIP library against the CPU oracle, through the C ABI (run with -m gpu)."""
 import math
+import time
 
 import numpy as np
 import pytest
@@ -1464,6 +1465,34 @@ def test_bounded_wait_expiry_gives_identical_results(am, wl):
     c, _, _ = G.run_gpu(am, batch, ws=ws, stats_path=2)   # and the workspace is clean afterwards
     for k, v in snap.items():
         assert torch.equal(getattr(c, k), v), k
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [70000, 70001])
+def test_rows_with_whole_slices_masked(am, wl, oracle, dtype, V):
+    """Masked logits over whole slices of a row (a constrained decoder leaves a few tokens only): the records of such
+    slices carry the valid flag like all others.  Without it every workgroup of the position waits in vain and
+    recomputes them all: 4.4 ms instead of 25 us at four positions."""
+    B, K = 2, 3
+    batch = wl.config_batched(B=B, k=K, V=V, dtype=dtype, seed=V)
+    batch.target[0, :, V // 4:] = -math.inf               # the target rows, from a quarter on
+    batch.draft[0, 1:, :V - 100] = -math.inf              # draft rows but for their end
+    batch.target[1, 1] = -math.inf                        # but for one token
+    batch.target[1, 1, 5] = 2.0
+    batch.draft[1, 2] = torch.finfo(dtype).min            # the type's lowest value as the mask
+    batch.draft[1, 2, 7:40] = 1.0
+    batch.draft_tokens[:] = 5
+    t, d, tok = batch.target.cuda(), batch.draft.cuda(), batch.draft_tokens.cuda()
+    ws, took = am.Workspace(B, K, V, dtype), []
+    for _ in range(4):
+        st = G.state_to_device(am, batch.state, B, batch.state["LA"].shape[1])
+        torch.cuda.synchronize()
+        at = time.perf_counter()
+        out = am.verify(t, d, tok, ws, state=st, seed=batch.seed, options=am.Options(stats_path=2))
+        torch.cuda.synchronize()
+        took.append(time.perf_counter() - at)
+    G.compare_verify(out, G.run_oracle(oracle, batch), info_bits=16 | 8)
+    assert min(took) < 2e-3, took                         # (a settlement in float64 takes under 1 ms of it)
 
 
 @pytest.mark.parametrize("dtype,B,V", [(torch.bfloat16, 128, 152064), (torch.float32, 128, 32000), (torch.float32, 900, 32000),
