@@ -1,0 +1,19 @@
+// log2(1 - t) for small t, plain float arithmetic: the CPU tests compile this file as it is and hold its error against
+// 64 bits.
+#pragma once
+#include "records.h"
+
+namespace adasd {
+
+// Below kSerBelow the logarithm of u = 1 - t is taken from t (which is exact to a rounding there, u is not).  The first
+// coefficient is -1/ln 2 (what decides at the smallest t), the other three make the largest relative error on
+// [0, 1/12] smallest: 1.0e-7.  Error of log2 |log2 u| over all words: 1.13e-7 rms, 7.4e-7 at most (1.08e-6 where the value
+// is near -32 and its own rounding is that large).  Five Taylor terms below 1/16 have 1.29e-7 rms, 9.4e-7 at most;
+// three below 1/64 2.2e-7 and 3.0e-6, and one multiplication and addition less.
+constexpr float kSer0 = -1.44269502f, kSer1 = -0.721385062f, kSer2 = -0.478304029f, kSer3 = -0.412017643f;
+constexpr float kSerBelow = 1.0f / 12;
+ADASD_ANYWHERE float log2_series(float t) {
+  return t * __builtin_fmaf(t, __builtin_fmaf(t, __builtin_fmaf(t, kSer3, kSer2), kSer1), kSer0);
+}
+
+}  // namespace adasd

@@ -4,6 +4,7 @@
 // runner-up, and the float64 settlement of close calls.
 #pragma once
 #include "internal.h"
+#include "noise_series.h"
 #include "records.h"
 
 namespace adasd {
@@ -65,13 +66,12 @@ __device__ __forceinline__ Top2 top2_wave_reduce(const Top2& v) {
 }
 
 // log2 of -log2(u), u = (word + 0.5) / 2^32, i.e. log2 of E = -ln u up to a constant that every key shares: accurate
-// to a few 1e-6.  u is formed from the word and t = 1 - u from its complement, so that each is exact to a rounding
-// where it is small (u as 1 - t would be 0 for the lowest 128 words).  The logarithm is u's, and where t is below
-// 1/64 its series -(t + t^2/2 + t^3/3)/ln2 (next term 1e-6 relative).
-constexpr float kSer0 = -1.44269504f, kSer1 = -0.72134752f, kSer2 = -0.48089835f, kSerBelow = 0.015625f;
+// to about 1e-6.  u is formed from the word and t = 1 - u from its complement, so that each is exact to a rounding
+// where it is small (u as 1 - t would be 0 for the lowest 128 words).  The logarithm is u's, or where t is small
+// the series of noise_series.h.
 __device__ __forceinline__ float log2_exponential(uint32_t word) {
   const float u = fmaf((float)word, 0x1p-32f, 0x1p-33f), t = fmaf((float)(~word), 0x1p-32f, 0x1p-33f);
-  const float series = t * fmaf(t, fmaf(t, kSer2, kSer1), kSer0), direct = lg2(u);
+  const float series = log2_series(t), direct = lg2(u);
   return lg2(fabsf(t < kSerBelow ? series : direct));
 }
 // The same for the four words of a block, transcendentals in groups (device_common.h).
@@ -85,7 +85,7 @@ __device__ __forceinline__ void log2_exponential4(const U4& r, float (&lE)[4]) {
   lg2_group(u, l);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float series = t[i] * fmaf(t[i], fmaf(t[i], kSer2, kSer1), kSer0);
+    const float series = log2_series(t[i]);
     lE[i] = t[i] < kSerBelow ? series : l[i];
   }
   lg2_abs_group(lE);

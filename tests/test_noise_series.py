@@ -1,0 +1,65 @@
+"""Error of log2 E, E = -ln u of a 32-bit noise word, as the scans form it, against 64 bits: the kernels' own series
+(csrc/noise_series.h) compiled for the CPU, with logarithms that are exact to a rounding.  The bound is what five Taylor
+terms below t = 1/16 reach (largest error 1.11e-6, which is the rounding of values near -32; 1.29e-7 rms)."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SOURCE = r"""
+#include <cmath>
+#include "noise_series.h"
+using namespace adasd;
+static float lg2(float x) { return (float)std::log2((double)x); }
+extern "C" void errors(long n, const uint32_t* words, double* largest, double* rms) {
+  double worst = 0, sum = 0;
+  for (long k = 0; k < n; ++k) {
+    const uint32_t w = words[k];
+    const float u = __builtin_fmaf((float)w, 0x1p-32f, 0x1p-33f), t = __builtin_fmaf((float)(~w), 0x1p-32f, 0x1p-33f);
+    const float lE = lg2(std::fabs(t < kSerBelow ? log2_series(t) : lg2(u)));   // log2 of -log2 u
+    const double td = ((double)(~w) + 0.5) * 0x1p-32, ud = ((double)w + 0.5) * 0x1p-32;
+    const double exact = std::log2(-(td < 0.5 ? std::log1p(-td) : std::log(ud)) / 0.69314718055994530942);
+    const double e = std::fabs((double)lE - exact);
+    if (e > worst) worst = e;
+    sum += e * e;
+  }
+  *largest = worst;
+  *rms = std::sqrt(sum / n);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("noise")
+    (d / "noise.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-ffp-contract=off", "-shared", "-fPIC", "-I",
+                    os.path.join(ROOT, "paper_2512_11280_amd", "csrc"), str(d / "noise.cpp"), "-o", str(d / "noise.so")], check=True)
+    return C.CDLL(str(d / "noise.so"))
+
+
+def _errors(lib, words):
+    words = np.ascontiguousarray(words, np.uint32)
+    largest, rms = C.c_double(), C.c_double()
+    lib.errors(C.c_long(words.size), words.ctypes.data_as(C.c_void_p), C.byref(largest), C.byref(rms))
+    return largest.value, rms.value
+
+
+def test_error_over_the_whole_range(lib):
+    largest, rms = _errors(lib, np.random.default_rng(0).integers(0, 1 << 32, 4_000_000, dtype=np.uint64))
+    print(f"log2 E: largest error {largest:.3e}, rms {rms:.3e}")
+    assert largest < 1.11e-6 and rms < 1.29e-7
+
+
+@pytest.mark.parametrize("lo,hi", [(0, 1 << 20), (1 << 31, (1 << 31) + (1 << 20)), ((1 << 32) - (1 << 20), 1 << 32),
+                                   (int((1 - 1 / 11) * 2**32), int((1 - 1 / 13) * 2**32)),
+                                   (int((1 - 1 / 15) * 2**32), int((1 - 1 / 17) * 2**32)),
+                                   (int((1 - 1 / 60) * 2**32), int((1 - 1 / 68) * 2**32))])
+def test_error_where_it_can_be_largest(lib, lo, hi):
+    """The ends of the range, and both sides of every line the series has been cut at."""
+    words = lo + np.arange(0, hi - lo, max(1, (hi - lo) >> 20), dtype=np.uint64)
+    assert _errors(lib, words)[0] < 1.11e-6
