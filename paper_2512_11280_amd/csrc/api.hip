@@ -184,9 +184,9 @@ int adasd_state_refresh(const adasd_state* st, void* stream) {
   return launch_state_refresh(u, (hipStream_t)stream) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
 }
 
-int adasd_draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
-                        const float* T_G, const uint8_t* active, int step, int k_max, float* H_out,
-                        uint8_t* stop_out, void* workspace, size_t ws_bytes, void* stream) {
+static int draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
+                         const float* T_G, const uint8_t* active, int step, int k_max, float* H_out,
+                         uint8_t* stop_out, void* workspace, size_t ws_bytes, void* stream, int polls) {
   int rc = check_shape(B, 0, V, (int)dt);
   if (rc) return rc;
   if (B == 0) return ADASD_OK;
@@ -207,17 +207,24 @@ int adasd_draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V, 
   map.K = 0;
   map.B = B;
   map.V = V;
-  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0};
+  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, polls};
   hipStream_t st = (hipStream_t)stream;
   Scope sc(5, st);
   return launch_draft_step(map, (int)dt, ws, dout, nullptr, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
 }
 
-int adasd_draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
-                     const float* T_G, const uint8_t* active, int step, int k_max, uint64_t seed,
-                     const uint32_t* seq_id, const uint32_t* round, uint32_t round0, float* H_out,
-                     uint8_t* stop_out, int32_t* token_out, uint32_t* status_out, void* workspace,
-                     size_t ws_bytes, void* stream) {
+int adasd_draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
+                        const float* T_G, const uint8_t* active, int step, int k_max, float* H_out,
+                        uint8_t* stop_out, void* workspace, size_t ws_bytes, void* stream) {
+  return draft_entropy(draft_logits, dt, B, V, row_stride, T_G, active, step, k_max, H_out, stop_out, workspace, ws_bytes,
+                       stream, kWaitPolls);
+}
+
+static int draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
+                      const float* T_G, const uint8_t* active, int step, int k_max, uint64_t seed,
+                      const uint32_t* seq_id, const uint32_t* round, uint32_t round0, float* H_out,
+                      uint8_t* stop_out, int32_t* token_out, uint32_t* status_out, void* workspace,
+                      size_t ws_bytes, void* stream, int polls) {
   int rc = check_shape(B, 0, V, (int)dt);
   if (rc) return rc;
   if (B == 0) return ADASD_OK;
@@ -241,11 +248,32 @@ int adasd_draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, int
   map.K = 0;
   map.B = B;
   map.V = V;
-  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0};
+  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, polls};
   DraftDraw draw{(uint32_t)seed, (uint32_t)(seed >> 32), seq_id, round, round0, (uint32_t)step, token_out, status_out};
   hipStream_t st = (hipStream_t)stream;
   Scope sc(5, st);
   return launch_draft_step(map, (int)dt, ws, dout, &draw, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
+}
+
+int adasd_draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
+                     const float* T_G, const uint8_t* active, int step, int k_max, uint64_t seed,
+                     const uint32_t* seq_id, const uint32_t* round, uint32_t round0, float* H_out,
+                     uint8_t* stop_out, int32_t* token_out, uint32_t* status_out, void* workspace,
+                     size_t ws_bytes, void* stream) {
+  return draft_step(draft_logits, dt, B, V, row_stride, T_G, active, step, k_max, seed, seq_id, round, round0, H_out, stop_out,
+                    token_out, status_out, workspace, ws_bytes, stream, kWaitPolls);
+}
+
+// For the tests, not part of the ABI: the drafting calls (token_out null: entropy only) on the path behind a wait that
+// has run out.
+int adasd_test_draft_unarrived(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride, int step, uint64_t seed,
+                               uint32_t round0, float* H_out, uint8_t* stop_out, int32_t* token_out, uint32_t* status_out,
+                               void* workspace, size_t ws_bytes, void* stream) {
+  if (!token_out)
+    return draft_entropy(draft_logits, dt, B, V, row_stride, nullptr, nullptr, step, 1 << 30, H_out, stop_out, workspace, ws_bytes,
+                         stream, -1);
+  return draft_step(draft_logits, dt, B, V, row_stride, nullptr, nullptr, step, 1 << 30, seed, nullptr, nullptr, round0, H_out,
+                    stop_out, token_out, status_out, workspace, ws_bytes, stream, -1);
 }
 
 namespace {
@@ -379,6 +407,7 @@ SampleArgs sample_args(const adasd_verify_args* a, const VerifySetup& v) {
   s.round0 = a->round0;
   s.next_token = a->next_token;
   s.status = a->status;
+  s.polls = kWaitPolls;
   return s;
 }
 
@@ -396,7 +425,7 @@ int sample_split(int V, int dt, int B) {
 
 }  // namespace
 
-int adasd_verify(const adasd_verify_args* a, const adasd_options* opt_in, void* stream) {
+static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void* stream, int token_polls) {
   VerifySetup v;
   int rc = verify_setup(a, opt_in, kWantLogits | kWantOutputs | kWantToken, &v);
   if (rc) return rc < 0 ? rc : ADASD_OK;
@@ -449,13 +478,21 @@ int adasd_verify(const adasd_verify_args* a, const adasd_options* opt_in, void* 
     if (launch_decide(d, upd, ws, st) != hipSuccess) return ADASD_ERR_HIP;
   }
 
-  const SampleArgs s = sample_args(a, v);
+  SampleArgs s = sample_args(a, v);
+  s.polls = token_polls;
   const int S3 = sample_split(V, (int)a->dt, B);
   {
     Scope sc(3, st);
     if (launch_sample(s, S3, ws, st) != hipSuccess) return ADASD_ERR_HIP;
   }
   return ADASD_OK;
+}
+
+int adasd_verify(const adasd_verify_args* a, const adasd_options* opt, void* stream) { return verify(a, opt, stream, kWaitPolls); }
+
+// For the tests, not part of the ABI: verification with the token kernel on the path behind a wait that has run out.
+int adasd_test_verify_unarrived(const adasd_verify_args* a, const adasd_options* opt, void* stream) {
+  return verify(a, opt, stream, -1);
 }
 
 // ---- verification without a caller-provided workspace -------------------------------------------

@@ -27,11 +27,33 @@ template <bool DRAW> __device__ __forceinline__ void fold_wave(Lse& l, Top2& t) 
   if (DRAW) t = top2_wave_reduce(t);
 }
 
+// Sums of a whole row by one wavefront, from the logits (where the slices' records did not arrive, which never happens
+// to calls that are ordered as they have to be).
+template <int DT> __device__ __forceinline__ Lse wave_row_sums(const char* row, int V) {
+  const int lane = threadIdx.x & 63;
+  float top = kNegHuge;
+#pragma unroll 1
+  for (int v = lane; v < V; v += 64) {
+    const float z = load_elem<DT>(row, v);
+    if (z < INFINITY) top = fmaxf(top, z);
+  }
+  top = wave_max_f(top);
+  const float m = top > kNegHuge ? top * kLog2e : kNegHuge;
+  double s = 0.0, u = 0.0;
+#pragma unroll 1
+  for (int v = lane; v < V; v += 64) {
+    const float t = fmaf(load_elem<DT>(row, v), kLog2e, -m), e = ex2(t);
+    s += (double)e;
+    u += (double)fmaxf(t, -200.f) * (double)e;            // (masked logits: 0; a broken one shows in s)
+  }
+  return Lse{m, (float)wave_sum(s), (float)wave_sum(u)};
+}
+
 struct DraftShared {
   Lse l[kWaves];
   Top2 t[kWaves];
   int mode;      // 0 not the last workgroup of the row; 1 final; 2 settle among the close candidates;
-                 // 3 broken row; 4 whole row in float64
+                 // 3 broken row; 4 whole row in float64; 5 the same, and the entropy from the logits too
   float tau;
   double red[kWaves];
 };
@@ -126,6 +148,14 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
     st.u += u0 + u1;
   }
 
+  auto write_row = [&](const RowResult& res) {
+    dout.H_out[rho] = res.H;
+    if (dout.stop_out) {
+      const bool over = dout.T_G ? (res.H > dout.T_G[rho]) : false;
+      dout.stop_out[rho] = (uint8_t)(over || dout.force_stop || res.bad);
+    }
+  };
+
   // ---- the slice's record
   fold_wave<DRAW>(st, best);
   if (lane == 0) {
@@ -152,9 +182,10 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
     }
     if (last) {
       // ---- last workgroup of the row
+      bool arrived = true;
       if (S > 1) {
         uint64_t w[kXchgWords];
-        take_words(ws.xchg + ((size_t)rho * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w);
+        arrived = take_words(ws.xchg + ((size_t)rho * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w, dout.polls);
         st = lse_empty();
         best = Top2{-INFINITY, -1, -INFINITY, -1};
         if (lane < S) {
@@ -171,7 +202,8 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
       const RowResult res = finish_row(st);
       int mode = 1;
       if (DRAW) {
-        if (res.bad) mode = 3;
+        if (!arrived) mode = 5;
+        else if (res.bad) mode = 3;
         else if (best.i1 < 0) mode = 4;
         else if (!(best.k1 - best.k2 > kGuard)) mode = 2;
         if (mode == 2 && lane < S) {          // the slices' records, for the search for close candidates
@@ -183,17 +215,17 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
         }
       }
       if (lane == 0) {
-        dout.H_out[rho] = res.H;
-        if (dout.stop_out) {
-          const bool over = dout.T_G ? (res.H > dout.T_G[rho]) : false;
-          dout.stop_out[rho] = (uint8_t)(over || dout.force_stop || res.bad);
-        }
+        write_row(res);
         if (DRAW && (mode == 1 || mode == 3)) {
           dr.token_out[rho] = mode == 1 ? best.i1 : -1;
           if (dr.status) dr.status[rho] = mode == 1 ? 0u : (uint32_t)ADASD_ST_NONFINITE;
         }
         sh.mode = mode;
         sh.tau = best.k1 - kGuard;
+      }
+      if (!DRAW && __builtin_expect(!arrived, 0)) {
+        const RowResult whole = finish_row(wave_row_sums<DT>(r.ptr, V));
+        if (lane == 0) write_row(whole);
       }
     } else if (lane == 0) {
       sh.mode = 0;
@@ -203,6 +235,10 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
   __syncthreads();
   const int mode = sh.mode;
   if (mode == 0 || mode == 1 || mode == 3) return;
+  if (mode == 5 && wave == 0) {
+    const RowResult whole = finish_row(wave_row_sums<DT>(r.ptr, V));
+    if (lane == 0) write_row(whole);
+  }
   uint32_t bits = ADASD_ST_EXACT_PATH;
   int tok = -1;
   if (mode == 2) {

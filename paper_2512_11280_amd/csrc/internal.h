@@ -18,7 +18,7 @@ constexpr int kNarrowMax = kWideCap; // so the one-workgroup form never sees a l
 constexpr int kMaxSplit = 64;        // vocabulary slices per row (statistics kernels)
 constexpr int kMaxSampleSplit = 128; // vocabulary slices per sequence (sampling kernel)
 constexpr int kXchgWords = 3;        // 64-bit hand-off words per (position, slice) of the single-read statistics kernel
-constexpr int kWaitPolls = 16384;    // polls (about 25 ms) before a workgroup of that kernel stops waiting for the others
+constexpr int kWaitPolls = 16384;    // polls (about 4 ms) before a workgroup stops waiting for the words of others
 
 // Where the rows of one call live.  which = 0: target, 1: draft.
 struct RowMap {
@@ -68,6 +68,7 @@ struct DraftOut {     // draft-entropy epilogue
   float* H_out;
   uint8_t* stop_out;
   int32_t force_stop; // step + 1 >= k_max
+  int32_t polls;      // bound of the wait for the slices' records (see take_words)
 };
 
 struct DraftDraw {    // token draw of a drafting step (x_i ~ q_i)
@@ -196,6 +197,7 @@ struct SampleArgs {
   uint32_t round0;
   int32_t* next_token;
   uint32_t* status;
+  int32_t polls;        // bound of the wait for the slices' records (see take_words)
 };
 hipError_t launch_shard_sample(const SampleArgs& a, int S, int col0, const Workspace& ws, float4* top_out, hipStream_t st);
 hipError_t launch_shard_pick(int B, int G, const float4* top_all, const Workspace& ws, int32_t* next_token,

@@ -85,9 +85,10 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
     if (last) {
       // ---- last workgroup of this sequence: fold the S records
       Top2 t{-INFINITY, -1, -INFINITY, -1};
+      bool arrived = true;
       if (S > 1) {
         uint64_t w[kXchgWords];
-        take_words(ws.xchg + ((size_t)b * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w);
+        arrived = take_words(ws.xchg + ((size_t)b * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w, a.polls);
         if (lane < S) {
           const DrawRecord r = unpack_draw(w);
           t = Top2{r.k1, r.i1, r.k2, -1};
@@ -104,7 +105,9 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
       const Top2 top = top2_wave_reduce(t);
       float margin = kGuard;
       mode = 1;
-      if (poison) {
+      if (!arrived) {
+        mode = 4;   // (the float64 path looks at every logit, also for broken ones)
+      } else if (poison) {
         mode = 3;   // NaN / +inf in the bonus row
       } else if (top.i1 < 0) {
         mode = 4;   // nothing had (certain) mass

@@ -108,22 +108,27 @@ __device__ __forceinline__ float key_ub(float zp, float zq, float cp, float cq, 
 
 // Hand-off of slice records inside one launch: NW words per slice (records.h).  A workgroup sends its words, then takes a
 // ticket, and does not wait for the words to arrive in between: the one that takes the last ticket knows that all words
-// of the row have been sent, so it reads until they are there (which ends: nothing has to happen but stores already
-// under way), and clears them for the next launch.
-template <int NW> __device__ __forceinline__ void take_words(uint64_t* words, bool mine, uint64_t (&w)[NW]) {
-  bool ok;
+// of the row have been sent, so it reads until they are there, and clears them for the next launch.
+// The wait is bounded all the same: where calls that share a workspace are not ordered, one may clear the other's words.
+// After `polls` polls it returns false, and the caller settles the row from the logits themselves.  (polls < 0: false
+// once the words are there, which tests use to take that path.)
+template <int NW> __device__ __forceinline__ bool take_words(uint64_t* words, bool mine, uint64_t (&w)[NW], int polls) {
+  int left = polls < 0 ? kWaitPolls : polls;
+  bool all;
   do {
-    ok = true;
+    bool ok = true;
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       w[i] = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       ok = ok && (w[i] & 1ull);
     }
-  } while (!__all(ok || !mine));
+    all = __all(ok || !mine) != 0;
+  } while (!all && left-- > 0);
   if (mine) {
 #pragma unroll
     for (int i = 0; i < NW; ++i) __hip_atomic_store(words + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  return all && polls >= 0;
 }
 // (lane 0 takes it; true in every lane for the last of `count`)
 __device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {

@@ -1,4 +1,5 @@
 """GPU parity tests: the HIP library against the CPU oracle, through the C ABI (run with -m gpu)."""
+import ctypes as C
 import math
 import time
 
@@ -1465,6 +1466,72 @@ def test_bounded_wait_expiry_gives_identical_results(am, wl):
     c, _, _ = G.run_gpu(am, batch, ws=ws, stats_path=2)   # and the workspace is clean afterwards
     for k, v in snap.items():
         assert torch.equal(getattr(c, k), v), k
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [4001, 32000])
+def test_drafting_goes_on_where_slice_records_do_not_arrive(am, oracle, dtype, V):
+    """The path behind a wait that has run out (taken here although the records are there): entropy, stop flag and token
+    from the logits themselves; the workspace is clean afterwards."""
+    B = 5
+    g = torch.Generator().manual_seed(V)
+    z = (3.0 * torch.randn(B, V, generator=g)).to(dtype)
+    z[1, 10:] = -math.inf                                 # masked but for ten
+    z[2, V - 1] = math.nan
+    z[3, 7] = math.inf
+    z[4] = -math.inf
+    ws, zd = am.Workspace(B, 1, V, dtype), z.cuda()
+    Hn, stopn, tokn, stn = am.draft_step(zd, ws, step=1, seed=31, round0=4)
+    lib, code = am.load_library(), am.binding._dtype_code(zd)
+    fn = lib.adasd_test_draft_unarrived
+    fn.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int64, C.c_int, C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p,
+                   C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
+    H, He = torch.empty(2, B, device="cuda").unbind(0)
+    stop, tok, st = torch.zeros_like(stopn), torch.zeros_like(tokn), torch.zeros_like(stn)
+    stream = torch.cuda.current_stream().cuda_stream
+    for out, t, s in ((H, tok.data_ptr(), st.data_ptr()), (He, None, None)):
+        assert fn(zd.data_ptr(), code, B, V, V, 1, 31, 4, out.data_ptr(), stop.data_ptr(), t, s, ws.ptr, ws.bytes, stream) == 0
+    torch.cuda.synchronize()
+    Href, _ = oracle.draft_entropy(z, step=1)
+    assert G.close(H.cpu().numpy(), Href).all() and G.close(He.cpu().numpy(), Href).all()
+    assert torch.equal(tok, tokn) and torch.equal(stop, stopn)
+    bits = st.cpu().numpy()
+    assert (bits[[0, 1]] == am.binding.ST_EXACT_PATH).all() and (bits[2:] & am.binding.ST_NONFINITE).all()
+    again = am.draft_step(zd, ws, step=1, seed=31, round0=4)
+    for a, b in zip(again, (Hn, stopn, tokn, stn)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("literal", [0, 1])
+def test_token_draw_goes_on_where_slice_records_do_not_arrive(am, wl, oracle, dtype, literal):
+    """The same of the token kernel: replacement, excluded-token and bonus draws, a broken bonus row."""
+    B, K, V = 6, 3, 20011
+    batch = wl.config_batched(B=B, k=K, V=V, dtype=dtype, seed=52)
+    batch.draft[0] = batch.target[0, :K]                  # all accepted: the bonus row
+    batch.draft[1] = batch.target[1, :K]
+    batch.target[1, K, 3] = math.nan
+    options = am.Options(base_test=literal)
+    ref = G.run_oracle(oracle, batch, options=options)
+    t, d, tok = batch.target.cuda(), batch.draft.cuda(), batch.draft_tokens.cuda()
+    ws = am.Workspace(B, K, V, dtype)
+    st = G.state_to_device(am, batch.state, B, batch.state["LA"].shape[1])
+    out = am.binding.alloc_verify_result(B, K)
+    state, opt = st._c(), options._c()
+    a = am.binding._VerifyArgs(
+        t.data_ptr(), d.data_ptr(), am.binding._dtype_code(t), B, K, V, t.stride(0), t.stride(1), d.stride(0), d.stride(1),
+        tok.data_ptr(), None, C.pointer(state), batch.seed, None, None, batch.round0, out.n_accept.data_ptr(),
+        out.next_token.data_ptr(), out.H_p.data_ptr(), out.H_q.data_ptr(), out.d_js.data_ptr(), out.p_accept.data_ptr(),
+        out.accept_mask.data_ptr(), out.status.data_ptr(), ws.ptr, ws.bytes)
+    fn = am.load_library().adasd_test_verify_unarrived
+    fn.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
+    assert fn(C.byref(a), C.byref(opt), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    G.compare_verify(out, ref, info_bits=16 | 8)
+    drawn = ref["status"] & am.binding.ST_NONFINITE == 0
+    assert (out.status.cpu().numpy()[drawn] & am.binding.ST_EXACT_PATH).all()
+    again, _, _ = G.run_gpu(am, batch, options=options, ws=ws)
+    G.compare_verify(again, ref, info_bits=16 | 8)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
