@@ -411,18 +411,6 @@ SampleArgs sample_args(const adasd_verify_args* a, const VerifySetup& v) {
   return s;
 }
 
-// Slices per sequence of the sampling scan: as few vectors per thread as keep every workgroup resident (seven on each
-// of 256 compute units) and the slices within the limit of the hand-off words.
-int sample_split(int V, int dt, int B) {
-  const int epv = dt == ADASD_BF16 ? 8 : 4, nv = (V + epv - 1) / epv;
-  int turns = 1, S = 1;
-  while (true) {
-    S = (nv + turns * kBlock - 1) / (turns * kBlock);
-    if (S == 1 || (S <= kMaxSplit && (int64_t)S * B <= 1792)) return S;
-    ++turns;
-  }
-}
-
 }  // namespace
 
 static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void* stream, int token_polls) {
@@ -480,7 +468,7 @@ static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void*
 
   SampleArgs s = sample_args(a, v);
   s.polls = token_polls;
-  const int S3 = sample_split(V, (int)a->dt, B);
+  const int S3 = scan_split(B, V, (int)a->dt);
   {
     Scope sc(3, st);
     if (launch_sample(s, S3, ws, st) != hipSuccess) return ADASD_ERR_HIP;
@@ -647,7 +635,7 @@ int adasd_verify_shard_sample(const adasd_verify_args* local, const adasd_shard*
   hipStream_t st = (hipStream_t)stream;
   Scope sc(3, st);
   const SampleArgs s = sample_args(local, v);
-  return launch_shard_sample(s, sample_split(local->V, (int)local->dt, local->B), sh->col_begin, v.ws,
+  return launch_shard_sample(s, scan_split(local->B, local->V, (int)local->dt), sh->col_begin, v.ws,
                              reinterpret_cast<float4*>(top_out), st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
 }
 
@@ -678,7 +666,7 @@ int adasd_verify_shard_refine(const adasd_verify_args* local, const adasd_shard*
   hipStream_t st = (hipStream_t)stream;
   Scope sc(3, st);
   const SampleArgs s = sample_args(local, v);
-  return launch_shard_refine(s, sample_split(local->V, (int)local->dt, local->B), sh->col_begin, tau, exact_sums, v.ws, cand_out, st) == hipSuccess
+  return launch_shard_refine(s, scan_split(local->B, local->V, (int)local->dt), sh->col_begin, tau, exact_sums, v.ws, cand_out, st) == hipSuccess
              ? ADASD_OK : ADASD_ERR_HIP;
 }
 

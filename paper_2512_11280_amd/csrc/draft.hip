@@ -256,26 +256,11 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
 
 }  // namespace
 
-// Slices per row and vectors per slice of a drafting call: as few vectors per thread as keep every workgroup of the
-// call resident (seven workgroups on each of 256 compute units) and the slices within their limit; slices of
-// whole 128-byte lines.
-static void pick_draft_split(int rows, int V, int dt, int* S_out, int* chunk_out) {
-  const int epv = dt == ADASD_BF16 ? 8 : 4, nv = (V + epv - 1) / epv;
-  int turns = 1, S = 1;
-  while (true) {
-    S = (nv + turns * kBlock - 1) / (turns * kBlock);
-    if (S == 1 || (S <= kMaxSplit && (int64_t)S * rows <= 1792)) break;
-    ++turns;
-  }
-  *S_out = S;
-  *chunk_out = sampling::slice_chunk(nv, S);
-}
-
 hipError_t launch_draft_step(const RowMap& map, int dt, const Workspace& ws, const DraftOut& dout,
                              const DraftDraw* draw, hipStream_t st) {
   if (map.B <= 0) return hipSuccess;
-  int S, chunk;
-  pick_draft_split(map.B, map.V, dt, &S, &chunk);
+  const int S = scan_split(map.B, map.V, dt), epv = dt == ADASD_BF16 ? 8 : 4;
+  const int chunk = sampling::slice_chunk((map.V + epv - 1) / epv, S);
   const dim3 grid(S, map.B), block(kBlock);
   const DraftDraw dr = draw ? *draw : DraftDraw{};
   if (dt == ADASD_BF16) {

@@ -109,6 +109,24 @@ inline void launch_kernel(Kernel kernel, dim3 grid, dim3 block, hipStream_t st, 
 
 int pick_split(int rows, int V, int dt);
 
+// Slices per row of the drafting and token scans.  Up to 896 rows: as few vectors per thread (turns) as keep every
+// workgroup resident (seven on each of 256 compute units) and the slices within the limit of the hand-off words.  With more
+// rows that would be one slice per row, which leaves compute units with three workgroups beside others with four, or
+// a nearly empty second round: up to eight rounds then, in slices of four turns at least.  B rows of 128256, one slice
+// per row / eight rounds (kernel, us): token bf16 B=897 177 / 117, 1200 214 / 158, 1793 302 / 223; drafted tokens bf16
+// 127 / 115, 160 / 156, 240 / 224; entropies float 92 / 81, 105 / 108, 153 / 159 (four rounds: 86, 108, 159).  Rows of
+// 5003, which stay in one slice: token B=1793 15 us, in more slices 20.
+constexpr int kResidentGroups = 1792;
+inline int scan_split(int rows, int V, int dt) {
+  const int epv = dt == ADASD_BF16 ? 8 : 4, nv = (V + epv - 1) / epv;
+  const bool many = rows > kResidentGroups / 2;
+  const int64_t most = many ? 8 * kResidentGroups : kResidentGroups;
+  for (int turns = many ? 4 : 1;; ++turns) {
+    const int S = (nv + turns * kBlock - 1) / (turns * kBlock);
+    if (S == 1 || (S <= kMaxSplit && (int64_t)S * rows <= most)) return S;
+  }
+}
+
 // Ragged windows: the positions i < draft_len[b] of all sequences, packed into slots[0 .. n) in the order
 // (window position, sequence), -1 in the remaining slots up to B*K (one small kernel).
 hipError_t launch_pack_slots(const int32_t* draft_len, int B, int K, int32_t* slots, hipStream_t st);

@@ -1468,6 +1468,21 @@ def test_bounded_wait_expiry_gives_identical_results(am, wl):
         assert torch.equal(getattr(c, k), v), k
 
 
+@pytest.mark.parametrize("B,V,dtype", [(896, 2048, torch.float32), (897, 4096, torch.float32), (897, 4100, torch.float32),
+                                       (1793, 8200, torch.bfloat16), (2100, 16385, torch.bfloat16)])
+def test_batches_beyond_a_full_chip(am, wl, oracle, B, V, dtype):
+    """More rows than a full chip takes at a slice or two each: one slice per row (up to four turns of a workgroup), or
+    slices in several rounds.  Drafted tokens and tokens of a round, against the oracle."""
+    g = torch.Generator().manual_seed(B)
+    z = (3.0 * torch.randn(B, V, generator=g)).to(dtype)
+    H, stop, tok, st, ref_tok, gap = _draft_step_case(am, oracle, z, step=1, seed=8, round0=2)
+    Href, _ = oracle.draft_entropy(z, step=1)
+    assert G.close(H, Href).all() and np.array_equal(tok, ref_tok)
+    batch = wl.config_batched(B=B, k=1, V=V, dtype=dtype, seed=V)
+    out, _, _ = G.run_gpu(am, batch)
+    G.compare_verify(out, G.run_oracle(oracle, batch))
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V", [4001, 32000])
 def test_drafting_goes_on_where_slice_records_do_not_arrive(am, oracle, dtype, V):
