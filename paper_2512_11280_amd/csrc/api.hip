@@ -468,7 +468,7 @@ static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void*
 
   SampleArgs s = sample_args(a, v);
   s.polls = token_polls;
-  const int S3 = scan_split(B, V, (int)a->dt);
+  const int S3 = token_split(B, V, (int)a->dt);
   {
     Scope sc(3, st);
     if (launch_sample(s, S3, ws, st) != hipSuccess) return ADASD_ERR_HIP;
@@ -635,7 +635,7 @@ int adasd_verify_shard_sample(const adasd_verify_args* local, const adasd_shard*
   hipStream_t st = (hipStream_t)stream;
   Scope sc(3, st);
   const SampleArgs s = sample_args(local, v);
-  return launch_shard_sample(s, scan_split(local->B, local->V, (int)local->dt), sh->col_begin, v.ws,
+  return launch_shard_sample(s, token_split(local->B, local->V, (int)local->dt), sh->col_begin, v.ws,
                              reinterpret_cast<float4*>(top_out), st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
 }
 
@@ -666,7 +666,7 @@ int adasd_verify_shard_refine(const adasd_verify_args* local, const adasd_shard*
   hipStream_t st = (hipStream_t)stream;
   Scope sc(3, st);
   const SampleArgs s = sample_args(local, v);
-  return launch_shard_refine(s, scan_split(local->B, local->V, (int)local->dt), sh->col_begin, tau, exact_sums, v.ws, cand_out, st) == hipSuccess
+  return launch_shard_refine(s, token_split(local->B, local->V, (int)local->dt), sh->col_begin, tau, exact_sums, v.ws, cand_out, st) == hipSuccess
              ? ADASD_OK : ADASD_ERR_HIP;
 }
 

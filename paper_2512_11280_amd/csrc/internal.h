@@ -117,14 +117,24 @@ int pick_split(int rows, int V, int dt);
 // 127 / 115, 160 / 156, 240 / 224; entropies float 92 / 81, 105 / 108, 153 / 159 (four rounds: 86, 108, 159).  Rows of
 // 5003, which stay in one slice: token B=1793 15 us, in more slices 20.
 constexpr int kResidentGroups = 1792;
-inline int scan_split(int rows, int V, int dt) {
+inline int scan_split(int rows, int V, int dt, int slices = kMaxSplit) {
   const int epv = dt == ADASD_BF16 ? 8 : 4, nv = (V + epv - 1) / epv;
   const bool many = rows > kResidentGroups / 2;
   const int64_t most = many ? 8 * kResidentGroups : kResidentGroups;
   for (int turns = many ? 4 : 1;; ++turns) {
     const int S = (nv + turns * kBlock - 1) / (turns * kBlock);
-    if (S == 1 || (S <= kMaxSplit && (int64_t)S * rows <= most)) return S;
+    if (S == 1 || (S <= slices && (int64_t)S * rows <= most)) return S;
   }
+}
+
+// The same for the token scan.  Rows of more than 65536 vectors (four turns of a workgroup in each of 64 slices) are cut
+// into up to 128 slices, more than there are hand-off words, and take the form of the kernel for those: a few sequences'
+// slices do not fill the chip.  One sequence (kernel, us), 64 slices / 128: 400000 float 8.3 / 7.7, 1048576 bf16 11.1 / 9.0,
+// 1048576 float 13.4 / 9.4, 4194304 bf16 33 / 19, float 41 / 20.
+constexpr int kLongRow = 65536;
+inline int token_split(int rows, int V, int dt) {
+  const int epv = dt == ADASD_BF16 ? 8 : 4, nv = (V + epv - 1) / epv;
+  return scan_split(rows, V, dt, nv > kLongRow ? kMaxSampleSplit : kMaxSplit);
 }
 
 // Ragged windows: the positions i < draft_len[b] of all sequences, packed into slots[0 .. n) in the order

@@ -17,19 +17,27 @@ namespace {
 using namespace sampling;
 
 // The scan of a sequence's row(s) under its plan.
-template <int DT>
+template <int DT, bool LONG>
 __device__ __forceinline__ void scan_plan(const SamplePlan& plan, const char* prow, const char* qrow, int V, int v0, int v1,
                                           int col0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
                                           Top2& best, bool& poison) {
   const float cp = (float)plan.lse2_p, cq = (float)plan.lse2_q;
   const PhiloxRow noise = philox_row(c1, c2, c3, k0, k1);
+  if (LONG) {
+    if (plan.residual == kResidual) scan_long_slice<DT, kResidual>(prow, qrow, V, v0, v1, cp, cq, -1, noise, best, poison);
+    else if (plan.residual == kExclude) scan_long_slice<DT, kExclude>(prow, qrow, V, v0, v1, cp, cq, plan.excluded, noise, best, poison);
+    else scan_long_slice<DT, kPlain>(prow, qrow, V, v0, v1, cp, cq, -1, noise, best, poison);
+    return;
+  }
   if (plan.residual == kResidual) scan_slice<DT, kResidual>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, poison);
   else if (plan.residual == kExclude) scan_slice<DT, kExclude>(prow, qrow, V, v0, v1, cp, cq, plan.excluded, col0, noise, best, poison);
   else scan_slice<DT, kPlain>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, poison);
 }
 
-template <int DT>
-__global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int chunk, Workspace ws) {
+// LONG: a row of more slices than there are hand-off words (see token_split).  The records then go through part3, and have
+// landed before the ticket is taken; and a compute unit holds no more than one such workgroup of a few sequences.
+template <int DT, bool LONG>
+__global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, int S, int chunk, Workspace ws) {
   warm_kernargs<sizeof(SampleArgs) + 2 * sizeof(int) + sizeof(Workspace)>();
   const int b = blockIdx.y, s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const SamplePlan plan = ws.plan[b];
@@ -49,7 +57,7 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
   const int nv = vectors_of<DT>(V), v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
   Top2 best{-INFINITY, -1, -INFINITY, -1};
   bool poison = false;
-  scan_plan<DT>(plan, prow, qrow, V, v0, v1, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
+  scan_plan<DT, LONG>(plan, prow, qrow, V, v0, v1, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
 
   __shared__ Top2 sh_top[kWaves];
   // modes: 0 not the last workgroup; 1 final; 2 settle among the close candidates; 3 broken bonus row; 4 whole row in float64
@@ -73,7 +81,17 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
       zp = load_elem<DT>(prow, best.i1);
       if (plan.residual == kResidual) zq = load_elem<DT>(qrow, best.i1);
     }
-    if (S > 1) {
+    if (LONG) {
+      if (lane == 0) {
+        Top2* dst = &ws.part3[(size_t)b * kMaxSampleSplit + s];
+        st_agent(&dst->k1, best.k1);
+        st_agent(&dst->i1, best.i1);
+        st_agent(&dst->k2, best.k2);
+        st_agent(&dst->i2, poison ? -2 : -1);
+      }
+      publish_barrier();
+      last = take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S);
+    } else if (S > 1) {
       uint64_t* words = ws.xchg + ((size_t)b * kMaxSplit + s) * kXchgWords;
       uint64_t w[kXchgWords];
       pack_draw(DrawRecord{best.k1, best.k2, zp, zq, best.i1, poison}, w);
@@ -86,7 +104,15 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
       // ---- last workgroup of this sequence: fold the S records
       Top2 t{-INFINITY, -1, -INFINITY, -1};
       bool arrived = true;
-      if (S > 1) {
+      if (LONG) {
+        poison = false;
+        for (int j = lane; j < S; j += 64) {
+          const Top2* src = &ws.part3[(size_t)b * kMaxSampleSplit + j];
+          t = top2_merge(t, Top2{ld_agent(&src->k1), ld_agent(&src->i1), ld_agent(&src->k2), -1});
+          poison |= ld_agent(&src->i2) == -2;
+        }
+        poison = __any(poison);
+      } else if (S > 1) {
         uint64_t w[kXchgWords];
         arrived = take_words(ws.xchg + ((size_t)b * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w, a.polls);
         if (lane < S) {
@@ -114,6 +140,10 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
       } else {
         if (plan.residual == kResidual) {
           const int owner = S > 1 ? __ffsll((long long)__ballot(t.i1 == top.i1)) - 1 : 0;
+          if (LONG) {
+            zp = load_elem<DT>(prow, top.i1);
+            zq = load_elem<DT>(qrow, top.i1);
+          }
           const float p = ex2(fmaf(lane_value(zp, owner), kLog2e, -(float)plan.lse2_p));
           const float q = ex2(fmaf(lane_value(zq, owner), kLog2e, -(float)plan.lse2_q));
           const float err = kErrRel * (p + q), w = p - q;
@@ -124,7 +154,7 @@ __global__ void __launch_bounds__(kBlock, 7) k_sample(SampleArgs a, int S, int c
         // an element whose upper bound stays below the winner's lower bound cannot be the true winner
         if (mode == 1 && !(top.k1 - top.k2 > margin)) mode = 2;
       }
-      if (mode == 2 && lane < S) {            // the slices' records, for the search for close candidates
+      if (!LONG && mode == 2 && lane < S) {   // the slices' records, for the search for close candidates
         Top2* dst = &ws.part3[(size_t)b * kMaxSampleSplit + lane];
         st_agent(&dst->k1, t.k1);
         st_agent(&dst->i1, t.i1);
@@ -195,7 +225,7 @@ __global__ void __launch_bounds__(kBlock, 5) k_shard_scan(SampleArgs a, int S, i
   const int nv = vectors_of<DT>(V), chunk = slice_chunk(nv, S), v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
   Top2 best{-INFINITY, -1, -INFINITY, -1};
   bool poison = false;
-  scan_plan<DT>(plan, prow, qrow, V, v0, v1, col0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
+  scan_plan<DT, false>(plan, prow, qrow, V, v0, v1, col0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
   __shared__ Top2 sh_top[kWaves];
   __shared__ int sh_flag[kWaves];
   best = top2_wave_reduce(best);
@@ -458,8 +488,13 @@ hipError_t launch_sample(const SampleArgs& a, int S, const Workspace& ws, hipStr
   if (a.map.B <= 0) return hipSuccess;
   const dim3 grid(S, a.map.B), block(kBlock);
   const int epv = a.dt == ADASD_BF16 ? 8 : 4, chunk = slice_chunk((a.map.V + epv - 1) / epv, S);
-  if (a.dt == ADASD_BF16) launch_kernel(k_sample<ADASD_BF16>, grid, block, st, a, S, chunk, ws);
-  else launch_kernel(k_sample<ADASD_F32>, grid, block, st, a, S, chunk, ws);
+  if (S > kMaxSplit) {
+    if (a.dt == ADASD_BF16) launch_kernel((k_sample<ADASD_BF16, true>), grid, block, st, a, S, chunk, ws);
+    else launch_kernel((k_sample<ADASD_F32, true>), grid, block, st, a, S, chunk, ws);
+  } else {
+    if (a.dt == ADASD_BF16) launch_kernel((k_sample<ADASD_BF16, false>), grid, block, st, a, S, chunk, ws);
+    else launch_kernel((k_sample<ADASD_F32, false>), grid, block, st, a, S, chunk, ws);
+  }
   return hipGetLastError();
 }
 

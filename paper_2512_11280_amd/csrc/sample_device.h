@@ -139,6 +139,36 @@ __device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {
   return last;
 }
 
+// Four logits (group g of a vector, the first of index `first`) with their block of noise.
+template <int DT, int MODE>
+__device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int g, int first, const U4& block, float neg_cp,
+                                           float neg_cq, int excluded, Top2& best, bool& poison) {
+  float zp[4], key[4], lE[4];
+  unpack4<DT>(xp, g, zp);
+  if (MODE == kResidual) {
+    float zq[4], p[4], q[4];
+    unpack4<DT>(xq, g, zq);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      zp[i] = fma_log2e(zp[i], neg_cp);
+      zq[i] = fma_log2e(zq[i], neg_cq);
+    }
+    ex2_group(zp, p);
+    ex2_group(zq, q);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = max_raw(fmaf(kErrRel, p[i] + q[i], p[i] - q[i]), 0.f);
+    lg2_group(p, key);
+  }
+  log2_exponential4(block, lE);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (MODE == kPlain) poison |= !(zp[i] < INFINITY);       // NaN or +inf in the bonus row
+    float k = MODE == kResidual ? key[i] - lE[i] : fma_log2e(zp[i], -lE[i]);
+    if (MODE == kExclude) k = first + i == excluded ? -INFINITY : k;
+    top2_push(best, k, first + i);
+  }
+}
+
 // ---- the scan of one slice ----------------------------------------------------------------------
 // Vectors v0 .. v1 of the row(s), one per thread and turn, the next one always on its way.  col0: vocabulary index of
 // the row's first element (0 unless the row is a column slice; a multiple of eight); indices, the excluded token
@@ -179,31 +209,53 @@ __device__ __forceinline__ void scan_slice(const char* prow, const char* qrow, i
 #pragma unroll
     for (int g = 0; g < EPV / 4; ++g) {
       const int first = col0 + idx * EPV + 4 * g;
-      float zp[4], key[4], lE[4];
-      unpack4<DT>(xp, g, zp);
-      if (RESIDUAL) {
-        float zq[4], p[4], q[4];
-        unpack4<DT>(xq, g, zq);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          zp[i] = fma_log2e(zp[i], neg_cp);
-          zq[i] = fma_log2e(zq[i], neg_cq);
-        }
-        ex2_group(zp, p);
-        ex2_group(zq, q);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) p[i] = max_raw(fmaf(kErrRel, p[i] + q[i], p[i] - q[i]), 0.f);
-        lg2_group(p, key);
-      }
-      log2_exponential4(philox_block(noise, (uint32_t)first >> 2), lE);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (MODE == kPlain) poison |= !(zp[i] < INFINITY);       // NaN or +inf in the bonus row
-        float k = RESIDUAL ? key[i] - lE[i] : fma_log2e(zp[i], -lE[i]);
-        if (MODE == kExclude) k = first + i == excluded ? -INFINITY : k;
-        top2_push(best, k, first + i);
-      }
+      scan_group<DT, MODE>(xp, xq, g, first, philox_block(noise, (uint32_t)first >> 2), neg_cp, neg_cq, excluded, best, poison);
     }
+  }
+}
+
+// The same where a long row has no more than its slices on the chip, one wavefront to a SIMD: sixteen logits per thread
+// and turn, whose noise is formed ahead of the rest, so that the chains of four Philox blocks fill each other's gaps.
+template <int DT, int MODE>
+__device__ __forceinline__ void scan_long_slice(const char* prow, const char* qrow, int V, int v0, int v1, float cp, float cq,
+                                                int excluded, const PhiloxRow& noise, Top2& best, bool& poison) {
+  constexpr bool RESIDUAL = MODE == kResidual;
+  constexpr int EPV = Elem<DT>::per_vec, G = EPV / 4, NV = 4 / G;
+  const int tid = threadIdx.x, whole = V / EPV;
+  // (requested without a branch: between loads that may or may not be made the compiler waits for the one before)
+  uint4 next_p[NV], next_q[NV];
+  auto request = [&](int base) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int idx = min(base + tid + j * kBlock, whole - 1);
+      next_p[j] = load_vec_any(prow, idx);
+      if (RESIDUAL) next_q[j] = load_vec_any(qrow, idx);
+    }
+  };
+  auto settle = [&](const char* row, int idx, const uint4& x) {     // what stands there: past the slice's end -inf in every logit
+    const uint4 none = neutral_vec<DT>();
+    const bool in = idx < v1;
+    uint4 y = make_uint4(in ? x.x : none.x, in ? x.y : none.y, in ? x.z : none.z, in ? x.w : none.w);
+    if (in && idx == whole) y = load_last_vec<DT>(row, V);
+    return y;
+  };
+  request(v0);
+  for (int base = v0; base < v1; base += NV * kBlock) {
+    uint4 xp[NV], xq[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      xp[j] = xq[j] = settle(prow, base + tid + j * kBlock, next_p[j]);
+      if (RESIDUAL) xq[j] = settle(qrow, base + tid + j * kBlock, next_q[j]);
+    }
+    if (base + NV * kBlock < v1) request(base + NV * kBlock);
+    if (base + (tid & ~63) >= v1) continue;     // (a whole wavefront past the end)
+    U4 block[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) block[j] = philox_block(noise, (uint32_t)((base + tid + j / G * kBlock) * EPV + j % G * 4) >> 2);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      scan_group<DT, MODE>(xp[j / G], xq[j / G], j % G, (base + tid + j / G * kBlock) * EPV + j % G * 4, block[j], -cp, -cq, excluded,
+                           best, poison);
   }
 }
 
@@ -243,7 +295,7 @@ __device__ double row_lse_exact(const char* row, int V, double* sh) {
 
 // Returns the token (all threads), -1 if the row has no finite logit.
 template <int DT>
-__device__ int sample_exact(const char* prow, const char* qrow, bool residual, int excluded, int V, uint32_t c1,
+__device__ __forceinline__ int sample_exact(const char* prow, const char* qrow, bool residual, int excluded, int V, uint32_t c1,
                             uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1, double* sh,
                             uint32_t* status_bits) {
   const double lse_p = row_lse_exact<DT>(prow, V, sh);
@@ -413,7 +465,7 @@ __device__ bool refine_gather(const char* prow, const char* qrow, bool residual,
 // Settles a sequence among the elements whose upper-bound key is at least tau.  All threads of the
 // workgroup call it; returns the token, or -1 if the decision needs the whole row in float64.
 template <int DT>
-__device__ int sample_refine(const char* prow, const char* qrow, int mode, int excluded, int V, int b, int S,
+__device__ __forceinline__ int sample_refine(const char* prow, const char* qrow, int mode, int excluded, int V, int b, int S,
                              float tau, float cp, float cq, double lse2_p, double lse2_q, uint32_t c1,
                              uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1, const Workspace& ws,
                              double* sh_red, RefineShared& R) {

@@ -1483,6 +1483,38 @@ def test_batches_beyond_a_full_chip(am, wl, oracle, B, V, dtype):
     G.compare_verify(out, G.run_oracle(oracle, batch))
 
 
+@pytest.mark.parametrize("dtype,V", [(torch.float32, 262144), (torch.float32, 262145), (torch.float32, 800003),
+                                     (torch.float32, 1100000), (torch.bfloat16, 524289), (torch.bfloat16, 1600008)])
+@pytest.mark.parametrize("literal", [0, 1])
+def test_token_draws_from_long_rows(am, wl, oracle, dtype, V, literal):
+    """On both sides of the line from which a row has more slices than hand-off words: a bonus draw, replacement or
+    excluded-token draws, a broken bonus row, and two elements so close that float64 decides."""
+    B, K = 5, 1
+    batch = wl.config_batched(B=B, k=K, V=V, dtype=dtype, seed=V + literal)
+    for b in range(B):
+        x = int(batch.draft_tokens[b, 0])
+        if b in (1, 2):                                   # the draft puts all its mass where the target has none: rejected
+            batch.draft[b, 0, x], batch.target[b, 0, x] = 40.0, -40.0
+        else:                                             # both put all of it on the drafted token: accepted under either test
+            batch.draft[b, 0, x] = batch.target[b, 0, x] = 60.0
+    batch.target[3, K, V - 2] = math.nan
+    words = noise_words_of_row(batch.seed, 4, batch.round0, K, 1, V)      # sequence 4, its bonus row
+    order = np.argsort(words.astype(np.int64))
+    i, j = int(order[V // 2]), int(order[V // 2 + 1])     # neighbours among the noise words: keys 1e-6 nats apart
+    batch.target[4, K] = -30.0
+    batch.target[4, K, i] = batch.target[4, K, j] = 20.0
+    options = am.Options(base_test=literal)
+    ref = G.run_oracle(oracle, batch, options=options)
+    assert ref["n_accept"].tolist() == [1, 0, 0, 1, 1]
+    ws = am.Workspace(B, K, V, dtype)
+    for _ in range(2):
+        out, _, _ = G.run_gpu(am, batch, options=options, ws=ws)
+        G.compare_verify(out, ref, info_bits=16 | 8)
+        st = out.status.cpu().numpy() & (am.binding.ST_EXACT_PATH | am.binding.ST_NONFINITE)
+        assert st.tolist() == [0, 0, 0, am.binding.ST_NONFINITE, am.binding.ST_EXACT_PATH]
+        assert out.next_token[4].item() in (i, j)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V", [4001, 32000])
 def test_drafting_goes_on_where_slice_records_do_not_arrive(am, oracle, dtype, V):
