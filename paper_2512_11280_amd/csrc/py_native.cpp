@@ -11,6 +11,7 @@
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/adasd.h"
@@ -127,10 +128,16 @@ void* raw(PyObject* from, PyObject* name) {               // data pointer of a t
   Ref r(from, name);
   return r.o == Py_None ? nullptr : tensor(r.o, "state and result fields").data_ptr();
 }
-adasd_dtype logits_type(const at::Tensor& t) {
+adasd_dtype logits_type(PyObject* o) {
+  const at::Tensor& t = THPVariable_Unpack(o);
   if (t.scalar_type() == at::kBFloat16) return ADASD_BF16;
   if (t.scalar_type() == at::kFloat) return ADASD_F32;
-  fail(PyExc_TypeError, "logits must be bfloat16 or float32");
+  PyObject* type = PyObject_GetAttrString(o, "dtype");
+  if (type) {
+    PyErr_Format(PyExc_TypeError, "logits must be bfloat16 or float32, got %S", type);
+    Py_DECREF(type);
+  }
+  throw Fail{};
 }
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
@@ -186,8 +193,8 @@ template <class F> PyObject* guarded(F f) {
     return f();
   } catch (const Fail&) {
     return nullptr;
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {                      // out of memory, a failed stream look-up, ...: the classes that torch's own calls raise
+    torch::translate_exception_to_python(std::current_exception());
     return nullptr;
   }
 }
@@ -203,7 +210,7 @@ PyObject* py_draft_entropy(PyObject*, PyObject* const* args, Py_ssize_t nargs, P
     Output H(a[6], B, at::kFloat, x, "H_out"), stop(a[7], B, at::kByte, x, "stop_out");
     const float* tg = (const float*)maybe(a[2], at::kFloat, "T_G");
     const uint8_t* active = (const uint8_t*)maybe(a[3], at::kByte, "active");
-    const adasd_dtype dt = logits_type(x);
+    const adasd_dtype dt = logits_type(a[0]);
     const int step = (int)integer(a[4], 0), k_max = (int)integer(a[5], 1 << 30);
     const int64_t stride = B > 1 ? x.stride(0) : V;
     void *ws = (void*)int_attr(a[1], N->ptr), *st = stream(), *rows = x.data_ptr();
@@ -237,7 +244,7 @@ PyObject* py_draft_step(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyOb
     const uint32_t* rounds = (const uint32_t*)maybe(a[8], at::kInt, "rounds");
     Output H(a[10], B, at::kFloat, x, "H_out"), stop(a[11], B, at::kByte, x, "stop_out"),
         token(a[12], B, at::kInt, x, "token_out"), status(a[13], B, at::kInt, x, "status_out");
-    const adasd_dtype dt = logits_type(x);
+    const adasd_dtype dt = logits_type(a[0]);
     const int step = (int)integer(a[4], 0), k_max = (int)integer(a[5], 1 << 30);
     const uint64_t seed = integer(a[6], 0);
     const uint32_t round0 = (uint32_t)integer(a[9], 0);
@@ -283,7 +290,7 @@ PyObject* py_verify(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject
     v.round = (const uint32_t*)maybe(a[8], at::kInt, "rounds");
     v.target_logits = p.data_ptr();
     v.draft_logits = q.data_ptr();
-    v.dt = logits_type(p);
+    v.dt = logits_type(a[0]);
     v.B = (int32_t)B;
     v.k_max = (int32_t)K;
     v.V = (int32_t)V;

@@ -1122,6 +1122,26 @@ def test_draft_step_weighs_the_smallest_noise_words(am, oracle, round0, v, word,
     assert np.array_equal(tok, ref_tok)
 
 
+def test_native_binding_raises_the_errors_of_the_calls_it_makes(am):
+    """Output allocations that fail are torch's out-of-memory error (nothing is launched: the rows are one row repeated and
+    the output would be 4 GiB under a limit far below that); the type error names the type it got."""
+    row = torch.zeros(1, 64, dtype=torch.bfloat16, device="cuda")
+    ws = am.Workspace(1, 1, 64, torch.bfloat16)
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction(min(1.0, (torch.cuda.memory_reserved() + 2**30) / total))
+    try:
+        for call in (am.draft_step, am.draft_entropy):
+            with pytest.raises(torch.OutOfMemoryError):
+                call(row.expand(1 << 30, 64), ws)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    z, tok = torch.zeros(1, 3, 64, dtype=torch.float16, device="cuda"), torch.zeros(1, 2, dtype=torch.int32, device="cuda")
+    for call in (lambda: am.draft_step(z[0], ws), lambda: am.draft_entropy(z[0], ws), lambda: am.verify(z, z[:, :2], tok, ws)):
+        with pytest.raises(TypeError, match="got torch.float16"):
+            call()
+
+
 def test_draft_step_argument_errors(am):
     ws = am.Workspace(2, 1, 64, torch.float32)
     z = torch.zeros(2, 64, device="cuda")
