@@ -1,6 +1,7 @@
 """Builds libadasd.so (HIP, gfx950 only) and the native half of the binding in-tree with hipcc and g++."""
 from __future__ import annotations
 
+import importlib.metadata
 import importlib.util
 import os
 import subprocess
@@ -27,6 +28,12 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 
 NATIVE = os.path.join(HERE, "_native.so")
 NATIVE_SRC = os.path.join(CSRC, "py_native.cpp")
+NATIVE_FOR = os.path.join(BUILD, "native_for.txt")     # what the extension was built against
+
+
+def _native_abi() -> str:
+    """The extension is tied to the C++ interface of the installed torch and to the interpreter's."""
+    return f"torch {importlib.metadata.version('torch')} {sysconfig.get_config_var('SOABI')}"
 
 
 def _compile_native() -> str:
@@ -40,6 +47,8 @@ def _compile_native() -> str:
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"{cmd[0]} failed on {NATIVE_SRC}:\n{res.stderr}")
+    with open(NATIVE_FOR, "w") as f:
+        f.write(_native_abi())
     return NATIVE
 
 
@@ -56,12 +65,21 @@ def _compile(src: str) -> str:
     return obj
 
 
+def up_to_date() -> bool:
+    """Both libraries are newer than every source and header, and the extension was built against this torch."""
+    deps = [os.path.join(CSRC, f) for f in SOURCES] + HEADERS + [NATIVE_SRC]
+    newest = max(map(os.path.getmtime, deps))
+    if not all(os.path.exists(f) and os.path.getmtime(f) >= newest for f in (LIB, NATIVE)) or not os.path.exists(NATIVE_FOR):
+        return False
+    with open(NATIVE_FOR) as f:
+        return f.read() == _native_abi()
+
+
 def build(force: bool = True, jobs: int = 4) -> str:
     """Compile every HIP source and link the shared library.  With force=False the build is
-    skipped when the library is newer than every source and header."""
+    skipped when what is there is up to date."""
     os.makedirs(BUILD, exist_ok=True)
-    deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS + [NATIVE_SRC]
-    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= max(map(os.path.getmtime, deps)) for f in (LIB, NATIVE)):
+    if not force and up_to_date():
         return LIB
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         native = ex.submit(_compile_native)

@@ -111,6 +111,17 @@ def test_binding_refuses_to_run_without_the_library(monkeypatch, tmp_path):
         b.load_library()
 
 
+def test_extension_of_another_torch_is_not_up_to_date(monkeypatch):
+    """The native half of the binding is tied to torch's C++ interface: after a torch upgrade it has to be built again,
+    whatever the file times say."""
+    from paper_2512_11280_amd import build as b
+    b.build(force=False)
+    assert b.up_to_date()
+    there = b.importlib.metadata.version
+    monkeypatch.setattr(b.importlib.metadata, "version", lambda name: there(name) + ".next" if name == "torch" else there(name))
+    assert not b.up_to_date()
+
+
 @pytest.mark.parametrize("call, error, text", [
     (lambda am, z: am.draft_step(z[0], None), ValueError, "draft_logits must be a CUDA tensor"),
     (lambda am, z: am.draft_entropy(z, None), ValueError, "draft_logits must be a CUDA tensor"),
