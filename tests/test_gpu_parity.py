@@ -221,8 +221,9 @@ def test_small_and_ragged_vocabularies(am, wl, oracle, dtype, V, path):
     _report(f"V={V},{dtype}", rep)
 
 
-def test_unaligned_rows_take_the_elementwise_path(am, wl, oracle):
-    # an odd vocabulary stride makes most rows start off a 16-byte boundary
+def test_unaligned_rows(am, wl, oracle, path):
+    # an odd vocabulary stride makes most rows start off a 16-byte boundary: read by element in the two-kernel path, by
+    # vectors at any address in the single-read one
     batch = wl.config_batched(B=4, k=3, V=3001, seed=5)
     t = torch.zeros(4, 4, 3003, dtype=torch.bfloat16)
     d = torch.zeros(4, 3, 3003, dtype=torch.bfloat16)
@@ -231,7 +232,7 @@ def test_unaligned_rows_take_the_elementwise_path(am, wl, oracle):
     tg, dg = t.cuda()[:, :, :3001], d.cuda()[:, :, :3001]
     ws = am.Workspace(4, 3, 3001, torch.bfloat16)
     st = G.state_to_device(am, batch.state, 4, batch.state["LA"].shape[1])
-    out = am.verify(tg, dg, batch.draft_tokens.cuda(), ws, state=st, seed=batch.seed)
+    out = am.verify(tg, dg, batch.draft_tokens.cuda(), ws, state=st, seed=batch.seed, options=am.Options(stats_path=path))
     torch.cuda.synchronize()
     rep = G.compare_verify(out, G.run_oracle(oracle, batch))
     _report("unaligned", rep)
@@ -1652,21 +1653,14 @@ def test_entropies_are_as_accurate_as_their_sums_allow(am, dtype, B, V):
         assert rms < 5e-8 and abs(mean) < 2e-8
 
 
-@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("vectors,extra", [(1, 0), (1, 1), (2, -1), (256, 1), (257, 3), (512, 1), (1024, 3), (2048, -1),
-                                           (2048, 1), (4096, 1), (8017, 3)])
-@pytest.mark.parametrize("offset", [0, 1])
-def test_single_read_kernel_takes_rows_of_any_length_and_start(am, wl, oracle, dtype, vectors, extra, offset):
-    """A last vector that is not whole, alone in its turn or in a slice of its own, with the favoured token or a masked one
-    in it and in the logits that the vector before shares with it; rows that start off a 16-byte boundary."""
-    V, B, K = vectors * (8 if dtype == torch.bfloat16 else 4) + extra, 4, 3
+def _rows_at(am, wl, oracle, dtype, B, K, V, offset):
     batch = wl.config_batched(B=B, k=K, V=V, dtype=dtype, seed=V + offset)
     top = batch.target.float().amax().item() + 2.0
-    batch.target[1, :, V - 1] = top                       # the last logit carries the row
-    batch.draft[1, :, max(V - 2, 0)] = top
-    batch.target[2, :, max(V - 9, 1):V - 1] = -math.inf   # masked logits on both sides of the cut
-    batch.draft[2, :, max(V - 9, 1):V - 2] = -math.inf
-    batch.draft[3, :, V - 1] = -math.inf
+    batch.target[1:2, :, V - 1] = top                     # the last logit carries the row
+    batch.draft[1:2, :, max(V - 2, 0)] = top
+    batch.target[2:3, :, max(V - 9, 1):V - 1] = -math.inf # masked logits on both sides of the cut
+    batch.draft[2:3, :, max(V - 9, 1):V - 2] = -math.inf
+    batch.draft[3:, :, V - 1] = -math.inf
     batch.draft_tokens[1:] = 0                            # (never a masked one)
 
     def placed(x):
@@ -1686,6 +1680,24 @@ def test_single_read_kernel_takes_rows_of_any_length_and_start(am, wl, oracle, d
     again = call(stats_path=2, wait_polls=-1)             # and where the slices are loaded a second time
     for name in ("n_accept", "next_token", "H_p", "H_q", "d_js"):
         assert torch.equal(getattr(out, name), getattr(again, name)), name
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("vectors,extra", [(1, 0), (1, 1), (2, -1), (256, 1), (257, 3), (512, 1), (1024, 3), (2048, -1),
+                                           (2048, 1), (4096, 1), (8017, 3)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_single_read_kernel_takes_rows_of_any_length_and_start(am, wl, oracle, dtype, vectors, extra, offset):
+    """A last vector that is not whole, alone in its turn or in a slice of its own, with the favoured token or a masked one
+    in it and in the logits that the vector before shares with it; rows that start off a 16-byte boundary."""
+    _rows_at(am, wl, oracle, dtype, 4, 3, vectors * (8 if dtype == torch.bfloat16 else 4) + extra, offset)
+
+
+@pytest.mark.parametrize("dtype,V", [(torch.float32, 524288), (torch.float32, 524289), (torch.float32, 1048575),
+                                     (torch.bfloat16, 1048577), (torch.bfloat16, 1300007)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_single_read_kernel_takes_very_long_rows(am, wl, oracle, dtype, V, offset):
+    """Rows of more than 64 slices of four vectors per thread take eight per thread (above 131072 vectors, up to 262144)."""
+    _rows_at(am, wl, oracle, dtype, 2, 1, V, offset)
 
 
 def test_results_are_bitwise_reproducible(am, wl, path):
