@@ -28,8 +28,9 @@
  *     that depend on device data (token id outside the vocabulary, NaN/+inf logits,
  *     full history list, ...) are reported per sequence in a `status` bit mask;
  *   - logits are row-major with the vocabulary contiguous; strides are in ELEMENTS;
- *     rows may start at any element's address and have any length (128-bit loads either
- *     way; only the two-kernel statistics path reads rows off a 16-byte boundary by element);
+ *     rows may start at any element's address and have any length (128-bit loads either way;
+ *     only the two-kernel statistics path and the float64 settlement of close draws read rows off
+ *     a 16-byte boundary by element);
  *   - units: entropies in nats; the Jensen-Shannon distance is reported as
  *     d = sqrt(D_JS / ln 2), i.e. the base-2 normalisation under which the paper
  *     states the [0,1] bound and the "exactly 0 or 1" exclusion (Sections 2.2, 4.4);
@@ -146,7 +147,7 @@ typedef struct {
                           the update step, which leaves the same lists either way. */
   int32_t wait_polls;  /* single-read statistics kernel: how often a workgroup polls for the results of the
                           other workgroups of its position before it stops waiting and recomputes them
-                          itself (bit-identical results either way).  0: the default (16384, about 25 ms);
+                          itself (bit-identical results either way).  0: the default (16384, about 4.4 ms);
                           negative: do not wait at all, which tests use to exercise the recomputation
                           without any wave ever spinning. */
 } adasd_options;

@@ -390,8 +390,8 @@ __device__ __forceinline__ void lse_accum(const uint4& v, float m, float& s0, fl
 // wait for the payload stores to have completed before the counter's read-modify-write is issued
 // (s_waitcnt 0 below: a write-through store counts as complete when the memory side has acknowledged it),
 // and what remains of the acquire is that the payload loads are issued after the counter's value is known,
-// which the branch on that value and the in-order issue of a wavefront give.  The single-read statistics
-// kernel does not even need that much: its words carry their own validity (stats_fused.hip).
+// which the branch on that value and the in-order issue of a wavefront give.  Records that travel in
+// self-validating words (records.h: statistics, drafting and token kernels) do not even need that much.
 __device__ __forceinline__ void st_agent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

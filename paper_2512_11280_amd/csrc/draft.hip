@@ -59,12 +59,12 @@ struct DraftShared {
 };
 
 // What a drafting call has to do per logit is: 3 plain instructions and an exponential for the entropy, 18
-// multiplications and 19 exclusive ors per four logits for the noise, and for the key a conversion, two logarithms
+// multiplications and 19 exclusive ors per four logits for the noise, and for the key two conversions, two logarithms
 // and about a dozen more.  It is bound by the vector ALU, so everything here follows the issue rules
 // of device_common.h; the slices are cut so that the whole call is resident at once with equal shares per thread.
 // Back to back, bf16, against loops that alternated transcendentals with plain instructions and took the slices in
-// batches of vectors: 128 rows of 152064 39.1 -> 23.5 us, 24 of 32 rows of 128256 11.1 -> 8.7 us; one row of 128256
-// 8.6 -> 6.0 us (of which 2.2 are the call's host side).
+// batches of vectors: 128 rows of 152064 39.0 -> 24.3 us, 24 of 32 rows of 128256 11.1 -> 8.9 us; one row of 128256
+// 8.8 -> 6.0 us (3.4 us of it are the host's part of the call, which runs beside the kernel of the call before).
 //
 // One launch per drafting call, grid (slices, rows).  The workgroup that takes the last ticket of a row folds
 // the slices' records, and with DRAW settles a winner that does not lead by more than the rounding guard.

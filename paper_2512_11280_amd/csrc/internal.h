@@ -15,9 +15,9 @@ constexpr int kWideCap = 512;       // list capacity from which the decision sta
 constexpr int kSumsMin = 4096;      // list length from which the state's running sums are kept and used
 constexpr int kWideMin = 384;       // list length from which a sequence actually uses them
 constexpr int kNarrowMax = kWideCap; // so the one-workgroup form never sees a longer list: it stages both in shared memory
-constexpr int kMaxSplit = 64;        // vocabulary slices per row (statistics kernels)
-constexpr int kMaxSampleSplit = 128; // vocabulary slices per sequence (sampling kernel)
-constexpr int kXchgWords = 3;        // 64-bit hand-off words per (position, slice) of the single-read statistics kernel
+constexpr int kMaxSplit = 64;        // vocabulary slices per row: a fold takes one record per lane
+constexpr int kMaxSampleSplit = 128; // vocabulary slices per sequence of the token kernel's form for long rows
+constexpr int kXchgWords = 3;        // 64-bit hand-off words per record (records.h)
 constexpr int kWaitPolls = 16384;    // polls (about 4 ms) before a workgroup stops waiting for the words of others
 
 // Where the rows of one call live.  which = 0: target, 1: draft.
@@ -41,8 +41,9 @@ struct Workspace {
   SamplePlan* plan;   // [B]
   Top2* part3;        // [B][kMaxSampleSplit]
   int32_t* ticket3;   // [kTicket3Len]       arrival counters of the sampling kernel, zero between calls
-  uint64_t* xchg;     // [positions][kMaxSplit][kXchgWords] self-validating hand-off words of the single-read statistics
-                      // kernel (two floats each, valid flag in the lowest mantissa bit of the low one), zero between calls
+  uint64_t* xchg;     // [positions][kMaxSplit][kXchgWords] self-validating hand-off words (records.h), zero between kernels:
+                      // slice records of the single-read statistics kernel (cleared by the decision kernel), of the drafting
+                      // kernel [rows] and of the token kernel [sequences] (cleared by the workgroup that folds them)
   PosRecord* pos_rec; // [positions] outcomes of the positions (long-history decision kernel)
   float2* tok;        // [positions] logits of the drafted tokens (looked up by the JS kernel or by the column shards)
   int32_t* slots;     // [positions] packed list of the positions inside their windows (ragged calls)

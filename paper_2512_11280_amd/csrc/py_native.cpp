@@ -1,7 +1,7 @@
 // Native half of the binding: the calls a decode loop makes per token and per round (draft_entropy, draft_step,
 // verify), argument marshalling only.  At one sequence the kernels of such a call take 5 to 20 us, and building
 // the argument structs in Python took 5 to 12 us of host time per call, more than a drafting kernel runs.
-// Here a call costs the host about one microsecond besides its launches.
+// Here a drafting call takes 3.3 to 4 us of host time with its launch, a verification 9 us with its three.
 //
 // binding.py hands over the entry points of libadasd.so as it loaded it, and the Python objects that are needed
 // to raise and to allocate; keyword arguments, defaults, checks and exceptions are those of its signatures.

@@ -174,7 +174,8 @@ __device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int
 // the row's first element (0 unless the row is a column slice; a multiple of eight); indices, the excluded token
 // and the noise counters are in vocabulary indices.
 // Bound by the vector ALU as the drafting kernel is (draft.hip); the whole round against the scan in batches of two
-// vectors: 128 x 16 x 152064 385 -> 376 us, ragged 64 x 16 x 128256 127 -> 116 us, 32 x 8 x 128256 64.8 -> 62.2 us.
+// vectors: 128 x 16 x 152064 385 -> 376 us, ragged 64 x 16 x 128256 127 -> 116 us, 32 x 8 x 128256 64.8 -> 62.2 us (the
+// same statistics kernel in both).
 // kExclude gives a key to every finite logit but the excluded one, also to those whose probability is 0
 // in float64 (which the float64 path skips).  Such an element cannot win: this mode only runs after the
 // match test rejected the excluded token x, i.e. ln u1 >= ln p(x) with u1 < 1 - 2^-25, so the rest of the
