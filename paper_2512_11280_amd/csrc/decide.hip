@@ -7,11 +7,11 @@ namespace adasd {
 
 namespace {
 
-template <int DT, bool INLOOP>
-__global__ void __launch_bounds__(kBlock) k_decide(DecideArgs a, UpdateArgs upd, Workspace ws) {
+template <int DT, bool INLOOP, int T>
+__global__ void __launch_bounds__(T) k_decide(DecideArgs a, UpdateArgs upd, Workspace ws) {
   warm_kernargs<sizeof(DecideArgs) + sizeof(UpdateArgs) + sizeof(Workspace)>();
   __shared__ DecideShared sh;
-  decide_sequence<DT, INLOOP>(a, ws, blockIdx.x, sh);
+  decide_sequence<DT, INLOOP, T>(a, ws, blockIdx.x, sh);
   // the round applied to the state right away (the lists were only read above)
   if (upd.B > 0 && threadIdx.x < 64) update_sequence_shared(upd, blockIdx.x, threadIdx.x, sh.first_reject, sh.k_b, sh);
 }
@@ -32,7 +32,7 @@ __global__ void __launch_bounds__(kBlock) k_decide_wide(DecideArgs a, UpdateArgs
   const int n_long = min(max(max(a.nA[b], a.nR[b]), 0), a.cap);
   if (n_long < kWideMin) {
     if (pos != 0) return;
-    decide_sequence<DT, INLOOP>(a, ws, b, sh);
+    decide_sequence<DT, INLOOP, kBlock>(a, ws, b, sh);
     if (upd.B > 0 && threadIdx.x < 64) update_sequence_shared(upd, b, threadIdx.x, sh.first_reject, sh.k_b, sh);
     return;
   }
@@ -119,13 +119,20 @@ hipError_t launch_decide(const DecideArgs& a, const UpdateArgs& upd, const Works
     return hipGetLastError();
   }
   const dim3 grid(a.map.B);
-  if (a.dt == ADASD_BF16) {
-    if (a.list_update) launch_kernel(k_decide<ADASD_BF16, true>, grid, block, st, a, upd, ws);
-    else launch_kernel(k_decide<ADASD_BF16, false>, grid, block, st, a, upd, ws);
-  } else {
-    if (a.list_update) launch_kernel(k_decide<ADASD_F32, true>, grid, block, st, a, upd, ws);
-    else launch_kernel(k_decide<ADASD_F32, false>, grid, block, st, a, upd, ws);
-  }
+  // Half a wavefront to a position, all positions in one turn up to a window of 32: each turn is the same chain of
+  // latencies over again.  Kernel (us), 256 threads / now: 8 sequences, lists of 256, k = 12 12.7 / 10.4, 16 13.0 / 10.7,
+  // 20 16.4 / 13.0, 40 24.2 / 16.5; 128 sequences, lists of 64, k = 16 10.9 / 9.7, 20 13.5 / 11.7, 40 19.6 / 14.8.
+  const int T = a.map.K <= 8 ? 256 : a.map.K <= 16 ? 512 : 1024;
+#define ADASD_DECIDE_CASE(DTV, INLOOPV, TV) \
+  if (a.dt == DTV && (a.list_update != 0) == INLOOPV && T == TV) launch_kernel((k_decide<DTV, INLOOPV, TV>), grid, dim3(TV), st, a, upd, ws);
+#define ADASD_DECIDE_T(DTV, INLOOPV) \
+  ADASD_DECIDE_CASE(DTV, INLOOPV, 256) ADASD_DECIDE_CASE(DTV, INLOOPV, 512) ADASD_DECIDE_CASE(DTV, INLOOPV, 1024)
+  ADASD_DECIDE_T(ADASD_BF16, false)
+  ADASD_DECIDE_T(ADASD_BF16, true)
+  ADASD_DECIDE_T(ADASD_F32, false)
+  ADASD_DECIDE_T(ADASD_F32, true)
+#undef ADASD_DECIDE_T
+#undef ADASD_DECIDE_CASE
   return hipGetLastError();
 }
 

@@ -91,11 +91,13 @@ __device__ inline double half_log_joint_ext(double d, const float* L, int n, con
   return tmax + kLn2 * log2_acc((float)total) - k.log_norm;
 }
 
+constexpr int kMaxDecide = 1024;   // threads of the largest workgroup of the one-workgroup form
+
 struct DecideShared {
   int first_reject, k_b;            // of the sequence, for a fused update step
   float extra[ADASD_MAX_K];         // in-loop appends: this round's distances that pass the filter, in position order
   uint8_t n_before[ADASD_MAX_K];    // in-loop appends: how many of them come from earlier positions
-  double mom[kWaves][4];            // per-wave shifted moments of the two lists
+  double mom[kMaxDecide / 64][4];   // per-wave shifted moments of the two lists
   double lse2[ADASD_MAX_K][2];      // normalisers of the candidate positions (for the sampling plan)
   uint8_t acc[ADASD_MAX_K];         // 1: position accepted
   uint8_t bad[ADASD_MAX_K];
@@ -165,23 +167,24 @@ __device__ __forceinline__ float fold_distance(const PosLoad& L) {
 // back to zero (they are only read inside that kernel, which has finished; the next call finds them clear).
 // The stores are dealt to the threads from the last one backwards: the first wavefront, which carries the
 // latency chains of these kernels, gets none unless there are more than 192 words.
+template <int T>
 __device__ __forceinline__ void clear_exchange_words(const DecideArgs& a, const Workspace& ws, size_t first, int count) {
   if (a.xchg_split <= 0) return;
   const int per_pos = a.xchg_split * kXchgWords;
-  for (int j = kBlock - 1 - (int)threadIdx.x; j < count * per_pos; j += kBlock) {
+  for (int j = T - 1 - (int)threadIdx.x; j < count * per_pos; j += T) {
     const int i = j / per_pos, w = j - i * per_pos;
     __hip_atomic_store(ws.xchg + (first + i) * (size_t)(kMaxSplit * kXchgWords) + w, 0ull, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
-// The decisions of one sequence by one workgroup of 256 threads.  INLOOP: the accepted list grows
+// The decisions of one sequence by one workgroup of T threads, half a wavefront to a position.  INLOOP: the accepted list grows
 // inside the verification loop (Algorithm 1): position i sees the list of the state followed by the
 // distances of positions 0..i-1 of this round that pass the open-interval filter, up to the capacity.
-template <int DT, bool INLOOP>
+template <int DT, bool INLOOP, int T>
 __device__ void decide_sequence(const DecideArgs& a, const Workspace& ws, int b, DecideShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = tid & 31, grp = tid >> 5;
-  constexpr int kGroups = kBlock / 32;
+  constexpr int kGroups = T / 32;
   const int K = a.map.K;
   if (tid == 0) sh.status = 0;
 
@@ -253,14 +256,14 @@ __device__ void decide_sequence(const DecideArgs& a, const Workspace& ws, int b,
     cA = nA > 0 ? (double)LA[0] : (double)sh.extra[0];   // (with an empty list the shift is only used once an extra exists)
     cR = (double)LR[0];
     // (lists this short never have running sums in the state: they are added up here)
-    for (int j = tid; j < nA; j += kBlock) {
+    for (int j = tid; j < nA; j += T) {
       const float v = LA[j];
       if (j < kNarrowMax) sh.la[j] = v;
       const double e = (double)v - cA;
       m[0] += e;
       m[1] += e * e;
     }
-    for (int j = tid; j < nR; j += kBlock) {
+    for (int j = tid; j < nR; j += T) {
       const float v = LR[j];
       if (j < kNarrowMax) sh.lr[j] = v;
       const double e = (double)v - cR;
@@ -278,7 +281,11 @@ __device__ void decide_sequence(const DecideArgs& a, const Workspace& ws, int b,
     }
     __syncthreads();     // (also: the staged samples are in place)
 #pragma unroll
-    for (int x = 0; x < 4; ++x) m[x] = (sh.mom[0][x] + sh.mom[1][x]) + (sh.mom[2][x] + sh.mom[3][x]);
+    for (int x = 0; x < 4; ++x) {
+      m[x] = (sh.mom[0][x] + sh.mom[1][x]) + (sh.mom[2][x] + sh.mom[3][x]);
+#pragma unroll
+      for (int v = 4; v < T / 64; v += 4) m[x] += (sh.mom[v][x] + sh.mom[v + 1][x]) + (sh.mom[v + 2][x] + sh.mom[v + 3][x]);
+    }
     if (!INLOOP) {
       const bool okA = kde_constants(m[0], m[1], nA, nR, a.bw_rule, &kA);
       const bool okR = kde_constants(m[2], m[3], nR, nA, a.bw_rule, &kR);
@@ -413,7 +420,7 @@ __device__ void decide_sequence(const DecideArgs& a, const Workspace& ws, int b,
     sh.first_reject = r;
     sh.k_b = kb;
   }
-  clear_exchange_words(a, ws, (size_t)b * K, K);
+  clear_exchange_words<T>(a, ws, (size_t)b * K, K);
   __syncthreads();
 }
 
@@ -851,7 +858,7 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
     wsh.last = ticket == K - 1;
   }
   __syncthreads();
-  clear_exchange_words(a, ws, o, 1);
+  clear_exchange_words<kBlock>(a, ws, o, 1);
   if (!wsh.last || wave != 0) return;
 
   // ---- last workgroup of the sequence, one wavefront, one lane per position

@@ -497,6 +497,28 @@ def test_long_history_with_the_update_in_the_same_call_and_status_bits(am, wl, o
         assert np.array_equal(hb[k], host[k]), k
 
 
+@pytest.mark.parametrize("K", [1, 8, 9, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("literal", [0, 1])
+def test_short_history_windows_at_the_edges_of_the_workgroup_sizes(am, wl, oracle, K, literal):
+    """One workgroup takes a sequence's decisions, half a wavefront to a position: 256 threads up to k = 8, 512 up to
+    16, 1024 beyond, in turns above 32."""
+    B, cap = 4, 500
+    batch = wl.config_batched(B=B, k=K, V=1032, seed=700 + K, cap=cap)
+    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(K), n_hist=300)
+    batch.state["nA"][1], batch.state["nR"][2] = 1, 37            # too short a list, lists of different lengths
+    batch.draft_len = torch.tensor([K, K, max(K - 1, 1), 0], dtype=torch.int32)
+    options = am.Options(base_test=literal, list_update=literal, apply_update=1)
+    out, st, _ = G.run_gpu(am, batch, options=options)
+    ref = G.run_oracle(oracle, batch, options=options)
+    rep = G.compare_verify(out, ref, info_bits=16 | 8)
+    host = {k: np.array(v, copy=True) for k, v in batch.state.items() if k != "tau"}
+    oracle.update(host, ref["n_accept"], batch.draft_len.numpy(), ref["H_q"], ref["d_js"], K, d_eps=1e-6)
+    if rep["flips"] == rep["member_flips"] == 0:
+        got = st.to_host()
+        for k in ("nA", "nR", "ent_cnt"):
+            assert np.array_equal(got[k], host[k]), k
+
+
 def test_many_sequences_with_long_histories(am, wl, oracle):
     """More sequences than the arrival-counter arrays have cache lines: the counters of neighbouring
     sequences share lines again, in the sampling kernel and in the per-position decision kernel."""
