@@ -26,6 +26,19 @@ template <int BYTES> __device__ __forceinline__ void warm_kernargs() {
   asm volatile("" ::"s"(t));
 }
 
+// A value at a uniform address that no workgroup of the running kernel writes, through the scalar cache (left to itself
+// the compiler, which cannot know that, loads it lane by lane into vector registers).
+template <class T> __device__ __forceinline__ T scalar_load(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  const auto* w = (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p;
+  uint32_t v[sizeof(T) / 4];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 4; ++i) v[i] = w[i];
+  T t;
+  __builtin_memcpy(&t, v, sizeof(T));
+  return t;
+}
+
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }  // v_exp_f32
 __device__ __forceinline__ float lg2(float x) { return __builtin_amdgcn_logf(x); }   // v_log_f32
 

@@ -1,5 +1,5 @@
-// log2(1 - t) for small t, plain float arithmetic: the CPU tests compile this file as it is and hold its error against
-// 64 bits.
+// log2(1 - t) for small t, and what a logit can still reach under its noise, plain float arithmetic: the CPU tests compile
+// this file as it is and hold its error, and the bound, against 64 bits.
 #pragma once
 #include "records.h"
 
@@ -15,5 +15,13 @@ constexpr float kSerBelow = 1.0f / 12;
 ADASD_ANYWHERE float log2_series(float t) {
   return t * __builtin_fmaf(t, __builtin_fmaf(t, __builtin_fmaf(t, kSer3, kSer2), kSer1), kSer0);
 }
+
+// With E = -ln u >= 1 - u, a logit whose key without noise is k (log2 units) stays below k - log2((1 - u) log2 e).  So with
+// ef = 2^(k - floor + kReach) it stays below `floor` by more than 2^-13, the guard of the comparisons of keys, if
+// ef < (1 - u) 2^32: if noise_reach <= kNoiseTop, which is four ulps of the sum below 2^32.
+constexpr float kSlack = 9.765625e-04f;                    // 2^-10: the guard, and the rounding of ef and of k
+constexpr float kReach = 32.0f - 0.528766373f + kSlack;    // log2(2^32 / log2 e), and the slack
+constexpr float kNoiseTop = 4294966272.0f;                 // 2^32 - 1024
+ADASD_ANYWHERE float noise_reach(float e, float f, uint32_t word) { return __builtin_fmaf(e, f, (float)word); }
 
 }  // namespace adasd

@@ -17,30 +17,33 @@ namespace {
 using namespace sampling;
 
 // The scan of a sequence's row(s) under its plan.
-template <int DT, bool LONG>
+template <int DT, bool LONG, bool PRUNE>
 __device__ __forceinline__ void scan_plan(const SamplePlan& plan, const char* prow, const char* qrow, int V, int v0, int v1,
                                           int col0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
-                                          Top2& best, bool& poison) {
+                                          Top2& best, Floors& sh, bool& poison) {
   const float cp = (float)plan.lse2_p, cq = (float)plan.lse2_q;
   const PhiloxRow noise = philox_row(c1, c2, c3, k0, k1);
   if (LONG) {
-    if (plan.residual == kResidual) scan_long_slice<DT, kResidual>(prow, qrow, V, v0, v1, cp, cq, -1, noise, best, poison);
-    else if (plan.residual == kExclude) scan_long_slice<DT, kExclude>(prow, qrow, V, v0, v1, cp, cq, plan.excluded, noise, best, poison);
-    else scan_long_slice<DT, kPlain>(prow, qrow, V, v0, v1, cp, cq, -1, noise, best, poison);
+    if (plan.residual == kResidual) scan_long_slice<DT, kResidual, PRUNE>(prow, qrow, V, v0, v1, cp, cq, -1, noise, best, sh, poison);
+    else if (plan.residual == kExclude) scan_long_slice<DT, kExclude, PRUNE>(prow, qrow, V, v0, v1, cp, cq, plan.excluded, noise, best, sh, poison);
+    else scan_long_slice<DT, kPlain, PRUNE>(prow, qrow, V, v0, v1, cp, cq, -1, noise, best, sh, poison);
     return;
   }
-  if (plan.residual == kResidual) scan_slice<DT, kResidual>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, poison);
-  else if (plan.residual == kExclude) scan_slice<DT, kExclude>(prow, qrow, V, v0, v1, cp, cq, plan.excluded, col0, noise, best, poison);
-  else scan_slice<DT, kPlain>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, poison);
+  if (plan.residual == kResidual) scan_slice<DT, kResidual, PRUNE>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, sh, poison);
+  else if (plan.residual == kExclude) scan_slice<DT, kExclude, PRUNE>(prow, qrow, V, v0, v1, cp, cq, plan.excluded, col0, noise, best, sh, poison);
+  else scan_slice<DT, kPlain, PRUNE>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, sh, poison);
 }
 
 // LONG: a row of more slices than there are hand-off words (see token_split).  The records then go through part3, and have
 // landed before the ticket is taken; and a compute unit holds no more than one such workgroup of a few sequences.
-template <int DT, bool LONG>
+template <int DT, bool LONG, bool PRUNE>
 __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, int S, int chunk, Workspace ws) {
   warm_kernargs<sizeof(SampleArgs) + 2 * sizeof(int) + sizeof(Workspace)>();
   const int b = blockIdx.y, s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const SamplePlan plan = ws.plan[b];
+  // (by scalar loads, all at once: the kernel before this one has left them)
+  const SamplePlan plan = scalar_load(ws.plan + b);
+  const uint32_t c2 = a.round ? scalar_load(a.round + b) : a.round0;
+  const uint32_t c3 = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
   if (!plan.valid) {
     if (s == 0 && tid == 0) a.next_token[b] = -1;   // status already carries NONFINITE
     return;
@@ -51,13 +54,13 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
   const char* qrow = a.map.base[1] + ((int64_t)b * a.map.seq_stride[1] +
                                       (int64_t)plan.row * a.map.pos_stride[1]) * Elem<DT>::bytes;
   const uint32_t c1 = (uint32_t)plan.row | (1u << 16);
-  const uint32_t c2 = a.round ? a.round[b] : a.round0;
-  const uint32_t c3 = a.seq_id ? a.seq_id[b] : (uint32_t)b;
 
   const int nv = vectors_of<DT>(V), v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
   Top2 best{-INFINITY, -1, -INFINITY, -1};
   bool poison = false;
-  scan_plan<DT, LONG>(plan, prow, qrow, V, v0, v1, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
+  __shared__ Floors sh_floors;
+  if (PRUNE) floors_init(sh_floors);
+  scan_plan<DT, LONG, PRUNE>(plan, prow, qrow, V, v0, v1, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, sh_floors, poison);
 
   __shared__ Top2 sh_top[kWaves];
   // modes: 0 not the last workgroup; 1 final; 2 settle among the close candidates; 3 broken bonus row; 4 whole row in float64
@@ -225,7 +228,8 @@ __global__ void __launch_bounds__(kBlock, 5) k_shard_scan(SampleArgs a, int S, i
   const int nv = vectors_of<DT>(V), chunk = slice_chunk(nv, S), v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
   Top2 best{-INFINITY, -1, -INFINITY, -1};
   bool poison = false;
-  scan_plan<DT, false>(plan, prow, qrow, V, v0, v1, col0, c1, c2, c3, a.seed_lo, a.seed_hi, best, poison);
+  __shared__ Floors sh_floors;
+  scan_plan<DT, false, false>(plan, prow, qrow, V, v0, v1, col0, c1, c2, c3, a.seed_lo, a.seed_hi, best, sh_floors, poison);
   __shared__ Top2 sh_top[kWaves];
   __shared__ int sh_flag[kWaves];
   best = top2_wave_reduce(best);
@@ -488,13 +492,14 @@ hipError_t launch_sample(const SampleArgs& a, int S, const Workspace& ws, hipStr
   if (a.map.B <= 0) return hipSuccess;
   const dim3 grid(S, a.map.B), block(kBlock);
   const int epv = a.dt == ADASD_BF16 ? 8 : 4, chunk = slice_chunk((a.map.V + epv - 1) / epv, S);
-  if (S > kMaxSplit) {
-    if (a.dt == ADASD_BF16) launch_kernel((k_sample<ADASD_BF16, true>), grid, block, st, a, S, chunk, ws);
-    else launch_kernel((k_sample<ADASD_F32, true>), grid, block, st, a, S, chunk, ws);
-  } else {
-    if (a.dt == ADASD_BF16) launch_kernel((k_sample<ADASD_BF16, false>), grid, block, st, a, S, chunk, ws);
-    else launch_kernel((k_sample<ADASD_F32, false>), grid, block, st, a, S, chunk, ws);
-  }
+  const bool slices = S > kMaxSplit, prune = scan_prunes(chunk, a.dt);
+#define ADASD_SAMPLE_CASE(DTV, LONGV, PRUNEV) \
+  if (a.dt == DTV && slices == LONGV && prune == PRUNEV) launch_kernel((k_sample<DTV, LONGV, PRUNEV>), grid, block, st, a, S, chunk, ws);
+  ADASD_SAMPLE_CASE(ADASD_BF16, false, false) ADASD_SAMPLE_CASE(ADASD_BF16, false, true)
+  ADASD_SAMPLE_CASE(ADASD_BF16, true, false) ADASD_SAMPLE_CASE(ADASD_BF16, true, true)
+  ADASD_SAMPLE_CASE(ADASD_F32, false, false) ADASD_SAMPLE_CASE(ADASD_F32, false, true)
+  ADASD_SAMPLE_CASE(ADASD_F32, true, false) ADASD_SAMPLE_CASE(ADASD_F32, true, true)
+#undef ADASD_SAMPLE_CASE
   return hipGetLastError();
 }
 

@@ -76,17 +76,13 @@ __device__ __forceinline__ float log2_exponential(uint32_t word) {
 }
 // The same for the four words of a block, transcendentals in groups (device_common.h).
 __device__ __forceinline__ void log2_exponential4(const U4& r, float (&lE)[4]) {
-  float t[4], u[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) lE[i] = fmaf((float)r.w[i], 0x1p-32f, 0x1p-33f);
+  lg2_abs_group(lE);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    u[i] = fmaf((float)r.w[i], 0x1p-32f, 0x1p-33f);
-    t[i] = fmaf((float)(~r.w[i]), 0x1p-32f, 0x1p-33f);
-  }
-  lg2_group(u, l);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float series = log2_series(t[i]);
-    lE[i] = t[i] < kSerBelow ? series : l[i];
+    const float t = fmaf((float)(~r.w[i]), 0x1p-32f, 0x1p-33f), series = log2_series(t);
+    lE[i] = t < kSerBelow ? series : lE[i];
   }
   lg2_abs_group(lE);
 }
@@ -139,11 +135,51 @@ __device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {
   return last;
 }
 
-// Four logits (group g of a vector, the first of index `first`) with their block of noise.
-template <int DT, int MODE>
+// ---- logits that cannot win any more: the two logarithms of a logit's noise are only formed where its bound
+// (noise_series.h) comes up to `floor`, which is a lower bound of the true key of an element that was looked at.  Of the
+// n-th group of exchangeable logits that is one in n.  An element left out lies under the floor by more than the guard: it is
+// not the winner, and neither the winner nor whether it needs settling in float64 (a runner-up within the margin,
+// another element at or above the winner's lower bound) depends on it.
+// The factor that takes 2^(key without noise) to the scale of the noise words.
+__device__ __forceinline__ float reach(float floor) { return ex2(kReach - floor); }
+// Whether any lane's group of four may hold an element that reaches the floor.  (NaN: yes.)
+__device__ __forceinline__ bool may_win(const float (&e)[4], float f, const U4& block) {
+  float v[4], top;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = noise_reach(e[i], f, block.w[i]);
+  asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(top) : "v"(v[0]), "v"(v[1]), "v"(v[2]));
+  asm("v_maximum3_f32 %0, %0, %1, %1" : "+v"(top) : "v"(v[3]));
+  return __any(!(top <= kNoiseTop)) != 0;
+}
+
+// The floors of a workgroup's wavefronts, in shared memory: each turn starts from the highest.  (Which of them a wavefront
+// comes to see decides what it leaves out, and nothing else.)
+struct Floors {
+  float f[kWaves];
+};
+__device__ __forceinline__ void floors_init(Floors& sh) {
+  if (threadIdx.x < kWaves) sh.f[threadIdx.x] = -INFINITY;
+  __syncthreads();
+}
+__device__ __forceinline__ float highest_floor(const Floors& sh, float mine) {
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w)
+    mine = fmaxf(mine, __hip_atomic_load(&sh.f[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+  return mine;
+}
+__device__ __forceinline__ float raise_floor(Floors& sh, float mine, float lane_floor) {
+  mine = fmaxf(mine, wave_max_f(lane_floor));
+  __hip_atomic_store(&sh.f[__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)], mine, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_WORKGROUP);        // (every lane the same)
+  return mine;
+}
+
+// Four logits (group g of a vector, the first of index `first`) with their block of noise.  PRUNE: those that cannot win
+// are left out (floor, uniform: see above).
+template <int DT, int MODE, bool PRUNE>
 __device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int g, int first, const U4& block, float neg_cp,
-                                           float neg_cq, int excluded, Top2& best, bool& poison) {
-  float zp[4], key[4], lE[4];
+                                           float neg_cq, int excluded, Top2& best, Floors& sh, float& floor, bool& poison) {
+  float zp[4], e[4], lE[4], lane_floor = -INFINITY;
   unpack4<DT>(xp, g, zp);
   if (MODE == kResidual) {
     float zq[4], p[4], q[4];
@@ -156,17 +192,46 @@ __device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int
     ex2_group(zp, p);
     ex2_group(zq, q);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = max_raw(fmaf(kErrRel, p[i] + q[i], p[i] - q[i]), 0.f);
-    lg2_group(p, key);
-  }
-  log2_exponential4(block, lE);
+    for (int i = 0; i < 4; ++i) {
+      zq[i] = kErrRel * (p[i] + q[i]);                       // (the error of the difference)
+      e[i] = max_raw(zq[i] + (p[i] - q[i]), 0.f);
+    }
+    if (PRUNE) {
+      if (!may_win(e, reach(floor), block)) return;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (MODE == kPlain) poison |= !(zp[i] < INFINITY);       // NaN or +inf in the bonus row
-    float k = MODE == kResidual ? key[i] - lE[i] : fma_log2e(zp[i], -lE[i]);
-    if (MODE == kExclude) k = first + i == excluded ? -INFINITY : k;
-    top2_push(best, k, first + i);
+      for (int i = 0; i < 4; ++i) {                          // (how far the true key may lie below: see the margin in k_sample)
+        const float w = e[i] - zq[i];
+        zq[i] = w > 2.f * zq[i] ? 3.f * kLog2e * zq[i] * __builtin_amdgcn_rcpf(w) : INFINITY;
+      }
+    }
+    lg2_abs_group(e);
+    log2_exponential4(block, lE);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float k = e[i] - lE[i];
+      if (PRUNE) lane_floor = max_raw(lane_floor, k - zq[i]);
+      top2_push(best, k, first + i);
+    }
+  } else {
+    if (PRUNE) {
+      const float lift = kReach - floor;      // (+inf while nothing has been looked at)
+      float t[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[i] = fma_log2e(zp[i], lift);
+      ex2_group(t, e);
+      if (!may_win(e, 1.f, block)) return;
+    }
+    log2_exponential4(block, lE);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (MODE == kPlain) poison |= !(zp[i] < INFINITY);       // NaN or +inf in the bonus row
+      float k = fma_log2e(zp[i], -lE[i]);
+      if (MODE == kExclude) k = first + i == excluded ? -INFINITY : k;
+      top2_push(best, k, first + i);
+    }
+    lane_floor = best.k1;
   }
+  if (PRUNE) floor = raise_floor(sh, floor, lane_floor);
 }
 
 // ---- the scan of one slice ----------------------------------------------------------------------
@@ -175,15 +240,16 @@ __device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int
 // and the noise counters are in vocabulary indices.
 // Bound by the vector ALU as the drafting kernel is (draft.hip); the whole round against the scan in batches of two
 // vectors: 128 x 16 x 152064 385 -> 376 us, ragged 64 x 16 x 128256 127 -> 116 us, 32 x 8 x 128256 64.8 -> 62.2 us (the
-// same statistics kernel in both).
+// same statistics kernel in both).  With PRUNE, the token kernel alone: 128 x 16 x 152064 28.2 -> 23.5 us, ragged
+// 64 x 16 x 128256 15.0 -> 14.1 us.
 // kExclude gives a key to every finite logit but the excluded one, also to those whose probability is 0
 // in float64 (which the float64 path skips).  Such an element cannot win: this mode only runs after the
 // match test rejected the excluded token x, i.e. ln u1 >= ln p(x) with u1 < 1 - 2^-25, so the rest of the
 // row holds a mass of at least 3e-8 and some element at least 3e-8 / V of it; its key is above -50 nats
 // whatever its noise, the key of an element with p < 5e-324 below -720.
-template <int DT, int MODE>
+template <int DT, int MODE, bool PRUNE>
 __device__ __forceinline__ void scan_slice(const char* prow, const char* qrow, int V, int v0, int v1, float cp, float cq,
-                                           int excluded, int col0, const PhiloxRow& noise, Top2& best, bool& poison) {
+                                           int excluded, int col0, const PhiloxRow& noise, Top2& best, Floors& sh, bool& poison) {
   constexpr bool RESIDUAL = MODE == kResidual;
   constexpr int EPV = Elem<DT>::per_vec;
   const int tid = threadIdx.x, whole = V / EPV;
@@ -195,7 +261,7 @@ __device__ __forceinline__ void scan_slice(const char* prow, const char* qrow, i
     }
     return x;
   };
-  float neg_cp = -cp, neg_cq = -cq;
+  float neg_cp = -cp, neg_cq = -cq, floor = -INFINITY;
   asm volatile("" : "+v"(neg_cp), "+v"(neg_cq));
   uint4 next_p = load(prow, v0 + tid), next_q = next_p;
   if (RESIDUAL) next_q = load(qrow, v0 + tid);
@@ -207,19 +273,20 @@ __device__ __forceinline__ void scan_slice(const char* prow, const char* qrow, i
       if (RESIDUAL) next_q = load(qrow, idx + kBlock);
     }
     if (base + (tid & ~63) >= v1) continue;     // (a whole wavefront past the end)
+    if (PRUNE) floor = highest_floor(sh, floor);
 #pragma unroll
     for (int g = 0; g < EPV / 4; ++g) {
       const int first = col0 + idx * EPV + 4 * g;
-      scan_group<DT, MODE>(xp, xq, g, first, philox_block(noise, (uint32_t)first >> 2), neg_cp, neg_cq, excluded, best, poison);
+      scan_group<DT, MODE, PRUNE>(xp, xq, g, first, philox_block(noise, (uint32_t)first >> 2), neg_cp, neg_cq, excluded, best, sh, floor, poison);
     }
   }
 }
 
 // The same where a long row has no more than its slices on the chip, one wavefront to a SIMD: sixteen logits per thread
 // and turn, whose noise is formed ahead of the rest, so that the chains of four Philox blocks fill each other's gaps.
-template <int DT, int MODE>
+template <int DT, int MODE, bool PRUNE>
 __device__ __forceinline__ void scan_long_slice(const char* prow, const char* qrow, int V, int v0, int v1, float cp, float cq,
-                                                int excluded, const PhiloxRow& noise, Top2& best, bool& poison) {
+                                                int excluded, const PhiloxRow& noise, Top2& best, Floors& sh, bool& poison) {
   constexpr bool RESIDUAL = MODE == kResidual;
   constexpr int EPV = Elem<DT>::per_vec, G = EPV / 4, NV = 4 / G;
   const int tid = threadIdx.x, whole = V / EPV;
@@ -240,6 +307,7 @@ __device__ __forceinline__ void scan_long_slice(const char* prow, const char* qr
     if (in && idx == whole) y = load_last_vec<DT>(row, V);
     return y;
   };
+  float floor = -INFINITY;
   request(v0);
   for (int base = v0; base < v1; base += NV * kBlock) {
     uint4 xp[NV], xq[NV];
@@ -250,13 +318,14 @@ __device__ __forceinline__ void scan_long_slice(const char* prow, const char* qr
     }
     if (base + NV * kBlock < v1) request(base + NV * kBlock);
     if (base + (tid & ~63) >= v1) continue;     // (a whole wavefront past the end)
+    if (PRUNE) floor = highest_floor(sh, floor);
     U4 block[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) block[j] = philox_block(noise, (uint32_t)((base + tid + j / G * kBlock) * EPV + j % G * 4) >> 2);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      scan_group<DT, MODE>(xp[j / G], xq[j / G], j % G, (base + tid + j / G * kBlock) * EPV + j % G * 4, block[j], -cp, -cq, excluded,
-                           best, poison);
+      scan_group<DT, MODE, PRUNE>(xp[j / G], xq[j / G], j % G, (base + tid + j / G * kBlock) * EPV + j % G * 4, block[j], -cp, -cq, excluded,
+                           best, sh, floor, poison);
   }
 }
 

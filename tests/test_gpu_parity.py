@@ -1558,6 +1558,39 @@ def test_token_draws_from_long_rows(am, wl, oracle, dtype, V, literal):
         assert out.next_token[4].item() in (i, j)
 
 
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 4096), (torch.bfloat16, 4099), (torch.float32, 4096), (torch.float32, 8189)])
+@pytest.mark.parametrize("literal", [0, 1])
+def test_scans_that_leave_out_what_cannot_win(am, wl, oracle, dtype, V, literal):
+    """Batches with four groups of logits and more to a wavefront: only logits that may still win are looked at.  Peaked and
+    flat rows, rows masked but for a few logits or but for whole vectors, draft rows next to the target's and far from
+    them, broken rows: drawn tokens, replacements and bonus draws as the oracle's, in the same status."""
+    B, K = 920, 1
+    g = torch.Generator().manual_seed(V + literal)
+    batch = wl.config_batched(B=B, k=K, V=V, dtype=dtype, seed=31 + literal)
+    t, d = batch.target.float(), batch.draft.float()
+    kind = torch.arange(B) % 8
+    t[kind == 1] *= 0.01
+    t[kind == 2, :, V // 3] += 40.0
+    t[kind == 3] = torch.where(torch.rand((int((kind == 3).sum()), K + 1, V), generator=g) < 0.997, -math.inf, t[kind == 3])
+    t[kind == 4, :, : V - 60] = -math.inf
+    d[kind == 5] = t[kind == 5, :K] + 1e-3 * torch.randn((int((kind == 5).sum()), K, V), generator=g)
+    d[kind == 6] = t[kind == 6, :K].flip(-1)
+    t[kind == 7] *= 8.0
+    t[9, K, 17] = math.nan
+    t[17, K, V - 1] = math.inf
+    batch.target, batch.draft = t.to(dtype), d.to(dtype)
+    batch.draft_tokens[:] = torch.randint(0, V, (B, K), generator=g, dtype=torch.int32)      # mostly rejected
+    batch.draft_tokens[::5, 0] = batch.draft[::5, 0].float().argmax(dim=-1).to(torch.int32)
+    options = am.Options(base_test=literal, relaxed_off=1)
+    out, _, _ = G.run_gpu(am, batch, options=options)
+    ref = G.run_oracle(oracle, batch, options=options)
+    rep = G.compare_verify(out, ref, info_bits=16 | 8)
+    _report(f"leaving out V={V} {dtype} literal={literal}", rep)
+    assert 0 < (ref["n_accept"] == 0).sum() < B and rep["seq_skipped"] <= 2
+    _, _, tok, _, ref_tok, _ = _draft_step_case(am, oracle, batch.target[:, 0].contiguous(), step=3, seed=8, round0=2)
+    assert np.array_equal(tok, ref_tok)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V", [4001, 32000])
 def test_drafting_goes_on_where_slice_records_do_not_arrive(am, oracle, dtype, V):

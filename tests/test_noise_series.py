@@ -1,4 +1,4 @@
-"""Error of log2 E, E = -ln u of a 32-bit noise word, as the scans form it, against 64 bits: the kernels' own series
+"""The arithmetic of the noise that the kernels share (csrc/noise_series.h).  Error of log2 E, E = -ln u of a 32-bit noise word, as the scans form it, against 64 bits: the kernels' own series
 (csrc/noise_series.h) compiled for the CPU, with logarithms that are exact to a rounding.  The bound is what five Taylor
 terms below t = 1/16 reach (largest error 1.11e-6, which is the rounding of values near -32; 1.29e-7 rms)."""
 import ctypes as C
@@ -30,6 +30,24 @@ extern "C" void errors(long n, const uint32_t* words, double* largest, double* r
   *largest = worst;
   *rms = std::sqrt(sum / n);
 }
+// Largest (key - floor) of the elements that would be left out: words[k] with the keys without noise at which the bound comes
+// closest, times below[k], and the three floats that follow.
+extern "C" void bounds(long n, const uint32_t* words, const double* below, double* largest, long* left_out) {
+  *largest = -INFINITY;
+  *left_out = 0;
+  for (long k = 0; k < n; ++k) {
+    const uint32_t w = words[k];
+    const double td = ((double)(~w) + 0.5) * 0x1p-32, ud = ((double)w + 0.5) * 0x1p-32;
+    const double E2 = -(td < 0.5 ? std::log1p(-td) : std::log(ud)) / 0.69314718055994530942;     // -log2 u
+    float ef = (float)((4294967296.0 - (double)w) * below[k]);
+    for (int step = 0; step < 4; ++step, ef = std::nextafterf(ef, INFINITY)) {
+      if (!(noise_reach(ef, 1.0f, w) <= kNoiseTop)) continue;
+      const double over = std::log2((double)ef) - (double)kReach - std::log2(E2);                 // key - floor
+      if (over > *largest) *largest = over;
+      ++*left_out;
+    }
+  }
+}
 """
 
 
@@ -47,6 +65,22 @@ def _errors(lib, words):
     largest, rms = C.c_double(), C.c_double()
     lib.errors(C.c_long(words.size), words.ctypes.data_as(C.c_void_p), C.byref(largest), C.byref(rms))
     return largest.value, rms.value
+
+
+@pytest.mark.parametrize("lo,hi", [(0, 1 << 32), (0, 4096), ((1 << 32) - 65536, 1 << 32), (1 << 31, (1 << 31) + 4096),
+                                   ((1 << 32) - (1 << 23), (1 << 32) - (1 << 21))])
+def test_what_is_left_out_cannot_win(lib, lo, hi):
+    """Whatever the word and the logit: an element that the scans leave out has its key below the floor by the guard
+    (2^-13) at least."""
+    rng = np.random.default_rng(lo % 997)
+    words = rng.integers(lo, hi, 400_000, dtype=np.uint64).astype(np.uint32)
+    words[:4] = [lo, hi - 1, lo, hi - 1]
+    below = np.where(rng.random(words.size) < 0.5, 1.0, np.exp2(-rng.uniform(0, 40, words.size)))
+    below[rng.random(words.size) < 0.2] = 1.0 - 2.0**-20
+    largest, left = C.c_double(), C.c_long()
+    lib.bounds(C.c_long(words.size), words.ctypes.data_as(C.c_void_p), below.ctypes.data_as(C.c_void_p), C.byref(largest), C.byref(left))
+    print(f"left out {left.value}, largest key over the floor {largest.value:.3e}")
+    assert left.value > 1000 and largest.value < -2.0**-13
 
 
 def test_error_over_the_whole_range(lib):
