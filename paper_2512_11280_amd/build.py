@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libadasd.so")
 SOURCES = ["stats.hip", "stats_fused.hip", "decide.hip", "sample.hip", "draft.hip", "shard.hip", "diag.hip", "api.hip"]
-HEADERS = [os.path.join(CSRC, h) for h in ("device_common.h", "internal.h", "decide_device.h",
+HEADERS = [os.path.join(CSRC, h) for h in ("device_common.h", "internal.h", "decide_device.h", "history_device.h",
                                              "sample_device.h", "stats_device.h", "records.h", "noise_series.h")] + [
            os.path.join(os.path.dirname(HERE), "include", "adasd.h")]
 

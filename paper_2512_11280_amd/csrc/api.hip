@@ -436,7 +436,12 @@ static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void*
     vout.tokens = a->draft_tokens;
     vout.tok = a->draft_tokens ? ws.tok : nullptr;
     const int polls = opt.wait_polls == 0 ? kWaitPolls : (opt.wait_polls < 0 ? 0 : opt.wait_polls);
-    if (launch_stats_fused(smap, (int)a->dt, fT, fNB, fS, polls, ws, vout, st) != hipSuccess) return ADASD_ERR_HIP;
+    HistArgs hist{};
+    if (!d.relaxed_off && d.LA && d.LR && d.nA && d.nR) {
+      hist = HistArgs{d.LA, d.LR, d.nA, d.nR, d.mom, reinterpret_cast<HistRecord*>(ws.part1), d.cap, B, d.bw_rule};
+      d.hist = hist.rec;
+    }
+    if (launch_stats_fused(smap, (int)a->dt, fT, fNB, fS, polls, ws, vout, hist, st) != hipSuccess) return ADASD_ERR_HIP;
     d.jsd_split = fS;
     d.xchg_split = fS;
     d.tok = vout.tok;

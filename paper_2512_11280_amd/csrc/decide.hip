@@ -7,13 +7,11 @@ namespace adasd {
 
 namespace {
 
-template <int DT, bool INLOOP, int T>
+template <int DT, bool INLOOP, bool HIST, int T, int LP>
 __global__ void __launch_bounds__(T) k_decide(DecideArgs a, UpdateArgs upd, Workspace ws) {
   warm_kernargs<sizeof(DecideArgs) + sizeof(UpdateArgs) + sizeof(Workspace)>();
   __shared__ DecideShared sh;
-  decide_sequence<DT, INLOOP, T>(a, ws, blockIdx.x, sh);
-  // the round applied to the state right away (the lists were only read above)
-  if (upd.B > 0 && threadIdx.x < 64) update_sequence_shared(upd, blockIdx.x, threadIdx.x, sh.first_reject, sh.k_b, sh);
+  decide_sequence<DT, INLOOP, HIST, T, LP>(a, upd, ws, blockIdx.x, sh);
 }
 
 // Long histories: one workgroup per candidate position.  The workgroup of position 0 does all the work of
@@ -21,7 +19,7 @@ __global__ void __launch_bounds__(T) k_decide(DecideArgs a, UpdateArgs upd, Work
 // chip holds at a time those of position 0 have to come first in dispatch order or they queue behind the
 // idle ones: grid (sequences, k_max).  A launch that gives every workgroup a compute unit of its own
 // measured 0.4 us faster the other way round (grid (k_max, sequences)); `seq_first` says which it is.
-template <int DT, bool INLOOP>
+template <int DT, bool INLOOP, bool HIST>
 __global__ void __launch_bounds__(kBlock) k_decide_wide(DecideArgs a, UpdateArgs upd, Workspace ws, int seq_first) {
   warm_kernargs<sizeof(DecideArgs) + sizeof(UpdateArgs) + sizeof(Workspace) + sizeof(int)>();
   __shared__ DecideShared sh;
@@ -32,11 +30,10 @@ __global__ void __launch_bounds__(kBlock) k_decide_wide(DecideArgs a, UpdateArgs
   const int n_long = min(max(max(a.nA[b], a.nR[b]), 0), a.cap);
   if (n_long < kWideMin) {
     if (pos != 0) return;
-    decide_sequence<DT, INLOOP, kBlock>(a, ws, b, sh);
-    if (upd.B > 0 && threadIdx.x < 64) update_sequence_shared(upd, b, threadIdx.x, sh.first_reject, sh.k_b, sh);
+    decide_sequence<DT, INLOOP, HIST, kBlock, 32>(a, upd, ws, b, sh);
     return;
   }
-  decide_position_wide<DT, INLOOP>(a, upd, ws, ws.pos_rec, b, pos, sh, wsh);
+  decide_position_wide<DT, INLOOP, HIST>(a, upd, ws, ws.pos_rec, b, pos, sh, wsh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -86,8 +83,7 @@ __global__ void __launch_bounds__(kBlock) k_state_refresh(UpdateArgs a) {
   __shared__ double sh[kWaves][4];
 #pragma unroll
   for (int x = 0; x < 4; ++x) {
-    m[x] = half_sum_d(m[x]);
-    m[x] += __shfl_xor(m[x], 32);
+    m[x] = wave_sum_d(m[x]);
   }
   if (lane == 0)
     for (int x = 0; x < 4; ++x) sh[wave][x] = m[x];
@@ -109,28 +105,39 @@ hipError_t launch_decide(const DecideArgs& a, const UpdateArgs& upd, const Works
   if (a.cap >= kWideCap && a.map.K > 0 && !a.relaxed_off && a.LA && a.LR && a.nA && a.nR) {
     const int lead = a.map.B * a.map.K > 256 ? 1 : 0;   // (256 compute units)
     const dim3 grid(lead ? a.map.B : a.map.K, lead ? a.map.K : a.map.B);
-    if (a.dt == ADASD_BF16) {
-      if (a.list_update) launch_kernel(k_decide_wide<ADASD_BF16, true>, grid, block, st, a, upd, ws, lead);
-      else launch_kernel(k_decide_wide<ADASD_BF16, false>, grid, block, st, a, upd, ws, lead);
-    } else {
-      if (a.list_update) launch_kernel(k_decide_wide<ADASD_F32, true>, grid, block, st, a, upd, ws, lead);
-      else launch_kernel(k_decide_wide<ADASD_F32, false>, grid, block, st, a, upd, ws, lead);
-    }
+#define ADASD_WIDE_CASE(DTV, INLOOPV, HISTV) \
+    if (a.dt == DTV && (a.list_update != 0) == INLOOPV && (a.hist != nullptr) == HISTV) \
+      launch_kernel((k_decide_wide<DTV, INLOOPV, HISTV>), grid, block, st, a, upd, ws, lead);
+#define ADASD_WIDE_DT(DTV) \
+    ADASD_WIDE_CASE(DTV, false, false) ADASD_WIDE_CASE(DTV, false, true) ADASD_WIDE_CASE(DTV, true, false) ADASD_WIDE_CASE(DTV, true, true)
+    ADASD_WIDE_DT(ADASD_BF16)
+    ADASD_WIDE_DT(ADASD_F32)
+#undef ADASD_WIDE_DT
+#undef ADASD_WIDE_CASE
     return hipGetLastError();
   }
   const dim3 grid(a.map.B);
-  // Half a wavefront to a position, all positions in one turn up to a window of 32: each turn is the same chain of
-  // latencies over again.  Kernel (us), 256 threads / now: 8 sequences, lists of 256, k = 12 12.7 / 10.4, 16 13.0 / 10.7,
-  // 20 16.4 / 13.0, 40 24.2 / 16.5; 128 sequences, lists of 64, k = 16 10.9 / 9.7, 20 13.5 / 11.7, 40 19.6 / 14.8.
-  const int T = a.map.K <= 8 ? 256 : a.map.K <= 16 ? 512 : 1024;
-#define ADASD_DECIDE_CASE(DTV, INLOOPV, TV) \
-  if (a.dt == DTV && (a.list_update != 0) == INLOOPV && T == TV) launch_kernel((k_decide<DTV, INLOOPV, TV>), grid, dim3(TV), st, a, upd, ws);
-#define ADASD_DECIDE_T(DTV, INLOOPV) \
-  ADASD_DECIDE_CASE(DTV, INLOOPV, 256) ADASD_DECIDE_CASE(DTV, INLOOPV, 512) ADASD_DECIDE_CASE(DTV, INLOOPV, 1024)
-  ADASD_DECIDE_T(ADASD_BF16, false)
-  ADASD_DECIDE_T(ADASD_BF16, true)
-  ADASD_DECIDE_T(ADASD_F32, false)
-  ADASD_DECIDE_T(ADASD_F32, true)
+  // The kernel is one chain of latencies, and each turn of the positions is the same chain over again: one turn up to
+  // 16 positions with a wavefront each (a list per half: both at once), up to 32 with half a wavefront each.  Of the two, half
+  // a wavefront is the better one where it takes fewer turns, and where one batch of its lanes covers a list: the workgroup is
+  // half the size.  Kernel (us), a wavefront / half a wavefront, 32 sequences: k = 8, lists of 16 7.0 / 6.9, 256 7.8 / 8.9,
+  // 448 9.1 / 10.7; k = 16, lists of 16 8.2 / 7.4, 64 8.5 / 7.8, 256 8.8 / 9.0, 448 10.3 / 10.8; k = 20, lists of 64 8.4 / 8.1,
+  // 256 9.7 / 9.4; k = 40, lists of 64 11.8 / 9.7, 256 13.9 / 11.6.  Fewer threads and more turns: k = 16 with 8 wavefronts 8.9
+  // to 12.2, k = 8 with 4 wavefronts 7.3 to 9.6.
+  const bool halves = a.map.K > 16 || (a.map.K > 8 && a.cap <= 32 * kHalfU);
+  const int LP = halves ? 32 : 64, T = halves ? (a.map.K <= 16 ? 512 : 1024) : a.map.K <= 4 ? 256 : a.map.K <= 8 ? 512 : 1024;
+#define ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, TV, LPV) \
+  if (a.dt == DTV && (a.list_update != 0) == INLOOPV && (a.hist != nullptr) == HISTV && T == TV && LP == LPV) \
+    launch_kernel((k_decide<DTV, INLOOPV, HISTV, TV, LPV>), grid, dim3(TV), st, a, upd, ws);
+#define ADASD_DECIDE_T(DTV, INLOOPV, HISTV) \
+  ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 256, 64) ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 512, 64) \
+  ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 1024, 64) \
+  ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 512, 32) ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 1024, 32)
+#define ADASD_DECIDE_DT(DTV) \
+  ADASD_DECIDE_T(DTV, false, false) ADASD_DECIDE_T(DTV, false, true) ADASD_DECIDE_T(DTV, true, false) ADASD_DECIDE_T(DTV, true, true)
+  ADASD_DECIDE_DT(ADASD_BF16)
+  ADASD_DECIDE_DT(ADASD_F32)
+#undef ADASD_DECIDE_DT
 #undef ADASD_DECIDE_T
 #undef ADASD_DECIDE_CASE
   return hipGetLastError();

@@ -1,109 +1,204 @@
 // Device code of the acceptance decisions of one sequence (Section 2.1.3, Section 4.4 and the
 // verification loop of Algorithm 1 of the paper) and of the update step.
 #pragma once
-#include "internal.h"
+#include "history_device.h"
 
 namespace adasd {
-
-// ---- reductions over half a wavefront (32 lanes) in double precision: rotations inside the rows of
-// 16 lanes on the two 32-bit halves, then one exchange between the two rows.  All 32 lanes get the result.
-template <int CTRL> __device__ __forceinline__ double dpp_rot_d(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ double half_sum_d(double v) {
-  v += dpp_rot_d<0x121>(v);
-  v += dpp_rot_d<0x122>(v);
-  v += dpp_rot_d<0x124>(v);
-  v += dpp_rot_d<0x128>(v);
-  return v + __shfl_xor(v, 16);
-}
-__device__ __forceinline__ double half_max_d(double v) {
-  v = fmax(v, dpp_rot_d<0x121>(v));
-  v = fmax(v, dpp_rot_d<0x122>(v));
-  v = fmax(v, dpp_rot_d<0x124>(v));
-  v = fmax(v, dpp_rot_d<0x128>(v));
-  return fmax(v, __shfl_xor(v, 16));
-}
 
 // The lists hold distances strictly inside (d_eps, 1 - d_eps) (Section 4.4 leaves out the values "exactly 0
 // or 1").  1 - d is exact in float from d = 1/2 on, so this is the comparison of the real numbers; 1 - d_eps
 // rounded to float would shut out the float just below it.  NaN fails both.
 __device__ __forceinline__ bool inside_open_interval(float d, float d_eps) { return d > d_eps && 1.0f - d > d_eps; }
 
-struct Kde {
-  double inv2h2;   // 1 / (2 h^2)
-  double log_norm; // ln(n h sqrt(2 pi)) - ln prior  (subtracted from the log kernel sum)
-};
+constexpr int kHalfU = 4;      // samples per lane in flight where 32 lanes walk a list
 
-// Gaussian-kernel constants of a history list from its shifted moments (sum and sum of squares of
-// x - shift): sample variance with n-1, the bandwidth rule, the list-size prior.
-__device__ inline bool kde_constants(double s1, double s2, int n, int n_other, int bw_rule, Kde* out) {
-  const double var = (s2 - s1 * s1 / (double)n) / (double)(n - 1);
-  if (!(var > 0.0)) return false;
-  // x^(1/5) through the hardware exp2 / log2 (relative error about 1e-7: far inside what the
-  // posterior's tolerance asks of the bandwidth)
-  const float base = bw_rule == 1 ? 1.0f / (float)n : 4.0f / (3.0f * (float)n);
-  const double factor = (double)ex2((float)(0.2 * log2_acc(base)));
-  const double h = factor * sqrt(var);
-  out->inv2h2 = 1.0 / (2.0 * h * h);
-  const float prior = (float)n / (float)(n + n_other);
-  out->log_norm = kLn2 * (log2_acc((float)((double)n * h * 2.50662827463100050242)) - log2_acc(prior));
-  return true;
-}
-
-// ln [ p(d | list) P(list) ] evaluated by half a wavefront: max-shifted log-sum-exp of the kernels.
-__device__ inline double half_log_joint(double d, const float* L, int n, const Kde& k) {
+// Sums of x - c and of its square over a list, by 32 lanes.
+__device__ __forceinline__ void half_moments(const float* L, int n, double c, double& s1, double& s2) {
   const int l32 = threadIdx.x & 31;
-  double tmax = -INFINITY;
-  for (int j = l32; j < n; j += 32) {
-    double e = d - (double)L[j];
-    tmax = fmax(tmax, -(e * e) * k.inv2h2);
+  s1 = s2 = 0.0;
+#pragma unroll 1
+  for (int base = 0; base < n; base += 32 * kHalfU) {
+    float x[kHalfU];
+#pragma unroll
+    for (int u = 0; u < kHalfU; ++u) x[u] = L[min(base + l32 + 32 * u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < kHalfU; ++u) {
+      const double e = base + l32 + 32 * u < n ? (double)x[u] - c : 0.0;
+      s1 += e;
+      s2 += e * e;
+    }
   }
-  tmax = half_max_d(tmax);
-  float acc = 0.f;
-  for (int j = l32; j < n; j += 32) {
-    double e = d - (double)L[j];
-    double t = -(e * e) * k.inv2h2 - tmax;            // <= 0
-    acc += ex2((float)(t * 1.44269504088896340736));  // e^t; terms below 2^-126 vanish
-  }
-  const double total = half_sum_d((double)acc);
-  return tmax + kLn2 * log2_acc((float)total) - k.log_norm;
+  s1 = half_sum_d(s1);
+  s2 = half_sum_d(s2);
 }
 
-// The same over a list that continues in a second array: samples 0..n-1 from L, n..n+nx-1 from X.
-__device__ inline double half_log_joint_ext(double d, const float* L, int n, const float* X, int nx, const Kde& k) {
-  const int l32 = threadIdx.x & 31, nt = n + nx;
-  double tmax = -INFINITY;
-  for (int j = l32; j < nt; j += 32) {
-    double e = d - (double)(j < n ? L[j] : X[j - n]);
-    tmax = fmax(tmax, -(e * e) * k.inv2h2);
-  }
-  tmax = half_max_d(tmax);
-  float acc = 0.f;
-  for (int j = l32; j < nt; j += 32) {
-    double e = d - (double)(j < n ? L[j] : X[j - n]);
-    double t = -(e * e) * k.inv2h2 - tmax;
-    acc += ex2((float)(t * 1.44269504088896340736));
-  }
-  const double total = half_sum_d((double)acc);
-  return tmax + kLn2 * log2_acc((float)total) - k.log_norm;
+// Sums of x - c and of its square over the nx <= 64 samples of X, by 32 lanes, onto s1 and s2.
+__device__ __forceinline__ void add_moments(const float* X, int nx, double c, double& s1, double& s2) {
+  const int l32 = threadIdx.x & 31;
+  const double e0 = l32 < nx ? (double)X[l32] - c : 0.0, e1 = l32 + 32 < nx ? (double)X[l32 + 32] - c : 0.0;
+  s1 += half_sum_d(e0 + e1);
+  s2 += half_sum_d(e0 * e0 + e1 * e1);
 }
 
-constexpr int kMaxDecide = 1024;   // threads of the largest workgroup of the one-workgroup form
+// ln [ p(d | list) P(list) ] by 32 lanes: max-shifted log-sum-exp of the kernels, each batch's largest exponent joining the
+// lane's reference.  EXTRA: the list goes on in X (nx <= 64 samples).
+template <bool EXTRA>
+__device__ __forceinline__ double half_log_joint(double d, const float* L, int n, const float* X, int nx, const Kde& k) {
+  const int l32 = threadIdx.x & 31;
+  double m = -INFINITY;
+  float acc = 0.f;
+  auto join = [&](const auto& t, double hi) {
+    if (!(hi > -INFINITY)) return;         // (a lane past the end of the list has nothing to add)
+    float add = 0.f;
+#pragma unroll
+    for (unsigned u = 0; u < sizeof(t) / sizeof(t[0]); ++u) add += ex2((float)((t[u] - hi) * 1.44269504088896340736));   // terms below 2^-126 vanish
+    acc = fmaf(acc, ex2((float)((m - hi) * 1.44269504088896340736)), add);
+    m = hi;
+  };
+#pragma unroll 1
+  for (int base = 0; base < n; base += 32 * kHalfU) {
+    double t[kHalfU], hi = m;
+#pragma unroll
+    for (int u = 0; u < kHalfU; ++u) {
+      const double e = d - (double)L[min(base + l32 + 32 * u, n - 1)];
+      t[u] = base + l32 + 32 * u < n ? -(e * e) * k.inv2h2 : -INFINITY;
+      hi = fmax(hi, t[u]);
+    }
+    join(t, hi);
+  }
+  if (EXTRA && nx > 0) {
+    double t[2], hi = m;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const double e = d - (double)X[min(l32 + 32 * u, nx - 1)];
+      t[u] = l32 + 32 * u < nx ? -(e * e) * k.inv2h2 : -INFINITY;
+      hi = fmax(hi, t[u]);
+    }
+    join(t, hi);
+  }
+  const double top = half_max_d(m);
+  const double total = half_sum_d(m > -INFINITY ? (double)acc * (double)ex2((float)((m - top) * 1.44269504088896340736)) : 0.0);
+  return top + kLn2 * log2_acc((float)total) - k.log_norm;
+}
+
+// Update step of one sequence (Section 4.3, last paragraph of Section 4.4; update lines of Algorithm 1)
+// by one wavefront, one lane per candidate position (k_max <= 64).  Every lane reads its position's
+// distance at once; accepted positions that pass the open-interval filter are appended in position
+// order (rank = number of passing positions before it, from a ballot).
+// d: the lane's distance (lanes <= r, below kb), H: the draft entropy of the rejected position (lane r).
+// Returns the status bits of the step (complete in the lane that finishes the sequence: lane r, or 63);
+// with or_status they are also OR-ed into status[b].
+struct UpdateIn {
+  int nA, nR, ent_cnt;
+  double ent_sum;
+};
+// (by scalar loads, early: the last lane needs them at the very end)
+__device__ __forceinline__ UpdateIn update_inputs(const UpdateArgs& a, int b) {
+  return UpdateIn{scalar_load(a.nA + b), scalar_load(a.nR + b), scalar_load(a.ent_cnt + b), scalar_load(a.ent_sum + b)};
+}
+__device__ inline uint32_t update_sequence_core(const UpdateArgs& a, const UpdateIn& in, int b, int lane, int r, int kb, float d,
+                                                float H, bool or_status = true) {
+  const int nA = in.nA, nR = in.nR;
+  double ent_sum = in.ent_sum;
+  int ent_cnt = in.ent_cnt;
+  if (!(lane <= r && lane < kb)) d = 0.f;
+  const bool pass = inside_open_interval(d, a.d_eps);
+  uint32_t st = 0;
+  // accepted positions 0 .. r-1
+  const unsigned long long acc = __ballot(pass && lane < r);
+  if (pass && lane < r) {
+    const int slot = nA + __popcll(acc & ((1ull << lane) - 1ull));
+    if (slot < a.cap) a.LA[(size_t)b * a.cap + slot] = d;
+  }
+  const int nA_new = min(nA + __popcll(acc), a.cap);
+  if (nA + __popcll(acc) > a.cap) st |= ADASD_ST_OVERFLOW;
+  // the lane of the rejected position finishes the sequence (with all 64 positions accepted: the last lane)
+  const int fin = r < 64 ? r : 63;
+  // Running sums of the lists about their first elements: kept from the moment a list reaches kSumsMin
+  // samples (added up from scratch in that call), so short lists cost nothing here.
+  if (a.mom && (nA_new >= kSumsMin || nR + 1 >= kSumsMin)) {       // (uniform)
+    const bool rej_appended = r < kb && __shfl((int)pass, fin) && nR < a.cap;
+    const int nR_after = nR + (rej_appended ? 1 : 0);
+    const float d_rej = __shfl(d, fin);
+    if (nA_new >= kSumsMin && nA_new > nA) {
+      const float* LAb = a.LA + (size_t)b * a.cap;
+      const double c = (double)LAb[0];          // nA >= kSumsMin - 64 > 0: the first element is an old one
+      double s1 = 0.0, s2 = 0.0;
+      if (nA < kSumsMin) {                       // the list crosses the mark: everything it held before
+        for (int j = lane; j < nA; j += 64) {
+          const double e = (double)LAb[j] - c;
+          s1 += e;
+          s2 += e * e;
+        }
+      }
+      if (pass && lane < r && nA + __popcll(acc & ((1ull << lane) - 1ull)) < a.cap) {
+        const double e = (double)d - c;
+        s1 += e;
+        s2 += e * e;
+      }
+      s1 = wave_sum_d(s1);
+      s2 = wave_sum_d(s2);
+      if (lane == 0) {
+        const bool fresh = nA < kSumsMin;
+        a.mom[4 * b + 0] = (fresh ? 0.0 : a.mom[4 * b + 0]) + s1;
+        a.mom[4 * b + 1] = (fresh ? 0.0 : a.mom[4 * b + 1]) + s2;
+      }
+    }
+    if (nR_after >= kSumsMin && rej_appended) {
+      const float* LRb = a.LR + (size_t)b * a.cap;
+      const double c = (double)LRb[0];
+      double s1 = 0.0, s2 = 0.0;
+      if (nR < kSumsMin) {
+        for (int j = lane; j < nR; j += 64) {
+          const double e = (double)LRb[j] - c;
+          s1 += e;
+          s2 += e * e;
+        }
+      }
+      if (lane == 0) {
+        const double e = (double)d_rej - c;
+        s1 += e;
+        s2 += e * e;
+      }
+      s1 = wave_sum_d(s1);
+      s2 = wave_sum_d(s2);
+      if (lane == 0) {
+        const bool fresh = nR < kSumsMin;
+        a.mom[4 * b + 2] = (fresh ? 0.0 : a.mom[4 * b + 2]) + s1;
+        a.mom[4 * b + 3] = (fresh ? 0.0 : a.mom[4 * b + 3]) + s2;
+      }
+    }
+  }
+  if (lane != fin) return st;
+  int nR_new = nR;
+  if (r < kb) {
+    if (isfinite(H)) {
+      ent_sum += (double)H;
+      ent_cnt += 1;
+      a.ent_sum[b] = ent_sum;
+      a.ent_cnt[b] = ent_cnt;
+    }
+    if (pass) {
+      if (nR < a.cap) a.LR[(size_t)b * a.cap + nR_new++] = d;
+      else st |= ADASD_ST_OVERFLOW;
+    }
+  }
+  a.nA[b] = nA_new;
+  a.nR[b] = nR_new;
+  a.T_G[b] = ent_cnt > 0 ? (float)(ent_sum / (double)ent_cnt) : 0.f;
+  if (or_status && a.status && st) a.status[b] |= st;
+  return st;
+}
 
 struct DecideShared {
-  int first_reject, k_b;            // of the sequence, for a fused update step
   float extra[ADASD_MAX_K];         // in-loop appends: this round's distances that pass the filter, in position order
   uint8_t n_before[ADASD_MAX_K];    // in-loop appends: how many of them come from earlier positions
-  double mom[kMaxDecide / 64][4];   // per-wave shifted moments of the two lists
+  double mom[kWaves][4];            // per-wave shifted moments of the two lists (long histories)
   double lse2[ADASD_MAX_K][2];      // normalisers of the candidate positions (for the sampling plan)
-  uint8_t acc[ADASD_MAX_K];         // 1: position accepted
-  uint8_t bad[ADASD_MAX_K];
+  uint8_t outcome[ADASD_MAX_K];     // 1: position accepted, 0: rejected, 2: broken rows
+  int32_t token[ADASD_MAX_K];       // the drafted tokens
   float dist[ADASD_MAX_K];          // the round's distances (in-loop appends; the fused update step)
   float hq[ADASD_MAX_K];            // the round's draft entropies (the fused update step)
-  float la[kNarrowMax], lr[kNarrowMax];   // both lists, staged while their moments are formed
   uint32_t status;
 };
 
@@ -178,62 +273,62 @@ __device__ __forceinline__ void clear_exchange_words(const DecideArgs& a, const 
   }
 }
 
-// The decisions of one sequence by one workgroup of T threads, half a wavefront to a position.  INLOOP: the accepted list grows
+// The decisions of one sequence by one workgroup of T threads, LP lanes to a position: with 64 the lower half of the
+// wavefront takes the accepted list and the upper half the rejected one, with 32 one list comes after the other.  HIST: the
+// lists' constants were formed by the statistics launch; else every group of lanes adds up the lists' moments
+// for itself.  Either way nothing but the outcomes goes through shared memory, and nobody waits for anybody before the round
+// is decided.  INLOOP: the accepted list grows
 // inside the verification loop (Algorithm 1): position i sees the list of the state followed by the
 // distances of positions 0..i-1 of this round that pass the open-interval filter, up to the capacity.
-template <int DT, bool INLOOP, int T>
-__device__ void decide_sequence(const DecideArgs& a, const Workspace& ws, int b, DecideShared& sh) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = tid & 31, grp = tid >> 5;
-  constexpr int kGroups = T / 32;
+template <int DT, bool INLOOP, bool HIST, int T, int LP>
+__device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, const Workspace& ws, int b, DecideShared& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = tid / LP;
+  const bool lead = (tid & (LP - 1)) == 0;
+  constexpr int kGroups = T / LP;
   const int K = a.map.K;
   if (tid == 0) sh.status = 0;
 
   int kb = K;
   uint32_t st = 0;
   if (a.map.draft_len) {
-    int raw = a.map.draft_len[b];
+    int raw = scalar_load(a.map.draft_len + b);
     kb = min(max(raw, 0), K);
     if (raw != kb) st |= ADASD_ST_BAD_LENGTH;
   }
 
-  const uint32_t seq = a.seq_id ? a.seq_id[b] : (uint32_t)b;
-  const uint32_t rnd = a.round ? a.round[b] : a.round0;
-
-  // Two chains of dependent loads run side by side: list lengths -> samples and, where the token's
-  // logits were not looked up beforehand, token -> its logits.  The lengths are asked for first, then
-  // the first position of each group, then the samples: a wavefront issues in order, so whatever
-  // stands behind the wait for the token must not be the start of the other chain.
+  // (by scalar loads: only this workgroup writes the sequence's state, and only at its end)
+  const uint32_t seq = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
+  const uint32_t rnd = a.round ? scalar_load(a.round + b) : a.round0;
   const int min_n = a.kde_min_n < 2 ? 2 : a.kde_min_n;
   int nA = 0, nR = 0;
   const float* LA = nullptr;
   const float* LR = nullptr;
   if (a.LA && a.LR && a.nA && a.nR) {
-    nA = min(max(a.nA[b], 0), a.cap);
-    nR = min(max(a.nR[b], 0), a.cap);
+    nA = min(max(scalar_load(a.nA + b), 0), a.cap);
+    nR = min(max(scalar_load(a.nR + b), 0), a.cap);
     LA = a.LA + (size_t)b * a.cap;
     LR = a.LR + (size_t)b * a.cap;
   }
+  UpdateIn before{};
+  if (upd.B > 0) before = update_inputs(upd, b);
   auto load_pos = [&](int i) { return load_position<DT>(a, ws, b, i, rnd, seq); };
-  PosLoad first;
-  if (grp < kb) first = load_pos(grp);
+  PosLoad pos;
+  if (grp < kb) pos = load_pos(grp);
 
-  // ---- Bayesian test set-up: both lists need enough samples and spread (else P(A|d) = 0).
-  // One pass over both lists (moments about the first element), one workgroup reduction; the samples
-  // stay in shared memory for the kernel sums of the positions.
   int n_room = 0;        // in-loop appends the list can still take
   if (INLOOP) {
     // All distances of the round first: the groups fold them, one wavefront ranks those that pass.
     for (int i = grp; i < kb; i += kGroups) {
       const size_t o = (size_t)b * K + i;
-      const PosLoad L = (i == grp) ? first : load_pos(i);
+      const PosLoad L = (i == grp) ? pos : load_pos(i);
       float dv;
       if (a.jsd_split > 0) {
         dv = fold_distance(L);
-        if (l32 == 0) a.d_js[o] = dv;
+        if (lead) a.d_js[o] = dv;
       } else {
         dv = (L.rp.bad || L.rq.bad) ? NAN : a.d_js[o];
       }
-      if (l32 == 0) sh.dist[i] = dv;
+      if (lead) sh.dist[i] = dv;
     }
     __syncthreads();
     if (wave == 0) {
@@ -247,153 +342,144 @@ __device__ void decide_sequence(const DecideArgs& a, const Workspace& ws, int b,
     __syncthreads();
     n_room = LA ? max(a.cap - nA, 0) : 0;
   }
-  // (no positions, no test: the launch sends lists of kNarrowMax samples or more to the other form unless k_max is 0)
-  bool kde_on = K > 0 && !a.relaxed_off && nR >= min_n && (INLOOP ? (LA != nullptr && nA + n_room >= min_n) : nA >= min_n);
-  Kde kA, kR;
-  double cA = 0.0, cR = 0.0;
-  double m[4] = {0.0, 0.0, 0.0, 0.0};
+  // the Bayesian test needs enough samples in both lists, and spread (else P(A|d) = 0).
+  const bool kde_on = kb > 0 && !a.relaxed_off && LA != nullptr && nR >= min_n && (INLOOP ? nA + n_room >= min_n : nA >= min_n);
+
+  // ---- the lists: this lane's (LP = 64), or both
+  constexpr int Q = LP == 64 ? 1 : 2;
+  const bool upper = LP == 64 && (tid & 32) != 0;
+  const float* L[Q];
+  int n[Q];
+  double c[Q], s1[Q], s2[Q];
+  Kde k[Q];
+  bool ok[Q];
+  auto constants = [&](int q, int ne) {
+    const bool rej = upper || q == 1;
+    double m1 = s1[q], m2 = s2[q];
+    if (INLOOP) add_moments(sh.extra, rej ? 0 : ne, c[q], m1, m2);
+    ok[q] = kde_constants(m1, m2, rej ? nR : nA + ne, rej ? nA + ne : nR, a.bw_rule, &k[q]);
+  };
   if (kde_on) {          // uniform over the workgroup
-    cA = nA > 0 ? (double)LA[0] : (double)sh.extra[0];   // (with an empty list the shift is only used once an extra exists)
-    cR = (double)LR[0];
-    // (lists this short never have running sums in the state: they are added up here)
-    for (int j = tid; j < nA; j += T) {
-      const float v = LA[j];
-      if (j < kNarrowMax) sh.la[j] = v;
-      const double e = (double)v - cA;
-      m[0] += e;
-      m[1] += e * e;
-    }
-    for (int j = tid; j < nR; j += T) {
-      const float v = LR[j];
-      if (j < kNarrowMax) sh.lr[j] = v;
-      const double e = (double)v - cR;
-      m[2] += e;
-      m[3] += e * e;
-    }
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      m[x] = half_sum_d(m[x]);
-      m[x] += __shfl_xor(m[x], 32);
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) sh.mom[wave][x] = m[x];
-    }
-    __syncthreads();     // (also: the staged samples are in place)
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      m[x] = (sh.mom[0][x] + sh.mom[1][x]) + (sh.mom[2][x] + sh.mom[3][x]);
-#pragma unroll
-      for (int v = 4; v < T / 64; v += 4) m[x] += (sh.mom[v][x] + sh.mom[v + 1][x]) + (sh.mom[v + 2][x] + sh.mom[v + 3][x]);
-    }
-    if (!INLOOP) {
-      const bool okA = kde_constants(m[0], m[1], nA, nR, a.bw_rule, &kA);
-      const bool okR = kde_constants(m[2], m[3], nR, nA, a.bw_rule, &kR);
-      kde_on = okA && okR;
+    for (int q = 0; q < Q; ++q) {
+      const bool rej = upper || q == 1;
+      L[q] = rej ? LR : LA;
+      n[q] = rej ? nR : nA;
+      if (HIST) {
+        const HistRecord* rec = a.hist + b;
+        k[q] = rec->k[rej];
+        ok[q] = rec->ok[rej] != 0;
+        if (INLOOP) {
+          c[q] = rec->c[rej];
+          s1[q] = rec->s1[rej];
+          s2[q] = rec->s2[rej];
+        }
+      } else {
+        c[q] = n[q] > 0 ? (double)L[q][0] : 0.0;
+        half_moments(L[q], n[q], c[q], s1[q], s2[q]);
+        if (!INLOOP) constants(q, 0);
+      }
+      if (INLOOP && n[q] == 0) c[q] = (double)sh.extra[0];       // (only used once an extra exists)
     }
   }
 
-  // ---- half a wavefront per candidate position
-  for (int i = grp; i < K; i += kGroups) {
+  for (int i = grp; i < kb; i += kGroups) {
+    if (i != grp) pos = load_pos(i);
     const size_t o = (size_t)b * K + i;
-    if (i >= kb) {
-      if (l32 == 0) {
-        if (a.H_p) a.H_p[o] = 0.f;
-        a.H_q[o] = 0.f;
-        a.d_js[o] = 0.f;
-        if (a.p_accept) a.p_accept[o] = 0.f;
-        if (a.accept_mask) a.accept_mask[o] = 0;
-        sh.acc[i] = 0;
-        sh.bad[i] = 0;
-      }
-      continue;
-    }
-    const PosLoad L = (i == grp) ? first : load_pos(i);
-    const RowResult& rp = L.rp;
-    const RowResult& rq = L.rq;
+    const RowResult& rp = pos.rp;
+    const RowResult& rq = pos.rq;
     const bool bad = rp.bad || rq.bad;
-    double d;
+    float dv;
     if (INLOOP) {
-      d = (double)sh.dist[i];
-    } else if (a.jsd_split > 0) {
-      const float d_out = fold_distance(L);
-      if (l32 == 0) {
-        a.d_js[o] = d_out;
-        sh.dist[i] = d_out;
-      }
-      d = (double)d_out;
+      dv = sh.dist[i];
     } else {
-      const float d_in = a.d_js[o];
-      if (l32 == 0) sh.dist[i] = bad ? NAN : d_in;
-      d = (double)d_in;
-    }
-    if (l32 == 0) sh.hq[i] = bad ? NAN : rq.H;
-    double PA = 0.0;
-    if (INLOOP) {
-      if (!bad && kde_on) {
-        // the list as position i sees it: its size, its moments, the prior on the sizes
-        const int ne = min((int)sh.n_before[i], n_room), n_i = nA + ne;
-        double s1 = m[0], s2 = m[1];
-        for (int j = 0; j < ne; ++j) {
-          const double e = (double)sh.extra[j] - cA;
-          s1 += e;
-          s2 += e * e;
-        }
-        if (n_i >= min_n && kde_constants(s1, s2, n_i, nR, a.bw_rule, &kA) &&
-            kde_constants(m[2], m[3], nR, n_i, a.bw_rule, &kR)) {
-          double ja = half_log_joint_ext(d, sh.la, nA, sh.extra, ne, kA);
-          double jr = half_log_joint(d, sh.lr, nR, kR);
-          PA = 1.0 / (1.0 + (double)ex2((float)((jr - ja) * 1.44269504088896340736)));
-        }
+      if (a.jsd_split > 0) {
+        dv = fold_distance(pos);
+        if (lead) a.d_js[o] = dv;
+      } else {
+        dv = a.d_js[o];
       }
-    } else if (!bad && kde_on) {
-      double ja = half_log_joint(d, sh.la, nA, kA);
-      double jr = half_log_joint(d, sh.lr, nR, kR);
-      PA = 1.0 / (1.0 + (double)ex2((float)((jr - ja) * 1.44269504088896340736)));
+      if (lead) sh.dist[i] = bad ? NAN : dv;
     }
-    if (l32 != 0) continue;
+    double PA = 0.0;
+    const int ne = INLOOP ? min((int)sh.n_before[i], n_room) : 0;
+    if (kde_on && !bad && (!INLOOP || nA + ne >= min_n)) {       // (uniform over the position's lanes)
+      double j[2];
+      bool both = true;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (INLOOP) constants(q, ne);
+        j[q] = half_log_joint<INLOOP>((double)dv, L[q], n[q], sh.extra, upper || q == 1 ? 0 : ne, k[q]);
+        both = both && ok[q];
+      }
+      if (LP == 64) {
+        j[1] = j[0];
+        swap_halves(j[0], j[1]);
+        both = __all(both) != 0;
+      }
+      if (both) PA = 1.0 / (1.0 + (double)ex2((float)((j[1] - j[0]) * 1.44269504088896340736)));
+    }
+    if (!lead) continue;
+    sh.hq[i] = bad ? NAN : rq.H;
     sh.lse2[i][0] = rp.lse2;
     sh.lse2[i][1] = rq.lse2;
-    sh.bad[i] = bad;
+    sh.token[i] = pos.x;
     if (bad) {
       if (a.H_p) a.H_p[o] = NAN;
       a.H_q[o] = NAN;
       a.d_js[o] = NAN;
       if (a.p_accept) a.p_accept[o] = NAN;
       if (a.accept_mask) a.accept_mask[o] = 0;
-      sh.acc[i] = 0;
+      sh.outcome[i] = 2;
       atomicOr(&sh.status, (uint32_t)ADASD_ST_NONFINITE);
       continue;
     }
     // speculative-sampling test: accept with probability min(1, p(x)/q(x)), in the log domain; or the
     // loop's own match test: accept with probability p(x)
     int base = 0;
-    if (!L.x_ok) {
+    if (!pos.x_ok) {
       atomicOr(&sh.status, (uint32_t)ADASD_ST_BAD_TOKEN);
     } else if (a.base_test == 1) {
-      base = L.log_u1 < (double)L.zp - rp.lse2 * kLn2;
+      base = pos.log_u1 < (double)pos.zp - rp.lse2 * kLn2;
     } else {
-      double lp = (double)L.zp - rp.lse2 * kLn2;
-      double lq = (double)L.zq - rq.lse2 * kLn2;
+      double lp = (double)pos.zp - rp.lse2 * kLn2;
+      double lq = (double)pos.zq - rq.lse2 * kLn2;
       double log_ratio = lp - lq;
       if (log_ratio > 0.0) log_ratio = 0.0;
-      base = L.log_u1 < log_ratio;   // false for NaN (both probabilities zero)
+      base = pos.log_u1 < log_ratio;   // false for NaN (both probabilities zero)
     }
-    const int relaxed = a.reject_rule == 1 ? (PA >= 0.5) : (L.u2 < PA);
+    const int relaxed = a.reject_rule == 1 ? (PA >= 0.5) : (pos.u2 < PA);
     if (a.p_accept) a.p_accept[o] = (float)PA;
     if (a.accept_mask) a.accept_mask[o] = (uint8_t)(base | (relaxed << 1));
-    sh.acc[i] = (uint8_t)(base || relaxed);   // rejected only if both tests reject
+    sh.outcome[i] = (base || relaxed) ? 1 : 0;   // rejected only if both tests reject
+  }
+  for (int i = kb + tid; i < K; i += T) {      // positions past the window
+    const size_t o = (size_t)b * K + i;
+    if (a.H_p) a.H_p[o] = 0.f;
+    a.H_q[o] = 0.f;
+    a.d_js[o] = 0.f;
+    if (a.p_accept) a.p_accept[o] = 0.f;
+    if (a.accept_mask) a.accept_mask[o] = 0;
   }
   __syncthreads();
-  if (tid == 0) {
-    int r = kb;
-    for (int i = 0; i < kb; ++i)
-      if (!sh.acc[i]) {
-        r = i;
-        break;
-      }
+  clear_exchange_words<T>(a, ws, (size_t)b * K, K);
+  if (wave != 0) return;
+
+  // ---- one wavefront, one lane per position: first rejection, sampling plan, the round applied to the state
+  const int outcome = lane < kb ? sh.outcome[lane] : 1;
+  const unsigned long long rejected = __ballot(outcome != 1);
+  const int r = rejected ? __ffsll((long long)rejected) - 1 : kb;
+  uint32_t st_upd = 0;
+  if (upd.B > 0) {
+    // (the lists were only read above)
+    float d = 0.f, H = 0.f;
+    if (lane <= r && lane < kb) d = sh.dist[lane];
+    if (lane == r && r < kb) H = sh.hq[r];
+    st_upd = update_sequence_core(upd, before, b, lane, r, kb, d, H, false);
+  }
+  st_upd = __builtin_amdgcn_readlane((int)st_upd, r < 64 ? r : 63);
+  if (lane == 0) {
     a.n_accept[b] = r;
-    st |= sh.status;
     SamplePlan plan;
     plan.row = r;
     plan.excluded = -1;
@@ -401,12 +487,12 @@ __device__ void decide_sequence(const DecideArgs& a, const Workspace& ws, int b,
       plan.residual = 1;
       if (a.base_test == 1) {
         // replacement from the target row without the drafted token (a broken token excludes nothing)
-        const int x = a.draft_tokens[(size_t)b * K + r];
+        const int x = sh.token[r];
         const bool x_ok = x >= 0 && x < a.map.V;
         plan.residual = x_ok ? 2 : 0;
         plan.excluded = x_ok ? x : -1;
       }
-      plan.valid = !sh.bad[r];
+      plan.valid = sh.outcome[r] != 2;
       plan.lse2_p = sh.lse2[r][0];
       plan.lse2_q = sh.lse2[r][1];
     } else {
@@ -416,138 +502,19 @@ __device__ void decide_sequence(const DecideArgs& a, const Workspace& ws, int b,
       plan.lse2_q = 0.0;
     }
     ws.plan[b] = plan;
-    a.status[b] = st;
-    sh.first_reject = r;
-    sh.k_b = kb;
+    a.status[b] = st | sh.status | st_upd;
   }
-  clear_exchange_words<T>(a, ws, (size_t)b * K, K);
-  __syncthreads();
 }
 
 }  // namespace adasd
 
 namespace adasd {
 
-// Update step of one sequence (Section 4.3, last paragraph of Section 4.4; update lines of Algorithm 1)
-// by one wavefront, one lane per candidate position (k_max <= 64).  Every lane reads its position's
-// distance at once; accepted positions that pass the open-interval filter are appended in position
-// order (rank = number of passing positions before it, from a ballot).
-// d: the lane's distance (lanes <= r, below kb), H: the draft entropy of the rejected position (lane r).
-// Returns the status bits of the step (complete in the lane that finishes the sequence: lane r, or 63);
-// with or_status they are also OR-ed into status[b].
-__device__ inline uint32_t update_sequence_core(const UpdateArgs& a, int b, int lane, int r, int kb, float d, float H,
-                                                bool or_status = true) {
-  const int nA = a.nA[b], nR = a.nR[b];
-  double ent_sum = a.ent_sum[b];      // (asked for with the lengths: the last lane needs them at the very end)
-  int ent_cnt = a.ent_cnt[b];
-  if (!(lane <= r && lane < kb)) d = 0.f;
-  const bool pass = inside_open_interval(d, a.d_eps);
-  uint32_t st = 0;
-  // accepted positions 0 .. r-1
-  const unsigned long long acc = __ballot(pass && lane < r);
-  if (pass && lane < r) {
-    const int slot = nA + __popcll(acc & ((1ull << lane) - 1ull));
-    if (slot < a.cap) a.LA[(size_t)b * a.cap + slot] = d;
-  }
-  const int nA_new = min(nA + __popcll(acc), a.cap);
-  if (nA + __popcll(acc) > a.cap) st |= ADASD_ST_OVERFLOW;
-  // the lane of the rejected position finishes the sequence (with all 64 positions accepted: the last lane)
-  const int fin = r < 64 ? r : 63;
-  // Running sums of the lists about their first elements: kept from the moment a list reaches kSumsMin
-  // samples (added up from scratch in that call), so short lists cost nothing here.
-  if (a.mom && (nA_new >= kSumsMin || nR + 1 >= kSumsMin)) {       // (uniform)
-    const bool rej_appended = r < kb && __shfl((int)pass, fin) && nR < a.cap;
-    const int nR_after = nR + (rej_appended ? 1 : 0);
-    const float d_rej = __shfl(d, fin);
-    if (nA_new >= kSumsMin && nA_new > nA) {
-      const float* LAb = a.LA + (size_t)b * a.cap;
-      const double c = (double)LAb[0];          // nA >= kSumsMin - 64 > 0: the first element is an old one
-      double s1 = 0.0, s2 = 0.0;
-      if (nA < kSumsMin) {                       // the list crosses the mark: everything it held before
-        for (int j = lane; j < nA; j += 64) {
-          const double e = (double)LAb[j] - c;
-          s1 += e;
-          s2 += e * e;
-        }
-      }
-      if (pass && lane < r && nA + __popcll(acc & ((1ull << lane) - 1ull)) < a.cap) {
-        const double e = (double)d - c;
-        s1 += e;
-        s2 += e * e;
-      }
-      s1 = half_sum_d(s1);
-      s1 += __shfl_xor(s1, 32);
-      s2 = half_sum_d(s2);
-      s2 += __shfl_xor(s2, 32);
-      if (lane == 0) {
-        const bool fresh = nA < kSumsMin;
-        a.mom[4 * b + 0] = (fresh ? 0.0 : a.mom[4 * b + 0]) + s1;
-        a.mom[4 * b + 1] = (fresh ? 0.0 : a.mom[4 * b + 1]) + s2;
-      }
-    }
-    if (nR_after >= kSumsMin && rej_appended) {
-      const float* LRb = a.LR + (size_t)b * a.cap;
-      const double c = (double)LRb[0];
-      double s1 = 0.0, s2 = 0.0;
-      if (nR < kSumsMin) {
-        for (int j = lane; j < nR; j += 64) {
-          const double e = (double)LRb[j] - c;
-          s1 += e;
-          s2 += e * e;
-        }
-      }
-      if (lane == 0) {
-        const double e = (double)d_rej - c;
-        s1 += e;
-        s2 += e * e;
-      }
-      s1 = half_sum_d(s1);
-      s1 += __shfl_xor(s1, 32);
-      s2 = half_sum_d(s2);
-      s2 += __shfl_xor(s2, 32);
-      if (lane == 0) {
-        const bool fresh = nR < kSumsMin;
-        a.mom[4 * b + 2] = (fresh ? 0.0 : a.mom[4 * b + 2]) + s1;
-        a.mom[4 * b + 3] = (fresh ? 0.0 : a.mom[4 * b + 3]) + s2;
-      }
-    }
-  }
-  if (lane != fin) return st;
-  int nR_new = nR;
-  if (r < kb) {
-    if (isfinite(H)) {
-      ent_sum += (double)H;
-      ent_cnt += 1;
-      a.ent_sum[b] = ent_sum;
-      a.ent_cnt[b] = ent_cnt;
-    }
-    if (pass) {
-      if (nR < a.cap) a.LR[(size_t)b * a.cap + nR_new++] = d;
-      else st |= ADASD_ST_OVERFLOW;
-    }
-  }
-  a.nA[b] = nA_new;
-  a.nR[b] = nR_new;
-  a.T_G[b] = ent_cnt > 0 ? (float)(ent_sum / (double)ent_cnt) : 0.f;
-  if (or_status && a.status && st) a.status[b] |= st;
-  return st;
-}
-
-// The update step right after the decisions of the same workgroup: distances and entropies as that
-// left them in shared memory (the values it wrote to d_js / H_q).
-__device__ inline void update_sequence_shared(const UpdateArgs& a, int b, int lane, int r, int kb,
-                                              const DecideShared& sh) {
-  float d = 0.f, H = 0.f;
-  if (lane <= r && lane < kb) d = sh.dist[lane];
-  if (lane == r && r < kb) H = sh.hq[r];
-  update_sequence_core(a, b, lane, r, kb, d, H);
-}
-
 __device__ inline void update_sequence(const UpdateArgs& a, int b, int lane, int r, int kb) {
   float d = 0.f, H = 0.f;
   if (lane <= r && lane < kb) d = a.d_js[(size_t)b * a.K + lane];
   if (lane == r && r < kb) H = a.H_q[(size_t)b * a.K + r];
-  update_sequence_core(a, b, lane, r, kb, d, H);
+  update_sequence_core(a, update_inputs(a, b), b, lane, r, kb, d, H);
 }
 
 
@@ -599,10 +566,11 @@ __device__ __forceinline__ void joint_reduce(const double (&m)[N], const double 
 #pragma unroll
   for (int q = 0; q < N; ++q) {
     M[q] = half_max_d(m[q]);
-    M[q] = fmax(M[q], __shfl_xor(M[q], 32));
+    double other = M[q];
+    swap_halves(M[q], other);
+    M[q] = fmax(M[q], other);
     sc[q] = m[q] > -INFINITY ? s[q] * (double)ex2((float)((m[q] - M[q]) * 1.44269504088896340736)) : 0.0;
-    sc[q] = half_sum_d(sc[q]);
-    sc[q] += __shfl_xor(sc[q], 32);
+    sc[q] = wave_sum_d(sc[q]);
   }
   __syncthreads();
   if (lane == 0) {
@@ -626,40 +594,80 @@ __device__ __forceinline__ void joint_reduce(const double (&m)[N], const double 
   }
 }
 
-// ln [ p(d | list) P(list) ] by the whole workgroup, streaming a list of any length; the list continues
-// in X (nx samples).
-__device__ inline double block_log_joint(double d, const float* L, int n, const float* X, int nx, const Kde& k,
-                                         WideShared& w) {
-  const int tid = threadIdx.x, nt = n + nx;
-  double m[1] = {-INFINITY}, s[1] = {0.0}, out[1];
-  for (int base = 0; base < nt; base += kWideU * kBlock) {
-    float x[kWideU];
-#pragma unroll
-    for (int u = 0; u < kWideU; ++u) {
-      const int j = min(base + tid + u * kBlock, nt - 1);
-      x[u] = j < n ? L[j] : X[j - n];
-    }
-    joint_terms(d, x, base + tid, nt, k.inv2h2, m[0], s[0]);
-  }
-  joint_reduce<1>(m, s, w, out);
-  return out[0] - k.log_norm;
+// One more sample per thread (tid < nx) of a list that goes on in X.
+__device__ __forceinline__ void joint_extra(double d, const float* X, int nx, double inv2h2, double& m, double& s) {
+  if ((int)threadIdx.x >= nx) return;
+  const double e = d - (double)X[threadIdx.x], t = -(e * e) * inv2h2, hi = fmax(m, t);
+  s = s * (double)ex2((float)((m - hi) * 1.44269504088896340736)) + (double)ex2((float)((t - hi) * 1.44269504088896340736));
+  m = hi;
 }
 
-template <int DT, bool INLOOP>
+// Exponents of a list of any length, streamed.
+__device__ inline void stream_terms(double d, const float* L, int n, double inv2h2, double& m, double& s) {
+#pragma unroll 1
+  for (int base = threadIdx.x; base < n; base += kWideU * kBlock) {
+    float x[kWideU];
+#pragma unroll
+    for (int u = 0; u < kWideU; ++u) x[u] = L[min(base + u * kBlock, n - 1)];
+    joint_terms(d, x, base, n, inv2h2, m, s);
+  }
+}
+
+// Sums of x - c and of its square over the two lists, by the workgroup (where no earlier kernel left them).
+__device__ inline void list_moments(const DecideArgs& a, int b, const float* LA, const float* LR, int nA, int nR,
+                                    const double (&c)[2], DecideShared& sh, double (&m)[4]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float* L[2] = {LA, LR};
+  const int n[2] = {nA, nR};
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    double s1 = 0.0, s2 = 0.0;
+    if (!(a.mom && n[q] > kSumsMin)) {
+#pragma unroll 1
+      for (int base = tid; base < n[q]; base += kWideU * kBlock) {
+        float x[kWideU];
+#pragma unroll
+        for (int u = 0; u < kWideU; ++u) x[u] = L[q][min(base + u * kBlock, n[q] - 1)];
+#pragma unroll
+        for (int u = 0; u < kWideU; ++u) {
+          const double e = base + u * kBlock < n[q] ? (double)x[u] - c[q] : 0.0;
+          s1 += e;
+          s2 += e * e;
+        }
+      }
+    }
+    m[2 * q] = wave_sum_d(s1);
+    m[2 * q + 1] = wave_sum_d(s2);
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) sh.mom[wave][x] = m[x];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+    m[x] = a.mom && n[x >> 1] > kSumsMin ? a.mom[4 * b + x] : (sh.mom[0][x] + sh.mom[1][x]) + (sh.mom[2][x] + sh.mom[3][x]);
+}
+
+template <int DT, bool INLOOP, bool HIST>
 __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd, const Workspace& ws,
                                      PosRecord* records, int b, int i, DecideShared& sh, WideShared& wsh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = tid & 31, grp = tid >> 5;
   constexpr int kGroups = kBlock / 32;
   const int K = a.map.K;
+  constexpr int U = kWideU;
   int kb = K;
   uint32_t st_seq = 0;
   if (a.map.draft_len) {
-    const int raw = a.map.draft_len[b];
+    const int raw = scalar_load(a.map.draft_len + b);
     kb = min(max(raw, 0), K);
     if (raw != kb) st_seq |= ADASD_ST_BAD_LENGTH;
   }
-  const uint32_t seq = a.seq_id ? a.seq_id[b] : (uint32_t)b;
-  const uint32_t rnd = a.round ? a.round[b] : a.round0;
+  const uint32_t seq = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
+  const uint32_t rnd = a.round ? scalar_load(a.round + b) : a.round0;
+  const int nA = min(max(scalar_load(a.nA + b), 0), a.cap), nR = min(max(scalar_load(a.nR + b), 0), a.cap);
+  const float* LA = a.LA + (size_t)b * a.cap;
+  const float* LR = a.LR + (size_t)b * a.cap;
   const size_t o = (size_t)b * K + i;
 
   PosRecord rec{0, 0u, 0.f, 0.f};
@@ -672,23 +680,22 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
       if (a.accept_mask) a.accept_mask[o] = 0;
     }
   } else {
+    // Lists of up to U samples per thread are read ONCE, both at the same time and ahead of everything else, and stay in
+    // registers; longer ones are streamed.
+    const bool resident = nA <= U * kBlock && nR <= U * kBlock;
+    float xa[U], xr[U];
+    if (resident) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        xa[u] = LA[max(min(tid + u * kBlock, nA - 1), 0)];
+        xr[u] = LR[max(min(tid + u * kBlock, nR - 1), 0)];
+      }
+    }
+    HistRecord hist;
+    if (HIST) hist = a.hist[b];
     const PosLoad L = load_position<DT>(a, ws, b, i, rnd, seq);
     const bool bad = L.rp.bad || L.rq.bad;
     const int min_n = a.kde_min_n < 2 ? 2 : a.kde_min_n;
-    int nA = 0, nR = 0;
-    const float* LA = nullptr;
-    const float* LR = nullptr;
-    if (a.LA && a.LR && a.nA && a.nR) {
-      nA = min(max(a.nA[b], 0), a.cap);
-      nR = min(max(a.nR[b], 0), a.cap);
-      LA = a.LA + (size_t)b * a.cap;
-      LR = a.LR + (size_t)b * a.cap;
-    }
-    // the state's running sums of a list are valid once it holds kSumsMin samples; requested with the lengths
-    const bool sums_A = a.mom && LA && nA >= kSumsMin, sums_R = a.mom && LA && nR >= kSumsMin;
-    double mom_pre[4] = {0.0, 0.0, 0.0, 0.0};
-    if (sums_A) { mom_pre[0] = a.mom[4 * b + 0]; mom_pre[1] = a.mom[4 * b + 1]; }
-    if (sums_R) { mom_pre[2] = a.mom[4 * b + 2]; mom_pre[3] = a.mom[4 * b + 3]; }
     int ne = 0;                            // in-loop appends this position sees
     if (INLOOP) {
       // distances of the earlier positions (each workgroup of the sequence forms them for itself)
@@ -708,7 +715,7 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
         if (lane == 0) wsh.n_pass = __popcll(mask);
       }
       __syncthreads();
-      ne = LA ? min(wsh.n_pass, max(a.cap - nA, 0)) : 0;
+      ne = min(wsh.n_pass, a.cap - nA);
     }
     float d_out;
     if (a.jsd_split > 0) {
@@ -720,101 +727,39 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
     const double d = (double)d_out;
     const int n_i = nA + ne;
     double PA = 0.0;
-    if (!a.relaxed_off && !bad && LA && n_i >= min_n && nR >= min_n) {      // uniform over the workgroup
-      const double cA = nA > 0 ? (double)LA[0] : (double)sh.extra[0], cR = (double)LR[0];
-      double m[4] = {0.0, 0.0, 0.0, 0.0};
-      constexpr int U = kWideU;
-      // Lists of up to U samples per thread are read ONCE, both at the same time, and stay in registers for
-      // the moments and for the kernel sums; longer ones are streamed twice.
-      const bool resident = n_i <= U * kBlock && nR <= U * kBlock;
-      float xa[U], xr[U];
-      if (resident) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int ja = min(tid + u * kBlock, n_i - 1), jr = min(tid + u * kBlock, nR - 1);
-          xa[u] = ja < nA ? LA[ja] : sh.extra[ja - nA];
-          xr[u] = LR[jr];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const double ea = tid + u * kBlock < n_i ? (double)xa[u] - cA : 0.0;
-          const double er = tid + u * kBlock < nR ? (double)xr[u] - cR : 0.0;
-          m[0] += ea;
-          m[1] += ea * ea;
-          m[2] += er;
-          m[3] += er * er;
-        }
-      } else {
-        if (!sums_A)
-          for (int base = 0; base < n_i; base += U * kBlock) {
-            float x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const int j = min(base + tid + u * kBlock, n_i - 1);
-              x[u] = j < nA ? LA[j] : sh.extra[j - nA];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const double e = base + tid + u * kBlock < n_i ? (double)x[u] - cA : 0.0;
-              m[0] += e;
-              m[1] += e * e;
-            }
-          }
-        if (!sums_R)
-          for (int base = 0; base < nR; base += U * kBlock) {
-            float x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = LR[min(base + tid + u * kBlock, nR - 1)];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const double e = base + tid + u * kBlock < nR ? (double)x[u] - cR : 0.0;
-              m[2] += e;
-              m[3] += e * e;
-            }
-          }
-      }
-      const bool both_sums = !resident && sums_A && sums_R;
-      if (!both_sums) {              // (uniform) something was added up by the threads
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          m[x] = half_sum_d(m[x]);
-          m[x] += __shfl_xor(m[x], 32);
-        }
-        if (lane == 0) {
-#pragma unroll
-          for (int x = 0; x < 4; ++x) sh.mom[wave][x] = m[x];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int x = 0; x < 4; ++x) m[x] = (sh.mom[0][x] + sh.mom[1][x]) + (sh.mom[2][x] + sh.mom[3][x]);
-      }
-      if (!resident && sums_A) {     // the state's sums, and the in-loop appends on top (every thread the same)
-        m[0] = mom_pre[0];
-        m[1] = mom_pre[1];
-        for (int j = 0; j < ne; ++j) {
-          const double e = (double)sh.extra[j] - cA;
-          m[0] += e;
-          m[1] += e * e;
-        }
-      }
-      if (!resident && sums_R) {
-        m[2] = mom_pre[2];
-        m[3] = mom_pre[3];
-      }
+    if (!bad && n_i >= min_n && nR >= min_n) {      // uniform over the workgroup
       Kde kA, kR;
-      if (kde_constants(m[0], m[1], n_i, nR, a.bw_rule, &kA) && kde_constants(m[2], m[3], nR, n_i, a.bw_rule, &kR)) {
-        double ja, jr;
-        if (resident) {
-          double mm[2] = {-INFINITY, -INFINITY}, ss[2] = {0.0, 0.0}, out[2];
-          joint_terms(d, xa, tid, n_i, kA.inv2h2, mm[0], ss[0]);
-          joint_terms(d, xr, tid, nR, kR.inv2h2, mm[1], ss[1]);
-          joint_reduce<2>(mm, ss, wsh, out);
-          ja = out[0] - kA.log_norm;
-          jr = out[1] - kR.log_norm;
+      bool ok;
+      if (HIST && ne == 0) {
+        kA = hist.k[0];
+        kR = hist.k[1];
+        ok = hist.ok[0] && hist.ok[1];
+      } else {
+        const double c[2] = {nA == 0 ? (double)sh.extra[0] : HIST ? hist.c[0] : (double)LA[0], HIST ? hist.c[1] : (double)LR[0]};
+        double m[4];
+        if (HIST) {
+          m[0] = hist.s1[0];
+          m[1] = hist.s2[0];
+          m[2] = hist.s1[1];
+          m[3] = hist.s2[1];
         } else {
-          ja = block_log_joint(d, LA, nA, sh.extra, ne, kA, wsh);
-          jr = block_log_joint(d, LR, nR, nullptr, 0, kR, wsh);
+          list_moments(a, b, LA, LR, nA, nR, c, sh, m);
         }
+        if (INLOOP) add_moments(sh.extra, ne, c[0], m[0], m[1]);
+        ok = kde_constants(m[0], m[1], n_i, nR, a.bw_rule, &kA) && kde_constants(m[2], m[3], nR, n_i, a.bw_rule, &kR);
+      }
+      if (ok) {                      // uniform over the workgroup
+        double mm[2] = {-INFINITY, -INFINITY}, ss[2] = {0.0, 0.0}, out[2];
+        if (resident) {
+          joint_terms(d, xa, tid, nA, kA.inv2h2, mm[0], ss[0]);
+          joint_terms(d, xr, tid, nR, kR.inv2h2, mm[1], ss[1]);
+        } else {
+          stream_terms(d, LA, nA, kA.inv2h2, mm[0], ss[0]);
+          stream_terms(d, LR, nR, kR.inv2h2, mm[1], ss[1]);
+        }
+        if (INLOOP) joint_extra(d, sh.extra, ne, kA.inv2h2, mm[0], ss[0]);
+        joint_reduce<2>(mm, ss, wsh, out);
+        const double ja = out[0] - kA.log_norm, jr = out[1] - kR.log_norm;
         PA = 1.0 / (1.0 + (double)ex2((float)((jr - ja) * 1.44269504088896340736)));
       }
     }
@@ -862,6 +807,8 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
   if (!wsh.last || wave != 0) return;
 
   // ---- last workgroup of the sequence, one wavefront, one lane per position
+  UpdateIn before{};
+  if (upd.B > 0) before = update_inputs(upd, b);
   // Every lane also asks for what the sampling plan and the update step need of ITS position (the
   // normalisers, the drafted token, the draft entropy: all left by earlier kernels), so that nothing is
   // loaded once the rejected position is known; its lane hands them over.
@@ -920,7 +867,7 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
   if (upd.B > 0) {
     // (a position with non-finite rows records nothing, whatever its entropy word holds by now)
     const float H = (lane == r && r < kb && !(bits & 2)) ? Hl : NAN;
-    st_upd = update_sequence_core(upd, b, lane, r, kb, dl, H, false);
+    st_upd = update_sequence_core(upd, before, b, lane, r, kb, dl, H, false);
   }
   // one store of the sequence's status word, the update step's bits included (they are complete in its last lane)
   st_upd = __shfl(st_upd, src_lane);

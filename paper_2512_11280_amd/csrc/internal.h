@@ -12,9 +12,8 @@
 namespace adasd {
 
 constexpr int kWideCap = 512;       // list capacity from which the decision stage is launched with a workgroup per position
-constexpr int kSumsMin = 4096;      // list length from which the state's running sums are kept and used
+constexpr int kSumsMin = 4096;      // list length from which the state's running sums are kept (a longer list is no longer added up)
 constexpr int kWideMin = 384;       // list length from which a sequence actually uses them
-constexpr int kNarrowMax = kWideCap; // so the one-workgroup form never sees a longer list: it stages both in shared memory
 constexpr int kMaxSplit = 64;        // vocabulary slices per row: a fold takes one record per lane
 constexpr int kMaxSampleSplit = 128; // vocabulary slices per sequence of the token kernel's form for long rows
 constexpr int kXchgWords = 3;        // 64-bit hand-off words per record (records.h)
@@ -159,8 +158,16 @@ hipError_t launch_rowstats(const RowMap& map, int dt, int rows, int S, const Wor
 // It leaves what the two-kernel path leaves (rows, entropies, per-slice JS sums, the drafted tokens' logits)
 // plus the hand-off words of the positions it worked on, which the decision kernel clears (DecideArgs::xchg_split).
 bool fused_plan(const RowMap& map, int dt, int* T_out, int* NB_out, int* S_out);
-hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, int wait_polls,
-                              const Workspace& ws, const VerifyOut& vout, hipStream_t st);
+struct HistRecord;
+struct HistArgs {       // the lists of a call's sequences (history_device.h), or rec == null: nothing to form
+  const float* LA;
+  const float* LR;
+  const int32_t* nA;
+  const int32_t* nR;
+  const double* mom;    // as DecideArgs::mom
+  HistRecord* rec;      // [B]
+  int32_t cap, B, bw_rule;
+};
 
 struct UpdateArgs {
   int32_t B, K, cap;
@@ -192,6 +199,7 @@ struct DecideArgs {
   const int32_t* nA;
   const int32_t* nR;
   const double* mom;    // [B,4] running sums of the lists about their first elements, or null: add them up here
+  const HistRecord* hist;   // [B], left by the statistics launch, or null: the lists' constants are formed here
   uint32_t seed_lo, seed_hi;
   const uint32_t* seq_id;
   const uint32_t* round;
@@ -210,6 +218,8 @@ struct DecideArgs {
   uint8_t* accept_mask;
   uint32_t* status;
 };
+hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, int wait_polls,
+                              const Workspace& ws, const VerifyOut& vout, const HistArgs& hist, hipStream_t st);
 // upd.B > 0: the round is also applied to the state (the update step) by the same kernel
 hipError_t launch_decide(const DecideArgs& a, const UpdateArgs& upd, const Workspace& ws, hipStream_t st);
 // JS distance: per-slice partial sums (the decision kernel adds them up), rows and entropies

@@ -26,6 +26,7 @@
 // whenever one waits, the ones it waits for are resident or next in line; all the same every wait is
 // bounded: after `wait_polls` polls the workgroup recomputes the other slices' results itself from memory
 // with the very same code (bit-identical), so every wave exits whatever the dispatch order is.
+#include "history_device.h"
 #include "stats_device.h"
 #include "records.h"
 
@@ -43,6 +44,7 @@ struct FusedGeom {
   int missing;     // logits that the last vector lacks of a whole one
   int last_byte;   // offset of the last 16 bytes of a row
   int chunk;       // vectors per slice
+  int hist_rows;   // rows of the grid, the first ones, that are for the history lists
   int wait_polls;  // polls before a workgroup stops waiting and recomputes what is missing
 };
 
@@ -281,12 +283,18 @@ __device__ __forceinline__ void fold_position(const Lse& tp, const Lse& tq, JsNo
 
 template <int DT, int T, int NB>
 __global__ void __launch_bounds__(T, NB <= 4 ? 8 : 4)
-k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout) {
-  warm_kernargs<sizeof(RowMap) + sizeof(FusedGeom) + sizeof(Workspace) + sizeof(VerifyOut)>();
+k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout, HistArgs hist) {
+  warm_kernargs<sizeof(RowMap) + sizeof(FusedGeom) + sizeof(Workspace) + sizeof(VerifyOut) + sizeof(HistArgs)>();
   constexpr int W = T / 64;
   __shared__ FusedShared<W> sh;
   const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int pos = position_of_slot(map, (int)blockIdx.y);
+  if ((int)blockIdx.y < g.hist_rows) {       // the first workgroups form the constants of the sequences' history lists
+    __shared__ HistShared hsh;
+    const int b = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    if (b < hist.B) form_history<T>(hist, b, hsh);
+    return;
+  }
+  const int pos = position_of_slot(map, (int)blockIdx.y - g.hist_rows);
   if (pos < 0) return;
   const RowRef rp = locate_row<DT>(map, 2 * pos), rq = locate_row<DT>(map, 2 * pos + 1);
   if (!rp.active) return;
@@ -436,7 +444,7 @@ bool fused_plan(const RowMap& map, int dt, int* T_out, int* NB_out, int* S_out) 
 }
 
 hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, int wait_polls,
-                              const Workspace& ws, const VerifyOut& vout, hipStream_t st) {
+                              const Workspace& ws, const VerifyOut& vout, const HistArgs& hist, hipStream_t st) {
   const int positions = map.B * map.K;
   if (positions <= 0) return hipSuccess;
   FusedGeom g;
@@ -451,10 +459,11 @@ hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, i
   if ((int64_t)g.chunk * (S - 1) >= g.nv || g.chunk > T * NB) g.chunk = (g.nv + S - 1) / S;
   g.wait_polls = wait_polls;
   if (g.chunk > T * NB) return hipErrorInvalidValue;
-  const dim3 grid(S, positions);
+  g.hist_rows = hist.rec ? (hist.B + S - 1) / S : 0;
+  const dim3 grid(S, positions + g.hist_rows);
 #define ADASD_FUSED_CASE(DTV, TV, NBV) \
   if (dt == DTV && T == TV && NB == NBV) { \
-    launch_kernel((k_stats_fused<DTV, TV, NBV>), grid, dim3(TV), st, map, g, ws, vout); \
+    launch_kernel((k_stats_fused<DTV, TV, NBV>), grid, dim3(TV), st, map, g, ws, vout, hist); \
     return hipGetLastError(); \
   }
 #define ADASD_FUSED_DT(DTV)      /* (what fused_plan can choose) */ \

@@ -497,14 +497,16 @@ def test_long_history_with_the_update_in_the_same_call_and_status_bits(am, wl, o
         assert np.array_equal(hb[k], host[k]), k
 
 
-@pytest.mark.parametrize("K", [1, 8, 9, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("K", [1, 4, 5, 8, 9, 16, 17, 32, 33, 64])
 @pytest.mark.parametrize("literal", [0, 1])
-def test_short_history_windows_at_the_edges_of_the_workgroup_sizes(am, wl, oracle, K, literal):
-    """One workgroup takes a sequence's decisions, half a wavefront to a position: 256 threads up to k = 8, 512 up to
-    16, 1024 beyond, in turns above 32."""
-    B, cap = 4, 500
+@pytest.mark.parametrize("cap", [500, 128])
+def test_short_history_windows_at_the_edges_of_the_workgroup_sizes(am, wl, oracle, K, literal, cap):
+    """One workgroup takes a sequence's decisions.  A wavefront to a position: 256 threads up to k = 4, 512 up to 8, 1024
+    up to 16.  Half a wavefront to a position: from k = 17, and with lists of at most 128 samples from k = 9 (512
+    threads up to 16, 1024 beyond, in turns above 32)."""
+    B = 4
     batch = wl.config_batched(B=B, k=K, V=1032, seed=700 + K, cap=cap)
-    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(K), n_hist=300)
+    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(K), n_hist=min(300, cap - 13))
     batch.state["nA"][1], batch.state["nR"][2] = 1, 37            # too short a list, lists of different lengths
     batch.draft_len = torch.tensor([K, K, max(K - 1, 1), 0], dtype=torch.int32)
     options = am.Options(base_test=literal, list_update=literal, apply_update=1)
@@ -517,6 +519,27 @@ def test_short_history_windows_at_the_edges_of_the_workgroup_sizes(am, wl, oracl
         got = st.to_host()
         for k in ("nA", "nR", "ent_cnt"):
             assert np.array_equal(got[k], host[k]), k
+
+
+@pytest.mark.parametrize("path", [1, 2])
+@pytest.mark.parametrize("literal", [0, 1])
+@pytest.mark.parametrize("cap", [500, 5000])
+def test_list_constants_at_the_edges_of_the_list_lengths(am, wl, oracle, cap, literal, path):
+    """The kernel constants of a sequence's lists come from the statistics launch (single-read kernel) or from the
+    decision kernel itself (two-kernel path): empty lists, one and two samples, a wavefront's or a workgroup's batch more
+    or less, full lists, lists of 4096 samples (added up) and longer ones (sums in the state); more sequences than
+    vocabulary slices."""
+    pairs = [(0, 0), (0, 9), (1, 5), (2, 2), (3, 1), (31, 33), (127, 128), (129, 2), (383, 384), (cap, cap), (cap - 3, 64)]
+    if cap > 4097:
+        pairs += [(2047, 2049), (2048, 1023), (1025, 1024), (4095, 4096), (4097, 300), (300, 4098), (4096, 4097)]
+    B, K = len(pairs), 5
+    batch = wl.config_batched(B=B, k=K, V=8200, seed=40 + cap, cap=cap)
+    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(cap), n_hist=cap)
+    batch.state["nA"][:], batch.state["nR"][:] = [p[0] for p in pairs], [p[1] for p in pairs]
+    options = am.Options(list_update=literal, base_test=literal)
+    out, _, _ = G.run_gpu(am, batch, options=options, stats_path=path)
+    rep = G.compare_verify(out, G.run_oracle(oracle, batch, options=options))
+    _report(f"list lengths cap={cap} literal={literal} path={path}", rep)
 
 
 def test_many_sequences_with_long_histories(am, wl, oracle):
