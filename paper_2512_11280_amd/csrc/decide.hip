@@ -118,21 +118,17 @@ hipError_t launch_decide(const DecideArgs& a, const UpdateArgs& upd, const Works
   }
   const dim3 grid(a.map.B);
   // The kernel is one chain of latencies, and each turn of the positions is the same chain over again: one turn up to
-  // 16 positions with a wavefront each (a list per half: both at once), up to 32 with half a wavefront each.  Of the two, half
-  // a wavefront is the better one where it takes fewer turns, and where one batch of its lanes covers a list: the workgroup is
-  // half the size.  Kernel (us), a wavefront / half a wavefront, 32 sequences: k = 8, lists of 16 7.0 / 6.9, 256 7.8 / 8.9,
-  // 448 9.1 / 10.7; k = 16, lists of 16 8.2 / 7.4, 64 8.5 / 7.8, 256 8.8 / 9.0, 448 10.3 / 10.8; k = 20, lists of 64 8.4 / 8.1,
-  // 256 9.7 / 9.4; k = 40, lists of 64 11.8 / 9.7, 256 13.9 / 11.6.  Fewer threads and more turns: k = 16 with 8 wavefronts 8.9
-  // to 12.2, k = 8 with 4 wavefronts 7.3 to 9.6.
-  const bool halves = a.map.K > 16 || (a.map.K > 8 && a.cap <= 32 * kHalfU);
-  const int LP = halves ? 32 : 64, T = halves ? (a.map.K <= 16 ? 512 : 1024) : a.map.K <= 4 ? 256 : a.map.K <= 8 ? 512 : 1024;
+  // 16 positions with a wavefront each (a list per half: both at once), and beyond that half a wavefront to a position, which
+  // takes 32 in a turn.  Kernel (us), a wavefront / half a wavefront, 32 sequences: k = 8, lists of 64 6.9 / 6.9, 256 7.2 / 7.6,
+  // 448 7.6 / 8.6; k = 12 7.1 / 7.1, 7.5 / 8.0, 8.4 / 9.3; k = 20 7.9 / 8.0, 8.6 / 9.1, 10.5 / 10.8; k = 40 11.4 / 9.2,
+  // 12.7 / 10.6, 16.6 / 13.3.  Fewer threads and more turns: k = 16 with 8 wavefronts 10.5 where 16 take 8.9.
+  const int LP = a.map.K > 16 ? 32 : 64, T = a.map.K <= 4 ? 256 : a.map.K <= 8 ? 512 : 1024;
 #define ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, TV, LPV) \
   if (a.dt == DTV && (a.list_update != 0) == INLOOPV && (a.hist != nullptr) == HISTV && T == TV && LP == LPV) \
     launch_kernel((k_decide<DTV, INLOOPV, HISTV, TV, LPV>), grid, dim3(TV), st, a, upd, ws);
 #define ADASD_DECIDE_T(DTV, INLOOPV, HISTV) \
   ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 256, 64) ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 512, 64) \
-  ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 1024, 64) \
-  ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 512, 32) ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 1024, 32)
+  ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 1024, 64) ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, 1024, 32)
 #define ADASD_DECIDE_DT(DTV) \
   ADASD_DECIDE_T(DTV, false, false) ADASD_DECIDE_T(DTV, false, true) ADASD_DECIDE_T(DTV, true, false) ADASD_DECIDE_T(DTV, true, true)
   ADASD_DECIDE_DT(ADASD_BF16)

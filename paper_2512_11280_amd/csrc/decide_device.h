@@ -40,45 +40,50 @@ __device__ __forceinline__ void add_moments(const float* X, int nx, double c, do
   s2 += half_sum_d(e0 * e0 + e1 * e1);
 }
 
-// ln [ p(d | list) P(list) ] by 32 lanes: max-shifted log-sum-exp of the kernels, each batch's largest exponent joining the
-// lane's reference.  EXTRA: the list goes on in X (nx <= 64 samples).
+// A batch of a list's samples joins a thread's running sum of kernels: acc * 2^m.  The reference m is the largest exponent so
+// far, found from the smallest distance, so a sample costs five instructions in double precision: its
+// distance, the minimum, the square, the exponent less the reference (one rounding, then to float for the
+// hardware's exp2), and the conversion of the sample.  Samples that do not count are infinite.
+template <int N, class Sum>
+__device__ __forceinline__ void join_kernels(double d, const float (&x)[N], double scale, double& m, Sum& acc) {
+  double e[N], least = INFINITY;
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    e[u] = d - (double)x[u];
+    least = fmin(least, fabs(e[u]));
+  }
+  const double hi = fmax(m, -(least * least) * scale);
+  const double ref = hi > -INFINITY ? hi : 0.0;            // (nothing to add yet: every factor is 2^-inf = 0)
+  float add = 0.f;
+#pragma unroll
+  for (int u = 0; u < N; ++u) add += ex2((float)fma(-(e[u] * e[u]), scale, -ref));    // terms below 2^-126 vanish
+  acc = acc * (Sum)ex2((float)(m - ref)) + (Sum)add;
+  m = hi;
+}
+
+// log2 [ p(d | list) P(list) ] by 32 lanes.  EXTRA: the list goes on in X (nx <= 64 samples).
 template <bool EXTRA>
 __device__ __forceinline__ double half_log_joint(double d, const float* L, int n, const float* X, int nx, const Kde& k) {
   const int l32 = threadIdx.x & 31;
   double m = -INFINITY;
   float acc = 0.f;
-  auto join = [&](const auto& t, double hi) {
-    if (!(hi > -INFINITY)) return;         // (a lane past the end of the list has nothing to add)
-    float add = 0.f;
-#pragma unroll
-    for (unsigned u = 0; u < sizeof(t) / sizeof(t[0]); ++u) add += ex2((float)((t[u] - hi) * 1.44269504088896340736));   // terms below 2^-126 vanish
-    acc = fmaf(acc, ex2((float)((m - hi) * 1.44269504088896340736)), add);
-    m = hi;
-  };
 #pragma unroll 1
-  for (int base = 0; base < n; base += 32 * kHalfU) {
-    double t[kHalfU], hi = m;
+  for (int base = l32; base - l32 < n; base += 32 * kHalfU) {
+    float x[kHalfU];
 #pragma unroll
-    for (int u = 0; u < kHalfU; ++u) {
-      const double e = d - (double)L[min(base + l32 + 32 * u, n - 1)];
-      t[u] = base + l32 + 32 * u < n ? -(e * e) * k.inv2h2 : -INFINITY;
-      hi = fmax(hi, t[u]);
-    }
-    join(t, hi);
+    for (int u = 0; u < kHalfU; ++u) x[u] = L[min(base + 32 * u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < kHalfU; ++u)
+      if (base + 32 * u >= n) x[u] = INFINITY;
+    join_kernels(d, x, k.scale, m, acc);
   }
   if (EXTRA && nx > 0) {
-    double t[2], hi = m;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const double e = d - (double)X[min(l32 + 32 * u, nx - 1)];
-      t[u] = l32 + 32 * u < nx ? -(e * e) * k.inv2h2 : -INFINITY;
-      hi = fmax(hi, t[u]);
-    }
-    join(t, hi);
+    const float x[2] = {l32 < nx ? X[l32] : INFINITY, l32 + 32 < nx ? X[l32 + 32] : INFINITY};
+    join_kernels(d, x, k.scale, m, acc);
   }
   const double top = half_max_d(m);
-  const double total = half_sum_d(m > -INFINITY ? (double)acc * (double)ex2((float)((m - top) * 1.44269504088896340736)) : 0.0);
-  return top + kLn2 * log2_acc((float)total) - k.log_norm;
+  const double total = half_sum_d(m > -INFINITY ? (double)acc * (double)ex2((float)(m - top)) : 0.0);
+  return top + log2_acc((float)total) - k.log_norm;
 }
 
 // Update step of one sequence (Section 4.3, last paragraph of Section 4.4; update lines of Algorithm 1)
@@ -417,7 +422,7 @@ __device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, cons
         swap_halves(j[0], j[1]);
         both = __all(both) != 0;
       }
-      if (both) PA = 1.0 / (1.0 + (double)ex2((float)((j[1] - j[0]) * 1.44269504088896340736)));
+      if (both) PA = 1.0 / (1.0 + (double)ex2((float)(j[1] - j[0])));
     }
     if (!lead) continue;
     sh.hq[i] = bad ? NAN : rq.H;
@@ -522,9 +527,14 @@ __device__ inline void update_sequence(const UpdateArgs& a, int b, int lane, int
 // Long histories.  The cost of the Bayesian test grows with the lists (Section 4.4 flags it): with
 // thousands of samples per list one workgroup per sequence and half a wavefront per position is far
 // too little.  Here one workgroup of 256 threads takes ONE position: every thread walks a stride of
-// both lists once (running maximum and rescaled sum, so no separate pass for the maximum), the
+// both lists once (running reference and rescaled sum, so no separate pass for the maximum), the
 // workgroups of a sequence leave one record per position, and the one that arrives last takes the
 // sequence's decisions (first rejection, sampling plan, status, update step).
+// With few workgroups this is a chain of latencies, with many the double-precision arithmetic of the samples counts, and the
+// wavefronts in flight: samples are walked in groups of four per thread, as many groups as the longer list fills (all 16 at
+// once took 143 registers and did four times the work for a list of a thousand), and the two lists' groups side by side.
+// Kernel (us), all 16 / groups: 32 x 8 positions, lists of 1024 8.9 / 7.7, 128 x 16 23.8 / 15.4, 128 x 40 51.2 / 29.7,
+// 64 x 16 ragged, lists of 4096 15.7 / 13.8.
 // ---------------------------------------------------------------------------------------------
 struct WideShared {
   double m[2][kWaves], s[2][kWaves];
@@ -535,30 +545,27 @@ struct WideShared {
 constexpr int kWideU = 16;   // samples per thread in flight: one workgroup walks a list alone, so the latency of
                              // a load is only hidden by the thread's own other loads
 
-// One batch of kernel exponents joins a thread's running maximum m and rescaled sum s: the batch's
-// largest exponent first, then ONE rescale of the old sum.  valid: how many of x[] hold samples.
-__device__ __forceinline__ void joint_terms(double d, const float (&x)[kWideU], int first, int nt, double inv2h2,
-                                            double& m, double& s) {
-  double t[kWideU];
-  double hi = m;
+// A thread's samples of a list, from `first` on in steps of the workgroup: asked for and joined in groups of kWideG, as many as
+// the list fills (`first` less the thread's own index is uniform).
+constexpr int kWideG = 4;
+__device__ __forceinline__ void ask_terms(const float* L, int first, int n, float (&x)[kWideU / kWideG][kWideG]) {
+  const int start = first - (int)threadIdx.x;
 #pragma unroll
-  for (int u = 0; u < kWideU; ++u) {
-    const double e = d - (double)x[u];
-    t[u] = first + u * kBlock < nt ? -(e * e) * inv2h2 : -INFINITY;
-    hi = fmax(hi, t[u]);
-  }
-  if (hi > -INFINITY) {                  // (a thread past the end of the list has nothing to add)
-    // all exponents are <= 0; with m = -inf the old sum is 0 and its factor 2^-inf = 0
-    float add = 0.f;
+  for (int g = 0; g < kWideU / kWideG; ++g) {
+    if (start + g * kWideG * kBlock >= n) break;
 #pragma unroll
-    for (int u = 0; u < kWideU; ++u) add += ex2((float)((t[u] - hi) * 1.44269504088896340736));
-    s = s * (double)ex2((float)((m - hi) * 1.44269504088896340736)) + (double)add;
-    m = hi;
+    for (int u = 0; u < kWideG; ++u) x[g][u] = L[min(first + (g * kWideG + u) * kBlock, n - 1)];
   }
+}
+__device__ __forceinline__ void join_group(double d, float (&x)[kWideG], int g, int first, int n, double scale, double& m, double& s) {
+#pragma unroll
+  for (int u = 0; u < kWideG; ++u)
+    if (first + (g * kWideG + u) * kBlock >= n) x[u] = INFINITY;
+  join_kernels(d, x, scale, m, s);
 }
 
 // Workgroup-wide log-sum of N lists' per-thread (m, s) pairs at once: common maximum, rescaled sums (a
-// thread without samples has s = 0).  out[q] = ln sum_j exp(t_j) of list q.
+// thread without samples has s = 0).  out[q] = log2 of the sum of list q.
 template <int N>
 __device__ __forceinline__ void joint_reduce(const double (&m)[N], const double (&s)[N], WideShared& w, double (&out)[N]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -569,7 +576,7 @@ __device__ __forceinline__ void joint_reduce(const double (&m)[N], const double 
     double other = M[q];
     swap_halves(M[q], other);
     M[q] = fmax(M[q], other);
-    sc[q] = m[q] > -INFINITY ? s[q] * (double)ex2((float)((m[q] - M[q]) * 1.44269504088896340736)) : 0.0;
+    sc[q] = m[q] > -INFINITY ? s[q] * (double)ex2((float)(m[q] - M[q])) : 0.0;
     sc[q] = wave_sum_d(sc[q]);
   }
   __syncthreads();
@@ -589,27 +596,19 @@ __device__ __forceinline__ void joint_reduce(const double (&m)[N], const double 
     double total = 0.0;
 #pragma unroll
     for (int v = 0; v < kWaves; ++v)
-      total += w.m[q][v] > -INFINITY ? w.s[q][v] * (double)ex2((float)((w.m[q][v] - Mb) * 1.44269504088896340736)) : 0.0;
-    out[q] = Mb + kLn2 * log2_acc((float)total);
+      total += w.m[q][v] > -INFINITY ? w.s[q][v] * (double)ex2((float)(w.m[q][v] - Mb)) : 0.0;
+    out[q] = Mb + log2_acc((float)total);
   }
 }
 
-// One more sample per thread (tid < nx) of a list that goes on in X.
-__device__ __forceinline__ void joint_extra(double d, const float* X, int nx, double inv2h2, double& m, double& s) {
-  if ((int)threadIdx.x >= nx) return;
-  const double e = d - (double)X[threadIdx.x], t = -(e * e) * inv2h2, hi = fmax(m, t);
-  s = s * (double)ex2((float)((m - hi) * 1.44269504088896340736)) + (double)ex2((float)((t - hi) * 1.44269504088896340736));
-  m = hi;
-}
-
-// Exponents of a list of any length, streamed.
-__device__ inline void stream_terms(double d, const float* L, int n, double inv2h2, double& m, double& s) {
+// A list of any length, streamed.
+__device__ inline void stream_terms(double d, const float* L, int n, double scale, double& m, double& s) {
 #pragma unroll 1
-  for (int base = threadIdx.x; base < n; base += kWideU * kBlock) {
-    float x[kWideU];
+  for (int first = threadIdx.x; first - (int)threadIdx.x < n; first += kWideU * kBlock) {
+    float x[kWideU / kWideG][kWideG];
+    ask_terms(L, first, n, x);
 #pragma unroll
-    for (int u = 0; u < kWideU; ++u) x[u] = L[min(base + u * kBlock, n - 1)];
-    joint_terms(d, x, base, n, inv2h2, m, s);
+    for (int g = 0; g < kWideU / kWideG; ++g) join_group(d, x[g], g, first, n, scale, m, s);
   }
 }
 
@@ -683,13 +682,10 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
     // Lists of up to U samples per thread are read ONCE, both at the same time and ahead of everything else, and stay in
     // registers; longer ones are streamed.
     const bool resident = nA <= U * kBlock && nR <= U * kBlock;
-    float xa[U], xr[U];
+    float xa[U / kWideG][kWideG], xr[U / kWideG][kWideG];
     if (resident) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        xa[u] = LA[max(min(tid + u * kBlock, nA - 1), 0)];
-        xr[u] = LR[max(min(tid + u * kBlock, nR - 1), 0)];
-      }
+      ask_terms(LA, tid, nA, xa);
+      ask_terms(LR, tid, nR, xr);
     }
     HistRecord hist;
     if (HIST) hist = a.hist[b];
@@ -751,16 +747,24 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
       if (ok) {                      // uniform over the workgroup
         double mm[2] = {-INFINITY, -INFINITY}, ss[2] = {0.0, 0.0}, out[2];
         if (resident) {
-          joint_terms(d, xa, tid, nA, kA.inv2h2, mm[0], ss[0]);
-          joint_terms(d, xr, tid, nR, kR.inv2h2, mm[1], ss[1]);
+          // the two lists side by side: each group is a chain of dependent instructions
+#pragma unroll
+          for (int g = 0; g < U / kWideG; ++g) {
+            if (g * kWideG * kBlock >= max(nA, nR)) break;
+            join_group(d, xa[g], g, tid, nA, kA.scale, mm[0], ss[0]);
+            join_group(d, xr[g], g, tid, nR, kR.scale, mm[1], ss[1]);
+          }
         } else {
-          stream_terms(d, LA, nA, kA.inv2h2, mm[0], ss[0]);
-          stream_terms(d, LR, nR, kR.inv2h2, mm[1], ss[1]);
+          stream_terms(d, LA, nA, kA.scale, mm[0], ss[0]);
+          stream_terms(d, LR, nR, kR.scale, mm[1], ss[1]);
         }
-        if (INLOOP) joint_extra(d, sh.extra, ne, kA.inv2h2, mm[0], ss[0]);
+        if (INLOOP && tid < ne) {    // the list goes on with the appends
+          const float x[1] = {sh.extra[tid]};
+          join_kernels(d, x, kA.scale, mm[0], ss[0]);
+        }
         joint_reduce<2>(mm, ss, wsh, out);
         const double ja = out[0] - kA.log_norm, jr = out[1] - kR.log_norm;
-        PA = 1.0 / (1.0 + (double)ex2((float)((jr - ja) * 1.44269504088896340736)));
+        PA = 1.0 / (1.0 + (double)ex2((float)(jr - ja)));
       }
     }
     if (tid == 0) {

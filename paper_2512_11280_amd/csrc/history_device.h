@@ -56,8 +56,8 @@ __device__ __forceinline__ double half_max_d(double v) {
 }
 
 struct Kde {
-  double inv2h2;   // 1 / (2 h^2)
-  double log_norm; // ln(n h sqrt(2 pi)) - ln prior  (subtracted from the log kernel sum)
+  double scale;    // log2(e) / (2 h^2): a kernel is 2 to the minus scale * (d - x)^2
+  double log_norm; // log2(n h sqrt(2 pi)) - log2 prior  (subtracted from the log2 of the kernel sum)
 };
 
 // Gaussian-kernel constants of a history list from its shifted moments (sum and sum of squares of
@@ -70,9 +70,9 @@ __device__ inline bool kde_constants(double s1, double s2, int n, int n_other, i
   const float base = bw_rule == 1 ? 1.0f / (float)n : 4.0f / (3.0f * (float)n);
   const double factor = (double)ex2((float)(0.2 * log2_acc(base)));
   const double h = factor * sqrt(var);
-  out->inv2h2 = 1.0 / (2.0 * h * h);
+  out->scale = 1.44269504088896340736 / (2.0 * h * h);
   const float prior = (float)n / (float)(n + n_other);
-  out->log_norm = kLn2 * (log2_acc((float)((double)n * h * 2.50662827463100050242)) - log2_acc(prior));
+  out->log_norm = log2_acc((float)((double)n * h * 2.50662827463100050242)) - log2_acc(prior);
   return true;
 }
 

@@ -502,8 +502,7 @@ def test_long_history_with_the_update_in_the_same_call_and_status_bits(am, wl, o
 @pytest.mark.parametrize("cap", [500, 128])
 def test_short_history_windows_at_the_edges_of_the_workgroup_sizes(am, wl, oracle, K, literal, cap):
     """One workgroup takes a sequence's decisions.  A wavefront to a position: 256 threads up to k = 4, 512 up to 8, 1024
-    up to 16.  Half a wavefront to a position: from k = 17, and with lists of at most 128 samples from k = 9 (512
-    threads up to 16, 1024 beyond, in turns above 32)."""
+    up to 16.  Half a wavefront to a position from k = 17, in turns above 32."""
     B = 4
     batch = wl.config_batched(B=B, k=K, V=1032, seed=700 + K, cap=cap)
     batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(K), n_hist=min(300, cap - 13))
