@@ -466,14 +466,17 @@ static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void*
     d.jsd_split = S;
     d.tok = vout.tok;
   }
+  SampleArgs s = sample_args(a, v);
+  s.polls = token_polls;
+  const int S3 = token_split(B, V, (int)a->dt);
+  if (merges_decisions(d, S3)) {
+    Scope sc(3, st);
+    return launch_decide_sample(d, upd, s, S3, ws, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
+  }
   {
     Scope sc(2, st);
     if (launch_decide(d, upd, ws, st) != hipSuccess) return ADASD_ERR_HIP;
   }
-
-  SampleArgs s = sample_args(a, v);
-  s.polls = token_polls;
-  const int S3 = token_split(B, V, (int)a->dt);
   {
     Scope sc(3, st);
     if (launch_sample(s, S3, ws, st) != hipSuccess) return ADASD_ERR_HIP;

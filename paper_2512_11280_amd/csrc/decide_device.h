@@ -278,6 +278,20 @@ __device__ __forceinline__ void clear_exchange_words(const DecideArgs& a, const 
   }
 }
 
+__device__ __forceinline__ double first_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)), __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
+// The round, as decided, applied to the sequence's state by one wavefront.  Returns the status bits (in every lane).
+__device__ __forceinline__ uint32_t apply_round(const UpdateArgs& upd, const UpdateIn& before, int b, int r, int kb, const DecideShared& sh) {
+  const int lane = threadIdx.x & 63;
+  float d = 0.f, H = 0.f;
+  if (lane <= r && lane < kb) d = sh.dist[lane];
+  if (lane == r && r < kb) H = sh.hq[r];
+  const uint32_t st = update_sequence_core(upd, before, b, lane, r, kb, d, H, false);
+  return (uint32_t)__builtin_amdgcn_readlane((int)st, r < 64 ? r : 63);
+}
+
 // The decisions of one sequence by one workgroup of T threads, LP lanes to a position: with 64 the lower half of the
 // wavefront takes the accepted list and the upper half the rejected one, with 32 one list comes after the other.  HIST: the
 // lists' constants were formed by the statistics launch; else every group of lanes adds up the lists' moments
@@ -285,8 +299,16 @@ __device__ __forceinline__ void clear_exchange_words(const DecideArgs& a, const 
 // is decided.  INLOOP: the accepted list grows
 // inside the verification loop (Algorithm 1): position i sees the list of the state followed by the
 // distances of positions 0..i-1 of this round that pass the open-interval filter, up to the capacity.
-template <int DT, bool INLOOP, bool HIST, int T, int LP>
-__device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, const Workspace& ws, int b, DecideShared& sh) {
+// REPLICA: several workgroups decide the same sequence, each for itself.  One of them (`writer`) leaves what is decided,
+// and the caller applies the round and leaves the status once all of them have read the state.
+struct Decided {        // the same in every lane (REPLICA)
+  int r, kb;
+  uint32_t st;
+  SamplePlan plan;
+};
+template <int DT, bool INLOOP, bool HIST, int T, int LP, bool REPLICA = false>
+__device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const UpdateArgs& upd, const Workspace& ws, int b, DecideShared& sh,
+                                                   bool writer = true) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = tid / LP;
   const bool lead = (tid & (LP - 1)) == 0;
   constexpr int kGroups = T / LP;
@@ -315,7 +337,7 @@ __device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, cons
     LR = a.LR + (size_t)b * a.cap;
   }
   UpdateIn before{};
-  if (upd.B > 0) before = update_inputs(upd, b);
+  if (!REPLICA && upd.B > 0) before = update_inputs(upd, b);
   auto load_pos = [&](int i) { return load_position<DT>(a, ws, b, i, rnd, seq); };
   PosLoad pos;
   if (grp < kb) pos = load_pos(grp);
@@ -329,7 +351,7 @@ __device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, cons
       float dv;
       if (a.jsd_split > 0) {
         dv = fold_distance(L);
-        if (lead) a.d_js[o] = dv;
+        if (lead && writer) a.d_js[o] = dv;
       } else {
         dv = (L.rp.bad || L.rq.bad) ? NAN : a.d_js[o];
       }
@@ -400,7 +422,7 @@ __device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, cons
     } else {
       if (a.jsd_split > 0) {
         dv = fold_distance(pos);
-        if (lead) a.d_js[o] = dv;
+        if (lead && writer) a.d_js[o] = dv;
       } else {
         dv = a.d_js[o];
       }
@@ -430,11 +452,13 @@ __device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, cons
     sh.lse2[i][1] = rq.lse2;
     sh.token[i] = pos.x;
     if (bad) {
-      if (a.H_p) a.H_p[o] = NAN;
-      a.H_q[o] = NAN;
-      a.d_js[o] = NAN;
-      if (a.p_accept) a.p_accept[o] = NAN;
-      if (a.accept_mask) a.accept_mask[o] = 0;
+      if (writer) {
+        if (a.H_p) a.H_p[o] = NAN;
+        a.H_q[o] = NAN;
+        a.d_js[o] = NAN;
+        if (a.p_accept) a.p_accept[o] = NAN;
+        if (a.accept_mask) a.accept_mask[o] = 0;
+      }
       sh.outcome[i] = 2;
       atomicOr(&sh.status, (uint32_t)ADASD_ST_NONFINITE);
       continue;
@@ -454,11 +478,13 @@ __device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, cons
       base = pos.log_u1 < log_ratio;   // false for NaN (both probabilities zero)
     }
     const int relaxed = a.reject_rule == 1 ? (PA >= 0.5) : (pos.u2 < PA);
-    if (a.p_accept) a.p_accept[o] = (float)PA;
-    if (a.accept_mask) a.accept_mask[o] = (uint8_t)(base | (relaxed << 1));
+    if (writer) {
+      if (a.p_accept) a.p_accept[o] = (float)PA;
+      if (a.accept_mask) a.accept_mask[o] = (uint8_t)(base | (relaxed << 1));
+    }
     sh.outcome[i] = (base || relaxed) ? 1 : 0;   // rejected only if both tests reject
   }
-  for (int i = kb + tid; i < K; i += T) {      // positions past the window
+  for (int i = kb + tid; writer && i < K; i += T) {      // positions past the window
     const size_t o = (size_t)b * K + i;
     if (a.H_p) a.H_p[o] = 0.f;
     a.H_q[o] = 0.f;
@@ -467,48 +493,48 @@ __device__ void decide_sequence(const DecideArgs& a, const UpdateArgs& upd, cons
     if (a.accept_mask) a.accept_mask[o] = 0;
   }
   __syncthreads();
-  clear_exchange_words<T>(a, ws, (size_t)b * K, K);
-  if (wave != 0) return;
+  if (writer) clear_exchange_words<T>(a, ws, (size_t)b * K, K);
+  if (!REPLICA && wave != 0) return {};
 
   // ---- one wavefront, one lane per position: first rejection, sampling plan, the round applied to the state
   const int outcome = lane < kb ? sh.outcome[lane] : 1;
   const unsigned long long rejected = __ballot(outcome != 1);
   const int r = rejected ? __ffsll((long long)rejected) - 1 : kb;
-  uint32_t st_upd = 0;
-  if (upd.B > 0) {
-    // (the lists were only read above)
-    float d = 0.f, H = 0.f;
-    if (lane <= r && lane < kb) d = sh.dist[lane];
-    if (lane == r && r < kb) H = sh.hq[r];
-    st_upd = update_sequence_core(upd, before, b, lane, r, kb, d, H, false);
-  }
-  st_upd = __builtin_amdgcn_readlane((int)st_upd, r < 64 ? r : 63);
-  if (lane == 0) {
-    a.n_accept[b] = r;
-    SamplePlan plan;
-    plan.row = r;
-    plan.excluded = -1;
+  const auto plan_of = [&](int x, bool valid, double lse2_p, double lse2_q) {
+    SamplePlan plan{r, 0, 1, -1, 0.0, 0.0};          // bonus row: Gumbel-max needs no normaliser
     if (r < kb) {
       plan.residual = 1;
       if (a.base_test == 1) {
         // replacement from the target row without the drafted token (a broken token excludes nothing)
-        const int x = sh.token[r];
         const bool x_ok = x >= 0 && x < a.map.V;
         plan.residual = x_ok ? 2 : 0;
         plan.excluded = x_ok ? x : -1;
       }
-      plan.valid = sh.outcome[r] != 2;
-      plan.lse2_p = sh.lse2[r][0];
-      plan.lse2_q = sh.lse2[r][1];
-    } else {
-      plan.residual = 0;   // bonus row: Gumbel-max needs no normaliser
-      plan.valid = 1;
-      plan.lse2_p = 0.0;
-      plan.lse2_q = 0.0;
+      plan.valid = valid;
+      plan.lse2_p = lse2_p;
+      plan.lse2_q = lse2_q;
     }
-    ws.plan[b] = plan;
-    a.status[b] = st | sh.status | st_upd;
+    return plan;
+  };
+  if (!REPLICA) {
+    uint32_t st_upd = 0;
+    if (upd.B > 0) st_upd = apply_round(upd, before, b, r, kb, sh);      // (the lists were only read above)
+    if (lane == 0) {
+      a.n_accept[b] = r;
+      ws.plan[b] = r < kb ? plan_of(sh.token[r], sh.outcome[r] != 2, sh.lse2[r][0], sh.lse2[r][1]) : plan_of(-1, true, 0.0, 0.0);
+      a.status[b] = st | sh.status | st_upd;
+    }
+    return {};
   }
+  Decided out{r, kb, st | (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.status), {}};
+  const int at = min(r, ADASD_MAX_K - 1);
+  out.plan = plan_of(__builtin_amdgcn_readfirstlane(sh.token[at]), __builtin_amdgcn_readfirstlane((int)sh.outcome[at]) != 2,
+                     first_lane(sh.lse2[at][0]), first_lane(sh.lse2[at][1]));
+  if (writer && tid == 0) {
+    a.n_accept[b] = r;
+    ws.plan[b] = out.plan;
+  }
+  return out;
 }
 
 }  // namespace adasd

@@ -253,6 +253,10 @@ hipError_t launch_shard_refine(const SampleArgs& a, int S, int col0, const float
                                void* cand_out, hipStream_t st);
 hipError_t launch_shard_settle(const SampleArgs& a, int G, float* tau, const void* cand_all, const Workspace& ws,
                                hipStream_t st);
+// Whether the decisions of a round are taken inside the token kernel, S slices per sequence (sample.hip): up to so many workgroups.
+constexpr int kMergeGroups = 512, kMergeInLoop = 256;      // (256 compute units)
+bool merges_decisions(const DecideArgs& d, int S);
+hipError_t launch_decide_sample(const DecideArgs& d, const UpdateArgs& upd, const SampleArgs& a, int S, const Workspace& ws, hipStream_t st);
 hipError_t launch_sample(const SampleArgs& a, int S, const Workspace& ws, hipStream_t st);
 
 hipError_t launch_update(const UpdateArgs& a, hipStream_t st);

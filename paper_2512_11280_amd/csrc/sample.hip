@@ -8,6 +8,7 @@
 // elements whose upper bound reaches the winner's lower bound (found from the per-slice records, a
 // slice with two such elements is scanned again), and only if that is still too close to call, or the
 // winner's mass is not certain, over the whole row (exact path).
+#include "decide_device.h"
 #include "sample_device.h"
 
 namespace adasd {
@@ -34,20 +35,48 @@ __device__ __forceinline__ void scan_plan(const SamplePlan& plan, const char* pr
   else scan_slice<DT, kPlain, PRUNE>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, sh, poison);
 }
 
+// Where a sequence's slices leave their words: the first slots of its part of the hand-off region.
+struct PlainWords {
+  uint64_t* base;
+  __device__ __forceinline__ uint64_t* at(int s) const { return base + s * kXchgWords; }
+};
+// In the slots of its positions that the statistics kernel does not use (free_slots of them per position, at least half of
+// them: a sequence's slices take those of two positions at most): the words of that kernel are being cleared meanwhile.
+struct FreeWords {
+  uint64_t* base;      // the first free slot of the sequence's first position
+  int free_slots;
+  __device__ __forceinline__ uint64_t* at(int s) const {
+    return base + (s < free_slots ? s : s - free_slots + kMaxSplit) * kXchgWords;
+  }
+};
+
+// What the token kernel does beside the draw: nothing, or (MERGED) the round is still to be applied and the status word to be
+// left, by the workgroup that arrives last.
+struct DrawOnly {
+  static constexpr bool kMerged = false;
+  __device__ __forceinline__ void ask() {}
+  __device__ __forceinline__ uint32_t finish() { return 0u; }
+};
+struct DrawAndApply {
+  static constexpr bool kMerged = true;
+  const UpdateArgs& upd;
+  const DecideShared& sh;
+  const Decided& dec;
+  int b;
+  UpdateIn before;
+  __device__ __forceinline__ void ask() {
+    if (upd.B > 0) before = update_inputs(upd, b);
+  }
+  __device__ __forceinline__ uint32_t finish() { return dec.st | (upd.B > 0 ? apply_round(upd, before, b, dec.r, dec.kb, sh) : 0u); }
+};
+
+// The token of sequence b, slice s of S, by one workgroup of kBlock threads.
 // LONG: a row of more slices than there are hand-off words (see token_split).  The records then go through part3, and have
 // landed before the ticket is taken; and a compute unit holds no more than one such workgroup of a few sequences.
-template <int DT, bool LONG, bool PRUNE>
-__global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, int S, int chunk, Workspace ws) {
-  warm_kernargs<sizeof(SampleArgs) + 2 * sizeof(int) + sizeof(Workspace)>();
+template <int DT, bool LONG, bool PRUNE, class Words, class Round>
+__device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk, const Workspace& ws, const SamplePlan& plan, uint32_t c2,
+                                           uint32_t c3, const Words& slots, Round& round) {
   const int b = blockIdx.y, s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // (by scalar loads, all at once: the kernel before this one has left them)
-  const SamplePlan plan = scalar_load(ws.plan + b);
-  const uint32_t c2 = a.round ? scalar_load(a.round + b) : a.round0;
-  const uint32_t c3 = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
-  if (!plan.valid) {
-    if (s == 0 && tid == 0) a.next_token[b] = -1;   // status already carries NONFINITE
-    return;
-  }
   const int V = a.map.V;
   const char* prow = a.map.base[0] + ((int64_t)b * a.map.seq_stride[0] +
                                       (int64_t)plan.row * a.map.pos_stride[0]) * Elem<DT>::bytes;
@@ -65,6 +94,7 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
   __shared__ Top2 sh_top[kWaves];
   // modes: 0 not the last workgroup; 1 final; 2 settle among the close candidates; 3 broken bonus row; 4 whole row in float64
   __shared__ int sh_mode;
+  __shared__ uint32_t sh_status;              // (MERGED) what the status word holds so far
   __shared__ float sh_tau;
   __shared__ double sh_red[kWaves];
   best = top2_wave_reduce(best);
@@ -95,7 +125,7 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
       publish_barrier();
       last = take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S);
     } else if (S > 1) {
-      uint64_t* words = ws.xchg + ((size_t)b * kMaxSplit + s) * kXchgWords;
+      uint64_t* words = slots.at(s);
       uint64_t w[kXchgWords];
       pack_draw(DrawRecord{best.k1, best.k2, zp, zq, best.i1, poison}, w);
       if (lane < kXchgWords)
@@ -105,6 +135,7 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
     int mode = 0;
     if (last) {
       // ---- last workgroup of this sequence: fold the S records
+      round.ask();
       Top2 t{-INFINITY, -1, -INFINITY, -1};
       bool arrived = true;
       if (LONG) {
@@ -117,7 +148,7 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
         poison = __any(poison);
       } else if (S > 1) {
         uint64_t w[kXchgWords];
-        arrived = take_words(ws.xchg + ((size_t)b * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w, a.polls);
+        arrived = take_words(slots.at(min(lane, S - 1)), lane < S, w, a.polls);
         if (lane < S) {
           const DrawRecord r = unpack_draw(w);
           t = Top2{r.k1, r.i1, r.k2, -1};
@@ -166,6 +197,13 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
       }
       if (mode == 1 && lane == 0) a.next_token[b] = top.i1;
       if (lane == 0) sh_tau = top.k1 - margin;
+      if (Round::kMerged) {
+        const uint32_t st = round.finish();
+        if (lane == 0) {
+          sh_status = st;
+          if (mode == 1) a.status[b] = st;
+        }
+      }
     }
     if (lane == 0) sh_mode = mode;
   }
@@ -175,7 +213,7 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
   if (mode == 3) {
     if (tid == 0) {
       a.next_token[b] = -1;
-      a.status[b] |= ADASD_ST_NONFINITE;
+      a.status[b] = (Round::kMerged ? sh_status : a.status[b]) | ADASD_ST_NONFINITE;
     }
     return;
   }
@@ -192,8 +230,52 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
                            a.seed_hi, sh_red, &bits);
   if (tid == 0) {
     a.next_token[b] = tok;
-    a.status[b] |= bits;
+    a.status[b] = (Round::kMerged ? sh_status : a.status[b]) | bits;
   }
+}
+
+template <int DT, bool LONG, bool PRUNE>
+__global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, int S, int chunk, Workspace ws) {
+  warm_kernargs<sizeof(SampleArgs) + 2 * sizeof(int) + sizeof(Workspace)>();
+  const int b = blockIdx.y;
+  // (by scalar loads, all at once: the kernel before this one has left them)
+  const SamplePlan plan = scalar_load(ws.plan + b);
+  const uint32_t c2 = a.round ? scalar_load(a.round + b) : a.round0;
+  const uint32_t c3 = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
+  if (!plan.valid) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.next_token[b] = -1;   // status already carries NONFINITE
+    return;
+  }
+  DrawOnly round;
+  draw_token<DT, LONG, PRUNE>(a, S, chunk, ws, plan, c2, c3, PlainWords{ws.xchg + (size_t)b * kMaxSplit * kXchgWords}, round);
+}
+
+// Decisions and token in one launch, for rounds of so few positions and slices that deciding a sequence in every
+// workgroup of its token scan costs less than a launch: the first one leaves what is decided, and the one that
+// arrives last applies the round, when all have read the state.  One turn of the positions: a wavefront to each of up
+// to four, half a wavefront to each of up to eight.
+template <int DT, bool INLOOP, int LP, bool PRUNE>
+__global__ void __launch_bounds__(kBlock, 4) k_decide_sample(DecideArgs d, UpdateArgs upd, SampleArgs a, int S, int chunk, Workspace ws) {
+  warm_kernargs<sizeof(DecideArgs) + sizeof(UpdateArgs) + sizeof(SampleArgs) + 2 * sizeof(int) + sizeof(Workspace)>();
+  __shared__ DecideShared sh;
+  const int b = blockIdx.y, K = d.map.K;
+  const Decided dec = decide_sequence<DT, INLOOP, true, kBlock, LP, true>(d, upd, ws, b, sh, blockIdx.x == 0);
+  const uint32_t c2 = a.round ? scalar_load(a.round + b) : a.round0;
+  const uint32_t c3 = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
+  DrawAndApply round{upd, sh, dec, b, {}};
+  if (!dec.plan.valid) {          // (uniform over the sequence's workgroups)
+    if (threadIdx.x >= 64) return;
+    if (S > 1 && !take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S)) return;
+    round.ask();
+    const uint32_t st = round.finish();
+    if (threadIdx.x == 0) {
+      a.next_token[b] = -1;
+      a.status[b] = st;
+    }
+    return;
+  }
+  const FreeWords slots{ws.xchg + ((size_t)b * K * kMaxSplit + d.xchg_split) * kXchgWords, kMaxSplit - d.xchg_split};
+  draw_token<DT, false, PRUNE>(a, S, chunk, ws, dec.plan, c2, c3, slots, round);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -500,6 +582,42 @@ hipError_t launch_sample(const SampleArgs& a, int S, const Workspace& ws, hipStr
   ADASD_SAMPLE_CASE(ADASD_F32, false, false) ADASD_SAMPLE_CASE(ADASD_F32, false, true)
   ADASD_SAMPLE_CASE(ADASD_F32, true, false) ADASD_SAMPLE_CASE(ADASD_F32, true, true)
 #undef ADASD_SAMPLE_CASE
+  return hipGetLastError();
+}
+
+// Deciding in every workgroup of the token scan takes about as long as deciding in one while each workgroup has a
+// compute unit (or, without appends inside the loop, half of one) to itself; then it saves a launch.  Beyond that the workgroups
+// hold one another up.  Windows above 8 would take a second turn of the positions; long histories have their own kernel;
+// the slices' words need room beside those of the statistics kernel.  Whole calls (us), two kernels / one: 1 x 4 x 32000
+// float 17.3 / 16.2, 1 x 8 x 128256 19.8 / 18.9, 4 x 4 x 128256 20.4 / 19.0, 16 x 6 x 32003 literal 22.4 / 20.7; 504
+// workgroups (8 x 8 x 128256) 27.4 / 26.5, 512 (16 x 8 x 32000) 23.8 / 22.4, literal 512 (32 x 4 x 32003) 22.5 / 23.0;
+// 1008 (16 x 8 x 128256) 37.8 / 38.6, 2016 55.0 / 56.1.
+bool merges_decisions(const DecideArgs& d, int S) {
+  const int free_slots = kMaxSplit - d.xchg_split;
+  const bool wide = d.cap >= kWideCap && !d.relaxed_off && d.LA && d.LR && d.nA && d.nR;
+  const bool hist = d.hist != nullptr || d.relaxed_off || !(d.LA && d.LR && d.nA && d.nR);
+  return d.xchg_split > 0 && hist && !wide && d.map.K <= 8 && S <= kMaxSplit && 2 * free_slots >= kMaxSplit &&
+         S <= (d.map.K > 1 ? kMaxSplit : free_slots) && S * d.map.B <= (d.list_update ? kMergeInLoop : kMergeGroups);
+}
+
+hipError_t launch_decide_sample(const DecideArgs& d, const UpdateArgs& upd, const SampleArgs& a, int S, const Workspace& ws, hipStream_t st) {
+  if (a.map.B <= 0) return hipSuccess;
+  const dim3 grid(S, a.map.B), block(kBlock);
+  const int epv = a.dt == ADASD_BF16 ? 8 : 4, chunk = slice_chunk((a.map.V + epv - 1) / epv, S);
+  const bool prune = scan_prunes(chunk, a.dt);
+  const int LP = d.map.K <= 4 ? 64 : 32;
+#define ADASD_MERGED_CASE(DTV, INLOOPV, LPV, PRUNEV) \
+  if (a.dt == DTV && (d.list_update != 0) == INLOOPV && LP == LPV && prune == PRUNEV) \
+    launch_kernel((k_decide_sample<DTV, INLOOPV, LPV, PRUNEV>), grid, block, st, d, upd, a, S, chunk, ws);
+#define ADASD_MERGED_DT(DTV) \
+  ADASD_MERGED_CASE(DTV, false, 32, false) ADASD_MERGED_CASE(DTV, false, 32, true) \
+  ADASD_MERGED_CASE(DTV, true, 32, false) ADASD_MERGED_CASE(DTV, true, 32, true) \
+  ADASD_MERGED_CASE(DTV, false, 64, false) ADASD_MERGED_CASE(DTV, false, 64, true) \
+  ADASD_MERGED_CASE(DTV, true, 64, false) ADASD_MERGED_CASE(DTV, true, 64, true)
+  ADASD_MERGED_DT(ADASD_BF16)
+  ADASD_MERGED_DT(ADASD_F32)
+#undef ADASD_MERGED_DT
+#undef ADASD_MERGED_CASE
   return hipGetLastError();
 }
 

@@ -520,6 +520,38 @@ def test_short_history_windows_at_the_edges_of_the_workgroup_sizes(am, wl, oracl
             assert np.array_equal(got[k], host[k]), k
 
 
+@pytest.mark.parametrize("B,K,V,dtype", [(1, 1, 9, torch.bfloat16), (2, 1, 128256, torch.bfloat16), (2, 2, 128256, torch.bfloat16),
+                                         (3, 4, 32003, torch.bfloat16), (4, 5, 32000, torch.float32), (6, 8, 20011, torch.float32),
+                                         (6, 9, 20011, torch.float32), (51, 2, 4100, torch.float32), (52, 2, 4100, torch.float32),
+                                         (102, 2, 4100, torch.float32), (103, 2, 4100, torch.float32)])
+@pytest.mark.parametrize("literal", [0, 1])
+def test_small_rounds_decide_inside_the_token_kernel(am, wl, oracle, B, K, V, dtype, literal):
+    """Windows up to 8 (4: a wavefront to a position), up to 512 workgroups (256 with appends inside the loop), slices in
+    the free hand-off slots of one position or of two; beyond each of these the decisions are a kernel of their own.  Twice on
+    one workspace: the first call leaves its hand-off words and counters clear."""
+    cap = 300
+    batch = wl.config_batched(B=B, k=K, V=V, seed=900 + V + K, cap=cap)
+    batch.target, batch.draft = batch.target.to(dtype), batch.draft.to(dtype)
+    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(V), n_hist=280)
+    if B > 2:
+        batch.draft_len = torch.tensor([K, 0, max(K - 1, 1)] + [K] * (B - 3), dtype=torch.int32)
+        batch.target[0, 0, 3] = float("nan")                      # a broken row: no token
+        batch.draft_tokens[2, 0] = V                              # a broken drafted token
+    options = am.Options(base_test=literal, list_update=literal, apply_update=1)
+    ref = G.run_oracle(oracle, batch, options=options)
+    host = {k: np.array(v, copy=True) for k, v in batch.state.items() if k != "tau"}
+    lens = np.full(B, K, np.int32) if batch.draft_len is None else batch.draft_len.numpy()
+    oracle.update(host, ref["n_accept"], lens, ref["H_q"], ref["d_js"], K, d_eps=1e-6)
+    ws = am.Workspace(B, K, V, dtype)
+    for _ in range(2):
+        out, st, _ = G.run_gpu(am, batch, options=options, ws=ws)
+        rep = G.compare_verify(out, ref, info_bits=16 | 8)
+        if rep["flips"] == rep["member_flips"] == 0:
+            got = st.to_host()
+            for k in ("nA", "nR", "ent_cnt"):
+                assert np.array_equal(got[k], host[k]), k
+
+
 @pytest.mark.parametrize("path", [1, 2])
 @pytest.mark.parametrize("literal", [0, 1])
 @pytest.mark.parametrize("cap", [500, 5000])
