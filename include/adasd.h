@@ -377,7 +377,8 @@ int adasd_update_thresholds(const adasd_state *st /* host */, int k_max, const i
  * returns the summed duration and the number of kernels of one class since the last enable;
  * adasd_profile_disable frees the events.  Kernel classes: 0 row statistics (normalisers + entropy; on
  * the single-read path the one kernel of the whole statistics stage, class 1 then stays empty),
- * 1 JS distance (two-kernel path), 2 decision, 3 token sampling, 4 state update, 5 drafting calls
+ * 1 JS distance (two-kernel path), 2 decision, 3 token sampling (a small round's decisions are taken in
+ * the same kernel, class 2 then stays empty), 4 state update, 5 drafting calls
  * (adasd_draft_entropy and adasd_draft_step: one kernel per call), 6 adasd_stream_read.
  * NOT thread-safe: there is one set of events per process, and while it is enabled every entry point
  * records into it.  Enable, the calls to be timed, read and disable must all come from one thread, with

@@ -200,12 +200,12 @@ struct DecideShared {
   uint8_t n_before[ADASD_MAX_K];    // in-loop appends: how many of them come from earlier positions
   double mom[kWaves][4];            // per-wave shifted moments of the two lists (long histories)
   double lse2[ADASD_MAX_K][2];      // normalisers of the candidate positions (for the sampling plan)
-  uint8_t outcome[ADASD_MAX_K];     // 1: position accepted, 0: rejected, 2: broken rows
+  uint8_t outcome[ADASD_MAX_K];     // kAccepted, kBroken (non-finite rows), kBadToken; none of them: rejected
   int32_t token[ADASD_MAX_K];       // the drafted tokens
   float dist[ADASD_MAX_K];          // the round's distances (in-loop appends; the fused update step)
   float hq[ADASD_MAX_K];            // the round's draft entropies (the fused update step)
-  uint32_t status;
 };
+constexpr int kAccepted = 1, kBroken = 2, kBadToken = 4;
 
 // Everything a candidate position needs from memory, and its two uniforms.
 struct PosLoad {
@@ -313,7 +313,6 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
   const bool lead = (tid & (LP - 1)) == 0;
   constexpr int kGroups = T / LP;
   const int K = a.map.K;
-  if (tid == 0) sh.status = 0;
 
   int kb = K;
   uint32_t st = 0;
@@ -459,18 +458,15 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
         if (a.p_accept) a.p_accept[o] = NAN;
         if (a.accept_mask) a.accept_mask[o] = 0;
       }
-      sh.outcome[i] = 2;
-      atomicOr(&sh.status, (uint32_t)ADASD_ST_NONFINITE);
+      sh.outcome[i] = kBroken;
       continue;
     }
     // speculative-sampling test: accept with probability min(1, p(x)/q(x)), in the log domain; or the
     // loop's own match test: accept with probability p(x)
     int base = 0;
-    if (!pos.x_ok) {
-      atomicOr(&sh.status, (uint32_t)ADASD_ST_BAD_TOKEN);
-    } else if (a.base_test == 1) {
+    if (pos.x_ok && a.base_test == 1) {
       base = pos.log_u1 < (double)pos.zp - rp.lse2 * kLn2;
-    } else {
+    } else if (pos.x_ok) {
       double lp = (double)pos.zp - rp.lse2 * kLn2;
       double lq = (double)pos.zq - rq.lse2 * kLn2;
       double log_ratio = lp - lq;
@@ -482,7 +478,7 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
       if (a.p_accept) a.p_accept[o] = (float)PA;
       if (a.accept_mask) a.accept_mask[o] = (uint8_t)(base | (relaxed << 1));
     }
-    sh.outcome[i] = (base || relaxed) ? 1 : 0;   // rejected only if both tests reject
+    sh.outcome[i] = (base || relaxed ? kAccepted : 0) | (pos.x_ok ? 0 : kBadToken);   // rejected only if both tests reject
   }
   for (int i = kb + tid; writer && i < K; i += T) {      // positions past the window
     const size_t o = (size_t)b * K + i;
@@ -497,8 +493,12 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
   if (!REPLICA && wave != 0) return {};
 
   // ---- one wavefront, one lane per position: first rejection, sampling plan, the round applied to the state
-  const int outcome = lane < kb ? sh.outcome[lane] : 1;
-  const unsigned long long rejected = __ballot(outcome != 1);
+  // (the status comes from the outcomes: a word of its own would have to be cleared, with a barrier, before the first position
+  // can set a bit of it)
+  const int outcome = lane < kb ? sh.outcome[lane] : kAccepted;
+  const unsigned long long rejected = __ballot(!(outcome & kAccepted));
+  if (__any(outcome & kBroken)) st |= ADASD_ST_NONFINITE;
+  if (__any(outcome & kBadToken)) st |= ADASD_ST_BAD_TOKEN;
   const int r = rejected ? __ffsll((long long)rejected) - 1 : kb;
   const auto plan_of = [&](int x, bool valid, double lse2_p, double lse2_q) {
     SamplePlan plan{r, 0, 1, -1, 0.0, 0.0};          // bonus row: Gumbel-max needs no normaliser
@@ -521,14 +521,14 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
     if (upd.B > 0) st_upd = apply_round(upd, before, b, r, kb, sh);      // (the lists were only read above)
     if (lane == 0) {
       a.n_accept[b] = r;
-      ws.plan[b] = r < kb ? plan_of(sh.token[r], sh.outcome[r] != 2, sh.lse2[r][0], sh.lse2[r][1]) : plan_of(-1, true, 0.0, 0.0);
-      a.status[b] = st | sh.status | st_upd;
+      ws.plan[b] = r < kb ? plan_of(sh.token[r], !(sh.outcome[r] & kBroken), sh.lse2[r][0], sh.lse2[r][1]) : plan_of(-1, true, 0.0, 0.0);
+      a.status[b] = st | st_upd;
     }
     return {};
   }
-  Decided out{r, kb, st | (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.status), {}};
+  Decided out{r, kb, st, {}};
   const int at = min(r, ADASD_MAX_K - 1);
-  out.plan = plan_of(__builtin_amdgcn_readfirstlane(sh.token[at]), __builtin_amdgcn_readfirstlane((int)sh.outcome[at]) != 2,
+  out.plan = plan_of(__builtin_amdgcn_readfirstlane(sh.token[at]), !(__builtin_amdgcn_readfirstlane((int)sh.outcome[at]) & kBroken),
                      first_lane(sh.lse2[at][0]), first_lane(sh.lse2[at][1]));
   if (writer && tid == 0) {
     a.n_accept[b] = r;

@@ -42,7 +42,8 @@ struct Workspace {
   int32_t* ticket3;   // [kTicket3Len]       arrival counters of the sampling kernel, zero between calls
   uint64_t* xchg;     // [positions][kMaxSplit][kXchgWords] self-validating hand-off words (records.h), zero between kernels:
                       // slice records of the single-read statistics kernel (cleared by the decision kernel), of the drafting
-                      // kernel [rows] and of the token kernel [sequences] (cleared by the workgroup that folds them)
+                      // kernel [rows] and of the token kernel [sequences] (cleared by the workgroup that folds them; where it takes
+                      // the decisions too, in slots that the statistics kernel left unused)
   PosRecord* pos_rec; // [positions] outcomes of the positions (long-history decision kernel)
   float2* tok;        // [positions] logits of the drafted tokens (looked up by the JS kernel or by the column shards)
   int32_t* slots;     // [positions] packed list of the positions inside their windows (ragged calls)

@@ -1817,3 +1817,20 @@ def test_results_are_bitwise_reproducible(am, wl, path):
         b, _, _ = G.run_gpu(am, batch, ws=ws, stats_path=path)
         for k, v in snap.items():
             assert torch.equal(getattr(b, k), v), k
+
+
+@pytest.mark.parametrize("K", [1, 4, 8, 9, 17, 40])
+@pytest.mark.parametrize("broken", ["row", "token"])
+def test_status_names_a_broken_position_wherever_it_stands(am, wl, K, broken):
+    """One broken position per sequence, at every place of the window: the status bit comes from whichever wavefront took the
+    position, and no other sequence has it."""
+    B = K + 1
+    batch = wl.config_batched(B=B, k=K, V=1032, seed=50 + K, cap=300)
+    for i in range(K):
+        if broken == "row":
+            batch.draft[i, i, 5] = float("nan")
+        else:
+            batch.draft_tokens[i, i] = batch.V
+    out, _, _ = G.run_gpu(am, batch)
+    bit = am.binding.ST_NONFINITE if broken == "row" else am.binding.ST_BAD_TOKEN
+    assert (out.status.cpu().numpy() & bit != 0).tolist() == [True] * K + [False]
