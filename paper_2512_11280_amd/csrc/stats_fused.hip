@@ -427,6 +427,15 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout, HistArgs hi
 // 23.6 / 28.2, 64 x 3 x 16001 23 / 33, 48 x 16 x 64001 78 / 209; float 1 x 4 x 32003 20.1 / 21.6, 48 x 16 x 64001
 // 97 / 250: faster at all of the 48 odd shapes timed.  The statistics alone, from 9 to 1501 logits and 4 to 32000 positions,
 // both types: 0.5 to 0.75 of the two kernels' time (1 x 4 x 9 4.1 / 8.1, 2000 x 16 x 101 float 105 / 161).
+//
+// Few positions leave most of the chip idle, and the kernel is then one chain of latencies in which a wavefront's own vectors
+// and the eight wavefronts of a workgroup that share a compute unit stand one after the other: smaller workgroups, as long as
+// each has a compute unit to itself (256), and as long as half of a position's hand-off slots stay free, for the decisions
+// inside the token kernel (merges_decisions).  Whole calls (us), slices by V alone / up to 256 workgroups: 1 x 4 x 32000 bf16
+// 17.9 / 16.1, float 16.0 / 15.7, 1 x 1 x 128256 bf16 18.7 / 17.5, 1 x 8 18.5 / 17.4, 4 x 4 18.8 / 18.5, 16 x 4 x 16001
+// 17.9 / 16.0.  Up to 128: 1 x 8 x 128256 18.2, 16 x 4 x 16001 17.2; up to 512: 17.6, 16.2, but 1 x 20 x 128256 21.3 -> 22.5,
+// 2 x 8 x 32000 float 16.6 -> 17.4.
+constexpr int kSmallGroups = 256, kSmallSplit = kMaxSplit / 2;
 bool fused_plan(const RowMap& map, int dt, int* T_out, int* NB_out, int* S_out) {
   const int epv = dt == ADASD_BF16 ? 8 : 4;
   if (map.K <= 0 || map.V < epv) return false;
@@ -435,8 +444,15 @@ bool fused_plan(const RowMap& map, int dt, int* T_out, int* NB_out, int* S_out) 
   while (T > 256 && nv <= (T / 2) * NB) T /= 2;                 // small vocabularies: smaller workgroups
   while (NB > 1 && nv <= T * (NB / 2)) NB /= 2;
   while (NB < 8 && (nv + T * NB - 1) / (T * NB) > kMaxSplit) NB *= 2;   // very large ones: more vectors per thread
-  const int S = (nv + T * NB - 1) / (T * NB);
+  int S = (nv + T * NB - 1) / (T * NB);
   if (S > kMaxSplit) return false;
+  while (NB <= 4 && (T > 256 || NB > 1)) {                      // few positions: more, smaller workgroups
+    const int fewer = T * NB / 2, more = (nv + fewer - 1) / fewer;
+    if (more > kSmallSplit || (int64_t)more * map.B * map.K > kSmallGroups) break;
+    if (T > 256) T = 256;
+    else NB /= 2;
+    S = more;
+  }
   *T_out = T;
   *NB_out = NB;
   *S_out = S;

@@ -1834,3 +1834,18 @@ def test_status_names_a_broken_position_wherever_it_stands(am, wl, K, broken):
     out, _, _ = G.run_gpu(am, batch)
     bit = am.binding.ST_NONFINITE if broken == "row" else am.binding.ST_BAD_TOKEN
     assert (out.status.cpu().numpy() & bit != 0).tolist() == [True] * K + [False]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,K,vectors", [(1, 1, 8192), (1, 8, 8192), (1, 9, 8192), (1, 8, 8193), (4, 16, 1024), (5, 13, 1024),
+                                         (16, 8, 512), (43, 3, 512), (1, 4, 16032)])
+@pytest.mark.parametrize("extra", [0, 1, -3])
+def test_few_positions_in_smaller_workgroups(am, wl, oracle, dtype, B, K, vectors, extra):
+    """The single-read kernel's tiling for few positions: at 256 workgroups and just beyond, at 32 slices of a position and
+    just beyond, whole and broken last vectors."""
+    V = vectors * (8 if dtype == torch.bfloat16 else 4) + extra
+    batch = wl.config_batched(B=B, k=K, V=V, seed=70 + vectors + extra, cap=300)
+    batch.target, batch.draft = batch.target.to(dtype), batch.draft.to(dtype)
+    out, _, _ = G.run_gpu(am, batch, stats_path=2)
+    rep = G.compare_verify(out, G.run_oracle(oracle, batch))
+    _report(f"few positions {B}x{K}x{V} {dtype}", rep)
