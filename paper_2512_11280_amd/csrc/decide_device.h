@@ -40,23 +40,24 @@ __device__ __forceinline__ void add_moments(const float* X, int nx, double c, do
   s2 += half_sum_d(e0 * e0 + e1 * e1);
 }
 
-// A batch of a list's samples joins a thread's running sum of kernels: acc * 2^m.  The reference m is the largest exponent so
-// far, found from the smallest distance, so a sample costs five instructions in double precision: its
-// distance, the minimum, the square, the exponent less the reference (one rounding, then to float for the
-// hardware's exp2), and the conversion of the sample.  Samples that do not count are infinite.
+// A batch of a list's samples joins a thread's running sum of kernels: acc * 2^m, where m is the largest exponent so far.
+// An exponent is rounded before the reference is taken from it, as the reference was, so that the nearest sample counts as 1
+// exactly: a list whose samples agree to an ulp has exponents of -1e20, where one rounding is 1e4.  (Product and reference in
+// one fma, the nearest sample found by its distance: an instruction less per sample and the same time, 128 x 16 positions with
+// lists of 4000 53.0 us a round either way, 32 x 8 30.6, 128 x 16 with lists of 448 41.1.)  Samples that do not count are infinite.
 template <int N, class Sum>
 __device__ __forceinline__ void join_kernels(double d, const float (&x)[N], double scale, double& m, Sum& acc) {
-  double e[N], least = INFINITY;
+  double t[N], hi = m;
 #pragma unroll
   for (int u = 0; u < N; ++u) {
-    e[u] = d - (double)x[u];
-    least = fmin(least, fabs(e[u]));
+    const double e = d - (double)x[u];
+    t[u] = -(e * e) * scale;
+    hi = fmax(hi, t[u]);
   }
-  const double hi = fmax(m, -(least * least) * scale);
   const double ref = hi > -INFINITY ? hi : 0.0;            // (nothing to add yet: every factor is 2^-inf = 0)
   float add = 0.f;
 #pragma unroll
-  for (int u = 0; u < N; ++u) add += ex2((float)fma(-(e[u] * e[u]), scale, -ref));    // terms below 2^-126 vanish
+  for (int u = 0; u < N; ++u) add += ex2((float)(t[u] - ref));    // terms below 2^-126 vanish
   acc = acc * (Sum)ex2((float)(m - ref)) + (Sum)add;
   m = hi;
 }

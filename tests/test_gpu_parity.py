@@ -573,6 +573,26 @@ def test_list_constants_at_the_edges_of_the_list_lengths(am, wl, oracle, cap, li
     _report(f"list lengths cap={cap} literal={literal} path={path}", rep)
 
 
+@pytest.mark.parametrize("n_hist,cap", [(280, 300), (560, 600), (4600, 5000)], ids=["short", "long", "streamed"])
+def test_lists_of_hardly_any_spread(am, wl, oracle, n_hist, cap, path):
+    """Distances that agree to an ulp or two make bandwidths of 1e-9 and less: the kernels' exponents at an ordinary distance
+    are about -1e20, where one rounding is 1e4.  The nearest sample must still count as 1."""
+    B, K = 12, 6
+    batch = wl.config_batched(B=B, k=K, V=1032, seed=71, cap=cap)
+    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(cap), n_hist=n_hist)
+    rng = np.random.default_rng(cap)
+    narrow = lambda base: (np.float32(base) + np.spacing(np.float32(base)) * rng.integers(0, 3, n_hist)).astype(np.float32)
+    for b in range(B):                                # one list, the other one, both
+        near, far = rng.uniform(1e-5, 3e-5), rng.uniform(2e-4, 3e-4)
+        if b % 3 != 1:
+            batch.state["LA"][b, :n_hist] = narrow(near if b % 2 else far)
+        if b % 3 != 0:
+            batch.state["LR"][b, :n_hist] = narrow(far if b % 2 else near)
+    out, _, _ = G.run_gpu(am, batch, stats_path=path)
+    rep = G.compare_verify(out, G.run_oracle(oracle, batch))
+    _report(f"narrow lists n={n_hist} path={path}", rep)
+
+
 def test_many_sequences_with_long_histories(am, wl, oracle):
     """More sequences than the arrival-counter arrays have cache lines: the counters of neighbouring
     sequences share lines again, in the sampling kernel and in the per-position decision kernel."""
