@@ -14,8 +14,8 @@ __global__ void __launch_bounds__(T) k_decide(DecideArgs a, UpdateArgs upd, Work
   decide_sequence<DT, INLOOP, HIST, T, LP>(a, upd, ws, blockIdx.x, sh);
 }
 
-// Long histories: one workgroup per candidate position.  The workgroup of position 0 does all the work of
-// a sequence whose lists are still short and the others leave at once, so with more workgroups than the
+// Long histories: one workgroup per candidate position.  One workgroup, that of position 0 where it can be, does all the
+// work of a sequence whose lists are still short and the others leave at once, so with more workgroups than the
 // chip holds at a time those of position 0 have to come first in dispatch order or they queue behind the
 // idle ones: grid (sequences, k_max).  A launch that gives every workgroup a compute unit of its own
 // measured 0.4 us faster the other way round (grid (k_max, sequences)); `seq_first` says which it is.
@@ -26,10 +26,25 @@ __global__ void __launch_bounds__(kBlock) k_decide_wide(DecideArgs a, UpdateArgs
   __shared__ WideShared wsh;
   const int b = seq_first ? blockIdx.x : blockIdx.y, pos = seq_first ? blockIdx.y : blockIdx.x;
   // The launch is sized for long lists (the host only knows their capacity); a sequence whose lists are
-  // still short is cheaper in the one-workgroup form, so its first workgroup takes that and the others leave.
+  // still short is cheaper in the one-workgroup form, so one of its workgroups takes that and the others leave.
+  // All of them have to go by the same lengths, but the one that decides also applies the round, maybe before another one
+  // has started.  With HIST the first workgroup decides, and one that finds lengths which the round may have taken past the
+  // line looks up what they were (decide_position_wide).  Without, the one that arrives last decides, when all have read
+  // them (nobody applies anything: the first one).
   const int n_long = min(max(max(a.nA[b], a.nR[b]), 0), a.cap);
   if (n_long < kWideMin) {
-    if (pos != 0) return;
+    if (HIST || upd.B == 0) {
+      if (pos != 0) return;
+    } else {
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        int32_t* ticket = &ws.ticket2[b * ticket_stride(a.map.B, kTicket2Len)];
+        wsh.last = atomicAdd(ticket, 1) == a.map.K - 1;
+        if (wsh.last) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __syncthreads();
+      if (!wsh.last) return;
+    }
     decide_sequence<DT, INLOOP, HIST, kBlock, 32>(a, upd, ws, b, sh);
     return;
   }

@@ -697,7 +697,12 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
   const size_t o = (size_t)b * K + i;
 
   PosRecord rec{0, 0u, 0.f, 0.f};
+  HistRecord hist;
+  // Lists that were short when the statistics ran have been taken past the line by the round itself: the sequence is done.
+  const auto applied_already = [&] { return HIST && max(hist.n[0], hist.n[1]) < kWideMin; };
   if (i >= kb) {
+    if (HIST) hist = a.hist[b];
+    if (applied_already()) return;
     if (tid == 0) {
       if (a.H_p) a.H_p[o] = 0.f;
       a.H_q[o] = 0.f;
@@ -714,9 +719,9 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
       ask_terms(LA, tid, nA, xa);
       ask_terms(LR, tid, nR, xr);
     }
-    HistRecord hist;
     if (HIST) hist = a.hist[b];
     const PosLoad L = load_position<DT>(a, ws, b, i, rnd, seq);
+    if (applied_already()) return;       // (here, where the constants are waited for: at the top it was a miss of its own)
     const bool bad = L.rp.bad || L.rq.bad;
     const int min_n = a.kde_min_n < 2 ? 2 : a.kde_min_n;
     int ne = 0;                            // in-loop appends this position sees
@@ -750,6 +755,7 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
     const double d = (double)d_out;
     const int n_i = nA + ne;
     double PA = 0.0;
+    bool reduced = false;
     if (!bad && n_i >= min_n && nR >= min_n) {      // uniform over the workgroup
       Kde kA, kR;
       bool ok;
@@ -790,10 +796,14 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
           join_kernels(d, x, kA.scale, mm[0], ss[0]);
         }
         joint_reduce<2>(mm, ss, wsh, out);
+        reduced = true;
         const double ja = out[0] - kA.log_norm, jr = out[1] - kR.log_norm;
         PA = 1.0 / (1.0 + (double)ex2((float)(jr - ja)));
       }
     }
+    // Once all workgroups of the sequence have arrived, the last one changes the state: what a wavefront reads of it (lengths,
+    // running sums) and goes by, it has to have read before this one arrives.  joint_reduce has barriers; else one here.
+    if (!reduced) __syncthreads();
     if (tid == 0) {
       rec.d = d_out;
       if (bad) {

@@ -26,8 +26,8 @@ template <int BYTES> __device__ __forceinline__ void warm_kernargs() {
   asm volatile("" ::"s"(t));
 }
 
-// A value at a uniform address that no workgroup of the running kernel writes, through the scalar cache (left to itself
-// the compiler, which cannot know that, loads it lane by lane into vector registers).
+// A value at a uniform address that no workgroup of the running kernel writes while this one may read it, through the scalar
+// cache (left to itself the compiler, which cannot know that, loads it lane by lane into vector registers).
 template <class T> __device__ __forceinline__ T scalar_load(const T* p) {
   static_assert(sizeof(T) % 4 == 0, "whole words");
   const auto* w = (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p;

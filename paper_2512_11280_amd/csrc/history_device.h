@@ -82,6 +82,7 @@ struct HistRecord {
   double c[2], s1[2], s2[2];     // accepted list, rejected list: first sample, sums of x - c and of its square
   Kde k[2];
   int32_t ok[2];                 // the constants hold: enough samples, and spread
+  int32_t n[2];                  // the lengths, as the round finds them (the state's own words change while the decisions run)
 };
 static_assert(sizeof(HistRecord) <= 2 * kMaxSplit * sizeof(float4), "one record per position fits the region of the two-kernel path's partial sums");
 
@@ -142,6 +143,7 @@ __device__ __forceinline__ void form_history(const HistArgs& h, int b, HistShare
   }
   HistRecord* rec = h.rec + b;
   Kde k{0.0, 0.0};
+  rec->n[q] = mine;
   rec->ok[q] = mine >= 2 && kde_constants(s1, s2, mine, other, h.bw_rule, &k);
   rec->c[q] = q ? c[1] : c[0];
   rec->s1[q] = s1;

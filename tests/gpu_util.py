@@ -45,6 +45,12 @@ def run_gpu(am, batch, options=None, seq_id=None, rounds=None, ws=None, stats_pa
     return out, st, ws
 
 
+def hand_off_left_clear(ws, positions):
+    """The arrival counters and the hand-off words of the positions, which lie at the front of a workspace, are zero."""
+    off = ws.ptr - ws.buf.data_ptr()
+    return not ws.buf[off:off + 4 * (65536 + 32768 + 32768) + positions * 64 * 3 * 8].any().item()
+
+
 def run_oracle(oracle, batch, options=None, seq_id=None, rounds=None):
     kw = {}
     if options is not None:

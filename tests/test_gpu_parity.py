@@ -593,6 +593,36 @@ def test_lists_of_hardly_any_spread(am, wl, oracle, n_hist, cap, path):
     _report(f"narrow lists n={n_hist} path={path}", rep)
 
 
+@pytest.mark.parametrize("literal", [0, 1])
+def test_lists_that_grow_out_of_the_short_form_in_the_round(am, wl, oracle, literal, path):
+    """More workgroups than the chip holds, most lists long, some a few samples short of the length from which every position
+    has a workgroup of its own: those that start after the round has been applied still go by the lengths it began with.
+    Also long lists beside ones that the round takes from one sample to two.  Two rounds on one workspace."""
+    B, K, cap = 128, 16, 700
+    batch = wl.config_batched(B=B, k=K, V=520, seed=31, cap=cap)
+    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(8), n_hist=600)
+    for b in range(0, B, 3):
+        batch.state["nA"][b], batch.state["nR"][b] = [(380 + b % 4, 370), (100, 383), (600, 1), (383, 383)][b // 3 % 4]
+    options = am.Options(base_test=literal, list_update=literal, apply_update=1)
+    ws = am.Workspace(B, K, batch.V, batch.target.dtype)
+    lens = np.full(B, K, np.int32)
+    for _ in range(2):
+        before = np.maximum(batch.state["nA"], batch.state["nR"])
+        out, st, _ = G.run_gpu(am, batch, options=options, ws=ws, stats_path=path)
+        assert G.hand_off_left_clear(ws, B * K)
+        ref = G.run_oracle(oracle, batch, options=options)
+        rep = G.compare_verify(out, ref, info_bits=16 | 8)
+        host = {k: np.array(v, copy=True) for k, v in batch.state.items() if k != "tau"}
+        oracle.update(host, ref["n_accept"], lens, ref["H_q"], ref["d_js"], K, d_eps=1e-6)
+        if rep["flips"] == rep["member_flips"] == 0:
+            got = st.to_host()
+            for k in ("nA", "nR", "ent_cnt"):
+                assert np.array_equal(got[k], host[k]), k
+        batch.state.update(host)
+        batch.round0 += 1
+    assert ((before >= 384) & (np.arange(B) % 3 == 0)).any()      # (some have crossed in the first round)
+
+
 def test_many_sequences_with_long_histories(am, wl, oracle):
     """More sequences than the arrival-counter arrays have cache lines: the counters of neighbouring
     sequences share lines again, in the sampling kernel and in the per-position decision kernel."""
