@@ -19,9 +19,12 @@ ADASD_ANYWHERE float log2_series(float t) {
 // With E = -ln u >= 1 - u, a logit whose key without noise is k (log2 units) stays below k - log2((1 - u) log2 e).  So with
 // ef = 2^(k - floor + kReach) it stays below `floor` by more than 2^-13, the guard of the comparisons of keys, if
 // ef < (1 - u) 2^32: if noise_reach <= kNoiseTop, which is four ulps of the sum below 2^32.
-constexpr float kSlack = 9.765625e-04f;                    // 2^-10: the guard, and the rounding of ef and of k
+constexpr float kSlack = 9.765625e-04f;                    // 2^-10: the guard, and the rounding of ef
 constexpr float kReach = 32.0f - 0.528766373f + kSlack;    // log2(2^32 / log2 e), and the slack
 constexpr float kNoiseTop = 4294966272.0f;                 // 2^32 - 1024
+// Which floor a key is good for: below it by what the roundings of large keys can add up to, 2^-24 of its size for the key itself,
+// for the other's, and for the lift of the other's logit (logits around 1e7 have keys a whole unit apart).
+ADASD_ANYWHERE float floor_of(float key) { return __builtin_fmaf(__builtin_fabsf(key), -0x1p-22f, key); }
 ADASD_ANYWHERE float noise_reach(float e, float f, uint32_t word) { return __builtin_fmaf(e, f, (float)word); }
 
 }  // namespace adasd

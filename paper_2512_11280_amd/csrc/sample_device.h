@@ -136,7 +136,7 @@ __device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {
 }
 
 // ---- logits that cannot win any more: the two logarithms of a logit's noise are only formed where its bound
-// (noise_series.h) comes up to `floor`, which is a lower bound of the true key of an element that was looked at.  Of the
+// (noise_series.h) comes up to `floor`, which is good for a lower bound of the true key of an element that was looked at.  Of the
 // n-th group of exchangeable logits that is one in n.  An element left out lies under the floor by more than the guard: it is
 // not the winner, and neither the winner nor whether it needs settling in float64 (a runner-up within the margin,
 // another element at or above the winner's lower bound) depends on it.
@@ -168,7 +168,7 @@ __device__ __forceinline__ float highest_floor(const Floors& sh, float mine) {
   return mine;
 }
 __device__ __forceinline__ float raise_floor(Floors& sh, float mine, float lane_floor) {
-  mine = fmaxf(mine, wave_max_f(lane_floor));
+  mine = fmaxf(mine, wave_max_f(floor_of(lane_floor)));
   __hip_atomic_store(&sh.f[__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)], mine, __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_WORKGROUP);        // (every lane the same)
   return mine;

@@ -1696,6 +1696,31 @@ def test_scans_that_leave_out_what_cannot_win(am, wl, oracle, dtype, V, literal)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("offset", [65536.0, 1.0e6, 1.0e7, -1.0e7])
+def test_flat_rows_give_the_same_token_at_any_offset(am, wl, dtype, offset):
+    """All logits alike: the noise alone decides, however large the logits and however coarse their keys (drafted tokens and
+    bonus draws, groups that cannot win left out)."""
+    B, V = 128, 65536
+    ws = am.Workspace(B, 1, V, dtype)
+    batch = wl.config_batched(B=B, k=1, V=V, dtype=dtype, seed=2)
+    x = torch.arange(B)
+    batch.draft_tokens[:, 0] = x.to(torch.int32)
+    batch.draft[:], batch.target[:] = 0.0, 0.0
+    batch.draft[x, 0, x] = batch.target[x, 0, x] = 60.0               # accepted
+    t, d, tok = batch.target.cuda(), batch.draft.cuda(), batch.draft_tokens.cuda()
+    for r in range(12):
+        drawn = []
+        for z in (0.0, offset):
+            rows = torch.full((B, V), z, device="cuda").to(dtype)
+            token = am.draft_step(rows, ws, step=0, k_max=20, seed=5, round0=r)[2].clone()
+            t[:, 1] = rows
+            out = am.verify(t, d, tok, ws, seed=5, round0=r)
+            assert (out.n_accept == 1).all()
+            drawn.append((token, out.next_token.clone()))
+        assert torch.equal(drawn[0][0], drawn[1][0]) and torch.equal(drawn[0][1], drawn[1][1]), r
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V", [4001, 32000])
 def test_drafting_goes_on_where_slice_records_do_not_arrive(am, oracle, dtype, V):
     """The path behind a wait that has run out (taken here although the records are there): entropy, stop flag and token

@@ -48,6 +48,24 @@ extern "C" void bounds(long n, const uint32_t* words, const double* below, doubl
     }
   }
 }
+// Flat rows of logit z: keys as the scans form them, words[k] seen first and others[k] after it.  How many of the others are left
+// out, and how many of those should not have been (within the guard of the first key, or above it).
+extern "C" void large(long n, float z, const uint32_t* words, const uint32_t* others, long* left_out, long* wrong) {
+  const float log2e = 1.44269504088896340736f;
+  auto key = [&](uint32_t w) {
+    const double td = ((double)(~w) + 0.5) * 0x1p-32, ud = ((double)w + 0.5) * 0x1p-32;
+    const float lE = (float)std::log2(-(td < 0.5 ? std::log1p(-td) : std::log(ud)) / 0.69314718055994530942);
+    return __builtin_fmaf(z, log2e, -lE);
+  };
+  *left_out = *wrong = 0;
+  for (long k = 0; k < n; ++k) {
+    const float first = key(words[k]), lift = kReach - floor_of(first);
+    const float e = (float)std::exp2((double)__builtin_fmaf(z, log2e, lift));
+    if (!(noise_reach(e, 1.0f, others[k]) <= kNoiseTop)) continue;
+    ++*left_out;
+    *wrong += !((double)first - (double)key(others[k]) > 0x1p-13);
+  }
+}
 """
 
 
@@ -81,6 +99,22 @@ def test_what_is_left_out_cannot_win(lib, lo, hi):
     lib.bounds(C.c_long(words.size), words.ctypes.data_as(C.c_void_p), below.ctypes.data_as(C.c_void_p), C.byref(largest), C.byref(left))
     print(f"left out {left.value}, largest key over the floor {largest.value:.3e}")
     assert left.value > 1000 and largest.value < -2.0**-13
+
+
+@pytest.mark.parametrize("z", [0.0, 30.0, 700.0, -5000.0, 65536.0, 1.0e6, -1.0e7, 1.0e7, 3.0e8])
+def test_what_is_left_out_cannot_win_among_large_logits(lib, z):
+    """Large logits have keys whose own roundings outgrow the guard.  Noise words near the top, whose keys lead a row, against
+    words a little below: by so much that the other key is a rounding or two lower."""
+    rng = np.random.default_rng(5)
+    E = 10.0 ** rng.uniform(-7, -1, 400_000)              # -ln u of the first, and of the other one
+    ulp = np.spacing(np.float32(abs(z) * 1.4427 + 30))
+    other = E * np.exp2(rng.uniform(0, 1, E.size) ** 2 * 4 * max(ulp, 1e-2))
+    words, others = ((np.exp(-x) * 2.0**32).clip(0, 2.0**32 - 1).astype(np.uint32) for x in (E, other))
+    left, wrong = C.c_long(), C.c_long()
+    lib.large(C.c_long(words.size), C.c_float(z), words.ctypes.data_as(C.c_void_p), others.ctypes.data_as(C.c_void_p),
+              C.byref(left), C.byref(wrong))
+    print(f"z = {z}: left out {left.value}, wrongly {wrong.value}")
+    assert wrong.value == 0 and (left.value > 1000 or z > 1e8)
 
 
 def test_error_over_the_whole_range(lib):
