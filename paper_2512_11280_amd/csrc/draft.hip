@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
   if (DRAW) noise = philox_row(c1, c2, c3, dr.seed_lo, dr.seed_hi);
   Lse st = lse_empty();
   Top2 best{-INFINITY, -1, -INFINITY, -1};
-  float floor = -INFINITY;       // (uniform in the wavefront) see may_win
+  float floor = kNoFloor;        // (uniform in the wavefront) see may_win
   for (int base = v0; base < v1; base += kBlock) {
     const uint4 x = next;
     const int idx = base + tid;

@@ -143,6 +143,8 @@ inline int token_split(int rows, int V, int dt) {
 // about a tenth of what looking at a group costs.  Rows of 128256, without / with (kernel, us): drafting bf16, 32 rows (2 groups) 9.8 / 9.8,
 // 64 (4) 13.7 / 13.0, 128 (9) 21.8 / 18.5, 256 (18) 34.7 / 26.3, 896 (63) 109 / 77; float, 32 (2) 10.4 / 11.0, 64 (4) 15.1 / 14.2, 128 (9)
 // 22.7 / 19.0; token bf16, 8 (1) 6.0 / 6.5, 64 (4) 13.9 / 13.6, 128 (9) 21.8 / 18.7, 256 (18) 37.1 / 29.2.
+// Rows in which little or nothing falls out cost no more than without: drafting 128 x 152064 bf16, logits rising along the row
+// 23.9 / 23.2; masked but for the last 1000 29.1 / 22.5, but for one in a thousand 25.5 / 20.1.
 constexpr int kPruneGroups = 4;
 inline bool scan_prunes(int chunk, int dt) { return chunk * (dt == ADASD_BF16 ? 2 : 1) >= kPruneGroups * kBlock; }
 

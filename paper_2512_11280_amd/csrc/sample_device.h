@@ -141,7 +141,7 @@ __device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {
 // not the winner, and neither the winner nor whether it needs settling in float64 (a runner-up within the margin,
 // another element at or above the winner's lower bound) depends on it.
 // The factor that takes 2^(key without noise) to the scale of the noise words.
-__device__ __forceinline__ float reach(float floor) { return ex2(kReach - floor); }
+__device__ __forceinline__ float reach(float floor) { return ex2(reach_exponent(floor)); }
 // Whether any lane's group of four may hold an element that reaches the floor.  (NaN: yes.)
 __device__ __forceinline__ bool may_win(const float (&e)[4], float f, const U4& block) {
   float v[4], top;
@@ -158,7 +158,7 @@ struct Floors {
   float f[kWaves];
 };
 __device__ __forceinline__ void floors_init(Floors& sh) {
-  if (threadIdx.x < kWaves) sh.f[threadIdx.x] = -INFINITY;
+  if (threadIdx.x < kWaves) sh.f[threadIdx.x] = kNoFloor;
   __syncthreads();
 }
 __device__ __forceinline__ float highest_floor(const Floors& sh, float mine) {
@@ -214,7 +214,7 @@ __device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int
     }
   } else {
     if (PRUNE) {
-      const float lift = kReach - floor;      // (+inf while nothing has been looked at)
+      const float lift = kReach - floor;
       float t[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) t[i] = fma_log2e(zp[i], lift);
@@ -261,7 +261,7 @@ __device__ __forceinline__ void scan_slice(const char* prow, const char* qrow, i
     }
     return x;
   };
-  float neg_cp = -cp, neg_cq = -cq, floor = -INFINITY;
+  float neg_cp = -cp, neg_cq = -cq, floor = kNoFloor;
   asm volatile("" : "+v"(neg_cp), "+v"(neg_cq));
   uint4 next_p = load(prow, v0 + tid), next_q = next_p;
   if (RESIDUAL) next_q = load(qrow, v0 + tid);
@@ -307,7 +307,7 @@ __device__ __forceinline__ void scan_long_slice(const char* prow, const char* qr
     if (in && idx == whole) y = load_last_vec<DT>(row, V);
     return y;
   };
-  float floor = -INFINITY;
+  float floor = kNoFloor;
   request(v0);
   for (int base = v0; base < v1; base += NV * kBlock) {
     uint4 xp[NV], xq[NV];

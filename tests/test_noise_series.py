@@ -66,6 +66,14 @@ extern "C" void large(long n, float z, const uint32_t* words, const uint32_t* ot
     *wrong += !((double)first - (double)key(others[k]) > 0x1p-13);
   }
 }
+// While nothing has been looked at: may an element win, by its logit (the lift of a row's logits) or by its weight e (the factor)?
+extern "C" int first_by_logit(float z, uint32_t word) {
+  const float t = __builtin_fmaf(z, 1.44269504088896340736f, kReach - kNoFloor);
+  return !(noise_reach((float)std::exp2((double)t), 1.0f, word) <= kNoiseTop);
+}
+extern "C" int first_by_weight(float e, uint32_t word) {
+  return !(noise_reach(e, (float)std::exp2((double)reach_exponent(kNoFloor)), word) <= kNoiseTop);
+}
 """
 
 
@@ -115,6 +123,15 @@ def test_what_is_left_out_cannot_win_among_large_logits(lib, z):
               C.byref(left), C.byref(wrong))
     print(f"z = {z}: left out {left.value}, wrongly {wrong.value}")
     assert wrong.value == 0 and (left.value > 1000 or z > 1e8)
+
+
+@pytest.mark.parametrize("word", [0, 1 << 31, (1 << 32) - 4096])
+def test_masked_logits_fall_out_before_anything_has_been_looked_at(lib, word):
+    by_logit = lambda z: lib.first_by_logit(C.c_float(z), C.c_uint32(word))
+    by_weight = lambda e: lib.first_by_weight(C.c_float(e), C.c_uint32(word))
+    assert not by_logit(-np.inf) and not by_weight(0.0)
+    assert all(by_logit(z) for z in (-2e38, -1e30, -1e4, 0.0, 50.0, 1e38, np.inf, np.nan))
+    assert all(by_weight(e) for e in (2.0**-94, 2.0**-38, 1.0, 2.0**20, np.inf, np.nan))
 
 
 def test_error_over_the_whole_range(lib):
