@@ -639,32 +639,47 @@ __device__ inline void stream_terms(double d, const float* L, int n, double scal
   }
 }
 
-// Sums of x - c and of its square over the two lists, by the workgroup (where no earlier kernel left them).
-__device__ inline void list_moments(const DecideArgs& a, int b, const float* LA, const float* LR, int nA, int nR,
+// Sums of x - c and of its square over a group of a thread's samples.
+__device__ __forceinline__ void group_moments(const float (&x)[kWideG], int g, int first, int n, double c, double& s1, double& s2) {
+#pragma unroll
+  for (int u = 0; u < kWideG; ++u) {
+    const double e = first + (g * kWideG + u) * kBlock < n ? (double)x[u] - c : 0.0;
+    s1 += e;
+    s2 += e * e;
+  }
+}
+
+// The same over the two lists, by the workgroup (where no earlier kernel left them): from the registers that hold the lists
+// (`resident`; a second read of them cost a round of 128 x 16 positions 2 to 4 us of 70), or streamed.
+__device__ inline void list_moments(const DecideArgs& a, int b, const float* LA, const float* LR, int nA, int nR, bool resident,
+                                    const float (&xa)[kWideU / kWideG][kWideG], const float (&xr)[kWideU / kWideG][kWideG],
                                     const double (&c)[2], DecideShared& sh, double (&m)[4]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* L[2] = {LA, LR};
   const int n[2] = {nA, nR};
+  m[0] = m[1] = m[2] = m[3] = 0.0;
+  if (resident) {
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    double s1 = 0.0, s2 = 0.0;
-    if (!(a.mom && n[q] > kSumsMin)) {
+    for (int g = 0; g < kWideU / kWideG; ++g) {
+      if (g * kWideG * kBlock >= max(nA, nR)) break;
+      group_moments(xa[g], g, tid, nA, c[0], m[0], m[1]);
+      group_moments(xr[g], g, tid, nR, c[1], m[2], m[3]);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (a.mom && n[q] > kSumsMin) continue;
 #pragma unroll 1
-      for (int base = tid; base < n[q]; base += kWideU * kBlock) {
-        float x[kWideU];
+      for (int first = tid; first - tid < n[q]; first += kWideU * kBlock) {
+        float x[kWideU / kWideG][kWideG];
+        ask_terms(L[q], first, n[q], x);
 #pragma unroll
-        for (int u = 0; u < kWideU; ++u) x[u] = L[q][min(base + u * kBlock, n[q] - 1)];
-#pragma unroll
-        for (int u = 0; u < kWideU; ++u) {
-          const double e = base + u * kBlock < n[q] ? (double)x[u] - c[q] : 0.0;
-          s1 += e;
-          s2 += e * e;
-        }
+        for (int g = 0; g < kWideU / kWideG; ++g) group_moments(x[g], g, first, n[q], c[q], m[2 * q], m[2 * q + 1]);
       }
     }
-    m[2 * q] = wave_sum_d(s1);
-    m[2 * q + 1] = wave_sum_d(s2);
   }
+#pragma unroll
+  for (int x = 0; x < 4; ++x) m[x] = wave_sum_d(m[x]);
   if (lane == 0) {
 #pragma unroll
     for (int x = 0; x < 4; ++x) sh.mom[wave][x] = m[x];
@@ -772,7 +787,7 @@ __device__ void decide_position_wide(const DecideArgs& a, const UpdateArgs& upd,
           m[2] = hist.s1[1];
           m[3] = hist.s2[1];
         } else {
-          list_moments(a, b, LA, LR, nA, nR, c, sh, m);
+          list_moments(a, b, LA, LR, nA, nR, resident, xa, xr, c, sh, m);
         }
         if (INLOOP) add_moments(sh.extra, ne, c[0], m[0], m[1]);
         ok = kde_constants(m[0], m[1], n_i, nR, a.bw_rule, &kA) && kde_constants(m[2], m[3], nR, n_i, a.bw_rule, &kR);
