@@ -527,29 +527,43 @@ def test_short_history_windows_at_the_edges_of_the_workgroup_sizes(am, wl, oracl
 @pytest.mark.parametrize("literal", [0, 1])
 def test_small_rounds_decide_inside_the_token_kernel(am, wl, oracle, B, K, V, dtype, literal):
     """Windows up to 8 (4: a wavefront to a position), up to 512 workgroups (256 with appends inside the loop), slices in
-    the free hand-off slots of one position or of two; beyond each of these the decisions are a kernel of their own.  Twice on
-    one workspace: the first call leaves its hand-off words and counters clear."""
+    the free hand-off slots of one position or of two; beyond each of these the decisions are a kernel of their own.  Rounds of
+    other logits, seeds, windows and vocabularies follow one another on a workspace, with a drafting call in between: each leaves
+    hand-off words and counters clear, and the slots that one of them uses are others' of the next."""
     cap = 300
-    batch = wl.config_batched(B=B, k=K, V=V, seed=900 + V + K, cap=cap)
-    batch.target, batch.draft = batch.target.to(dtype), batch.draft.to(dtype)
-    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(V), n_hist=280)
-    if B > 2:
-        batch.draft_len = torch.tensor([K, 0, max(K - 1, 1)] + [K] * (B - 3), dtype=torch.int32)
-        batch.target[0, 0, 3] = float("nan")                      # a broken row: no token
-        batch.draft_tokens[2, 0] = V                              # a broken drafted token
+    positions = B * (K + 2)
+    ws = am.Workspace(B, K + 2, V, dtype)
     options = am.Options(base_test=literal, list_update=literal, apply_update=1)
-    ref = G.run_oracle(oracle, batch, options=options)
-    host = {k: np.array(v, copy=True) for k, v in batch.state.items() if k != "tau"}
-    lens = np.full(B, K, np.int32) if batch.draft_len is None else batch.draft_len.numpy()
-    oracle.update(host, ref["n_accept"], lens, ref["H_q"], ref["d_js"], K, d_eps=1e-6)
-    ws = am.Workspace(B, K, V, dtype)
-    for _ in range(2):
+
+    def round_of(K, V, seed):
+        batch = wl.config_batched(B=B, k=K, V=V, seed=seed, cap=cap)
+        batch.round0 = seed
+        batch.target, batch.draft = batch.target.to(dtype), batch.draft.to(dtype)
+        batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(seed), n_hist=280)
+        if B > 2:
+            batch.draft_len = torch.tensor([K, 0, max(K - 1, 1)] + [K] * (B - 3), dtype=torch.int32)
+            batch.target[0, 0, 3] = float("nan")                  # a broken row: no token
+            batch.draft_tokens[2, 0] = V                          # a broken drafted token
+        ref = G.run_oracle(oracle, batch, options=options)
+        host = {k: np.array(v, copy=True) for k, v in batch.state.items() if k != "tau"}
+        lens = np.full(B, K, np.int32) if batch.draft_len is None else batch.draft_len.numpy()
+        oracle.update(host, ref["n_accept"], lens, ref["H_q"], ref["d_js"], K, d_eps=1e-6)
         out, st, _ = G.run_gpu(am, batch, options=options, ws=ws)
         rep = G.compare_verify(out, ref, info_bits=16 | 8)
         if rep["flips"] == rep["member_flips"] == 0:
             got = st.to_host()
             for k in ("nA", "nR", "ent_cnt"):
                 assert np.array_equal(got[k], host[k]), k
+        assert G.hand_off_left_clear(ws, positions)
+
+    round_of(K, V, 900 + V + K)
+    round_of(K, V, 901 + V + K)
+    rows = (3.0 * torch.randn(B, V, generator=torch.Generator().manual_seed(V))).to(dtype)
+    token = am.draft_step(rows.cuda(), ws, seed=7, round0=3)[2]
+    assert np.array_equal(token.cpu().numpy(), oracle.draft_sample(rows, seed=7, round0=3)[0])
+    assert G.hand_off_left_clear(ws, positions)
+    round_of(max(K - 1, 1), V // 3 + 8, 902 + V + K)
+    round_of(K + 2, V, 903 + V + K)
 
 
 @pytest.mark.parametrize("path", [1, 2])
