@@ -566,6 +566,35 @@ def test_small_rounds_decide_inside_the_token_kernel(am, wl, oracle, B, K, V, dt
     round_of(K + 2, V, 903 + V + K)
 
 
+@pytest.mark.parametrize("B,K,V,dtype", [(1, 1, 262147, torch.bfloat16), (3, 2, 400003, torch.bfloat16), (2, 8, 524288, torch.bfloat16),
+                                         (4, 4, 262141, torch.float32), (1, 8, 262144, torch.float32)])
+@pytest.mark.parametrize("literal", [0, 1])
+def test_small_rounds_of_long_rows(am, wl, oracle, B, K, V, dtype, literal):
+    """Decisions inside the token kernel where its slices have four groups of logits per wavefront and more (262144 logits in 64
+    slices, the most there are here), so that logits which cannot win are left out: a bonus draw, replacements at the
+    first and at the last position."""
+    batch = wl.config_batched(B=B, k=K, V=V, dtype=dtype, seed=V + literal, cap=64)
+    for b in range(B):
+        last = K if b % 3 == 0 else (0 if b % 3 == 1 else K - 1)      # the position that is rejected
+        for i in range(K):
+            x = int(batch.draft_tokens[b, i])
+            batch.draft[b, i, x] = 60.0 if i < last else 40.0
+            batch.target[b, i, x] = 60.0 if i < last else -40.0
+    options = am.Options(base_test=literal, list_update=literal, apply_update=1, relaxed_off=1)
+    ref = G.run_oracle(oracle, batch, options=options)
+    assert ref["n_accept"].tolist() == [K, 0, K - 1, K][:B]
+    ws = am.Workspace(B, K, V, dtype)
+    am.profile_enable(8)
+    try:
+        out, _, _ = G.run_gpu(am, batch, options=options, ws=ws)
+        launches = [am.profile_read(c)[1] for c in (2, 3)]
+    finally:
+        am.profile_disable()
+    G.compare_verify(out, ref, info_bits=16 | 8)
+    assert G.hand_off_left_clear(ws, B * K)
+    assert launches == [0, 1], launches                               # (no kernel for the decisions alone)
+
+
 @pytest.mark.parametrize("path", [1, 2])
 @pytest.mark.parametrize("literal", [0, 1])
 @pytest.mark.parametrize("cap", [500, 5000])
