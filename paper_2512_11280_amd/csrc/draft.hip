@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
       if (DRAW) {
         const int first = idx * EPV + 4 * g;
         const U4 block = philox_block(noise, (uint32_t)first >> 2);
-        if (!PRUNE || may_win(e, reach(floor - m), block)) {
+        if (!PRUNE || may_win(e, reach(m, floor), block)) {
           float lE[4];
           log2_exponential4(block, lE);
 #pragma unroll

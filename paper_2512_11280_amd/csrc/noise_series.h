@@ -22,16 +22,17 @@ ADASD_ANYWHERE float log2_series(float t) {
 constexpr float kSlack = 9.765625e-04f;                    // 2^-10: the guard, and the rounding of ef
 constexpr float kReach = 32.0f - 0.528766373f + kSlack;    // log2(2^32 / log2 e), and the slack
 constexpr float kNoiseTop = 4294966272.0f;                 // 2^32 - 1024
-// Which floor a key is good for: below it by what the roundings of large keys can add up to, 2^-24 of its size for the key itself,
-// for the other's, and for the lift of the other's logit (logits around 1e7 have keys a whole unit apart).
-ADASD_ANYWHERE float floor_of(float key) { return __builtin_fmaf(__builtin_fabsf(key), -0x1p-22f, key); }
+ADASD_ANYWHERE float noise_reach(float e, float f, uint32_t word) { return __builtin_fmaf(e, f, (float)word); }
+// Floors are kept less kReach.  The one that a key is good for lies below it by what the roundings of large keys can add up to:
+// 2^-24 of its size each for the key, for the other's, and for the two here, and a little more (logits around 1e7 have keys a
+// whole unit apart).
+ADASD_ANYWHERE float floor_of(float key) { return __builtin_fmaf(__builtin_fabsf(key), -0x1.4p-22f, key - kReach); }
 // While nothing has been looked at: below every finite key, and finite itself, so that a masked logit (-inf, or 2^-inf = 0)
 // comes to nothing and not to -inf + inf or 0 * inf, which would count as one that may win.
 constexpr float kNoFloor = -3.402823466e38f;
-// The exponent of the factor f, for the same reason no more than 127.  What falls out for that has e <= 2^-95 and a key below
-// -62, and the row (drafting: the lane's own vector) has an element with e >= 2^-38, whose key is -43.1 at least and which
-// is looked at: neither the best nor within its margin (2.2 at most where the best is certain).
-ADASD_ANYWHERE float reach_exponent(float floor) { return __builtin_fminf(kReach - floor, 127.0f); }
-ADASD_ANYWHERE float noise_reach(float e, float f, uint32_t word) { return __builtin_fmaf(e, f, (float)word); }
+// The exponent k - floor of the factor f, for the same reason no more than 127.  What falls out for that has e <= 2^-95 and a
+// key below -62, and the row (drafting: the lane's own vector) has an element with e >= 2^-38, whose key is -43.1 at least and
+// which is looked at: neither the best nor within its margin (2.2 at most where the best is certain).
+ADASD_ANYWHERE float reach_exponent(float above) { return __builtin_fminf(above, 127.0f); }
 
 }  // namespace adasd

@@ -140,8 +140,8 @@ __device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {
 // n-th group of exchangeable logits that is one in n.  An element left out lies under the floor by more than the guard: it is
 // not the winner, and neither the winner nor whether it needs settling in float64 (a runner-up within the margin,
 // another element at or above the winner's lower bound) depends on it.
-// The factor that takes 2^(key without noise) to the scale of the noise words.
-__device__ __forceinline__ float reach(float floor) { return ex2(reach_exponent(floor)); }
+// The factor that takes 2^(key without noise, less `of`) to the scale of the noise words.
+__device__ __forceinline__ float reach(float of, float floor) { return ex2(reach_exponent(of - floor)); }
 // Whether any lane's group of four may hold an element that reaches the floor.  (NaN: yes.)
 __device__ __forceinline__ bool may_win(const float (&e)[4], float f, const U4& block) {
   float v[4], top;
@@ -197,7 +197,7 @@ __device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int
       e[i] = max_raw(zq[i] + (p[i] - q[i]), 0.f);
     }
     if (PRUNE) {
-      if (!may_win(e, reach(floor), block)) return;
+      if (!may_win(e, reach(0.f, floor), block)) return;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {                          // (how far the true key may lie below: see the margin in k_sample)
         const float w = e[i] - zq[i];
@@ -214,10 +214,9 @@ __device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int
     }
   } else {
     if (PRUNE) {
-      const float lift = kReach - floor;
       float t[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) t[i] = fma_log2e(zp[i], lift);
+      for (int i = 0; i < 4; ++i) t[i] = fma_log2e(zp[i], -floor);
       ex2_group(t, e);
       if (!may_win(e, 1.f, block)) return;
     }

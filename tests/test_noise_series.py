@@ -59,7 +59,7 @@ extern "C" void large(long n, float z, const uint32_t* words, const uint32_t* ot
   };
   *left_out = *wrong = 0;
   for (long k = 0; k < n; ++k) {
-    const float first = key(words[k]), lift = kReach - floor_of(first);
+    const float first = key(words[k]), lift = -floor_of(first);
     const float e = (float)std::exp2((double)__builtin_fmaf(z, log2e, lift));
     if (!(noise_reach(e, 1.0f, others[k]) <= kNoiseTop)) continue;
     ++*left_out;
@@ -68,11 +68,11 @@ extern "C" void large(long n, float z, const uint32_t* words, const uint32_t* ot
 }
 // While nothing has been looked at: may an element win, by its logit (the lift of a row's logits) or by its weight e (the factor)?
 extern "C" int first_by_logit(float z, uint32_t word) {
-  const float t = __builtin_fmaf(z, 1.44269504088896340736f, kReach - kNoFloor);
+  const float t = __builtin_fmaf(z, 1.44269504088896340736f, -kNoFloor);
   return !(noise_reach((float)std::exp2((double)t), 1.0f, word) <= kNoiseTop);
 }
 extern "C" int first_by_weight(float e, uint32_t word) {
-  return !(noise_reach(e, (float)std::exp2((double)reach_exponent(kNoFloor)), word) <= kNoiseTop);
+  return !(noise_reach(e, (float)std::exp2((double)reach_exponent(-kNoFloor)), word) <= kNoiseTop);
 }
 """
 
