@@ -32,7 +32,8 @@ struct RowMap {
 };
 
 struct Workspace {
-  float4* part1;      // [rows][kMaxSplit]   (m, s, u, -) partial log-sum-exp states
+  float4* part1;      // [rows][kMaxSplit]   (m, s, u, -) partial log-sum-exp states of the two-kernel path; with the single-read
+                      // statistics kernel, which has none, the HistRecords of the sequences
   int32_t* ticket1;   // [kTicket1Len]       arrival counters of the drafting kernel (row rho at rho * ticket_stride), zero between calls
   RowResult* rows;    // [rows]
   float2* part2;      // [positions][kMaxSplit] partial KL sums (p side, q side), log2 units
@@ -140,9 +141,9 @@ inline int token_split(int rows, int V, int dt) {
 
 // Whether a scan over slices of `chunk` vectors leaves out the logits that cannot win any more (sample_device.h): from four
 // groups of 256 logits per wavefront on.  The first groups are looked at in any case, and the test costs a wavefront
-// about a tenth of what looking at a group costs.  Rows of 128256, without / with (kernel, us): drafting bf16, 32 rows (2 groups) 9.8 / 9.8,
-// 64 (4) 13.7 / 13.0, 128 (9) 21.8 / 18.5, 256 (18) 34.7 / 26.3, 896 (63) 109 / 77; float, 32 (2) 10.4 / 11.0, 64 (4) 15.1 / 14.2, 128 (9)
-// 22.7 / 19.0; token bf16, 8 (1) 6.0 / 6.5, 64 (4) 13.9 / 13.6, 128 (9) 21.8 / 18.7, 256 (18) 37.1 / 29.2.
+// about a tenth of what looking at a group costs.  Rows of 128256, without / with (kernel, us): drafting bf16, 32 rows (3.9 groups) 9.8 / 9.8,
+// 64 (6) 13.7 / 13.0, 128 (9.7) 21.8 / 18.5, 256 (18) 34.7 / 26.3, 896 (63) 109 / 77; float, 32 (3) 10.4 / 11.0, 64 (4.8) 15.1 / 14.2,
+// 128 (9) 22.7 / 19.0; token bf16, 8 (2) 6.0 / 6.5, 64 (6) 13.9 / 13.6, 128 (9.7) 21.8 / 18.7, 256 (18) 37.1 / 29.2.
 // Rows in which little or nothing falls out cost no more than without: drafting 128 x 152064 bf16, logits rising along the row
 // 23.9 / 23.2; masked but for the last 1000 29.1 / 22.5, but for one in a thousand 25.5 / 20.1.
 constexpr int kPruneGroups = 4;

@@ -136,7 +136,7 @@ __device__ __forceinline__ bool take_ticket(int32_t* ticket, int count) {
 }
 
 // ---- logits that cannot win any more: the two logarithms of a logit's noise are only formed where its bound
-// (noise_series.h) comes up to `floor`, which is good for a lower bound of the true key of an element that was looked at.  Of the
+// (noise_series.h) comes up to `floor`, a lower bound (less kReach) of the true key of an element that was looked at.  Of the
 // n-th group of exchangeable logits that is one in n.  An element left out lies under the floor by more than the guard: it is
 // not the winner, and neither the winner nor whether it needs settling in float64 (a runner-up within the margin,
 // another element at or above the winner's lower bound) depends on it.
@@ -239,8 +239,8 @@ __device__ __forceinline__ void scan_group(const uint4& xp, const uint4& xq, int
 // and the noise counters are in vocabulary indices.
 // Bound by the vector ALU as the drafting kernel is (draft.hip); the whole round against the scan in batches of two
 // vectors: 128 x 16 x 152064 385 -> 376 us, ragged 64 x 16 x 128256 127 -> 116 us, 32 x 8 x 128256 64.8 -> 62.2 us (the
-// same statistics kernel in both).  With PRUNE, the token kernel alone: 128 x 16 x 152064 28.2 -> 23.5 us, ragged
-// 64 x 16 x 128256 15.0 -> 14.1 us.
+// same statistics kernel in both).  With PRUNE, the token kernel alone: 128 x 16 x 152064 28.2 -> 24.4 us, ragged
+// 64 x 16 x 128256 15.0 -> 14.3 us.
 // kExclude gives a key to every finite logit but the excluded one, also to those whose probability is 0
 // in float64 (which the float64 path skips).  Such an element cannot win: this mode only runs after the
 // match test rejected the excluded token x, i.e. ln u1 >= ln p(x) with u1 < 1 - 2^-25, so the rest of the
