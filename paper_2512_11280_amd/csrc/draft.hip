@@ -63,7 +63,8 @@ struct DraftShared {
 // multiplications and 19 exclusive ors per four logits for the noise, and for the key two conversions, two logarithms
 // and about a dozen more; from four groups of logits per wavefront on, the key's part is only done where the logit may
 // still win (PRUNE: three instructions to find out; the kernel alone, 128 rows of 152064 25.8 -> 21.5 us, 896 of 128256
-// 108 -> 77).  It is bound by the vector ALU, so everything here follows the issue rules of device_common.h; the slices are cut so that the whole call is resident at once with equal shares per thread.
+// 108 -> 77).  It is bound by the vector ALU, so everything here follows the issue rules of device_common.h; the slices
+// are cut so that the whole call is resident at once with equal shares per thread.
 // Back to back, bf16, against loops that alternated transcendentals with plain instructions and took the slices in
 // batches of vectors: 128 rows of 152064 39.0 -> 24.3 us, 24 of 32 rows of 128256 11.1 -> 8.9 us; one row of 128256
 // 8.8 -> 6.0 us (3.4 us of it are the host's part of the call, which runs beside the kernel of the call before).

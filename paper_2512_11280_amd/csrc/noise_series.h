@@ -31,8 +31,8 @@ ADASD_ANYWHERE float floor_of(float key) { return __builtin_fmaf(__builtin_fabsf
 // comes to nothing and not to -inf + inf or 0 * inf, which would count as one that may win.
 constexpr float kNoFloor = -3.402823466e38f;
 // The exponent k - floor of the factor f, for the same reason no more than 127.  What falls out for that has e <= 2^-95 and a
-// key below -62, and the row (drafting: the lane's own vector) has an element with e >= 2^-38, whose key is -43.1 at least and
-// which is looked at: neither the best nor within its margin (2.2 at most where the best is certain).
+// key below -62, and the row (drafting: the lane's own logits) has an element with e >= 2^-38, whose key is -43.1 at least and
+// which is looked at, or lies below one that was: neither the best nor within its margin (2.2 at most where the best is certain).
 ADASD_ANYWHERE float reach_exponent(float above) { return __builtin_fminf(above, 127.0f); }
 
 }  // namespace adasd
