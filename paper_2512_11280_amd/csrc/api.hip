@@ -207,7 +207,7 @@ static int draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V,
   map.K = 0;
   map.B = B;
   map.V = V;
-  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, polls};
+  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, polls < 0 ? polls : words_polls(B)};
   hipStream_t st = (hipStream_t)stream;
   Scope sc(5, st);
   return launch_draft_step(map, (int)dt, ws, dout, nullptr, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
@@ -248,7 +248,7 @@ static int draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, in
   map.K = 0;
   map.B = B;
   map.V = V;
-  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, polls};
+  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, polls < 0 ? polls : words_polls(B)};
   DraftDraw draw{(uint32_t)seed, (uint32_t)(seed >> 32), seq_id, round, round0, (uint32_t)step, token_out, status_out};
   hipStream_t st = (hipStream_t)stream;
   Scope sc(5, st);

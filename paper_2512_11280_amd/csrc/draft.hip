@@ -2,8 +2,8 @@
 // logits: entropy of the draft row (Appendix A), stop rule H(q_i) > T_G (Section 4.3) and, for
 // adasd_draft_step, the token x_i ~ q_i.  The Gumbel-max key of an element, ln q_v - ln(-ln u_v),
 // differs from z_v - ln(-ln u_v) only by the row's normaliser, so the argmax needs no second pass: the
-// scan forms the entropy sums and the keys from the same registers.  The workgroup that takes the
-// last ticket of a row folds the row's slice records and settles close calls of the argmax in float64.
+// scan forms the entropy sums and the keys from the same registers.  One workgroup of a row folds
+// the row's slice records and settles close calls of the argmax in float64.
 #include "sample_device.h"
 #include "stats_device.h"
 
@@ -16,7 +16,10 @@ using namespace sampling;
 // One wavefront folds its lanes' states: common reference (which carries the valid flag of the hand-off words),
 // plain sums, winner and runner-up.  Uniform results.
 template <bool DRAW> __device__ __forceinline__ void fold_wave(Lse& l, Top2& t) {
-  const float top = wave_max_f(l.m), M = __uint_as_float(__float_as_uint(top) | 1u);
+  float top = l.m, best = t.k1;
+  if (DRAW) wave_max2(top, best);              // (one chain of exchanges for both)
+  else top = wave_max_f(top);
+  const float M = __uint_as_float(__float_as_uint(top) | 1u);
   const float d = top > kNegHuge ? l.m - M : 0.f, f = ex2(d);     // (nothing finite seen: the sums are 0, or a NaN)
   float a = l.s * f, b = (l.u + d * l.s) * f;
   swap32(a, b);
@@ -24,7 +27,23 @@ template <bool DRAW> __device__ __forceinline__ void fold_wave(Lse& l, Top2& t) 
   swap16(x, y);
   x = row_sum16(x + y);                        // lower half of the lanes: the sum, upper half: the weighted sum
   l = Lse{M, lane_value(x, 0), lane_value(x, 32)};
-  if (DRAW) t = top2_wave_reduce(t);
+  if (DRAW) t = top2_below(t, best);
+}
+// The same of the workgroup's wavefronts, whose states (folded, with references that carry the flag) are in shared memory: every
+// lane goes through them by itself, which is shorter than the exchanges between lanes (drafting 1 x 32000 float 4.43 -> 4.25 us a call).
+template <bool DRAW> __device__ __forceinline__ void fold_workgroup(const Lse (&ls)[kWaves], const Top2 (&ts)[kWaves], Lse& l, Top2& t) {
+  float M = ls[0].m;
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) M = fmaxf(M, ls[w].m);
+  float s[kWaves], u[kWaves];
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const float d = M > kNegHuge ? ls[w].m - M : 0.f, f = ex2(d);
+    s[w] = ls[w].s * f;
+    u[w] = (ls[w].u + d * ls[w].s) * f;
+  }
+  l = Lse{__uint_as_float(__float_as_uint(M) | 1u), (s[0] + s[1]) + (s[2] + s[3]), (u[0] + u[1]) + (u[2] + u[3])};
+  if (DRAW) t = top2_merge(top2_merge(ts[0], ts[1]), top2_merge(ts[2], ts[3]));
 }
 
 // Sums of a whole row by one wavefront, from the logits (where the slices' records did not arrive, which never happens
@@ -68,8 +87,13 @@ struct DraftShared {
 // Back to back, bf16, against loops that alternated transcendentals with plain instructions and took the slices in
 // batches of vectors: 128 rows of 152064 39.0 -> 24.3 us, 24 of 32 rows of 128256 11.1 -> 8.9 us; one row of 128256
 // 8.8 -> 6.0 us (3.4 us of it are the host's part of the call, which runs beside the kernel of the call before).
+// With few rows it is a chain of latencies: 0.6 us to the first logits, 0.6 to 0.9 for the scan, 0.5 for the wavefronts' and the
+// workgroup's fold, 0.6 until the last slice's record has arrived, 0.5 for the row's fold and the results.  The wavefronts
+// without logits behind a row's end stood in it with 1 us (top2_below), the ticket with 0.4, threshold and active flag with
+// 0.3: 1 x 128256 bf16 5.95 -> 4.56 us a call, 1 x 32000 float 5.96 -> 4.36, 32 x 128256 8.82 -> 8.18, entropies of 32 x 128256
+// float 6.57 -> 6.10.  (More than one vector ahead on its way: 6.2 -> 6.4 us with the entropies, 8.4 -> 8.5 with the draw.)
 //
-// One launch per drafting call, grid (slices, rows).  The workgroup that takes the last ticket of a row folds
+// One launch per drafting call, grid (slices, rows).  One workgroup of a row (few_rows) folds
 // the slices' records, and with DRAW settles a winner that does not lead by more than the rounding guard.
 template <int DT, bool DRAW, bool PRUNE>
 __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chunk, Workspace ws, DraftOut dout, DraftDraw dr) {
@@ -78,6 +102,23 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
   __shared__ DraftShared sh;
   const int rho = blockIdx.y, s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const RowRef r = locate_row<DT>(map, rho);
+
+  // ---- the slice: vectors v0 .. v1 of the row, one per thread and turn, the next one always on its way
+  const int V = map.V, nv = vectors_of<DT>(V), whole = V / EPV;
+  const int v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
+  const uint4 neutral = neutral_vec<DT>();
+  auto load = [&](int idx) {
+    uint4 x = neutral;
+    if (idx < v1) {
+      if (idx < whole) x = load_vec_any(r.ptr, idx);
+      else x = load_last_vec<DT>(r.ptr, V);
+    }
+    return x;
+  };
+  // (asked for before it is known whether the row is active, and so is the threshold, which is needed at the very end: each
+  // was a latency of its own, 0.3 us of a call of 32 x 128256 float)
+  uint4 next = load(v0 + tid);
+  const float threshold = dout.T_G ? scalar_load(dout.T_G + rho) : INFINITY;
   if (!r.active) {
     if (s == 0 && tid == 0) {
       dout.H_out[rho] = 0.f;
@@ -89,24 +130,9 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
     }
     return;
   }
-  const int V = map.V;
   const uint32_t c1 = dr.step | (2u << 16);
-  const uint32_t c2 = DRAW ? (dr.round ? dr.round[rho] : dr.round0) : 0u;
-  const uint32_t c3 = DRAW ? (dr.seq_id ? dr.seq_id[rho] : (uint32_t)rho) : 0u;
-
-  // ---- the slice: vectors v0 .. v1 of the row, one per thread and turn, the next one always on its way
-  const int nv = vectors_of<DT>(V), whole = V / EPV;
-  const int v0 = min(s * chunk, nv), v1 = min(v0 + chunk, nv);
-  const uint4 neutral = neutral_vec<DT>();
-  auto load = [&](int idx) {
-    uint4 x = neutral;
-    if (idx < v1) {
-      if (idx < whole) x = load_vec_any(r.ptr, idx);
-      else x = load_last_vec<DT>(r.ptr, V);
-    }
-    return x;
-  };
-  uint4 next = load(v0 + tid);
+  const uint32_t c2 = DRAW ? (dr.round ? scalar_load(dr.round + rho) : dr.round0) : 0u;
+  const uint32_t c3 = DRAW ? (dr.seq_id ? scalar_load(dr.seq_id + rho) : (uint32_t)rho) : 0u;
   if (PRUNE) floors_init(sh.floors);
   PhiloxRow noise;
   if (DRAW) noise = philox_row(c1, c2, c3, dr.seed_lo, dr.seed_hi);
@@ -161,8 +187,7 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
   auto write_row = [&](const RowResult& res) {
     dout.H_out[rho] = res.H;
     if (dout.stop_out) {
-      const bool over = dout.T_G ? (res.H > dout.T_G[rho]) : false;
-      dout.stop_out[rho] = (uint8_t)(over || dout.force_stop || res.bad);
+      dout.stop_out[rho] = (uint8_t)(res.H > threshold || dout.force_stop || res.bad);
     }
   };
 
@@ -174,13 +199,7 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
   }
   __syncthreads();
   if (wave == 0) {
-    st = lse_empty();
-    best = Top2{-INFINITY, -1, -INFINITY, -1};
-    if (lane < kWaves) {
-      st = sh.l[lane];
-      if (DRAW) best = sh.t[lane];
-    }
-    fold_wave<DRAW>(st, best);
+    fold_workgroup<DRAW>(sh.l, sh.t, st, best);
     bool last = true;
     if (S > 1) {
       uint64_t* words = ws.xchg + ((size_t)rho * kMaxSplit + s) * kXchgWords;
@@ -188,7 +207,7 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
       pack_draft(DraftRecord{st.m, st.s, st.u, best.k1, best.k2, best.i1}, w);
       if (lane < kXchgWords)
         __hip_atomic_store(words + lane, lane == 0 ? w[0] : (lane == 1 ? w[1] : w[2]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = take_ticket(&ws.ticket1[rho * ticket_stride(map.B, kTicket1Len)], S);
+      last = few_rows(map.B) ? s == S - 1 : take_ticket(&ws.ticket1[rho * ticket_stride(map.B, kTicket1Len)], S);
     }
     if (last) {
       // ---- last workgroup of the row

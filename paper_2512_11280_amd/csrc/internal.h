@@ -18,6 +18,7 @@ constexpr int kMaxSplit = 64;        // vocabulary slices per row: a fold takes 
 constexpr int kMaxSampleSplit = 128; // vocabulary slices per sequence of the token kernel's form for long rows
 constexpr int kXchgWords = 3;        // 64-bit hand-off words per record (records.h)
 constexpr int kWaitPolls = 16384;    // polls (about 4 ms) before a workgroup stops waiting for the words of others
+constexpr int kArrivalPolls = 1 << 20;   // the same (about a second) where words that come later would meet the next call
 
 // Where the rows of one call live.  which = 0: target, 1: draft.
 struct RowMap {
@@ -138,6 +139,14 @@ inline int token_split(int rows, int V, int dt) {
   const int epv = dt == ADASD_BF16 ? 8 : 4, nv = (V + epv - 1) / epv;
   return scan_split(rows, V, dt, nv > kLongRow ? kMaxSampleSplit : kMaxSplit);
 }
+
+// Who folds the slices' records of a drafting or token scan: of a few rows the workgroup of the last slice, which waits for the
+// others' words; else the one that takes the last ticket, which costs a round trip more.  Workgroups start in order, so
+// whatever the last slice waits for has started before it.  The waiting ones take a place on the chip per row; a die has 256, and
+// four calls of 64 rows on four streams at once would be the least with which those of several calls could fill one.
+constexpr int kFewRows = 64;
+__host__ __device__ inline bool few_rows(int rows) { return rows <= kFewRows; }
+inline int words_polls(int rows) { return few_rows(rows) ? kArrivalPolls : kWaitPolls; }
 
 // Whether a scan over slices of `chunk` vectors leaves out the logits that cannot win any more (sample_device.h): from four
 // groups of 256 logits per wavefront on.  The first groups are looked at in any case, and the test costs a wavefront

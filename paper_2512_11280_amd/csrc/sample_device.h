@@ -44,12 +44,12 @@ __device__ __forceinline__ Top2 top2_merge(const Top2& a, const Top2& b) {
   return r;
 }
 
-// Wave-uniform result.  The best key of the wavefront, its lane by a ballot (the lowest index of all of them where
+// Wave-uniform result, given the best key of the wavefront: its lane by a ballot (the lowest index of all of them where
 // several lanes hold that very key), then the best of what is left.
-__device__ __forceinline__ Top2 top2_wave_reduce(const Top2& v) {
+__device__ __forceinline__ Top2 top2_below(const Top2& v, float best) {
   Top2 r;
   r.i2 = -1;
-  r.k1 = wave_max_f(v.k1);
+  r.k1 = best;
   unsigned long long at = __ballot(v.k1 == r.k1);
   const int first = __ffsll((long long)at) - 1;
   r.i1 = __builtin_amdgcn_readlane(v.i1, first);
@@ -58,12 +58,16 @@ __device__ __forceinline__ Top2 top2_wave_reduce(const Top2& v) {
     return r;
   }
   r.k2 = r.k1;
+  // (a wavefront without a logit, behind the end of a row or all masked, has -inf and no index in every lane: lane by lane it
+  // took 1 us, and a row's slices wait for the slowest)
+  if (__builtin_amdgcn_readfirstlane(__float_as_int(r.k1)) == (int)0xff800000) return r;
   while (at &= at - 1) {
     const int i = __builtin_amdgcn_readlane(v.i1, __ffsll((long long)at) - 1);
     r.i1 = (unsigned)i < (unsigned)r.i1 ? i : r.i1;
   }
   return r;
 }
+__device__ __forceinline__ Top2 top2_wave_reduce(const Top2& v) { return top2_below(v, wave_max_f(v.k1)); }
 
 // log2 of -log2(u), u = (word + 0.5) / 2^32, i.e. log2 of E = -ln u up to a constant that every key shares: accurate
 // to about 1e-6.  u is formed from the word and t = 1 - u from its complement, so that each is exact to a rounding
@@ -102,14 +106,14 @@ __device__ __forceinline__ float key_ub(float zp, float zq, float cp, float cq, 
   return lg2(w) - lE;
 }
 
-// Hand-off of slice records inside one launch: NW words per slice (records.h).  A workgroup sends its words, then takes a
-// ticket, and does not wait for the words to arrive in between: the one that takes the last ticket knows that all words
-// of the row have been sent, so it reads until they are there, and clears them for the next launch.
+// Hand-off of slice records inside one launch: NW words per slice (records.h).  A workgroup sends its words and does not
+// wait for them to arrive.  One of the row (few_rows: that of the last slice, or the one that takes the last ticket) reads until
+// they are all there, and clears them for the next launch.
 // The wait is bounded all the same: where calls that share a workspace are not ordered, one may clear the other's words.
 // After `polls` polls it returns false, and the caller settles the row from the logits themselves.  (polls < 0: false
 // once the words are there, which tests use to take that path.)
 template <int NW> __device__ __forceinline__ bool take_words(uint64_t* words, bool mine, uint64_t (&w)[NW], int polls) {
-  int left = polls < 0 ? kWaitPolls : polls;
+  int left = polls < 0 ? kArrivalPolls : polls;
   bool all;
   do {
     bool ok = true;

@@ -42,7 +42,7 @@ __device__ __forceinline__ RowRef locate_row(const RowMap& map, int rho) {
 // window position second, which at least moves the empty positions to the end of the dispatch order.
 __device__ __forceinline__ int position_of_slot(const RowMap& map, int m) {
   if (!map.draft_len) return m;
-  if (map.slots) return map.slots[m];
+  if (map.slots) return scalar_load(map.slots + m);
   const int i = m / map.B, b = m - i * map.B;
   return b * map.K + i;
 }
@@ -69,17 +69,13 @@ __device__ __forceinline__ void lse_push(Lse& st, float z) {
 // A row's log2-sum-exp and entropy, in double precision, from the fold of all its partial states.
 __device__ __forceinline__ RowResult finish_row(const Lse& t) {
   const bool ok = (t.s > 0.f) && (t.s < INFINITY) && (fabsf(t.u) < INFINITY) && (t.m > kNegHuge) && (t.m < INFINITY);
+  const float sum = ok ? t.s : NAN;
+  const double l2s = log2_acc(sum);
   RowResult res;
-  if (ok) {
-    const double l2s = log2_acc(t.s);
-    res.lse2 = (double)t.m + l2s;
-    res.H = fmaxf((float)(kLn2 * (l2s - (double)t.u / (double)t.s)), 0.f);   // (a one-hot row: a few 1e-8 either side of 0)
-    res.bad = 0;
-  } else {
-    res.lse2 = NAN;
-    res.H = NAN;
-    res.bad = 1;
-  }
+  res.lse2 = (double)t.m + l2s;                                       // (NaN where the row is broken)
+  const float H = fmaxf((float)(kLn2 * (l2s - (double)t.u / (double)t.s)), 0.f);   // (a one-hot row: a few 1e-8 either side of 0)
+  res.H = ok ? H : NAN;
+  res.bad = ok ? 0 : 1;
   return res;
 }
 // Fold of up to 64 partial states of one row held one per lane (an empty state in the other lanes), by

@@ -1673,6 +1673,31 @@ def test_batches_beyond_a_full_chip(am, wl, oracle, B, V, dtype):
     G.compare_verify(out, G.run_oracle(oracle, batch))
 
 
+@pytest.mark.parametrize("B", [1, 64, 65])
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 4160), (torch.bfloat16, 2049), (torch.float32, 2080), (torch.float32, 1027)])
+def test_slices_that_end_within_a_workgroup(am, wl, oracle, B, dtype, V):
+    """Slices of fewer vectors than threads: wavefronts without a logit, and one with a few masked ones only.  Up to 64 rows the
+    last slice waits for the others' records, beyond that the last ticket decides who folds them.  Drafting calls with rows at
+    rest and with thresholds on either side of the entropies, tokens of a round, against the oracle; twice on a workspace."""
+    g = torch.Generator().manual_seed(V + B)
+    z = (3.0 * torch.randn(B, V, generator=g)).to(dtype)
+    z[0, V - V // 5:] = -math.inf                         # the last slice masked
+    active = (torch.arange(B) % 4 != 3).numpy().astype(np.uint8)
+    tg = (5.0 + 3.0 * torch.rand(B, generator=g)).numpy().astype(np.float32)
+    for round0 in (3, 4):
+        H, stop, tok, st, ref_tok, gap = _draft_step_case(am, oracle, z, T_G=tg, active=active, step=1, k_max=9, seed=8, round0=round0)
+        Href, sref = oracle.draft_entropy(z, T_G=tg, active=active, step=1, k_max=9)
+        assert np.array_equal(tok, ref_tok), gap
+        assert G.close(H, Href).all() and np.array_equal(stop != 0, sref != 0)
+    batch = wl.config_batched(B=B, k=9, V=V, dtype=dtype, seed=V)     # (a window of 9: decisions and token in two kernels)
+    batch.target[0, :, V - V // 5:] = -math.inf
+    ref, ws = G.run_oracle(oracle, batch), am.Workspace(B, 9, V, dtype)
+    for _ in range(2):
+        out, _, _ = G.run_gpu(am, batch, ws=ws)
+        G.compare_verify(out, ref, info_bits=16 | 8)
+        assert G.hand_off_left_clear(ws, B * 9)
+
+
 @pytest.mark.parametrize("dtype,V", [(torch.float32, 262144), (torch.float32, 262145), (torch.float32, 800003),
                                      (torch.float32, 1100000), (torch.bfloat16, 524289), (torch.bfloat16, 1600008)])
 @pytest.mark.parametrize("literal", [0, 1])
