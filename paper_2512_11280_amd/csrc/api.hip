@@ -413,6 +413,7 @@ SampleArgs sample_args(const adasd_verify_args* a, const VerifySetup& v) {
 
 }  // namespace
 
+// (token_polls < 0: the token kernel takes the path behind a wait that has run out)
 static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void* stream, int token_polls) {
   VerifySetup v;
   int rc = verify_setup(a, opt_in, kWantLogits | kWantOutputs | kWantToken, &v);
@@ -467,7 +468,7 @@ static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void*
     d.tok = vout.tok;
   }
   SampleArgs s = sample_args(a, v);
-  s.polls = token_polls;
+  s.polls = token_polls < 0 ? token_polls : words_polls(B);
   const int S3 = token_split(B, V, (int)a->dt);
   if (merges_decisions(d, S3)) {
     Scope sc(3, st);
@@ -484,7 +485,7 @@ static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void*
   return ADASD_OK;
 }
 
-int adasd_verify(const adasd_verify_args* a, const adasd_options* opt, void* stream) { return verify(a, opt, stream, kWaitPolls); }
+int adasd_verify(const adasd_verify_args* a, const adasd_options* opt, void* stream) { return verify(a, opt, stream, 0); }
 
 // For the tests, not part of the ABI: verification with the token kernel on the path behind a wait that has run out.
 int adasd_test_verify_unarrived(const adasd_verify_args* a, const adasd_options* opt, void* stream) {

@@ -279,6 +279,15 @@ __device__ __forceinline__ void clear_exchange_words(const DecideArgs& a, const 
   }
 }
 
+// The same for the positions of sequence b by the wavefronts of a workgroup but the first.
+__device__ __forceinline__ void clear_words_beside(const DecideArgs& a, const Workspace& ws, int b) {
+  const int K = a.map.K, per_pos = a.xchg_split * kXchgWords;
+  uint64_t* words = ws.xchg + (size_t)b * K * (kMaxSplit * kXchgWords);
+  for (int i = 0; i < K; ++i, words += kMaxSplit * kXchgWords)
+    for (int w = (int)threadIdx.x - 64; w < per_pos; w += kBlock - 64)
+      __hip_atomic_store(words + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ double first_lane(double v) {
   return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)), __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
@@ -490,7 +499,7 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
     if (a.accept_mask) a.accept_mask[o] = 0;
   }
   __syncthreads();
-  if (writer) clear_exchange_words<T>(a, ws, (size_t)b * K, K);
+  if (!REPLICA) clear_exchange_words<T>(a, ws, (size_t)b * K, K);      // (REPLICA: by the caller)
   if (!REPLICA && wave != 0) return {};
 
   // ---- one wavefront, one lane per position: first rejection, sampling plan, the round applied to the state
@@ -531,10 +540,7 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
   const int at = min(r, ADASD_MAX_K - 1);
   out.plan = plan_of(__builtin_amdgcn_readfirstlane(sh.token[at]), !(__builtin_amdgcn_readfirstlane((int)sh.outcome[at]) & kBroken),
                      first_lane(sh.lse2[at][0]), first_lane(sh.lse2[at][1]));
-  if (writer && tid == 0) {
-    a.n_accept[b] = r;
-    ws.plan[b] = out.plan;
-  }
+  if (writer && tid == 0) a.n_accept[b] = r;
   return out;
 }
 

@@ -50,20 +50,32 @@ struct FreeWords {
   }
 };
 
+__device__ __forceinline__ FreeWords free_words(const DecideArgs& d, const Workspace& ws, int b) {
+  return FreeWords{ws.xchg + ((size_t)b * d.map.K * kMaxSplit + d.xchg_split) * kXchgWords, kMaxSplit - d.xchg_split};
+}
+
 // What the token kernel does beside the draw: nothing, or (MERGED) the round is still to be applied and the status word to be
 // left, by the workgroup that arrives last.
 struct DrawOnly {
   static constexpr bool kMerged = false;
+  __device__ __forceinline__ void beside() {}
   __device__ __forceinline__ void ask() {}
   __device__ __forceinline__ uint32_t finish() { return 0u; }
 };
 struct DrawAndApply {
   static constexpr bool kMerged = true;
+  const DecideArgs& d;
   const UpdateArgs& upd;
+  const Workspace& ws;
   const DecideShared& sh;
   const Decided& dec;
   int b;
   UpdateIn before;
+  // (not before the record is under way: the first workgroup's would be the one that the others' wait for, 0.8 us with 8
+  // positions of 32 slices)
+  __device__ __forceinline__ void beside() {
+    if (blockIdx.x == 0) clear_words_beside(d, ws, b);
+  }
   __device__ __forceinline__ void ask() {
     if (upd.B > 0) before = update_inputs(upd, b);
   }
@@ -71,6 +83,9 @@ struct DrawAndApply {
 };
 
 // The token of sequence b, slice s of S, by one workgroup of kBlock threads.
+// Who folds the slices' records: see few_rows.  With that, without the tie loop for wavefronts that have no logit, with the best's
+// logits asked for before the folds and the wavefronts folded by every lane for itself, whole calls (us): 1 x 4 x 32000 float 15.79
+// -> 14.17, 1 x 8 x 128256 bf16 17.23 -> 16.18, 16 x 6 x 32003 literal 20.35 -> 19.31, 32 x 8 x 128256 58.39 -> 57.96.
 // LONG: a row of more slices than there are hand-off words (see token_split).  The records then go through part3, and have
 // landed before the ticket is taken; and a compute unit holds no more than one such workgroup of a few sequences.
 template <int DT, bool LONG, bool PRUNE, class Words, class Round>
@@ -92,28 +107,36 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
   scan_plan<DT, LONG, PRUNE>(plan, prow, qrow, V, v0, v1, 0, c1, c2, c3, a.seed_lo, a.seed_hi, best, sh_floors, poison);
 
   __shared__ Top2 sh_top[kWaves];
+  __shared__ float2 sh_logits[kWaves];
   // modes: 0 not the last workgroup; 1 final; 2 settle among the close candidates; 3 broken bonus row; 4 whole row in float64
   __shared__ int sh_mode;
   __shared__ uint32_t sh_status;              // (MERGED) what the status word holds so far
   __shared__ float sh_tau;
   __shared__ double sh_red[kWaves];
+  // (residual) the logits of the best element, which the error of its key depends on: every lane asks for its own best's, so
+  // that they arrive while the wavefront looks for its best
+  const int own = best.i1;
+  const bool residual = plan.residual == kResidual;
+  float zp = 0.f, zq = 0.f;
+  if (!LONG && residual && own >= 0) {
+    zp = load_elem<DT>(prow, own);
+    zq = load_elem<DT>(qrow, own);
+  }
   best = top2_wave_reduce(best);
   best.i2 = __any(poison) ? -2 : -1;          // (the poison marker travels in the runner-up's index)
   if (lane == 0) sh_top[wave] = best;
+  if (own == best.i1 && own >= 0) sh_logits[wave] = make_float2(zp, zq);     // (one lane)
   __syncthreads();
   if (wave == 0) {
-    best = Top2{-INFINITY, -1, -INFINITY, -1};
-    if (lane < kWaves) best = sh_top[lane];
-    poison = __any(best.i2 == -2);
-    best = top2_wave_reduce(best);
-    // the slice's record: best key and its index, runner-up key, the logits of the best (they arrive while the others
-    // are under way: the error of the best key depends on them)
+    // the slice's record: best key and its index, runner-up key, the logits of the best
+    const Top2 t0 = sh_top[0], t1 = sh_top[1], t2 = sh_top[2], t3 = sh_top[3];
+    static_assert(kWaves == 4, "four wavefronts");
+    poison = t0.i2 == -2 || t1.i2 == -2 || t2.i2 == -2 || t3.i2 == -2;
+    best = top2_merge(top2_merge(t0, t1), top2_merge(t2, t3));
+    const float2 z = sh_logits[best.i1 == t0.i1 ? 0 : best.i1 == t1.i1 ? 1 : best.i1 == t2.i1 ? 2 : 3];
+    zp = best.i1 >= 0 ? z.x : 0.f;
+    zq = best.i1 >= 0 ? z.y : 0.f;
     bool last = true;
-    float zp = 0.f, zq = 0.f;
-    if (best.i1 >= 0) {
-      zp = load_elem<DT>(prow, best.i1);
-      if (plan.residual == kResidual) zq = load_elem<DT>(qrow, best.i1);
-    }
     if (LONG) {
       if (lane == 0) {
         Top2* dst = &ws.part3[(size_t)b * kMaxSampleSplit + s];
@@ -130,7 +153,7 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
       pack_draw(DrawRecord{best.k1, best.k2, zp, zq, best.i1, poison}, w);
       if (lane < kXchgWords)
         __hip_atomic_store(words + lane, lane == 0 ? w[0] : (lane == 1 ? w[1] : w[2]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S);
+      last = few_rows(a.map.B) ? s == S - 1 : take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S);
     }
     int mode = 0;
     if (last) {
@@ -172,7 +195,7 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
       } else if (top.i1 < 0) {
         mode = 4;   // nothing had (certain) mass
       } else {
-        if (plan.residual == kResidual) {
+        if (residual) {
           const int owner = S > 1 ? __ffsll((long long)__ballot(t.i1 == top.i1)) - 1 : 0;
           if (LONG) {
             zp = load_elem<DT>(prow, top.i1);
@@ -206,6 +229,8 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
       }
     }
     if (lane == 0) sh_mode = mode;
+  } else {
+    round.beside();
   }
   __syncthreads();
   const int mode = sh_mode;
@@ -258,14 +283,25 @@ template <int DT, bool INLOOP, int LP, bool PRUNE>
 __global__ void __launch_bounds__(kBlock, 4) k_decide_sample(DecideArgs d, UpdateArgs upd, SampleArgs a, int S, int chunk, Workspace ws) {
   warm_kernargs<sizeof(DecideArgs) + sizeof(UpdateArgs) + sizeof(SampleArgs) + 2 * sizeof(int) + sizeof(Workspace)>();
   __shared__ DecideShared sh;
-  const int b = blockIdx.y, K = d.map.K;
+  const int b = blockIdx.y;
   const Decided dec = decide_sequence<DT, INLOOP, true, kBlock, LP, true>(d, upd, ws, b, sh, blockIdx.x == 0);
   const uint32_t c2 = a.round ? scalar_load(a.round + b) : a.round0;
   const uint32_t c3 = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
-  DrawAndApply round{upd, sh, dec, b, {}};
+  DrawAndApply round{d, upd, ws, sh, dec, b, {}};
   if (!dec.plan.valid) {          // (uniform over the sequence's workgroups)
-    if (threadIdx.x >= 64) return;
-    if (S > 1 && !take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S)) return;
+    if (threadIdx.x >= 64) {
+      round.beside();
+      return;
+    }
+    if (S > 1) {                  // (records without a content: that they are there tells that the state has been read)
+      const FreeWords slots = free_words(d, ws, b);
+      const int s = blockIdx.x, lane = threadIdx.x;
+      if (lane < kXchgWords)
+        __hip_atomic_store(slots.at(s) + lane, record_word(1u, 0.f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!(few_rows(a.map.B) ? s == S - 1 : take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S))) return;
+      uint64_t w[kXchgWords];
+      take_words(slots.at(min(lane, S - 1)), lane < S, w, a.polls);
+    }
     round.ask();
     const uint32_t st = round.finish();
     if (threadIdx.x == 0) {
@@ -274,8 +310,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_decide_sample(DecideArgs d, Updat
     }
     return;
   }
-  const FreeWords slots{ws.xchg + ((size_t)b * K * kMaxSplit + d.xchg_split) * kXchgWords, kMaxSplit - d.xchg_split};
-  draw_token<DT, false, PRUNE>(a, S, chunk, ws, dec.plan, c2, c3, slots, round);
+  draw_token<DT, false, PRUNE>(a, S, chunk, ws, dec.plan, c2, c3, free_words(d, ws, b), round);
 }
 
 // ---------------------------------------------------------------------------------------------
