@@ -45,6 +45,7 @@ struct FusedGeom {
   int last_byte;   // offset of the last 16 bytes of a row
   int chunk;       // vectors per slice
   int hist_rows;   // rows of the grid, the first ones, that are for the history lists
+  int naps;        // naps before the first poll (see kManyGroups)
   int wait_polls;  // polls before a workgroup stops waiting and recomputes what is missing
 };
 
@@ -317,13 +318,20 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout, HistArgs hi
       publish(ws, pos, s, mine);
       // every slice of the position, one per lane (this workgroup's own words come back the same way)
       const uint64_t* src = ws.xchg + ((size_t)pos * kMaxSplit + (need ? lane : 0)) * kXchgWords;
-      uint64_t w0, w1, w2;
-      int polls = 0;
-      while (true) {
-        w0 = get_word(src + 0);
-        w1 = get_word(src + 1);
-        w2 = get_word(src + 2);
-        ok = __all(!need || ((w0 & w1 & w2 & 1ull) != 0));
+      uint64_t w0 = 0, w1 = 0, w2 = 0;
+      bool there = !need;
+      // The words are read past the caches, over the fabric that the logits come by: with a thousand workgroups waiting, their
+      // reads are what holds up the records that they wait for.  So the first look comes after a nap (launch_stats_fused
+      // says how long), and a later one asks for the records that are still missing alone.
+      for (int i = 0; i < g.naps; ++i) __builtin_amdgcn_s_sleep(12);
+      for (int polls = 0;;) {
+        if (!there) {
+          w0 = get_word(src + 0);
+          w1 = get_word(src + 1);
+          w2 = get_word(src + 2);
+          there = (w0 & w1 & w2 & 1ull) != 0;
+        }
+        ok = __all(there) != 0;
         if (ok || ++polls > g.wait_polls) break;
         __builtin_amdgcn_s_sleep(4);
       }
@@ -461,6 +469,17 @@ bool fused_plan(const RowMap& map, int dt, int* T_out, int* NB_out, int* S_out) 
   return true;
 }
 
+// Where the chip holds all workgroups of a round (1024 of 512 threads), or there is but one more set of them, a workgroup naps once
+// (about 0.35 us, which the other slices need at least) before it first looks for their records; where there are more sets, three
+// times, while other workgroups load.  Call times in us without a nap / with 1 / 2 / 3 / 4 (64 samples a list):
+//   1 x 4 x 32000 float (32 workgroups)   13.9 / 13.2 / 13.5 / 13.8 / 14.1     64 x 8 x 64000 (2048)         57.4 / 57.7 / 56.9 / 56.5 / 56.4
+//   1 x 8 x 128256 (256)                  16.8 / 16.1 / 16.2 / 16.6 / 16.9     64 x 8 x 32000 float (2048)   43.4 / 43.7 / 43.9 / 44.0 / 44.3
+//   16 x 4 x 16001 (256)                  16.0 / 15.9 / 16.2 / 16.5 / 16.9     8 x 20 x 128256 float (2560)  54.2 / 53.8 / 53.2 / 52.8 / 52.8
+//   16 x 8 x 128256 (1024)                36.5 / 36.5 / 36.5 / 36.8 / 37.1     256 x 8 x 32000 (4096)        94.1 / 94.7 / 94.2 / 93.2 / 93.3
+//   20 x 8 x 128256 (1280)                41.4 / 41.2 / 41.4 / 41.6 / 41.8     128 x 8 x 50257 float (7168)  106 / 105 / 104 / 104 / 104
+//   32 x 8 x 128256 (2048)                56.7 / 56.7 / 56.4 / 56.5 / 56.3     128 x 16 x 152064 (20480)     365 / 358 / 368 / 357 / 364
+constexpr int kManyGroups = 2048;
+
 hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, int wait_polls,
                               const Workspace& ws, const VerifyOut& vout, const HistArgs& hist, hipStream_t st) {
   const int positions = map.B * map.K;
@@ -476,6 +495,7 @@ hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, i
   g.chunk = ((g.nv + S - 1) / S + 7) / 8 * 8;
   if ((int64_t)g.chunk * (S - 1) >= g.nv || g.chunk > T * NB) g.chunk = (g.nv + S - 1) / S;
   g.wait_polls = wait_polls;
+  g.naps = (int64_t)S * positions > kManyGroups ? 3 : 1;
   if (g.chunk > T * NB) return hipErrorInvalidValue;
   g.hist_rows = hist.rec ? (hist.B + S - 1) / S : 0;
   const dim3 grid(S, positions + g.hist_rows);
