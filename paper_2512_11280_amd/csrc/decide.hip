@@ -11,7 +11,8 @@ template <int DT, bool INLOOP, bool HIST, int T, int LP>
 __global__ void __launch_bounds__(T) k_decide(DecideArgs a, UpdateArgs upd, Workspace ws) {
   warm_kernargs<sizeof(DecideArgs) + sizeof(UpdateArgs) + sizeof(Workspace)>();
   __shared__ DecideShared sh;
-  decide_sequence<DT, INLOOP, HIST, T, LP>(a, upd, ws, blockIdx.x, sh);
+  const SequenceIn in = ask_sequence(a, upd, blockIdx.x, true);
+  decide_sequence<DT, INLOOP, HIST, T, LP>(a, upd, ws, blockIdx.x, in, sh);
 }
 
 // Long histories: one workgroup per candidate position.  One workgroup, that of position 0 where it can be, does all the
@@ -32,7 +33,7 @@ __global__ void __launch_bounds__(kBlock) k_decide_wide(DecideArgs a, UpdateArgs
   // line looks up what they were (decide_position_wide).  Without, the one that arrives last decides, when all have read
   // them (nobody applies anything: the first one).
   const int n_long = min(max(max(a.nA[b], a.nR[b]), 0), a.cap);
-  if (n_long < kWideMin) {
+  if (__builtin_expect(n_long < kWideMin, 0)) {
     if (HIST || upd.B == 0) {
       if (pos != 0) return;
     } else {
@@ -45,7 +46,7 @@ __global__ void __launch_bounds__(kBlock) k_decide_wide(DecideArgs a, UpdateArgs
       __syncthreads();
       if (!wsh.last) return;
     }
-    decide_sequence<DT, INLOOP, HIST, kBlock, 32>(a, upd, ws, b, sh);
+    decide_sequence<DT, INLOOP, HIST, kBlock, 32>(a, upd, ws, b, ask_sequence(a, upd, b, true), sh);
     return;
   }
   decide_position_wide<DT, INLOOP, HIST>(a, upd, ws, ws.pos_rec, b, pos, sh, wsh);
@@ -136,7 +137,7 @@ hipError_t launch_decide(const DecideArgs& a, const UpdateArgs& upd, const Works
   // 16 positions with a wavefront each (a list per half: both at once), and beyond that half a wavefront to a position, which
   // takes 32 in a turn.  Kernel (us), a wavefront / half a wavefront, 32 sequences: k = 8, lists of 64 6.9 / 6.9, 256 7.2 / 7.6,
   // 448 7.6 / 8.6; k = 12 7.1 / 7.1, 7.5 / 8.0, 8.4 / 9.3; k = 20 7.9 / 8.0, 8.6 / 9.1, 10.5 / 10.8; k = 40 11.4 / 9.2,
-  // 12.7 / 10.6, 16.6 / 13.3.  Fewer threads and more turns: k = 16 with 8 wavefronts 10.5 where 16 take 8.9.
+  // 12.7 / 10.6, 16.6 / 13.3 (before ask_sequence, which takes 0.8 off each).  Fewer threads and more turns: k = 16 with 8 wavefronts 10.5 where 16 take 8.9.
   const int LP = a.map.K > 16 ? 32 : 64, T = a.map.K <= 4 ? 256 : a.map.K <= 8 ? 512 : 1024;
 #define ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, TV, LPV) \
   if (a.dt == DTV && (a.list_update != 0) == INLOOPV && (a.hist != nullptr) == HISTV && T == TV && LP == LPV) \

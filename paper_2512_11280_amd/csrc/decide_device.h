@@ -62,14 +62,21 @@ __device__ __forceinline__ void join_kernels(double d, const float (&x)[N], doub
   m = hi;
 }
 
-// log2 [ p(d | list) P(list) ] by 32 lanes.  EXTRA: the list goes on in X (nx <= 64 samples).
+// log2 [ p(d | list) P(list) ] by 32 lanes.  EXTRA: the list goes on in X (nx <= 64 samples); else head holds the lane's first ones.
 template <bool EXTRA>
-__device__ __forceinline__ double half_log_joint(double d, const float* L, int n, const float* X, int nx, const Kde& k) {
+__device__ __forceinline__ double half_log_joint(double d, const float* L, const float (&head)[kHalfU], int n, const float* X, int nx,
+                                                 const Kde& k) {
   const int l32 = threadIdx.x & 31;
   double m = -INFINITY;
   float acc = 0.f;
+  if (!EXTRA) {
+    float x[kHalfU];
+#pragma unroll
+    for (int u = 0; u < kHalfU; ++u) x[u] = l32 + 32 * u < n ? head[u] : INFINITY;
+    join_kernels(d, x, k.scale, m, acc);
+  }
 #pragma unroll 1
-  for (int base = l32; base - l32 < n; base += 32 * kHalfU) {
+  for (int base = l32 + (EXTRA ? 0 : 32 * kHalfU); base - l32 < n; base += 32 * kHalfU) {
     float x[kHalfU];
 #pragma unroll
     for (int u = 0; u < kHalfU; ++u) x[u] = L[min(base + 32 * u, n - 1)];
@@ -196,6 +203,33 @@ __device__ inline uint32_t update_sequence_core(const UpdateArgs& a, const Updat
   return st;
 }
 
+// The words of a sequence that its decisions and their update go by, all asked for ahead of everything else, so that they and
+// what the positions need are one latency.  The lists' constants and first samples come with them, before it is known how long
+// the lists are.  (By scalar loads the lengths were waited for one after the other, in front of everything else.)  Decision kernel (us),
+// k = 8, 32 sequences, lists of 64 6.8 -> 5.9, 128 x 16 8.8 -> 8.0, float 8 x 20, lists of 256 8.7 -> 7.8; whole calls,
+// decisions in the token kernel: 1 x 4 x 32000 float 13.3 -> 12.9, 1 x 8 x 128256 16.1 -> 15.6.
+// (The state is only written once all have read it.)
+struct SequenceIn {
+  int raw_len, seq, rnd, nA, nR;       // the same in every lane
+  int ent_cnt;
+  double ent_sum;
+};
+__device__ __forceinline__ SequenceIn ask_sequence(const DecideArgs& a, const UpdateArgs& upd, int b, bool update) {
+  SequenceIn in{a.map.K, b, (int)a.round0, 0, 0, 0, 0.0};
+  if (a.nA && a.nR) {
+    in.nA = lane_load(a.nA + b);
+    in.nR = lane_load(a.nR + b);
+  }
+  if (a.map.draft_len) in.raw_len = lane_load(a.map.draft_len + b);
+  if (a.seq_id) in.seq = (int)lane_load(a.seq_id + b);
+  if (a.round) in.rnd = (int)lane_load(a.round + b);
+  if (update && upd.B > 0) {
+    in.ent_cnt = lane_load(upd.ent_cnt + b);
+    in.ent_sum = lane_load(upd.ent_sum + b);
+  }
+  return in;
+}
+
 struct DecideShared {
   float extra[ADASD_MAX_K];         // in-loop appends: this round's distances that pass the filter, in position order
   uint8_t n_before[ADASD_MAX_K];    // in-loop appends: how many of them come from earlier positions
@@ -317,40 +351,59 @@ struct Decided {        // the same in every lane (REPLICA)
   SamplePlan plan;
 };
 template <int DT, bool INLOOP, bool HIST, int T, int LP, bool REPLICA = false>
-__device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const UpdateArgs& upd, const Workspace& ws, int b, DecideShared& sh,
-                                                   bool writer = true) {
+__device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const UpdateArgs& upd, const Workspace& ws, int b,
+                                                   const SequenceIn& in, DecideShared& sh, bool writer = true) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = tid / LP;
   const bool lead = (tid & (LP - 1)) == 0;
   constexpr int kGroups = T / LP;
   const int K = a.map.K;
 
-  int kb = K;
-  uint32_t st = 0;
-  if (a.map.draft_len) {
-    int raw = scalar_load(a.map.draft_len + b);
-    kb = min(max(raw, 0), K);
-    if (raw != kb) st |= ADASD_ST_BAD_LENGTH;
-  }
-
-  // (by scalar loads: only this workgroup writes the sequence's state, and only at its end)
-  const uint32_t seq = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
-  const uint32_t rnd = a.round ? scalar_load(a.round + b) : a.round0;
+  auto load_pos = [&](int i) { return load_position<DT>(a, ws, b, i, (uint32_t)uniform(in.rnd), (uint32_t)uniform(in.seq)); };
+  PosLoad pos;
+  // (what stands past the window is asked for as well, but for logits, so that nothing waits for its length)
+  if (grp < (a.tok ? K : min(max(uniform(in.raw_len), 0), K))) pos = load_pos(grp);
+  const int raw_len = uniform(in.raw_len), kb = min(max(raw_len, 0), K);
+  uint32_t st = raw_len != kb ? ADASD_ST_BAD_LENGTH : 0u;
   const int min_n = a.kde_min_n < 2 ? 2 : a.kde_min_n;
   int nA = 0, nR = 0;
   const float* LA = nullptr;
   const float* LR = nullptr;
   if (a.LA && a.LR && a.nA && a.nR) {
-    nA = min(max(scalar_load(a.nA + b), 0), a.cap);
-    nR = min(max(scalar_load(a.nR + b), 0), a.cap);
+    nA = min(max(uniform(in.nA), 0), a.cap);
+    nR = min(max(uniform(in.nR), 0), a.cap);
     LA = a.LA + (size_t)b * a.cap;
     LR = a.LR + (size_t)b * a.cap;
   }
-  UpdateIn before{};
-  if (!REPLICA && upd.B > 0) before = update_inputs(upd, b);
-  auto load_pos = [&](int i) { return load_position<DT>(a, ws, b, i, rnd, seq); };
-  PosLoad pos;
-  if (grp < kb) pos = load_pos(grp);
 
+  // What the statistics launch left of the lists, and the lists' first samples.  (INLOOP: without the samples.  Their joining, in front
+  // of the loop over lists that differ from position to position, cost 16 x 6 x 32003 0.3 us.)
+  constexpr int Q = LP == 64 ? 1 : 2;
+  const bool upper = LP == 64 && (tid & 32) != 0;
+  const bool listed = LA != nullptr && a.cap > 0 && !a.relaxed_off;
+  float head[Q][kHalfU] = {};
+  Kde k[Q] = {};
+  bool ok[Q] = {};
+  double c[Q] = {}, s1[Q] = {}, s2[Q] = {};
+  if (listed) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const bool rej = upper || q == 1;
+      if (HIST) {
+        const HistRecord* rec = a.hist + b;
+        k[q] = rec->k[rej];
+        ok[q] = rec->ok[rej] != 0;
+        if (INLOOP) {
+          c[q] = rec->c[rej];
+          s1[q] = rec->s1[rej];
+          s2[q] = rec->s2[rej];
+        }
+      }
+      if (!INLOOP) {
+#pragma unroll
+        for (int u = 0; u < kHalfU; ++u) head[q][u] = (rej ? LR : LA)[min((tid & 31) + 32 * u, a.cap - 1)];
+      }
+    }
+  }
   int n_room = 0;        // in-loop appends the list can still take
   if (INLOOP) {
     // All distances of the round first: the groups fold them, one wavefront ranks those that pass.
@@ -382,13 +435,8 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
   const bool kde_on = kb > 0 && !a.relaxed_off && LA != nullptr && nR >= min_n && (INLOOP ? nA + n_room >= min_n : nA >= min_n);
 
   // ---- the lists: this lane's (LP = 64), or both
-  constexpr int Q = LP == 64 ? 1 : 2;
-  const bool upper = LP == 64 && (tid & 32) != 0;
   const float* L[Q];
   int n[Q];
-  double c[Q], s1[Q], s2[Q];
-  Kde k[Q];
-  bool ok[Q];
   auto constants = [&](int q, int ne) {
     const bool rej = upper || q == 1;
     double m1 = s1[q], m2 = s2[q];
@@ -401,16 +449,7 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
       const bool rej = upper || q == 1;
       L[q] = rej ? LR : LA;
       n[q] = rej ? nR : nA;
-      if (HIST) {
-        const HistRecord* rec = a.hist + b;
-        k[q] = rec->k[rej];
-        ok[q] = rec->ok[rej] != 0;
-        if (INLOOP) {
-          c[q] = rec->c[rej];
-          s1[q] = rec->s1[rej];
-          s2[q] = rec->s2[rej];
-        }
-      } else {
+      if (!HIST) {
         c[q] = n[q] > 0 ? (double)L[q][0] : 0.0;
         half_moments(L[q], n[q], c[q], s1[q], s2[q]);
         if (!INLOOP) constants(q, 0);
@@ -445,7 +484,7 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         if (INLOOP) constants(q, ne);
-        j[q] = half_log_joint<INLOOP>((double)dv, L[q], n[q], sh.extra, upper || q == 1 ? 0 : ne, k[q]);
+        j[q] = half_log_joint<INLOOP>((double)dv, L[q], head[q], n[q], sh.extra, upper || q == 1 ? 0 : ne, k[q]);
         both = both && ok[q];
       }
       if (LP == 64) {
@@ -528,7 +567,7 @@ __device__ __forceinline__ Decided decide_sequence(const DecideArgs& a, const Up
   };
   if (!REPLICA) {
     uint32_t st_upd = 0;
-    if (upd.B > 0) st_upd = apply_round(upd, before, b, r, kb, sh);      // (the lists were only read above)
+    if (upd.B > 0) st_upd = apply_round(upd, UpdateIn{in.nA, in.nR, in.ent_cnt, in.ent_sum}, b, r, kb, sh);      // (the lists were only read above)
     if (lane == 0) {
       a.n_accept[b] = r;
       ws.plan[b] = r < kb ? plan_of(sh.token[r], !(sh.outcome[r] & kBroken), sh.lse2[r][0], sh.lse2[r][1]) : plan_of(-1, true, 0.0, 0.0);

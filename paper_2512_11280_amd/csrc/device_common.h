@@ -39,6 +39,13 @@ template <class T> __device__ __forceinline__ T scalar_load(const T* p) {
   return t;
 }
 
+// The same through the vector path, for several that are asked for one after the other: scalar loads do not come in order, so that
+// waiting for one is waiting for all before it.  In every lane; uniform() makes a scalar of it where it is needed.
+template <class T> __device__ __forceinline__ T lane_load(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }  // v_exp_f32
 __device__ __forceinline__ float lg2(float x) { return __builtin_amdgcn_logf(x); }   // v_log_f32
 

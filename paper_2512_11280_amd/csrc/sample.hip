@@ -284,9 +284,8 @@ __global__ void __launch_bounds__(kBlock, 4) k_decide_sample(DecideArgs d, Updat
   warm_kernargs<sizeof(DecideArgs) + sizeof(UpdateArgs) + sizeof(SampleArgs) + 2 * sizeof(int) + sizeof(Workspace)>();
   __shared__ DecideShared sh;
   const int b = blockIdx.y;
-  const Decided dec = decide_sequence<DT, INLOOP, true, kBlock, LP, true>(d, upd, ws, b, sh, blockIdx.x == 0);
-  const uint32_t c2 = a.round ? scalar_load(a.round + b) : a.round0;
-  const uint32_t c3 = a.seq_id ? scalar_load(a.seq_id + b) : (uint32_t)b;
+  const SequenceIn in = ask_sequence(d, upd, b, false);
+  const Decided dec = decide_sequence<DT, INLOOP, true, kBlock, LP, true>(d, upd, ws, b, in, sh, blockIdx.x == 0);
   DrawAndApply round{d, upd, ws, sh, dec, b, {}};
   if (!dec.plan.valid) {          // (uniform over the sequence's workgroups)
     if (threadIdx.x >= 64) {
@@ -310,7 +309,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_decide_sample(DecideArgs d, Updat
     }
     return;
   }
-  draw_token<DT, false, PRUNE>(a, S, chunk, ws, dec.plan, c2, c3, free_words(d, ws, b), round);
+  draw_token<DT, false, PRUNE>(a, S, chunk, ws, dec.plan, (uint32_t)uniform(in.rnd), (uint32_t)uniform(in.seq), free_words(d, ws, b), round);
 }
 
 // ---------------------------------------------------------------------------------------------
