@@ -89,6 +89,10 @@ __device__ __forceinline__ void load_slice(const char* prow, const char* qrow, i
 // What stands in a lane past the end, once the references are known: a finite logit (-2.3e38) whose exponential
 // is 0 against any reference a row can have, so that it adds nothing to any sum and needs no branch.  (An
 // infinite one would do the same in the sums of 2^t, but t 2^t has no value there.)
+// SKIP: a wavefront leaves out the vectors of which all its lanes are past the end (`left`: vectors of the slice from its first lane
+// on).  For slices that leave a wavefront such a vector: whole calls (us) without / with, 64 x 16 x 16392 (half of a workgroup's
+// vectors) 48.2 / 39.6, 64 x 16 x 20000 48.6 / 41.7, 32 x 8 x 50257 float 39.2 / 38.5, 64 x 16 x 100000 142 / 134,
+// 128 x 16 x 152064 (6 % of them) 369 / 360.  Where there is none the branches cost 32 x 8 x 128256 56.1 -> 56.5.
 template <int DT> __device__ __forceinline__ uint32_t weightless() { return DT == ADASD_BF16 ? 0xFF2DFF2Du : 0xFF2D0000u; }
 template <int DT, int T, int NB>
 __device__ __forceinline__ void pad_slice(int s, const FusedGeom& g, uint4 (&xp)[NB], uint4 (&xq)[NB]) {
@@ -118,6 +122,12 @@ __device__ __forceinline__ void pad_slice(int s, const FusedGeom& g, uint4 (&xp)
   }
 }
 
+// Vectors of slice s from the wavefront's first lane on.
+__device__ __forceinline__ int wave_left(int s, const FusedGeom& g) {
+  const int v0 = min(s * g.chunk, g.nv);
+  return min(g.chunk, g.nv - v0) - (__builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63);
+}
+
 __device__ __forceinline__ void record_rows(const SliceRecord& o, Lse& tp, Lse& tq) {
   tp = Lse{o.m[0], o.v[0], o.v[1]};
   tq = Lse{o.m[1], o.v[2], o.v[3]};
@@ -143,11 +153,12 @@ __device__ __forceinline__ void split_halves(const Lse& f, Lse& tp, Lse& tq) {
 // S and U of the wavefront's logits about their references.  MASKED: a logit of -inf is kept from making
 // (-inf) * 0 out of its weighted term; without it such a logit turns the weighted sum into a NaN (as a NaN
 // does), which the caller sees.
-template <int DT, int NB, bool MASKED>
-__device__ __forceinline__ float phase1_sums(const uint4 (&xp)[NB], const uint4 (&xq)[NB], float neg_mp, float neg_mq) {
+template <int DT, int T, int NB, bool MASKED, bool SKIP>
+__device__ __forceinline__ float phase1_sums(const uint4 (&xp)[NB], const uint4 (&xq)[NB], float neg_mp, float neg_mq, int left) {
   float s[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, u[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
 #pragma unroll
-  for (int j = 0; j < NB; ++j)
+  for (int j = 0; j < NB; ++j) {
+    if (SKIP && j > 0 && j * T >= left) break;
 #pragma unroll
     for (int half = 0; half < Elem<DT>::per_vec / 4; ++half)
 #pragma unroll
@@ -163,13 +174,14 @@ __device__ __forceinline__ float phase1_sums(const uint4 (&xp)[NB], const uint4 
           u[row][i & 1] = fmaf(MASKED ? fmaxf(t[i], -200.f) : t[i], e[i], u[row][i & 1]);
         }
       }
+  }
   return wave_sum4(s[0][0] + s[0][1], s[1][0] + s[1][1], u[0][0] + u[0][1], u[1][0] + u[1][1]);
 }
 
 // Phase 1 of the slice held in (xp, xq) by the whole workgroup.  In wavefront 0 the lower half of the lanes
 // returns the target row's (m, s, u), the upper half the draft row's; the other wavefronts return nothing of
 // use.  One workgroup barrier.  masked: whether a logit of -inf (or a NaN) was met by this wavefront.
-template <int DT, int T, int NB>
+template <int DT, int T, int NB, bool SKIP>
 __device__ __forceinline__ Lse phase1(int s, const FusedGeom& g, uint4 (&xp)[NB], uint4 (&xq)[NB], bool& masked,
                                       FusedShared<T / 64>& sh) {
   constexpr int W = T / 64;
@@ -179,9 +191,10 @@ __device__ __forceinline__ Lse phase1(int s, const FusedGeom& g, uint4 (&xp)[NB]
   mp = flagged(mp);
   mq = flagged(mq);
   pad_slice<DT, T, NB>(s, g, xp, xq);
-  float sum = phase1_sums<DT, NB, false>(xp, xq, -mp, -mq);
+  const int left = wave_left(s, g);
+  float sum = phase1_sums<DT, T, NB, false, SKIP>(xp, xq, -mp, -mq, left);
   masked = __any(!(fabsf(sum) < INFINITY)) != 0;
-  if (masked) sum = phase1_sums<DT, NB, true>(xp, xq, -mp, -mq);
+  if (masked) sum = phase1_sums<DT, T, NB, true, SKIP>(xp, xq, -mp, -mq, left);
   // rows 0..3 of the lanes: S of the target row, U of the target row, S of the draft row, U of the draft row
   if ((lane & 15) == 0) sh.wave[wave].v[lane >> 4] = sum;
   if ((lane & 31) == 1) sh.wave[wave].m[lane >> 5] = lane < 32 ? mp : mq;
@@ -197,11 +210,12 @@ __device__ __forceinline__ Lse phase1(int s, const FusedGeom& g, uint4 (&xp)[NB]
 
 // The JS sum of the wavefront's share.  One element's term (see jsd_push, of which this is the ordinary form,
 // four pairs at a time).  MASKED: as in phase 1.
-template <int DT, int NB, bool MASKED>
-__device__ __forceinline__ float phase2(const uint4 (&xp)[NB], const uint4 (&xq)[NB], float neg_cp, float neg_cq, float neg_dc) {
+template <int DT, int T, int NB, bool MASKED, bool SKIP>
+__device__ __forceinline__ float phase2(const uint4 (&xp)[NB], const uint4 (&xq)[NB], float neg_cp, float neg_cq, float neg_dc, int left) {
   float acc[2] = {0.f, 0.f};
 #pragma unroll
-  for (int j = 0; j < NB; ++j)
+  for (int j = 0; j < NB; ++j) {
+    if (SKIP && j > 0 && j * T >= left) break;
 #pragma unroll
     for (int half = 0; half < Elem<DT>::per_vec / 4; ++half) {
       float zp[4], zq[4], b[4], d[4], r[4], h[4], l[4];
@@ -225,6 +239,7 @@ __device__ __forceinline__ float phase2(const uint4 (&xp)[NB], const uint4 (&xq)
         acc[i & 1] = fmaf(b[i], fabsf(d[i]) < kJsSmall ? t_series : t_log, acc[i & 1]);
       }
     }
+  }
   return acc[0] + acc[1];
 }
 // Rows whose normalisers lie far apart (rare, and not to set the kernel's register count).
@@ -282,7 +297,7 @@ __device__ __forceinline__ void fold_position(const Lse& tp, const Lse& tq, JsNo
   }
 }
 
-template <int DT, int T, int NB>
+template <int DT, int T, int NB, bool SKIP>
 __global__ void __launch_bounds__(T, NB <= 4 ? 8 : 4)
 k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout, HistArgs hist) {
   warm_kernargs<sizeof(RowMap) + sizeof(FusedGeom) + sizeof(Workspace) + sizeof(VerifyOut) + sizeof(HistArgs)>();
@@ -308,7 +323,7 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout, HistArgs hi
   uint4 xp[NB], xq[NB];
   load_slice<DT, T, NB>(rp.ptr, rq.ptr, s, g, xp, xq);
   bool masked;
-  const Lse mine = phase1<DT, T, NB>(s, g, xp, xq, masked, sh);
+  const Lse mine = phase1<DT, T, NB, SKIP>(s, g, xp, xq, masked, sh);
 
   if (wave == 0) {
     const bool need = lane < g.S;
@@ -368,7 +383,7 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout, HistArgs hi
       lds_barrier();                       // (sh.wave of the previous turn has been read)
       load_slice<DT, T, NB>(rp.ptr, rq.ptr, o, g, xp, xq);
       bool masked_o;
-      keep(o, phase1<DT, T, NB>(o, g, xp, xq, masked_o, sh));
+      keep(o, phase1<DT, T, NB, SKIP>(o, g, xp, xq, masked_o, sh));
     }
     lds_barrier();
     if (wave == 0) {
@@ -401,10 +416,10 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout, HistArgs hi
       float neg_cp = -n.cp, neg_cq = -n.cq, neg_dc = -n.dc_hi;
       asm volatile("" : "+v"(neg_cp), "+v"(neg_cq), "+v"(neg_dc));
       if (!masked) {
-        acc = wave_sum_f(phase2<DT, NB, false>(xp, xq, neg_cp, neg_cq, neg_dc));
+        acc = wave_sum_f(phase2<DT, T, NB, false, SKIP>(xp, xq, neg_cp, neg_cq, neg_dc, wave_left(s, g)));
         masked = !(fabsf(acc) < INFINITY);       // (the difference of two logits beyond the float range)
       }
-      if (masked) acc = wave_sum_f(phase2<DT, NB, true>(xp, xq, neg_cp, neg_cq, neg_dc));
+      if (masked) acc = wave_sum_f(phase2<DT, T, NB, true, SKIP>(xp, xq, neg_cp, neg_cq, neg_dc, wave_left(s, g)));
     }
   }
   if (lane == 0) sh.acc[wave] = acc;
@@ -499,9 +514,11 @@ hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, i
   if (g.chunk > T * NB) return hipErrorInvalidValue;
   g.hist_rows = hist.rec ? (hist.B + S - 1) / S : 0;
   const dim3 grid(S, positions + g.hist_rows);
+  const bool skip = NB > 1 && g.chunk <= NB * T - 64;     // the last wavefront has no lane in its last vector
 #define ADASD_FUSED_CASE(DTV, TV, NBV) \
   if (dt == DTV && T == TV && NB == NBV) { \
-    launch_kernel((k_stats_fused<DTV, TV, NBV>), grid, dim3(TV), st, map, g, ws, vout, hist); \
+    if (skip) launch_kernel((k_stats_fused<DTV, TV, NBV, (NBV > 1)>), grid, dim3(TV), st, map, g, ws, vout, hist); \
+    else launch_kernel((k_stats_fused<DTV, TV, NBV, false>), grid, dim3(TV), st, map, g, ws, vout, hist); \
     return hipGetLastError(); \
   }
 #define ADASD_FUSED_DT(DTV)      /* (what fused_plan can choose) */ \

@@ -520,6 +520,53 @@ def test_short_history_windows_at_the_edges_of_the_workgroup_sizes(am, wl, oracl
             assert np.array_equal(got[k], host[k]), k
 
 
+@pytest.mark.parametrize("dtype,T,NB", [(torch.bfloat16, 256, 2), (torch.bfloat16, 256, 4), (torch.bfloat16, 512, 4), (torch.bfloat16, 512, 8),
+                                         (torch.float32, 256, 2), (torch.float32, 256, 4), (torch.float32, 512, 4), (torch.float32, 512, 8)])
+@pytest.mark.parametrize("short", [-1, 0, 1, 63, 64, 65, 128, 257])
+def test_wavefronts_leave_out_vectors_past_the_end_of_their_slice(am, wl, oracle, dtype, T, NB, short):
+    """Slices of T * NB - short vectors, about the lengths from which a wavefront has vectors without a lane in the slice, in a
+    workgroup of each size; with logits of -inf (the loops' other form), with the last one whole and cut."""
+    epv = 8 if dtype is torch.bfloat16 else 4
+    slices = 1 if NB <= 4 else 64                     # (512 threads of eight vectors: the slices of the longest rows)
+    K = 2
+    B = 65 if slices == 1 else 1                      # (of up to 256 workgroups the slices are cut again)
+    V = (T * NB - short) * epv * slices - (3 if short % 2 else 0)
+    batch = wl.config_batched(B=B, k=K, V=V, seed=1300 + short, dtype=dtype, cap=64)
+    batch.target[0, 0, ::7] = float("-inf")
+    batch.draft[0, 1, V - 9:] = float("-inf")
+    out, _, ws = G.run_gpu(am, batch)
+    rep = G.compare_verify(out, G.run_oracle(oracle, batch))
+    assert G.hand_off_left_clear(ws, B * K)
+    _report(f"slices of {T} x {NB} - {short}", rep)
+
+
+@pytest.mark.parametrize("K", [3, 7, 12, 20])
+@pytest.mark.parametrize("cap", [1, 31, 127, 128, 129, 300])
+@pytest.mark.parametrize("literal", [0, 1])
+def test_what_stands_past_a_list_or_a_window_does_not_count(am, wl, oracle, K, cap, literal):
+    """The lists' first samples and what the positions need are read before the lengths are known.  Lists of no, one, two and up to
+    all samples of the capacity with NaN and in-range values behind them, windows from none to all positions with broken rows
+    and tokens behind them; decisions in the token kernel (k = 3: a wavefront to a position, 7: half of one) and in one of their own."""
+    B = 8
+    batch = wl.config_batched(B=B, k=K, V=1032, seed=900 + K, cap=64)
+    batch.state = wl.threshold_state(B, cap, torch.Generator().manual_seed(cap), n_hist=cap)
+    lengths = np.array([0, 1, 2, cap // 2, cap - 1, cap, cap, cap])
+    batch.state["nA"][:] = np.minimum(lengths, cap)
+    batch.state["nR"][:] = np.minimum(lengths[::-1], cap)
+    for b in range(B):
+        batch.state["LA"][b, batch.state["nA"][b]:] = np.nan if b % 2 else 0.5
+        batch.state["LR"][b, batch.state["nR"][b]:] = 0.5 if b % 2 else np.nan
+    batch.draft_len = torch.tensor([0, 1, K - 1, K, K, max(K - 2, 1), K, K], dtype=torch.int32)
+    for b in range(B):
+        batch.target[b, batch.draft_len[b] + 1:] = float("nan")
+        batch.draft[b, batch.draft_len[b]:] = float("nan")
+        batch.draft_tokens[b, batch.draft_len[b]:] = -7
+    options = am.Options(base_test=literal, list_update=literal)
+    out, _, _ = G.run_gpu(am, batch, options=options)
+    rep = G.compare_verify(out, G.run_oracle(oracle, batch, options=options))
+    _report(f"past the lists k={K} cap={cap} literal={literal}", rep)
+
+
 @pytest.mark.parametrize("B,K,V,dtype", [(1, 1, 9, torch.bfloat16), (2, 1, 128256, torch.bfloat16), (2, 2, 128256, torch.bfloat16),
                                          (3, 4, 32003, torch.bfloat16), (4, 5, 32000, torch.float32), (6, 8, 20011, torch.float32),
                                          (6, 9, 20011, torch.float32), (51, 2, 4100, torch.float32), (52, 2, 4100, torch.float32),
