@@ -4,7 +4,7 @@
 //
 // Fast path: float keys in the log2 domain that are UPPER BOUNDS of the true keys, running top-2 per
 // slice and sequence.  The winner is final only if its lower bound beats the runner-up's upper bound.
-// Otherwise the workgroup that arrives last settles the sequence in float64: first among the few
+// Otherwise the workgroup that folds the slices settles the sequence in float64: first among the few
 // elements whose upper bound reaches the winner's lower bound (found from the per-slice records, a
 // slice with two such elements is scanned again), and only if that is still too close to call, or the
 // winner's mass is not certain, over the whole row (exact path).
@@ -55,7 +55,7 @@ __device__ __forceinline__ FreeWords free_words(const DecideArgs& d, const Works
 }
 
 // What the token kernel does beside the draw: nothing, or (MERGED) the round is still to be applied and the status word to be
-// left, by the workgroup that arrives last.
+// left, by the workgroup that folds the slices.
 struct DrawOnly {
   static constexpr bool kMerged = false;
   __device__ __forceinline__ void beside() {}
@@ -277,7 +277,7 @@ __global__ void __launch_bounds__(kBlock, LONG ? 4 : 7) k_sample(SampleArgs a, i
 
 // Decisions and token in one launch, for rounds of so few positions and slices that deciding a sequence in every
 // workgroup of its token scan costs less than a launch: the first one leaves what is decided, and the one that
-// arrives last applies the round, when all have read the state.  One turn of the positions: a wavefront to each of up
+// folds the slices applies the round, when all have read the state.  One turn of the positions: a wavefront to each of up
 // to four, half a wavefront to each of up to eight.
 template <int DT, bool INLOOP, int LP, bool PRUNE>
 __global__ void __launch_bounds__(kBlock, 4) k_decide_sample(DecideArgs d, UpdateArgs upd, SampleArgs a, int S, int chunk, Workspace ws) {
