@@ -89,8 +89,8 @@ struct DraftShared {
 // 8.8 -> 6.0 us (3.4 us of it are the host's part of the call, which runs beside the kernel of the call before).
 // With few rows it is a chain of latencies: 0.6 us to the first logits, 0.6 to 0.9 for the scan, 0.5 for the wavefronts' and the
 // workgroup's fold, 0.6 until the last slice's record has arrived, 0.5 for the row's fold and the results.  The wavefronts
-// without logits behind a row's end stood in it with 1 us (top2_below), the ticket with 0.4, threshold and active flag with
-// 0.3: 1 x 128256 bf16 5.95 -> 4.56 us a call, 1 x 32000 float 5.96 -> 4.36, 32 x 128256 8.82 -> 8.18, entropies of 32 x 128256
+// without logits behind a row's end stood in it with 1 us (top2_below), the ticket with 0.4, the threshold, asked for
+// when it was needed, with 0.3: 1 x 128256 bf16 5.95 -> 4.56 us a call, 1 x 32000 float 5.96 -> 4.36, 32 x 128256 8.82 -> 8.18, entropies of 32 x 128256
 // float 6.57 -> 6.10.  (More than one vector ahead on its way: 6.2 -> 6.4 us with the entropies, 8.4 -> 8.5 with the draw.)
 //
 // One launch per drafting call, grid (slices, rows).  One workgroup of a row (few_rows) folds
@@ -115,10 +115,6 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
     }
     return x;
   };
-  // (asked for before it is known whether the row is active, and so is the threshold, which is needed at the very end: each
-  // was a latency of its own, 0.3 us of a call of 32 x 128256 float)
-  uint4 next = load(v0 + tid);
-  const float threshold = dout.T_G ? scalar_load(dout.T_G + rho) : INFINITY;
   if (!r.active) {
     if (s == 0 && tid == 0) {
       dout.H_out[rho] = 0.f;
@@ -130,6 +126,10 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
     }
     return;
   }
+  // (only here: the logits of a row at rest need not be there)
+  uint4 next = load(v0 + tid);
+  // (needed at the very end, where it was a latency of its own; ahead of the row it would be one too)
+  const float threshold = dout.T_G ? scalar_load(dout.T_G + rho) : INFINITY;
   const uint32_t c1 = dr.step | (2u << 16);
   const uint32_t c2 = DRAW ? (dr.round ? scalar_load(dr.round + rho) : dr.round0) : 0u;
   const uint32_t c3 = DRAW ? (dr.seq_id ? scalar_load(dr.seq_id + rho) : (uint32_t)rho) : 0u;
