@@ -186,7 +186,7 @@ int adasd_state_refresh(const adasd_state* st, void* stream) {
 
 static int draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
                          const float* T_G, const uint8_t* active, int step, int k_max, float* H_out,
-                         uint8_t* stop_out, void* workspace, size_t ws_bytes, void* stream, int polls) {
+                         uint8_t* stop_out, void* workspace, size_t ws_bytes, void* stream, WordWait wait) {
   int rc = check_shape(B, 0, V, (int)dt);
   if (rc) return rc;
   if (B == 0) return ADASD_OK;
@@ -207,7 +207,7 @@ static int draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V,
   map.K = 0;
   map.B = B;
   map.V = V;
-  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, polls < 0 ? polls : words_polls(B)};
+  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, wait};
   hipStream_t st = (hipStream_t)stream;
   Scope sc(5, st);
   return launch_draft_step(map, (int)dt, ws, dout, nullptr, st) == hipSuccess ? ADASD_OK : ADASD_ERR_HIP;
@@ -217,14 +217,14 @@ int adasd_draft_entropy(const void* draft_logits, adasd_dtype dt, int B, int V, 
                         const float* T_G, const uint8_t* active, int step, int k_max, float* H_out,
                         uint8_t* stop_out, void* workspace, size_t ws_bytes, void* stream) {
   return draft_entropy(draft_logits, dt, B, V, row_stride, T_G, active, step, k_max, H_out, stop_out, workspace, ws_bytes,
-                       stream, kWaitPolls);
+                       stream, kWaits);
 }
 
 static int draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride,
                       const float* T_G, const uint8_t* active, int step, int k_max, uint64_t seed,
                       const uint32_t* seq_id, const uint32_t* round, uint32_t round0, float* H_out,
                       uint8_t* stop_out, int32_t* token_out, uint32_t* status_out, void* workspace,
-                      size_t ws_bytes, void* stream, int polls) {
+                      size_t ws_bytes, void* stream, WordWait wait) {
   int rc = check_shape(B, 0, V, (int)dt);
   if (rc) return rc;
   if (B == 0) return ADASD_OK;
@@ -248,7 +248,7 @@ static int draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, in
   map.K = 0;
   map.B = B;
   map.V = V;
-  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, polls < 0 ? polls : words_polls(B)};
+  DraftOut dout{T_G, H_out, stop_out, step + 1 >= k_max ? 1 : 0, wait};
   DraftDraw draw{(uint32_t)seed, (uint32_t)(seed >> 32), seq_id, round, round0, (uint32_t)step, token_out, status_out};
   hipStream_t st = (hipStream_t)stream;
   Scope sc(5, st);
@@ -261,19 +261,31 @@ int adasd_draft_step(const void* draft_logits, adasd_dtype dt, int B, int V, int
                      uint8_t* stop_out, int32_t* token_out, uint32_t* status_out, void* workspace,
                      size_t ws_bytes, void* stream) {
   return draft_step(draft_logits, dt, B, V, row_stride, T_G, active, step, k_max, seed, seq_id, round, round0, H_out, stop_out,
-                    token_out, status_out, workspace, ws_bytes, stream, kWaitPolls);
+                    token_out, status_out, workspace, ws_bytes, stream, kWaits);
 }
 
-// For the tests, not part of the ABI: the drafting calls (token_out null: entropy only) on the path behind a wait that
-// has run out.
+// For the tests, not part of the ABI: the drafting calls (token_out null: entropy only) where records that are there count as
+// not there, and where the last slice gives its rows up at once.
+static int test_draft(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride, int step, uint64_t seed,
+                      uint32_t round0, float* H_out, uint8_t* stop_out, int32_t* token_out, uint32_t* status_out,
+                      void* workspace, size_t ws_bytes, void* stream, WordWait wait) {
+  if (!token_out)
+    return draft_entropy(draft_logits, dt, B, V, row_stride, nullptr, nullptr, step, 1 << 30, H_out, stop_out, workspace, ws_bytes,
+                         stream, wait);
+  return draft_step(draft_logits, dt, B, V, row_stride, nullptr, nullptr, step, 1 << 30, seed, nullptr, nullptr, round0, H_out,
+                    stop_out, token_out, status_out, workspace, ws_bytes, stream, wait);
+}
 int adasd_test_draft_unarrived(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride, int step, uint64_t seed,
                                uint32_t round0, float* H_out, uint8_t* stop_out, int32_t* token_out, uint32_t* status_out,
                                void* workspace, size_t ws_bytes, void* stream) {
-  if (!token_out)
-    return draft_entropy(draft_logits, dt, B, V, row_stride, nullptr, nullptr, step, 1 << 30, H_out, stop_out, workspace, ws_bytes,
-                         stream, -1);
-  return draft_step(draft_logits, dt, B, V, row_stride, nullptr, nullptr, step, 1 << 30, seed, nullptr, nullptr, round0, H_out,
-                    stop_out, token_out, status_out, workspace, ws_bytes, stream, -1);
+  return test_draft(draft_logits, dt, B, V, row_stride, step, seed, round0, H_out, stop_out, token_out, status_out, workspace,
+                    ws_bytes, stream, kNotThere);
+}
+int adasd_test_draft_given_up(const void* draft_logits, adasd_dtype dt, int B, int V, int64_t row_stride, int step, uint64_t seed,
+                              uint32_t round0, float* H_out, uint8_t* stop_out, int32_t* token_out, uint32_t* status_out,
+                              void* workspace, size_t ws_bytes, void* stream) {
+  return test_draft(draft_logits, dt, B, V, row_stride, step, seed, round0, H_out, stop_out, token_out, status_out, workspace,
+                    ws_bytes, stream, kGivesUp);
 }
 
 namespace {
@@ -407,14 +419,12 @@ SampleArgs sample_args(const adasd_verify_args* a, const VerifySetup& v) {
   s.round0 = a->round0;
   s.next_token = a->next_token;
   s.status = a->status;
-  s.polls = kWaitPolls;
   return s;
 }
 
 }  // namespace
 
-// (token_polls < 0: the token kernel takes the path behind a wait that has run out)
-static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void* stream, int token_polls) {
+static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void* stream, WordWait wait) {
   VerifySetup v;
   int rc = verify_setup(a, opt_in, kWantLogits | kWantOutputs | kWantToken, &v);
   if (rc) return rc < 0 ? rc : ADASD_OK;
@@ -468,7 +478,7 @@ static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void*
     d.tok = vout.tok;
   }
   SampleArgs s = sample_args(a, v);
-  s.polls = token_polls < 0 ? token_polls : words_polls(B);
+  s.wait = wait;
   const int S3 = token_split(B, V, (int)a->dt);
   if (merges_decisions(d, S3)) {
     Scope sc(3, st);
@@ -485,11 +495,14 @@ static int verify(const adasd_verify_args* a, const adasd_options* opt_in, void*
   return ADASD_OK;
 }
 
-int adasd_verify(const adasd_verify_args* a, const adasd_options* opt, void* stream) { return verify(a, opt, stream, 0); }
+int adasd_verify(const adasd_verify_args* a, const adasd_options* opt, void* stream) { return verify(a, opt, stream, kWaits); }
 
-// For the tests, not part of the ABI: verification with the token kernel on the path behind a wait that has run out.
+// For the tests, not part of the ABI: the same of the token kernel.
 int adasd_test_verify_unarrived(const adasd_verify_args* a, const adasd_options* opt, void* stream) {
-  return verify(a, opt, stream, -1);
+  return verify(a, opt, stream, kNotThere);
+}
+int adasd_test_verify_given_up(const adasd_verify_args* a, const adasd_options* opt, void* stream) {
+  return verify(a, opt, stream, kGivesUp);
 }
 
 // ---- verification without a caller-provided workspace -------------------------------------------

@@ -72,7 +72,7 @@ struct DraftShared {
   Floors floors;
   Lse l[kWaves];
   Top2 t[kWaves];
-  int mode;      // 0 not the last workgroup of the row; 1 final; 2 settle among the close candidates;
+  int mode;      // 0 another workgroup folds the row; 1 final; 2 settle among the close candidates;
                  // 3 broken row; 4 whole row in float64; 5 the same, and the entropy from the logits too
   float tau;
   double red[kWaves];
@@ -200,21 +200,16 @@ __global__ void __launch_bounds__(kBlock, 7) k_draft(RowMap map, int S, int chun
   __syncthreads();
   if (wave == 0) {
     fold_workgroup<DRAW>(sh.l, sh.t, st, best);
-    bool last = true;
+    bool last = true, arrived = true;
+    uint64_t w[kXchgWords];
     if (S > 1) {
-      uint64_t* words = ws.xchg + ((size_t)rho * kMaxSplit + s) * kXchgWords;
-      uint64_t w[kXchgWords];
       pack_draft(DraftRecord{st.m, st.s, st.u, best.k1, best.k2, best.i1}, w);
-      if (lane < kXchgWords)
-        __hip_atomic_store(words + lane, lane == 0 ? w[0] : (lane == 1 ? w[1] : w[2]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = few_rows(map.B) ? s == S - 1 : take_ticket(&ws.ticket1[rho * ticket_stride(map.B, kTicket1Len)], S);
+      last = hand_off(PlainWords{ws.xchg + (size_t)rho * kMaxSplit * kXchgWords}, s, S, Arrivals{ws.ticket1, kTicket1Len, rho, map.B},
+                      dout.wait, [] {}, w, arrived);
     }
     if (last) {
-      // ---- last workgroup of the row
-      bool arrived = true;
+      // ---- the row's records folded
       if (S > 1) {
-        uint64_t w[kXchgWords];
-        arrived = take_words(ws.xchg + ((size_t)rho * kMaxSplit + min(lane, S - 1)) * kXchgWords, lane < S, w, dout.polls);
         st = lse_empty();
         best = Top2{-INFINITY, -1, -INFINITY, -1};
         if (lane < S) {

@@ -17,8 +17,10 @@ constexpr int kWideMin = 384;       // list length from which a sequence actuall
 constexpr int kMaxSplit = 64;        // vocabulary slices per row: a fold takes one record per lane
 constexpr int kMaxSampleSplit = 128; // vocabulary slices per sequence of the token kernel's form for long rows
 constexpr int kXchgWords = 3;        // 64-bit hand-off words per record (records.h)
-constexpr int kWaitPolls = 16384;    // polls (about 4 ms) before a workgroup stops waiting for the words of others
-constexpr int kArrivalPolls = 1 << 20;   // the same (about a second) where words that come later would meet the next call
+constexpr int kWaitPolls = 16384;    // polls (2.5 ms, 3.4 with a thousand waiting) before a workgroup stops waiting for the words of others
+// How the drafting and token kernels wait for the slices' records: as many polls, or as the tests have it: the last slice of few rows
+// gives up at once, or the records count as not there when they are.
+enum WordWait : int32_t { kWaits = kWaitPolls, kGivesUp = 0, kNotThere = -1 };
 
 // Where the rows of one call live.  which = 0: target, 1: draft.
 struct RowMap {
@@ -35,13 +37,13 @@ struct RowMap {
 struct Workspace {
   float4* part1;      // [rows][kMaxSplit]   (m, s, u, -) partial log-sum-exp states of the two-kernel path; with the single-read
                       // statistics kernel, which has none, the HistRecords of the sequences
-  int32_t* ticket1;   // [kTicket1Len]       arrival counters of the drafting kernel (row rho at rho * ticket_stride), zero between calls
+  int32_t* ticket1;   // [kTicket1Len]       arrival words of the drafting kernel (see Arrivals), zero between calls
   RowResult* rows;    // [rows]
   float2* part2;      // [positions][kMaxSplit] partial KL sums (p side, q side), log2 units
   int32_t* ticket2;   // [kTicket2Len]       arrival counters of the long-history decision kernel, zero between calls
   SamplePlan* plan;   // [B]
   Top2* part3;        // [B][kMaxSampleSplit]
-  int32_t* ticket3;   // [kTicket3Len]       arrival counters of the sampling kernel, zero between calls
+  int32_t* ticket3;   // [kTicket3Len]       the same of the token kernel
   uint64_t* xchg;     // [positions][kMaxSplit][kXchgWords] self-validating hand-off words (records.h), zero between kernels:
                       // slice records of the single-read statistics kernel (cleared by the decision kernel), of the drafting
                       // kernel [rows] and of the token kernel [sequences] (cleared by the workgroup that folds them; where it takes
@@ -71,7 +73,7 @@ struct DraftOut {     // draft-entropy epilogue
   float* H_out;
   uint8_t* stop_out;
   int32_t force_stop; // step + 1 >= k_max
-  int32_t polls;      // bound of the wait for the slices' records (see take_words)
+  WordWait wait;      // for the slices' records (see hand_off)
 };
 
 struct DraftDraw {    // token draw of a drafting step (x_i ~ q_i)
@@ -141,12 +143,15 @@ inline int token_split(int rows, int V, int dt) {
 }
 
 // Who folds the slices' records of a drafting or token scan: of a few rows the workgroup of the last slice, which waits for the
-// others' words; else the one that takes the last ticket, which costs a round trip more.  Workgroups start in order, so
-// whatever the last slice waits for has started before it.  The waiting ones take a place on the chip per row; a die has 256, and
-// four calls of 64 rows on four streams at once would be the least with which those of several calls could fill one.
+// others' words; else the last one to add to the row's count, which costs a round trip more (records.h).  Whole calls (us), waiting /
+// the last to add: drafting 1 x 32000 float 4.6 / 5.0, 64 x 32000 6.7 / 7.1, 64 x 128256 bf16 12.0 / 12.4, 128 x 128256 17.6 / 18.0,
+// 512 x 32000 float 18.3 / 18.8, a round of 16 x 2 x 32000 15.1 / 15.7.  The line is not where that ends: those who wait hold a
+// place on the chip per row, and where the slices are a multiple of eight all of them on one die, which has 160 to 224 (five to
+// seven workgroups on each of 32 compute units).  More than 64 would keep a good part of a die from the work of other streams.
+// (Workgroups of a die start in order, those of different dies need not, and other streams' work may come between: whoever is
+// waited for has mostly started, but nothing here relies on it.)
 constexpr int kFewRows = 64;
 __host__ __device__ inline bool few_rows(int rows) { return rows <= kFewRows; }
-inline int words_polls(int rows) { return few_rows(rows) ? kArrivalPolls : kWaitPolls; }
 
 // Whether a scan over slices of `chunk` vectors leaves out the logits that cannot win any more (sample_device.h): from four
 // groups of 256 logits per wavefront on.  The first groups are looked at in any case, and the test costs a wavefront
@@ -257,7 +262,7 @@ struct SampleArgs {
   uint32_t round0;
   int32_t* next_token;
   uint32_t* status;
-  int32_t polls;        // bound of the wait for the slices' records (see take_words)
+  WordWait wait;        // for the slices' records (see hand_off)
 };
 hipError_t launch_shard_sample(const SampleArgs& a, int S, int col0, const Workspace& ws, float4* top_out, hipStream_t st);
 hipError_t launch_shard_pick(int B, int G, const float4* top_all, const Workspace& ws, int32_t* next_token,

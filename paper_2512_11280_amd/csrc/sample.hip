@@ -35,13 +35,9 @@ __device__ __forceinline__ void scan_plan(const SamplePlan& plan, const char* pr
   else scan_slice<DT, kPlain, PRUNE>(prow, qrow, V, v0, v1, cp, cq, -1, col0, noise, best, sh, poison);
 }
 
-// Where a sequence's slices leave their words: the first slots of its part of the hand-off region.
-struct PlainWords {
-  uint64_t* base;
-  __device__ __forceinline__ uint64_t* at(int s) const { return base + s * kXchgWords; }
-};
-// In the slots of its positions that the statistics kernel does not use (free_slots of them per position, at least half of
-// them: a sequence's slices take those of two positions at most): the words of that kernel are being cleared meanwhile.
+// Where a sequence's slices leave their words (instead of PlainWords) while those of the statistics kernel are being cleared:
+// in the slots of its positions that that kernel does not use (free_slots of them per position, at least half of
+// them: a sequence's slices take those of two positions at most).
 struct FreeWords {
   uint64_t* base;      // the first free slot of the sequence's first position
   int free_slots;
@@ -108,7 +104,7 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
 
   __shared__ Top2 sh_top[kWaves];
   __shared__ float2 sh_logits[kWaves];
-  // modes: 0 not the last workgroup; 1 final; 2 settle among the close candidates; 3 broken bonus row; 4 whole row in float64
+  // modes: 0 another workgroup folds; 1 final; 2 settle among the close candidates; 3 broken bonus row; 4 whole row in float64
   __shared__ int sh_mode;
   __shared__ uint32_t sh_status;              // (MERGED) what the status word holds so far
   __shared__ float sh_tau;
@@ -136,7 +132,9 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
     const float2 z = sh_logits[best.i1 == t0.i1 ? 0 : best.i1 == t1.i1 ? 1 : best.i1 == t2.i1 ? 2 : 3];
     zp = best.i1 >= 0 ? z.x : 0.f;
     zq = best.i1 >= 0 ? z.y : 0.f;
-    bool last = true;
+    bool last = true, arrived = true;
+    uint64_t w[kXchgWords];
+    const Arrivals arrivals{ws.ticket3, kTicket3Len, b, a.map.B};
     if (LONG) {
       if (lane == 0) {
         Top2* dst = &ws.part3[(size_t)b * kMaxSampleSplit + s];
@@ -146,21 +144,22 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
         st_agent(&dst->i2, poison ? -2 : -1);
       }
       publish_barrier();
-      last = take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S);
+      int32_t* count = &ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)];
+      last = last_to_add(add_arrival(count, 1), S);
+      if (last) {
+        set_arrival(count, 0);
+        round.ask();
+      }
     } else if (S > 1) {
-      uint64_t* words = slots.at(s);
-      uint64_t w[kXchgWords];
       pack_draw(DrawRecord{best.k1, best.k2, zp, zq, best.i1, poison}, w);
-      if (lane < kXchgWords)
-        __hip_atomic_store(words + lane, lane == 0 ? w[0] : (lane == 1 ? w[1] : w[2]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = few_rows(a.map.B) ? s == S - 1 : take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S);
+      last = hand_off(slots, s, S, arrivals, a.wait, [&] { round.ask(); }, w, arrived);
+    } else {
+      round.ask();
     }
     int mode = 0;
     if (last) {
-      // ---- last workgroup of this sequence: fold the S records
-      round.ask();
+      // ---- the S records of this sequence folded
       Top2 t{-INFINITY, -1, -INFINITY, -1};
-      bool arrived = true;
       if (LONG) {
         poison = false;
         for (int j = lane; j < S; j += 64) {
@@ -170,8 +169,6 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
         }
         poison = __any(poison);
       } else if (S > 1) {
-        uint64_t w[kXchgWords];
-        arrived = take_words(slots.at(min(lane, S - 1)), lane < S, w, a.polls);
         if (lane < S) {
           const DrawRecord r = unpack_draw(w);
           t = Top2{r.k1, r.i1, r.k2, -1};
@@ -292,16 +289,16 @@ __global__ void __launch_bounds__(kBlock, 4) k_decide_sample(DecideArgs d, Updat
       round.beside();
       return;
     }
-    if (S > 1) {                  // (records without a content: that they are there tells that the state has been read)
-      const FreeWords slots = free_words(d, ws, b);
-      const int s = blockIdx.x, lane = threadIdx.x;
-      if (lane < kXchgWords)
-        __hip_atomic_store(slots.at(s) + lane, record_word(1u, 0.f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!(few_rows(a.map.B) ? s == S - 1 : take_ticket(&ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)], S))) return;
-      uint64_t w[kXchgWords];
-      take_words(slots.at(min(lane, S - 1)), lane < S, w, a.polls);
+    if (S > 1) {                  // (records without a content: once all have been sent, the state has been read)
+      const uint64_t none = record_word(1u, 0.f);
+      uint64_t w[kXchgWords] = {none, none, none};
+      bool arrived;               // (sent is enough)
+      if (!hand_off(free_words(d, ws, b), blockIdx.x, S, Arrivals{ws.ticket3, kTicket3Len, b, a.map.B}, a.wait, [&] { round.ask(); }, w,
+                    arrived))
+        return;
+    } else {
+      round.ask();
     }
-    round.ask();
     const uint32_t st = round.finish();
     if (threadIdx.x == 0) {
       a.next_token[b] = -1;

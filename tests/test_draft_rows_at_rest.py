@@ -44,6 +44,7 @@ template <class T> T across_lanes(T) { std::abort(); }
 #define __ballot(x) across_lanes((unsigned long long)(x))
 #define __shfl_xor(x, off) across_lanes(x)
 #define __ffsll(x) __builtin_ffsll(x)
+#define __popcll(x) __builtin_popcountll(x)
 #define __builtin_amdgcn_readlane(x, l) across_lanes((int)(x))
 #define __builtin_amdgcn_update_dpp(o, x, ...) across_lanes((int)(x))
 struct Pair { uint32_t v[2]; uint32_t operator[](int i) const { return v[i]; } };
@@ -90,7 +91,7 @@ template <int DT, bool DRAW, bool PRUNE> int rows_at_rest(const char* nothing, i
   map.active = active;
   map.B = B;
   map.V = V;
-  const DraftOut dout{T_G, H, stop, 0, 1};
+  const DraftOut dout{T_G, H, stop, 0, kWaits};
   const DraftDraw dr{1u, 2u, nullptr, nullptr, 3u, 0u, token, status};
   for (unsigned b = 0; b < (unsigned)B; ++b)
     for (unsigned s = 0; s < (unsigned)S; ++s)

@@ -1902,6 +1902,71 @@ def test_token_draw_goes_on_where_slice_records_do_not_arrive(am, wl, oracle, dt
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,V", [(1, 4001), (5, 32000), (64, 4160)])
+def test_drafting_where_the_last_slice_gives_a_row_up(am, oracle, dtype, B, V):
+    """The last slice does not wait for the others' records at all, so that whoever comes last folds the row (or the last slice, where
+    all were there already): the same bits, nothing settled anew, the workspace clean, and the calls that follow unharmed."""
+    g = torch.Generator().manual_seed(V)
+    z = (3.0 * torch.randn(B, V, generator=g)).to(dtype)
+    if B > 1:
+        z[1, 10:] = -math.inf
+        z[2, V - 1] = math.nan
+    ws, zd = am.Workspace(B, 1, V, dtype), z.cuda()
+    fn = am.load_library().adasd_test_draft_given_up
+    fn.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int64, C.c_int, C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p,
+                   C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
+    code, stream = am.binding._dtype_code(zd), torch.cuda.current_stream().cuda_stream
+    for round0 in range(8):
+        ref = [t.clone() for t in am.draft_step(zd, ws, step=1, seed=31, round0=round0)]
+        H, stop, tok, st = (torch.full_like(t, 9) for t in ref)
+        He = torch.full_like(H, 9)
+        assert fn(zd.data_ptr(), code, B, V, V, 1, 31, round0, H.data_ptr(), stop.data_ptr(), tok.data_ptr(), st.data_ptr(), ws.ptr,
+                  ws.bytes, stream) == 0
+        assert fn(zd.data_ptr(), code, B, V, V, 1, 31, round0, He.data_ptr(), None, None, None, ws.ptr, ws.bytes, stream) == 0
+        for a, b in zip((H, stop, tok, st, He), (*ref, ref[0])):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), round0
+        assert G.hand_off_left_clear(ws, B)
+        assert np.array_equal(ref[2].cpu().numpy(), oracle.draft_sample(z, step=1, seed=31, round0=round0)[0])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("literal", [0, 1])
+@pytest.mark.parametrize("B,K,V", [(1, 4, 32000), (6, 3, 20011), (6, 9, 20011), (64, 2, 4100)])
+def test_rounds_where_the_last_slice_gives_a_sequence_up(am, wl, oracle, dtype, literal, B, K, V):
+    """The same of the token kernel, alone (k = 9) and with the decisions inside it, where the one that folds applies the round:
+    replacements, bonus draws, a broken bonus row, a broken row in the window."""
+    batch = wl.config_batched(B=B, k=K, V=V, dtype=dtype, seed=52)
+    if B > 1:
+        batch.draft[0] = batch.target[0, :K]                  # all accepted: the bonus row
+        batch.draft[1] = batch.target[1, :K]
+        batch.target[1, K, 3] = math.nan
+        batch.target[2, 0, 5] = math.nan
+    options = am.Options(base_test=literal, list_update=literal, apply_update=1)
+    t, d, tok = batch.target.cuda(), batch.draft.cuda(), batch.draft_tokens.cuda()
+    ws, opt = am.Workspace(B, K, V, dtype), options._c()
+    fn = am.load_library().adasd_test_verify_given_up
+    fn.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
+    for turn in range(3):
+        ref, ref_st, _ = G.run_gpu(am, batch, options=options, ws=ws)
+        st = G.state_to_device(am, batch.state, B, batch.state["LA"].shape[1])
+        out, state = am.binding.alloc_verify_result(B, K), st._c()
+        a = am.binding._VerifyArgs(
+            t.data_ptr(), d.data_ptr(), am.binding._dtype_code(t), B, K, V, t.stride(0), t.stride(1), d.stride(0), d.stride(1),
+            tok.data_ptr(), None, C.pointer(state), batch.seed, None, None, batch.round0, out.n_accept.data_ptr(),
+            out.next_token.data_ptr(), out.H_p.data_ptr(), out.H_q.data_ptr(), out.d_js.data_ptr(), out.p_accept.data_ptr(),
+            out.accept_mask.data_ptr(), out.status.data_ptr(), ws.ptr, ws.bytes)
+        assert fn(C.byref(a), C.byref(opt), torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        for k in ("n_accept", "next_token", "H_p", "H_q", "d_js", "p_accept", "accept_mask", "status"):
+            assert torch.equal(getattr(out, k).view(torch.uint8), getattr(ref, k).view(torch.uint8)), (k, turn)
+        got, want = st.to_host(), ref_st.to_host()
+        for k in ("T_G", "ent_sum", "ent_cnt", "nA", "nR", "LA", "LR"):
+            assert np.array_equal(got[k], want[k], equal_nan=True), (k, turn)
+        assert G.hand_off_left_clear(ws, B * K)
+    G.compare_verify(out, G.run_oracle(oracle, batch, options=options), info_bits=16 | 8)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V", [70000, 70001])
 def test_rows_with_whole_slices_masked(am, wl, oracle, dtype, V):
     """Masked logits over whole slices of a row (a constrained decoder leaves a few tokens only): the records of such
