@@ -95,19 +95,26 @@ ADASD_ANYWHERE PairRecord unpack_pair(const uint64_t (&w)[3]) {
                     word_lo(w[1]), word_hi(w[1]), word_hi(w[2])};
 }
 
-// Who folds the records of a row of S > 1 slices, by its arrival words (a count and a set of slices, zero between launches).
-//  * Many rows: every slice sends its record and adds 1 to the count.  The last one to add folds: all records have been sent by
+// Who folds the records of a row of S > 1 slices, by the row's arrival word (zero between launches).
+//  * Many rows: a count.  Every slice sends its record and adds 1.  The last one to add folds: all records have been sent by
 //    then, and it reads until they are there.
 //  * Few rows: the last slice reads at once, which saves it a round trip.  Should it read for too long (those it waits for may
-//    not have been started, if work of other streams holds the chip) it gives up: it puts kDeciding in the set and, when that
-//    has got there, looks once more, and then leaves in the set the slices whose records are still missing and takes their
-//    number off the count.  A slice looks at the set when its record has got there.  So one that was found missing finds kDeciding
-//    or the set itself; it waits for the set, and adds 1 to the count.  Whoever makes that zero comes last and folds.
+//    not have been started, if work of other streams holds the chip) it gives up: it puts kLooking in the word and, when that
+//    has got there, looks once more.  A slice looks at the word when its record has got there; so one that still finds zero
+//    has its record found.  One that finds kLooking adds itself to the word, and need not be waited for any more.  The last slice then
+//    puts in the place of kLooking the slices whose records it has missed and that have not come meanwhile; they take themselves out
+//    again as they come.  Whoever leaves zero is the last and folds.  Each change is one compare-and-exchange, begun again where
+//    the word has changed meanwhile: nobody waits for anybody, and a word changes no more often than there are slices.
 // Either way all slices have sent before anybody folds, clears words or changes a state, and no word is left behind.
-constexpr uint64_t kDeciding = ~0ull;                                                       // (the last slice of 64, bit 63, is in no set)
-ADASD_ANYWHERE bool deciding(uint64_t set) { return (set >> 63) != 0; }
-ADASD_ANYWHERE bool is_missing(uint64_t set, int s) { return ((set >> s) & 1) != 0; }
 ADASD_ANYWHERE bool last_to_add(int before, int S) { return before == S - 1; }             // many rows
-ADASD_ANYWHERE bool last_to_come(int before, int added) { return before + added == 0; }    // few rows, given up
+constexpr uint64_t kLooking = 1ull << 63;                                                   // (the last slice of 64 is in no set)
+ADASD_ANYWHERE bool being_looked(uint64_t word) { return (word & kLooking) != 0; }
+// What a slice makes of the word, its record being there (the word itself: nothing is to be done), and whether it then folds.
+ADASD_ANYWHERE uint64_t after_coming(uint64_t word, int s) {
+  const uint64_t self = 1ull << s;
+  return word == 0 ? 0 : being_looked(word) ? word | self : word & ~self;
+}
+// What the last slice makes of it, having missed the records of these slices.  (It folds where that leaves zero.)
+ADASD_ANYWHERE uint64_t after_looking(uint64_t word, uint64_t missed) { return missed & ~word; }
 
 }  // namespace adasd

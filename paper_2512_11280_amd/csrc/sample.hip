@@ -145,7 +145,7 @@ __device__ __forceinline__ void draw_token(const SampleArgs& a, int S, int chunk
       }
       publish_barrier();
       int32_t* count = &ws.ticket3[b * ticket_stride(a.map.B, kTicket3Len)];
-      last = last_to_add(add_arrival(count, 1), S);
+      last = last_to_add(add_arrival(count), S);
       if (last) {
         set_arrival(count, 0);
         round.ask();

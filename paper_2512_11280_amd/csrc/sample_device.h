@@ -113,18 +113,18 @@ struct PlainWords {
   uint64_t* base;
   __device__ __forceinline__ uint64_t* at(int s) const { return base + s * kXchgWords; }
 };
-// The arrival words of the rows of a launch: a count each, and of few rows the set behind it, on a line of their own.
+// The arrival words of the rows of a launch: a count each, or of few rows a set (64 bits), on a line of its own.
 struct Arrivals {
   int32_t* base;
   int len, row, rows;
-  __device__ __forceinline__ int32_t* count() const { return base + row * (few_rows(rows) ? 32 : ticket_stride(rows, len)); }
-  __device__ __forceinline__ uint64_t* set() const { return reinterpret_cast<uint64_t*>(base + row * 32) + 1; }      // (few rows)
+  __device__ __forceinline__ int32_t* count() const { return base + row * ticket_stride(rows, len); }                // (many rows)
+  __device__ __forceinline__ uint64_t* set() const { return reinterpret_cast<uint64_t*>(base + row * 32); }          // (few rows)
 };
 static_assert(kFewRows * 32 <= kTicket1Len && kFewRows * 32 <= kTicket3Len, "a line of 128 bytes for each of few rows");
-// (lane 0 adds; what the word held before, in every lane)
-__device__ __forceinline__ int add_arrival(int32_t* word, int n) {
+// (lane 0 adds 1; what the word held before, in every lane)
+__device__ __forceinline__ int add_arrival(int32_t* word) {
   int before = 0;
-  if ((threadIdx.x & 63) == 0) before = __hip_atomic_fetch_add(word, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((threadIdx.x & 63) == 0) before = __hip_atomic_fetch_add(word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return __builtin_amdgcn_readfirstlane(before);
 }
 // What this wavefront has stored has got there before anything is looked at that it loads from here on.
@@ -138,6 +138,16 @@ template <class T> __device__ __forceinline__ void set_arrival(T* word, T v) {
 __device__ __forceinline__ uint64_t get_uniform(const uint64_t* word) {
   const uint64_t v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return (uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32 | (uint32_t)uniform((int)v);
+}
+// (lane 0 puts `next` in the place of `word`; where something else stood there, false, and word is what did)
+__device__ __forceinline__ bool exchange_arrival(uint64_t* at, uint64_t& word, uint64_t next) {
+  uint64_t seen = word;
+  if ((threadIdx.x & 63) == 0)
+    __hip_atomic_compare_exchange_strong(at, &seen, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  seen = (uint64_t)(uint32_t)uniform((int)(seen >> 32)) << 32 | (uint32_t)uniform((int)seen);
+  const bool done = seen == word;
+  word = seen;
+  return done;
 }
 // The words of the lane's slice, and whether they are all there.
 __device__ __forceinline__ bool look_at_words(const uint64_t* words, uint64_t (&w)[kXchgWords]) {
@@ -166,17 +176,19 @@ __device__ __forceinline__ bool hand_off(const Slots& slots, int s, int S, const
   if (lane < kXchgWords) __hip_atomic_store(slots.at(s) + lane, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   bool may_give_up = false;
   if (!few_rows(a.rows)) {
-    if (!last_to_add(add_arrival(a.count(), 1), S)) return false;
+    if (!last_to_add(add_arrival(a.count()), S)) return false;
     set_arrival(a.count(), 0);
   } else if (s == S - 1) {
     may_give_up = true;
   } else {
     stores_before_loads();
-    uint64_t set = get_uniform(a.set());
+    uint64_t set = get_uniform(a.set()), next;
     if (__builtin_expect(set == 0, 1)) return false;
-    for (int polls = kWaitPolls; deciding(set) && polls > 0; --polls) set = get_uniform(a.set());
-    if (!is_missing(set, s) || !last_to_come(add_arrival(a.count(), 1), 1)) return false;
-    set_arrival(a.set(), (uint64_t)0);
+    do {
+      next = after_coming(set, s);
+      if (next == set) return false;
+    } while (!exchange_arrival(a.set(), set, next));
+    if (next != 0) return false;
   }
   ask();
   const bool mine = lane < S;
@@ -186,15 +198,13 @@ __device__ __forceinline__ bool hand_off(const Slots& slots, int s, int S, const
     do arrived = __all(look_at_words(words, w) || !mine) != 0;
     while (!arrived && polls-- > 0);
     if (__builtin_expect(arrived || !may_give_up, 1)) break;
-    set_arrival(a.set(), kDeciding);
+    set_arrival(a.set(), kLooking);
     stores_before_loads();
-    const uint64_t missing = __ballot(mine && lane != s && !look_at_words(words, w));
-    const int n = __popcll(missing);
-    set_arrival(a.set(), missing);
-    if (n > 0) {
-      if (!last_to_come(add_arrival(a.count(), -n), -n)) return false;
-      set_arrival(a.set(), (uint64_t)0);
-    }
+    const uint64_t missed = __ballot(mine && lane != s && !look_at_words(words, w));
+    uint64_t set = kLooking, next;
+    do next = after_looking(set, missed);
+    while (!exchange_arrival(a.set(), set, next));
+    if (next != 0) return false;
     may_give_up = false;
     polls = kWaitPolls;
   }

@@ -71,6 +71,7 @@ template <class T> T atomicAdd(T* p, T v) { T o = *p; *p += v; return o; }
 #define __hip_atomic_load(p, o, s) (*(p))
 #define __hip_atomic_store(p, v, o, s) (*(p) = (v))
 #define __hip_atomic_fetch_add(p, v, o, s) atomicAdd(p, v)
+#define __hip_atomic_compare_exchange_strong(...) across_lanes(false)
 """
 
 MAIN = r"""

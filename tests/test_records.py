@@ -46,10 +46,9 @@ extern "C" void pair(int n, const float* f, uint64_t* words, float* f_out) {
   }
 }
 extern "C" int last(int before, int S) { return last_to_add(before, S); }
-extern "C" int come(int before, int added) { return last_to_come(before, added); }
-extern "C" int undecided(uint64_t set) { return deciding(set); }
-extern "C" int missing(uint64_t set, int s) { return is_missing(set, s); }
-extern "C" uint64_t mark() { return kDeciding; }
+extern "C" uint64_t come(uint64_t word, int s) { return after_coming(word, s); }
+extern "C" uint64_t look(uint64_t word, uint64_t missed) { return after_looking(word, missed); }
+extern "C" uint64_t mark() { return kLooking; }
 """
 
 
@@ -116,30 +115,28 @@ def test_row_pair_records_arrive_as_they_were_sent(lib):
 @pytest.mark.parametrize("few", [False, True])
 @pytest.mark.parametrize("S", [2, 3, 4])
 def test_every_row_is_folded_once_and_leaves_no_word_behind(lib, few, S):
-    """All orders in which the slices of a row can send, their words and additions can take effect, and the last slice of few rows
-    can give up, also before the others have started: one of them folds, after all have sent and with all words there, and
-    words, count and set are zero at the end, so that the next call finds nothing of this one.  (A record of two words here.)"""
-    lib.mark.restype = C.c_uint64
-    mark, undecided, missing = lib.mark(), lambda v: lib.undecided(C.c_uint64(v)), lambda v, s: lib.missing(C.c_uint64(v), s)
-    assert undecided(mark) and not undecided((1 << 63) - 1) and missing(1 << 62, 62) and not missing(1 << 62, 61)
-    last, none, names = S - 1, ((False, False),) * S, ("there", "sent", "at", "count", "set_", "left", "found", "folds")
-    # of each slice: its words that are there, its words that have got there, what it does next.  Then: count, set, and of the last
-    # slice: those it still has to look at, those it found missing.  How often the row was folded.
-    start = (none, none, ("start",) * S, 0, 0, frozenset(), frozenset(), 0)
+    """All orders in which the slices of a row can send, their words and changes of the arrival word can take effect, and the last slice
+    of few rows can give up, also before the others have started and however long a slice stays between two of its steps: one of
+    them folds, after all have sent and with all words there, and words and arrival word are zero at the end, so that the next call
+    finds nothing of this one.  (A record of two words here.)"""
+    lib.mark.restype = lib.come.restype = lib.look.restype = C.c_uint64
+    mark, come = lib.mark(), lambda v, s: lib.come(C.c_uint64(v), s)
+    assert come(0, 5) == 0 and come(1 << 62, 62) == 0 and come(1 << 62, 61) == 1 << 62 and come(mark, 62) == mark | 1 << 62
+    last, none, names = S - 1, ((False, False),) * S, ("there", "sent", "at", "seen_", "word", "left", "missed", "folds")
+    # of each slice: its words that are there, its words that have got there, what it does next, the arrival word as it has seen it.
+    # Then: the arrival word, and of the last slice: those it still has to look at, those it missed.  How often the row was folded.
+    start = (none, none, ("start",) * S, (0,) * S, 0, frozenset(), frozenset(), 0)
     seen, todo, ends = {start}, [start], 0
 
     def put(t, s, v):
         return t[:s] + (v,) + t[s + 1:]
     while todo:
         state = todo.pop()
-        there, sent, at, count, set_, left, found, folds = state
+        there, sent, at, seen_, word, left, missed, folds = state
         new = []
 
         def go(**kw):
             new.append(tuple(kw.get(n, v) for n, v in zip(names, state)))
-
-        def add(s, n, mine):                              # (the last to come clears the set)
-            go(count=count + n, set_=0 if mine else set_, at=put(at, s, "folds" if mine else "done"))
         for s in range(S):
             if at[s] == "start":
                 go(at=put(at, s, "adds" if not few else "reads" if s == last else "waits"))
@@ -148,31 +145,33 @@ def test_every_row_is_folded_once_and_leaves_no_word_behind(lib, few, S):
                 if not sent[s][i]:
                     go(there=put(there, s, put(there[s], i, True)), sent=put(sent, s, put(sent[s], i, True)))
             if at[s] == "adds":
-                mine = lib.last(count, S)
-                go(count=0 if mine else count + 1, at=put(at, s, "folds" if mine else "done"))
-            if at[s] == "waits" and all(sent[s]):         # its record has got there: it looks at the set
-                go(at=put(at, s, "done" if set_ == 0 else "looks"))
-            if at[s] == "looks" and not undecided(set_):
-                go(at=put(at, s, "comes" if missing(set_, s) else "done"))
-            if at[s] == "comes":
-                add(s, 1, lib.come(count, 1))
+                mine = lib.last(word, S)
+                go(word=0 if mine else word + 1, at=put(at, s, "folds" if mine else "done"))
+            if at[s] == "waits" and all(sent[s]):         # its record has got there: it looks at the word
+                go(seen_=put(seen_, s, word), at=put(at, s, "done" if word == 0 else "comes"))
+            if at[s] in ("comes", "leaves"):              # a compare-and-exchange, or a look at what stands there instead
+                nxt = come(seen_[s], s) if at[s] == "comes" else lib.look(C.c_uint64(seen_[s]), C.c_uint64(sum(1 << o for o in missed)))
+                if at[s] == "comes" and nxt == seen_[s]:
+                    go(at=put(at, s, "done"))
+                elif word == seen_[s]:
+                    go(word=nxt, at=put(at, s, "done" if nxt else "folds"))
+                else:
+                    go(seen_=put(seen_, s, word))
             if at[s] == "reads":
                 if all(map(all, there)):
                     go(at=put(at, s, "folds"))
-                go(at=put(at, s, "marked"), set_=mark, left=frozenset(range(S)) - {s})      # (the mark has got there before it looks)
-            if at[s] == "marked":
+                go(at=put(at, s, "looks"), word=mark, left=frozenset(range(S)) - {s})       # (the mark has got there before it looks)
+            if at[s] == "looks":
                 for o in left:
-                    go(left=left - {o}, found=found if all(there[o]) else found | {o})
+                    go(left=left - {o}, missed=missed if all(there[o]) else missed | {o})
                 if not left:
-                    go(set_=sum(1 << o for o in found), at=put(at, s, "counts" if found else "folds"))
-            if at[s] == "counts":
-                add(s, -len(found), lib.come(count, -len(found)))
+                    go(seen_=put(seen_, s, mark), at=put(at, s, "leaves"))
             if at[s] == "folds":
                 assert "start" not in at
                 if all(map(all, there)):
                     go(there=none, at=put(at, s, "done"), folds=folds + 1)
         if not new:
-            assert (there, at, count, set_, folds) == (none, ("done",) * S, 0, 0, 1), state
+            assert (there, at, word, folds) == (none, ("done",) * S, 0, 1), state
             ends += 1
         for n in new:
             if n not in seen:
