@@ -135,9 +135,10 @@ hipError_t launch_decide(const DecideArgs& a, const UpdateArgs& upd, const Works
   const dim3 grid(a.map.B);
   // The kernel is one chain of latencies, and each turn of the positions is the same chain over again: one turn up to
   // 16 positions with a wavefront each (a list per half: both at once), and beyond that half a wavefront to a position, which
-  // takes 32 in a turn.  Kernel (us), a wavefront / half a wavefront, 32 sequences: k = 8, lists of 64 6.9 / 6.9, 256 7.2 / 7.6,
-  // 448 7.6 / 8.6; k = 12 7.1 / 7.1, 7.5 / 8.0, 8.4 / 9.3; k = 20 7.9 / 8.0, 8.6 / 9.1, 10.5 / 10.8; k = 40 11.4 / 9.2,
-  // 12.7 / 10.6, 16.6 / 13.3 (before ask_sequence, which takes 0.8 off each).  Fewer threads and more turns: k = 16 with 8 wavefronts 10.5 where 16 take 8.9.
+  // takes 32 in a turn.  Kernel (us), a wavefront / half a wavefront (in as many groups up to 16), 32 sequences: k = 8, lists of
+  // 64 6.1 / 6.0, 256 6.5 / 6.9, 448 7.5 / 8.5; k = 12 6.6 / 6.5, 7.0 / 7.3, 7.9 / 8.8; k = 20 7.9 / 7.6, 8.6 / 8.7, 10.2 / 10.8;
+  // k = 40 11.8 / 9.6, 13.2 / 11.1, 16.1 / 13.9.  Fewer threads and more turns: k = 16 with 8 wavefronts 8.4, 9.1, 10.6 where 16 take
+  // 7.2, 7.8, 8.8.
   const int LP = a.map.K > 16 ? 32 : 64, T = a.map.K <= 4 ? 256 : a.map.K <= 8 ? 512 : 1024;
 #define ADASD_DECIDE_CASE(DTV, INLOOPV, HISTV, TV, LPV) \
   if (a.dt == DTV && (a.list_update != 0) == INLOOPV && (a.hist != nullptr) == HISTV && T == TV && LP == LPV) \

@@ -30,7 +30,7 @@ template <bool DRAW> __device__ __forceinline__ void fold_wave(Lse& l, Top2& t) 
   if (DRAW) t = top2_below(t, best);
 }
 // The same of the workgroup's wavefronts, whose states (folded, with references that carry the flag) are in shared memory: every
-// lane goes through them by itself, which is shorter than the exchanges between lanes (drafting 1 x 32000 float 4.43 -> 4.25 us a call).
+// lane goes through them by itself, which is shorter than the exchanges between lanes (0.18 us of a drafting call of 1 x 32000 float).
 template <bool DRAW> __device__ __forceinline__ void fold_workgroup(const Lse (&ls)[kWaves], const Top2 (&ts)[kWaves], Lse& l, Top2& t) {
   float M = ls[0].m;
 #pragma unroll
@@ -82,16 +82,18 @@ struct DraftShared {
 // multiplications and 19 exclusive ors per four logits for the noise, and for the key two conversions, two logarithms
 // and about a dozen more; from four groups of logits per wavefront on, the key's part is only done where the logit may
 // still win (PRUNE: three instructions to find out; the kernel alone, 128 rows of 152064 25.8 -> 21.5 us, 896 of 128256
-// 108 -> 77).  It is bound by the vector ALU, so everything here follows the issue rules of device_common.h; the slices
-// are cut so that the whole call is resident at once with equal shares per thread.
+// 108 -> 77).  While the wavefronts run it is bound by the vector ALU, so everything here follows the issue
+// rules of device_common.h; the slices are cut so that the whole call is resident at once with equal shares per thread.  A wavefront
+// of 128 rows of 152064 lives 12.3 of the call's 20.3 us, 44 % of it waiting for its turn to issue and 29 % for memory; one of 24
+// rows of 128256 about 6 of 8.2, 23 % and 47 %.  The rest of a call is its start, its hand-off and that not all end at once.
 // Back to back, bf16, against loops that alternated transcendentals with plain instructions and took the slices in
 // batches of vectors: 128 rows of 152064 39.0 -> 24.3 us, 24 of 32 rows of 128256 11.1 -> 8.9 us; one row of 128256
 // 8.8 -> 6.0 us (3.4 us of it are the host's part of the call, which runs beside the kernel of the call before).
 // With few rows it is a chain of latencies: 0.6 us to the first logits, 0.6 to 0.9 for the scan, 0.5 for the wavefronts' and the
 // workgroup's fold, 0.6 until the last slice's record has arrived, 0.5 for the row's fold and the results.  The wavefronts
 // without logits behind a row's end stood in it with 1 us (top2_below), the ticket with 0.4, the threshold, asked for
-// when it was needed, with 0.3: 1 x 128256 bf16 5.95 -> 4.56 us a call, 1 x 32000 float 5.96 -> 4.36, 32 x 128256 8.82 -> 8.18, entropies of 32 x 128256
-// float 6.57 -> 6.10.  (More than one vector ahead on its way: 6.2 -> 6.4 us with the entropies, 8.4 -> 8.5 with the draw.)
+// when it was needed, with 0.3: 1 x 128256 bf16 5.95 -> 4.60 us a call, 1 x 32000 float 5.96 -> 4.40, 24 of 32 rows of 128256 8.82 ->
+// 8.20, entropies of 32 x 128256 float 6.57 -> 6.17.  (More than one vector ahead on its way: 6.2 -> 6.4 us with the entropies, 8.4 -> 8.5 with the draw.)
 //
 // One launch per drafting call, grid (slices, rows).  One workgroup of a row (few_rows) folds
 // the slices' records, and with DRAW settles a winner that does not lead by more than the rounding guard.

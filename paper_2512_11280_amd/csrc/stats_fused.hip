@@ -454,10 +454,13 @@ k_stats_fused(RowMap map, FusedGeom g, Workspace ws, VerifyOut vout, HistArgs hi
 // Few positions leave most of the chip idle, and the kernel is then one chain of latencies in which a wavefront's own vectors
 // and the eight wavefronts of a workgroup that share a compute unit stand one after the other: smaller workgroups, as long as
 // each has a compute unit to itself (256), and as long as half of a position's hand-off slots stay free, for the decisions
-// inside the token kernel (merges_decisions).  Whole calls (us), slices by V alone / up to 256 workgroups: 1 x 4 x 32000 bf16
-// 17.9 / 16.1, float 16.0 / 15.7, 1 x 1 x 128256 bf16 18.7 / 17.5, 1 x 8 18.5 / 17.4, 4 x 4 18.8 / 18.5, 16 x 4 x 16001
-// 17.9 / 16.0.  Up to 128: 1 x 8 x 128256 18.2, 16 x 4 x 16001 17.2; up to 512: 17.6, 16.2, but 1 x 20 x 128256 21.3 -> 22.5,
-// 2 x 8 x 32000 float 16.6 -> 17.4.  Errors against 64 bits (rms, 60 rounds each), by V alone / up to 256: 1 x 4 x 32000 float
+// inside the token kernel (merges_decisions).  Whole calls (us), slices by V alone / up to 128 / 256 / 384 / 512 workgroups:
+//   1 x 4 x 32000 bf16    16.6 / 14.0 / 14.1 / 14.0 / 14.0     16 x 4 x 16001             17.7 / 16.9 / 15.7 / 15.7 / 15.5
+//   1 x 4 x 32000 float   14.6 / 13.1 / 13.1 / 13.1 / 13.2     4 x 8 x 50257              18.1 / 18.1 / 17.2 / 17.2 / 16.8
+//   1 x 1 x 128256        17.0 / 14.7 / 14.7 / 14.7 / 14.7     1 x 20 x 128256            20.4 / 20.4 / 20.4 / 21.1 / 21.1
+//   1 x 8 x 128256        17.1 / 16.1 / 15.0 / 15.0 / 15.0     16 x 6 x 32003 literal     19.4 / 19.4 / 19.4 / 19.8 / 19.8
+//   4 x 4 x 128256        18.0 / 17.9 / 17.5 / 17.5 / 17.2     24 x 4 x 32003             20.1 / 20.3 / 20.1 / 20.9 / 20.7
+// Beyond 256 some win 0.2 to 0.4 where their slices come to 512 workgroups, others lose as much or more.  Errors against 64 bits (rms, 60 rounds each), by V alone / up to 256: 1 x 4 x 32000 float
 // entropies 4.5e-8 / 3.9e-8, distances 9.7e-8 / 1.03e-7; 1 x 8 x 128256 bf16 4.4e-8 / 4.2e-8, 1.34e-7 / 1.32e-7; 8 x 4 x 16001 4.9e-8
 // / 4.9e-8, 1.69e-7 / 1.59e-7.
 constexpr int kSmallGroups = 256, kSmallSplit = kMaxSplit / 2;
@@ -486,13 +489,18 @@ bool fused_plan(const RowMap& map, int dt, int* T_out, int* NB_out, int* S_out) 
 
 // Where the chip holds all workgroups of a round (1024 of 512 threads), or there is but one more set of them, a workgroup naps once
 // (about 0.35 us, which the other slices need at least) before it first looks for their records; where there are more sets, three
-// times, while other workgroups load.  Call times in us without a nap / with 1 / 2 / 3 / 4 (64 samples a list):
-//   1 x 4 x 32000 float (32 workgroups)   13.9 / 13.2 / 13.5 / 13.8 / 14.1     64 x 8 x 64000 (2048)         57.4 / 57.7 / 56.9 / 56.5 / 56.4
-//   1 x 8 x 128256 (256)                  16.8 / 16.1 / 16.2 / 16.6 / 16.9     64 x 8 x 32000 float (2048)   43.4 / 43.7 / 43.9 / 44.0 / 44.3
-//   16 x 4 x 16001 (256)                  16.0 / 15.9 / 16.2 / 16.5 / 16.9     8 x 20 x 128256 float (2560)  54.2 / 53.8 / 53.2 / 52.8 / 52.8
-//   16 x 8 x 128256 (1024)                36.5 / 36.5 / 36.5 / 36.8 / 37.1     256 x 8 x 32000 (4096)        94.1 / 94.7 / 94.2 / 93.2 / 93.3
-//   20 x 8 x 128256 (1280)                41.4 / 41.2 / 41.4 / 41.6 / 41.8     128 x 8 x 50257 float (7168)  106 / 105 / 104 / 104 / 104
-//   32 x 8 x 128256 (2048)                56.7 / 56.7 / 56.4 / 56.5 / 56.3     128 x 16 x 152064 (20480)     365 / 358 / 368 / 357 / 364
+// times, while other workgroups load.  Call times in us without a nap / with 1 / 2 / 3 / 4 (64 samples a list; half of the
+// range of nine runs: 0.1 to 0.3 up to 1024 workgroups, 0.5 from there on, 1 to 2 from 4096 on):
+//   1 x 4 x 32000 float (32 workgroups)   13.9 / 13.3 / 13.5 / 13.7 / 14.0     64 x 8 x 32000 float (2048)   44.0 / 44.1 / 44.3 / 44.4 / 44.7
+//   1 x 8 x 128256 (256)                  15.6 / 15.0 / 15.1 / 15.4 / 15.7     36 x 8 x 128256 (2304)        64.1 / 64.5 / 64.4 / 63.6 / 62.9
+//   16 x 4 x 16001 (256)                  15.8 / 15.7 / 16.0 / 16.3 / 16.6     40 x 8 x 128256 (2560)        67.9 / 68.2 / 67.7 / 67.6 / 67.0
+//   16 x 8 x 128256 (1024)                36.2 / 36.2 / 36.1 / 36.5 / 36.7     8 x 20 x 128256 float (2560)  51.9 / 51.4 / 51.0 / 50.5 / 50.6
+//   20 x 8 x 128256 (1280)                43.1 / 43.0 / 42.9 / 43.1 / 42.8     64 x 8 x 96000 (3072)         78.0 / 78.4 / 78.5 / 77.3 / 76.1
+//   24 x 8 x 128256 (1536)                47.0 / 47.1 / 46.9 / 47.2 / 46.9     256 x 8 x 32000 (4096)        94.8 / 96.2 / 95.5 / 94.4 / 94.2
+//   32 x 8 x 128256 (2048)                57.9 / 58.1 / 57.3 / 57.5 / 56.9     128 x 8 x 50257 float (7168)  104 / 103 / 103 / 103 / 102
+//   64 x 8 x 64000 (2048)                 57.4 / 57.8 / 57.1 / 56.7 / 56.4     128 x 16 x 152064 (20480)     368 / 367 / 368 / 367 / 368
+// At 2048 the three shapes do not agree, so the line is behind them; up to 1536, and from 7168 on, it makes no difference that
+// shows but for the smallest rounds.
 constexpr int kManyGroups = 2048;
 
 hipError_t launch_stats_fused(const RowMap& map, int dt, int T, int NB, int S, int wait_polls,
