@@ -166,7 +166,8 @@ __device__ __forceinline__ bool look_at_words(const uint64_t* words, uint64_t (&
 // logits themselves.
 // (What a slice of few rows does behind its record stands beside the last slice's wait and shows in no call's time.  With one count
 // for them all, which every slice adds to, it did: one after the other, the returned additions were what the kernel ended with,
-// 1 x 8 x 128256 bf16 14.9 -> 15.3 us a call; and so did records sent by an exchange, 32 x 128256 float 6.2 -> 7.3.)
+// 1 x 8 x 128256 bf16 14.9 -> 15.3 us a call; and so did records sent by an exchange, 32 x 128256 float 6.2 -> 7.3.  Giving a row up stands behind
+// the wait and not in its loop, where it lay in the way: 1 x 8 x 128256 15.0 -> 14.9.)
 template <class Slots, class Ask>
 __device__ __forceinline__ bool hand_off(const Slots& slots, int s, int S, const Arrivals& a, WordWait wait, const Ask& ask,
                                          uint64_t (&w)[kXchgWords], bool& arrived) {
@@ -174,30 +175,33 @@ __device__ __forceinline__ bool hand_off(const Slots& slots, int s, int S, const
   const uint64_t w0 = w[0], w1 = w[1], w2 = w[2], word = lane == 0 ? w0 : lane == 1 ? w1 : w2;
   static_assert(kXchgWords == 3, "a lane per word");
   if (lane < kXchgWords) __hip_atomic_store(slots.at(s) + lane, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  bool may_give_up = false;
-  if (!few_rows(a.rows)) {
-    if (!last_to_add(add_arrival(a.count()), S)) return false;
-    set_arrival(a.count(), 0);
-  } else if (s == S - 1) {
-    may_give_up = true;
-  } else {
-    stores_before_loads();
-    uint64_t set = get_uniform(a.set()), next;
-    if (__builtin_expect(set == 0, 1)) return false;
-    do {
-      next = after_coming(set, s);
-      if (next == set) return false;
-    } while (!exchange_arrival(a.set(), set, next));
-    if (next != 0) return false;
+  const bool may_give_up = few_rows(a.rows) && s == S - 1;
+  if (!may_give_up) {
+    if (!few_rows(a.rows)) {
+      if (!last_to_add(add_arrival(a.count()), S)) return false;
+      set_arrival(a.count(), 0);
+    } else {
+      stores_before_loads();
+      uint64_t set = get_uniform(a.set()), next;
+      if (__builtin_expect(set == 0, 1)) return false;
+      do {
+        next = after_coming(set, s);
+        if (next == set) return false;
+      } while (!exchange_arrival(a.set(), set, next));
+      if (next != 0) return false;
+    }
   }
   ask();
   const bool mine = lane < S;
   uint64_t* words = slots.at(min(lane, S - 1));
-  int polls = may_give_up && wait == kGivesUp ? 0 : kWaitPolls;
-  while (true) {
-    do arrived = __all(look_at_words(words, w) || !mine) != 0;
-    while (!arrived && polls-- > 0);
-    if (__builtin_expect(arrived || !may_give_up, 1)) break;
+  auto wait_for_words = [&](int polls) {
+    bool there;
+    do there = __all(look_at_words(words, w) || !mine) != 0;
+    while (!there && polls-- > 0);
+    return there;
+  };
+  arrived = wait_for_words(may_give_up && wait == kGivesUp ? 0 : kWaitPolls);
+  if (__builtin_expect(!arrived && may_give_up, 0)) {
     set_arrival(a.set(), kLooking);
     stores_before_loads();
     const uint64_t missed = __ballot(mine && lane != s && !look_at_words(words, w));
@@ -205,8 +209,7 @@ __device__ __forceinline__ bool hand_off(const Slots& slots, int s, int S, const
     do next = after_looking(set, missed);
     while (!exchange_arrival(a.set(), set, next));
     if (next != 0) return false;
-    may_give_up = false;
-    polls = kWaitPolls;
+    arrived = wait_for_words(kWaitPolls);
   }
   if (mine) {
 #pragma unroll
