@@ -92,7 +92,7 @@ struct DraftShared {
 // With few rows it is a chain of latencies: 0.6 us to the first logits, 0.6 to 0.9 for the scan, 0.5 for the wavefronts' and the
 // workgroup's fold, 0.6 until the last slice's record has arrived, 0.5 for the row's fold and the results.  The wavefronts
 // without logits behind a row's end stood in it with 1 us (top2_below), the ticket with 0.4, the threshold, asked for
-// when it was needed, with 0.3: 1 x 128256 bf16 5.95 -> 4.60 us a call, 1 x 32000 float 5.96 -> 4.40, 24 of 32 rows of 128256 8.82 ->
+// when it was needed, with 0.3: 1 x 128256 bf16 5.95 -> 4.65 us a call, 1 x 32000 float 5.96 -> 4.35, 24 of 32 rows of 128256 8.82 ->
 // 8.20, entropies of 32 x 128256 float 6.57 -> 6.17.  (More than one vector ahead on its way: 6.2 -> 6.4 us with the entropies, 8.4 -> 8.5 with the draw.)
 //
 // One launch per drafting call, grid (slices, rows).  One workgroup of a row (few_rows) folds

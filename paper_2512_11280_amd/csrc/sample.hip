@@ -82,7 +82,7 @@ struct DrawAndApply {
 // Who folds the slices' records: see few_rows.  With that, without the tie loop for wavefronts that have no logit, with the best's
 // logits asked for before the folds and the wavefronts folded by every lane for itself, whole calls (us): 1 x 4 x 32000 float 15.79
 // -> 14.17, 1 x 8 x 128256 bf16 17.23 -> 16.18, 16 x 6 x 32003 literal 20.35 -> 19.31; 32 x 8 x 128256 the same within noise.  (That
-// a last slice can give a sequence up took 0.05 to 0.15 of it back.)
+// a last slice can give a sequence up takes up to 0.1 of it back.)
 // LONG: a row of more slices than there are hand-off words (see token_split).  The records then go through part3, and have
 // landed before the ticket is taken; and a compute unit holds no more than one such workgroup of a few sequences.
 template <int DT, bool LONG, bool PRUNE, class Words, class Round>
